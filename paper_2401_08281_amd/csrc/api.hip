@@ -178,12 +178,14 @@ struct Planes {
 };
 size_t planes_bytes(int64_t n, int d) {
   n = mfma_padded_rows(n);
+  d = mfma_padded_dim(d);
   return align_up((size_t)n * d * sizeof(unsigned short)) + align_up((size_t)2 * n * d * sizeof(unsigned short)) +
          align_up((size_t)n * sizeof(float)) + align_up(sizeof(PrepInfo));
 }
 Planes carve_planes(char* base, int64_t n, int d) {
   Planes p;
   n = mfma_padded_rows(n);
+  d = mfma_padded_dim(d);
   size_t o = 0;
   p.hi = reinterpret_cast<unsigned short*>(base + o); o += align_up((size_t)n * d * sizeof(unsigned short));
   // (operand preparation writes the fp16 heads right behind the bf16 tails: one block of two planes)
@@ -220,10 +222,19 @@ struct KnnPlan {
   int64_t rows = 0, cols = 0;     // canon tile shape
   size_t bytes = 0;               // scratch needed
 };
-KnnPlan knn_plan(int64_t na, int64_t nb, int d, int k, bool b_prepared) {
+// A problem so small that the launches of the matrix-core route (prepare, two sweeps, threshold,
+// re-rank, fallback: up to a dozen kernels) cost more than one canon tile pass and one selection
+// cost in full.  Measured on 256 - 65536 columns of 32 - 768 dimensions, 1 - 1000 rows: the canon
+// route is ahead up to about 6e8 multiply-adds (4096 x 128, 1000 rows: 63 against 74 us; 1 row: 35
+// against 60) while the columns fit one tile (65536 x 96, 1 row: 168 against 80).
+bool knn_small(int64_t na, int64_t nb, int d) { return nb <= 16384 && (double)na * nb * d <= 6e8; }
+// route: 1 / 0 = the matrix-core / the canon route (a plan made before for a larger piece of the
+// same rows), -1 = choose; small_canon: choose the canon route for problems that are small.
+KnnPlan knn_plan(int64_t na, int64_t nb, int d, int k, bool b_prepared, bool small_canon, int route = -1) {
   KnnPlan p;
   const int path = g_knn_path.load();
-  p.mfma = path != 1 && nb > 0 && mfma_knn_supported(d, k);
+  p.mfma = path != 1 && nb > 0 && mfma_knn_supported(d, k) &&
+           (route < 0 ? !(small_canon && path == 0 && knn_small(na, nb, d)) : route == 1);
   if (p.mfma) {
     size_t b = planes_bytes(na, d);
     if (!b_prepared) b += planes_bytes(nb, d);
@@ -241,10 +252,10 @@ KnnPlan knn_plan(int64_t na, int64_t nb, int d, int k, bool b_prepared) {
 // Plan for n rows of A processed in pieces of at most `piece` rows: the work space covers the
 // full pieces and the shorter last one (a shorter piece may be laid out with more splits of B,
 // so its work space is not bounded by that of a longer one).
-KnnPlan knn_plan_pieces(int64_t n, int64_t piece, int64_t nb, int d, int k, bool b_prepared) {
-  KnnPlan p = knn_plan(std::min(n, piece), nb, d, k, b_prepared);
+KnnPlan knn_plan_pieces(int64_t n, int64_t piece, int64_t nb, int d, int k, bool b_prepared, bool small_canon) {
+  KnnPlan p = knn_plan(std::min(n, piece), nb, d, k, b_prepared, small_canon);
   if (n > piece && n % piece != 0) {
-    const KnnPlan last = knn_plan(n % piece, nb, d, k, b_prepared);
+    const KnnPlan last = knn_plan(n % piece, nb, d, k, b_prepared, small_canon, p.mfma ? 1 : 0);
     p.bytes = std::max(p.bytes, last.bytes);
   }
   return p;
@@ -259,7 +270,7 @@ int knn_run(const KnnPlan& plan, char* ws, const float* A, int64_t na, const flo
   // fallback (valid once the call's kernels have run), or null when the canon tiles served the call
   if (fallback_count) *fallback_count = nullptr;
   {
-    const KnnPlan need = knn_plan(na, nb, d, k, b_planes != nullptr);
+    const KnnPlan need = knn_plan(na, nb, d, k, b_planes != nullptr, false, plan.mfma ? 1 : 0);
     if (need.mfma != plan.mfma || (plan.mfma && need.bytes > plan.bytes))
       return fail(VS_ERR_DEVICE, "k-nearest-rows: work space of %zu bytes planned, %zu needed for %lld rows",
                   plan.bytes, need.bytes, (long long)na);
@@ -279,8 +290,9 @@ int knn_run(const KnnPlan& plan, char* ws, const float* A, int64_t na, const flo
     const MfmaOperand oa = operand(A, na, pa), ob = operand(B, nb, pb);
     {
       StageTimer t(stage_dist, st);
-      launch_prep(A, na, d, pa.hi, pa.lo, pa.norm, pa.info, st);
-      if (!b_planes) launch_prep(B, nb, d, pb.hi, pb.lo, pb.norm, pb.info, st);
+      // (the fp16 heads are swept only next to an operand prepared for the attempt)
+      launch_prep(A, na, d, pa.hi, pa.lo, pa.norm, pa.info, st, false, pb.try_heads_only);
+      if (!b_planes) launch_prep(B, nb, d, pb.hi, pb.lo, pb.norm, pb.info, st, false, false);
       launch_mfma_shortlist(oa, ob, d, metric, k, plan.nsplit, shortlist, fb_count, st);
     }
     {
@@ -427,8 +439,8 @@ int64_t vs_knn_workspace_bytes(int64_t na, int64_t nb, int32_t d, int32_t k, int
     return -1;
   }
   if (na == 0) return 0;
-  const KnnPlan p = piece > 0 ? knn_plan_pieces(na, piece, nb, d, k, b_prepared != 0)
-                              : knn_plan(na, nb, d, k, b_prepared != 0);
+  const KnnPlan p = piece > 0 ? knn_plan_pieces(na, piece, nb, d, k, b_prepared != 0, false)
+                              : knn_plan(na, nb, d, k, b_prepared != 0, false);
   return (int64_t)p.bytes;
 }
 
@@ -457,7 +469,7 @@ int vs_flat_search(const float* x, int64_t nb, const float* q, int64_t nq, int32
   HIP_TRY(hipGetDevice(&dev));
   if (dev < 0 || dev >= 16) return fail(VS_ERR_UNSUPPORTED, "vs_flat_search: device %d", dev);
 
-  const KnnPlan plan = knn_plan(nq, nb, d, k, false);
+  const KnnPlan plan = knn_plan(nq, nb, d, k, false, d % 32 != 0);
   ScratchUse guard(g_flat_scratch[dev], st);
   Scratch& sc = g_flat_scratch[dev];
   if (int rc = sc.reserve(plan.bytes + (size_t)nq * k * sizeof(u64))) return rc;
@@ -559,7 +571,7 @@ int vs_flat_index_search(const vs_flat* ix, const float* q, int64_t nq, int32_t 
   const int64_t nb = ix->ntotal;
   const int d = ix->d, metric = ix->metric;
   const Planes* bp = ix->has_planes ? &ix->planes : nullptr;
-  const KnnPlan plan = knn_plan(nq, nb, d, k, bp != nullptr);
+  const KnnPlan plan = knn_plan(nq, nb, d, k, bp != nullptr, d % 32 != 0);
   ScratchUse guard(g_flat_scratch[dev], st);
   Scratch& sc = g_flat_scratch[dev];
   if (int rc = sc.reserve(plan.bytes + (size_t)nq * k * sizeof(u64))) return rc;
@@ -620,7 +632,7 @@ namespace {
 int nearest_rows(const float* A, int64_t n, const float* B, int64_t nb, int d, int metric,
                  int32_t* idx, float* val, Scratch& sc, hipStream_t st) {
   constexpr int64_t kPiece = 1 << 20;
-  const KnnPlan plan = knn_plan_pieces(n, kPiece, nb, d, 1, false);
+  const KnnPlan plan = knn_plan_pieces(n, kPiece, nb, d, 1, false, true);
   if (!plan.mfma) {
     // shapes the matrix-core kernels do not cover (sub-vectors of a few dimensions): fused canon
     // distance + arg-best tiles, one 64-bit key (value, row of B) per row of A
@@ -908,9 +920,9 @@ int ivf_assign_and_place(vs_ivfpq* ix, const float* x, int64_t n, size_t extra, 
   // short first call keeps the price of finding out small.
   constexpr int64_t kProbePiece = 8192;
   const int64_t first_piece = !ix->assign_probed && n > 4 * kProbePiece ? kProbePiece : 0;
-  KnnPlan plan = knn_plan_pieces(n - first_piece, kAssignPiece, g.nlist, g.d, 1, ix->has_planes);
+  KnnPlan plan = knn_plan_pieces(n - first_piece, kAssignPiece, g.nlist, g.d, 1, ix->has_planes, true);
   if (first_piece > 0) {
-    const KnnPlan probe = knn_plan(first_piece, g.nlist, g.d, 1, ix->has_planes);
+    const KnnPlan probe = knn_plan(first_piece, g.nlist, g.d, 1, ix->has_planes, false, plan.mfma ? 1 : 0);
     plan.bytes = std::max(plan.bytes, probe.bytes);
   }
   if (!plan.mfma) plan.bytes = 0;
@@ -1122,7 +1134,7 @@ int vs_ivfpq_coarse(const vs_ivfpq* ix, const float* q, int64_t nq, int32_t npro
   if (!q || !probes) return fail(VS_ERR_INVALID_ARG, "vs_ivfpq_coarse: null pointer");
   hipStream_t st = static_cast<hipStream_t>(hip_stream);
   const int npr = std::min<int>(nprobe, ix->g.nlist);
-  const KnnPlan plan = knn_plan(nq, ix->g.nlist, ix->g.d, npr, ix->has_planes);
+  const KnnPlan plan = knn_plan(nq, ix->g.nlist, ix->g.d, npr, ix->has_planes, true);
   ScratchUse use(ix->scratch, st);
   if (int rc = ix->scratch.reserve(plan.bytes)) return rc;
   if (int rc = coarse_select(ix, plan, static_cast<char*>(ix->scratch.p), q, nq, npr, probes, coarse_dist, st)) return rc;
@@ -1166,7 +1178,7 @@ void search_layout(const vs_ivfpq* ix, int64_t nq, int k, int nprobe, SearchLayo
   }
   const int ppb = (L.npr + L.nsplit - 1) / L.nsplit;
   L.nsplit = (L.npr + ppb - 1) / ppb;
-  L.plan = knn_plan(nq, g.nlist, g.d, L.npr, ix->has_planes);
+  L.plan = knn_plan(nq, g.nlist, g.d, L.npr, ix->has_planes, true);
   Carver cv;
   L.o_knn = cv.take(L.plan.bytes);
   L.o_pr = cv.take((size_t)nq * L.npr * sizeof(int32_t));
@@ -1400,7 +1412,7 @@ int vs_ivfflat_search(const vs_ivfflat* fx, const float* q, int64_t nq, int32_t 
   int nsplit = (int)std::min<int64_t>(npr, std::max<int64_t>(1, (4096 + nq - 1) / nq));
   const int ppb = (npr + nsplit - 1) / nsplit;
   nsplit = (npr + ppb - 1) / ppb;
-  const KnnPlan plan = knn_plan(nq, g.nlist, g.d, npr, ix->has_planes);
+  const KnnPlan plan = knn_plan(nq, g.nlist, g.d, npr, ix->has_planes, true);
   Carver cv;
   const size_t o_knn = cv.take(plan.bytes);
   const size_t o_pr = cv.take((size_t)nq * npr * sizeof(int32_t));
@@ -1548,7 +1560,7 @@ int vs_ivfsq8_search(const vs_ivfsq8* sx, const float* q, int64_t nq, int32_t k,
   int nsplit = (int)std::min<int64_t>(npr, std::max<int64_t>(1, (4096 + nq - 1) / nq));
   const int ppb = (npr + nsplit - 1) / nsplit;
   nsplit = (npr + ppb - 1) / ppb;
-  const KnnPlan plan = knn_plan(nq, g.nlist, g.d, npr, ix->has_planes);
+  const KnnPlan plan = knn_plan(nq, g.nlist, g.d, npr, ix->has_planes, true);
   Carver cv;
   const size_t o_knn = cv.take(plan.bytes);
   const size_t o_pr = cv.take((size_t)nq * npr * sizeof(int32_t));

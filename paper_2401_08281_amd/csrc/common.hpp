@@ -320,6 +320,20 @@ __device__ __forceinline__ int list_of_position(const int64_t* __restrict__ off,
   return lo;
 }
 
+// ---- rows of any length in pieces of eight --------------------------------------
+// Eight elements c .. c + 7 of one row of d floats, zeros past its end (c % 8 == 0).
+__device__ __forceinline__ void load_row8(const float* __restrict__ row, int c, int d, bool vec, float (&v)[8]) {
+  if (vec) {                                           // rows of 16-byte pieces: whole pieces are in or out
+    float4 a = make_float4(0.f, 0.f, 0.f, 0.f), b = a;
+    if (c < d) a = *reinterpret_cast<const float4*>(row + c);
+    if (c + 4 < d) b = *reinterpret_cast<const float4*>(row + c + 4);
+    v[0] = a.x; v[1] = a.y; v[2] = a.z; v[3] = a.w; v[4] = b.x; v[5] = b.y; v[6] = b.z; v[7] = b.w;
+  } else {
+#pragma unroll
+    for (int t = 0; t < 8; ++t) v[t] = c + t < d ? row[c + t] : 0.f;
+  }
+}
+
 // ---- canon distance of one pair ------------------------------------------------
 // The fp32 chain every exact decision of the library is defined in: dimension order,
 // diff = a - b rounded, acc = fma(diff, diff, acc) (inner product: acc = fma(a, b, acc)).

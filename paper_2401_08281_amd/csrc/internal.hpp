@@ -140,9 +140,9 @@ struct PrepInfo {
 };
 struct MfmaOperand {
   const float* x;             // [n, d] original fp32 rows
-  const unsigned short* hi;   // [n, d] bf16 heads
-  const unsigned short* lo;   // [n, d] bf16 tails
-  const unsigned short* h16;  // [n, d] fp16 heads (written by operand preparation right behind the tails)
+  const unsigned short* hi;   // [n, dp] bf16 heads, dp = mfma_padded_dim(d)
+  const unsigned short* lo;   // [n, dp] bf16 tails
+  const unsigned short* h16;  // [n, dp] fp16 heads (written by operand preparation right behind the tails)
   const float* norm;          // [n] squared norms
   const PrepInfo* info;
   int64_t n;
@@ -154,7 +154,10 @@ bool mfma_knn_supported(int d, int k);
 int64_t mfma_padded_rows(int64_t n);
 int mfma_knn_kp(int k);
 void launch_prep(const float* x, int64_t n, int d, unsigned short* hi, unsigned short* lo,
-                 float* norm, PrepInfo* info, hipStream_t st, bool try_heads_only = false);
+                 float* norm, PrepInfo* info, hipStream_t st, bool try_heads_only = false, bool write_f16 = true,
+                 bool keep_heads = false);   // keep_heads: the operand is prepared again, what was learnt of heads_only stays
+// operand planes hold this many dimensions per row (zeros past d)
+int mfma_padded_dim(int d);
 // bytes of the shortlist buffer [na, nsplit, kp] and the column split count to use
 size_t mfma_knn_shortlist_bytes(int64_t na, int64_t nb, int d, int k, int* nsplit_out);
 // (also clears *fb_count, the counter that launch_rerank of the same call adds to)
@@ -167,7 +170,28 @@ size_t mfma_knn_fallback_bytes(int64_t na, int64_t nb, int k);
 void launch_rerank(const MfmaOperand& A, const MfmaOperand& B, int d, int metric, int k, int nsplit,
                    const u64* shortlist, float eps_scale, const SelectOut& out, int* fb_count,
                    int* fb_rows, u64* fb_partial, hipStream_t st);
+// k best rows of B on the canon chain for the listed rows of A (count and list in device memory;
+// fb_partial as in launch_rerank; adapt: the operand whose heads_only bit a large count clears, or null)
+void launch_canon_rows(const float* A, int64_t na, const float* B, int64_t nb, int d, int metric, int k,
+                       const SelectOut& out, const int* fb_count, const int* fb_rows, u64* fb_partial,
+                       PrepInfo* adapt, hipStream_t st);
 int read_fallback_total(unsigned long long* out);
+
+// ---- nearest row in one sweep (kernels_nearest.hip) ------------------------------
+// idx[i] = best row of B for row i of x under the canon chain (ties to the smaller row), and
+// (L2 only) val[i] = its canon value where val is not null.  B: prepared with its fp16 heads.
+// work: nearest_bytes(n, B.n) bytes.  d in (16, 128].
+bool nearest_supported(int d);
+size_t nearest_bytes(int64_t n, int64_t nb);
+void launch_nearest(const float* x, int64_t n, int d, int metric, const MfmaOperand& B, float eps_scale,
+                    int32_t* idx, float* val, char* work, hipStream_t st);
+// codes[i * stride_i + m * stride_m] = nearest codeword (canon L2, ties to the smaller) of sub-vector
+// m of vector i: of x [n, d] minus the centroid of its list, or (centroids null) of x [M][n][dsub];
+// val [M][n] = its canon distance where not null.  dsub up to 16, K = 16 or 256.
+bool pq_nearest_supported(int dsub, int K);
+void launch_pq_nearest(const float* x, int64_t n, int d, int dsub, const float* centroids, const int32_t* list_of,
+                       const float* codebooks, int K, int M, uint8_t* codes, int64_t stride_i, int64_t stride_m,
+                       float* val, hipStream_t st);
 
 // ---- kernels_ivfflat.hip -------------------------------------------------------
 void launch_ivfflat_relayout(int d, int nlist, const float* old_rows, const int64_t* old_ids,

@@ -15,7 +15,7 @@
 // re-ranked (the listing threshold, or the kp-th best listed value when more than
 // kp rows were listed), v_k the k-th best canon value inside the shortlist, and
 // eps a bound on |approximate - canon| for that row.  Rows that fail the test are
-// recomputed by canon_rows_kernel over all columns, so the output never depends
+// recomputed by canon_rows_tiled_kernel over all columns, so the output never depends
 // on the approximation.
 #include <algorithm>
 #include <cmath>
@@ -74,17 +74,21 @@ __device__ __forceinline__ int precision_variant(const PrepInfo* a, const PrepIn
 // One lane per 8 consecutive elements (d % 8 == 0), 256 lanes per workgroup,
 // 2048 / d rows per group; a workgroup walks over groups and reports its flags
 // and largest norm once at the end.  Row sums are added in a fixed order.
-// The planes are [n_pad][d] row-major.
+// The planes are [n_pad][dp] row-major, dp = d rounded up to a multiple of 32: the padding
+// dimensions hold zeros, which add nothing to any product or norm, so that every d goes
+// through the matrix cores.  F16: also write the fp16 heads.
 // ---------------------------------------------------------------------------
+template <bool F16>
 __global__ __launch_bounds__(256) void prep_kernel(const float* __restrict__ x, int64_t n,
-                                                   int64_t n_pad, int d, int rows_per_group,
+                                                   int64_t n_pad, int d, int dp, int rows_per_group,
                                                    unsigned short* __restrict__ hi,
                                                    unsigned short* __restrict__ lo,
                                                    float* __restrict__ norm,
                                                    PrepInfo* __restrict__ info) {
   __shared__ float part[2][256];                       // two buffers: one barrier per group
   __shared__ u32 flags[4];                             // all_int, all_bf16, all_nonneg, largest norm
-  const int cpr = d / 8;                               // chunks per row
+  const int cpr = dp / 8;                              // chunks per row
+  const bool vec = (d & 3) == 0;
   const int tid = threadIdx.x;
   if (tid < 3) flags[tid] = 1u;
   if (tid == 3) flags[3] = 0u;
@@ -97,11 +101,9 @@ __global__ __launch_bounds__(256) void prep_kernel(const float* __restrict__ x, 
     const int64_t row0 = g * rows_per_group;
     float ss = 0.f;
     if (r < rows_per_group && row0 + r < n) {
-      const int64_t off = (row0 + r) * d + c * 8;
+      const int64_t off = (row0 + r) * dp + c * 8;
       float v[8];
-      const float4 a = *reinterpret_cast<const float4*>(x + off);
-      const float4 b = *reinterpret_cast<const float4*>(x + off + 4);
-      v[0] = a.x; v[1] = a.y; v[2] = a.z; v[3] = a.w; v[4] = b.x; v[5] = b.y; v[6] = b.z; v[7] = b.w;
+      load_row8(x + (row0 + r) * d, c * 8, d, vec, v);
       unsigned short h[8], l[8], f[8];
 #pragma unroll
       for (int t = 0; t < 8; ++t) {
@@ -123,13 +125,13 @@ __global__ __launch_bounds__(256) void prep_kernel(const float* __restrict__ x, 
       fv.z = f[4] | ((u32)f[5] << 16); fv.w = f[6] | ((u32)f[7] << 16);
       *reinterpret_cast<uint4*>(hi + off) = hv;
       *reinterpret_cast<uint4*>(lo + off) = lv;
-      *reinterpret_cast<uint4*>(lo + n_pad * d + off) = fv;   // the fp16 heads: a third plane behind the tails
+      if (F16) *reinterpret_cast<uint4*>(lo + n_pad * dp + off) = fv;   // the fp16 heads: a third plane behind the tails
     } else if (r < rows_per_group && row0 + r < n_pad) {   // padding rows: zeros (never selected)
-      const int64_t off = (row0 + r) * d + c * 8;
+      const int64_t off = (row0 + r) * dp + c * 8;
       const uint4 z = make_uint4(0u, 0u, 0u, 0u);
       *reinterpret_cast<uint4*>(hi + off) = z;
       *reinterpret_cast<uint4*>(lo + off) = z;
-      *reinterpret_cast<uint4*>(lo + n_pad * d + off) = z;
+      if (F16) *reinterpret_cast<uint4*>(lo + n_pad * dp + off) = z;
     }
     part[pb][tid] = ss;
     // (the buffer written two groups later is safe: every lane passes the next group's
@@ -166,15 +168,17 @@ __global__ __launch_bounds__(256) void prep_kernel(const float* __restrict__ x, 
 // rows at a time: lane (r, s) = (tid % 32, tid / 32) converts chunks s, s + 8, ... of row r,
 // so a wavefront writes one whole block (32 rows x 32 bytes, consecutive) per store and
 // reads 64-byte runs of 32 rows; the eight partial sums of a row are added in a fixed order.
+template <bool F16>
 __global__ __launch_bounds__(256) void prep_panel_kernel(const float* __restrict__ x, int64_t n,
-                                                         int64_t n_pad, int d,
+                                                         int64_t n_pad, int d, int dp,
                                                          unsigned short* __restrict__ hi,
                                                          unsigned short* __restrict__ lo,
                                                          float* __restrict__ norm,
                                                          PrepInfo* __restrict__ info) {
   __shared__ float part[2][8][32];
   __shared__ u32 flags[4];
-  const int cpr = d / 8;
+  const int cpr = dp / 8;
+  const bool vec = (d & 3) == 0;
   const int tid = threadIdx.x, r = tid & 31, s = tid >> 5;
   if (tid < 3) flags[tid] = 1u;
   if (tid == 3) flags[3] = 0u;
@@ -188,11 +192,8 @@ __global__ __launch_bounds__(256) void prep_panel_kernel(const float* __restrict
     if (row < n) {
 #pragma unroll 4
       for (int c = s; c < cpr; c += 8) {
-        const int64_t off = row * d + c * 8;
         float v[8];
-        const float4 a = *reinterpret_cast<const float4*>(x + off);
-        const float4 bq = *reinterpret_cast<const float4*>(x + off + 4);
-        v[0] = a.x; v[1] = a.y; v[2] = a.z; v[3] = a.w; v[4] = bq.x; v[5] = bq.y; v[6] = bq.z; v[7] = bq.w;
+        load_row8(x + row * d, c * 8, d, vec, v);
         unsigned short h[8], l[8], f[8];
 #pragma unroll
         for (int t = 0; t < 8; ++t) {
@@ -215,7 +216,7 @@ __global__ __launch_bounds__(256) void prep_panel_kernel(const float* __restrict
         const int64_t out = ((int64_t)(c >> 1) * n_pad + row) * 16 + (c & 1) * 8;
         *reinterpret_cast<uint4*>(hi + out) = hv;
         *reinterpret_cast<uint4*>(lo + out) = lv;
-        *reinterpret_cast<uint4*>(lo + n_pad * d + out) = fv;   // the fp16 heads: a third plane, same panels
+        if (F16) *reinterpret_cast<uint4*>(lo + n_pad * dp + out) = fv;   // the fp16 heads: a third plane, same panels
       }
     } else {                                               // padding rows: zeros (never selected)
       const uint4 z = make_uint4(0u, 0u, 0u, 0u);
@@ -223,7 +224,7 @@ __global__ __launch_bounds__(256) void prep_panel_kernel(const float* __restrict
         const int64_t out = ((int64_t)(c >> 1) * n_pad + row) * 16 + (c & 1) * 8;
         *reinterpret_cast<uint4*>(hi + out) = z;
         *reinterpret_cast<uint4*>(lo + out) = z;
-        *reinterpret_cast<uint4*>(lo + n_pad * d + out) = z;
+        if (F16) *reinterpret_cast<uint4*>(lo + n_pad * dp + out) = z;
       }
     }
     part[pb][s][r] = ss;
@@ -255,9 +256,9 @@ __global__ __launch_bounds__(256) void prep_panel_kernel(const float* __restrict
   }
 }
 
-__global__ void prep_info_init_kernel(PrepInfo* info, u32 heads_only) {
+__global__ void prep_info_init_kernel(PrepInfo* info, u32 heads_only, u32 keep_heads) {
   info->all_int = 1u; info->all_bf16 = 1u; info->max_norm_bits = 0u; info->all_nonneg = 1u;
-  info->heads_only = heads_only ? 3u : 0u;
+  if (!keep_heads) info->heads_only = heads_only ? 3u : 0u;
 }
 
 // ---------------------------------------------------------------------------
@@ -1085,70 +1086,13 @@ __device__ __forceinline__ FallbackSplit fallback_split(int count, int64_t nb, i
 // (listed row, column chunk) tasks, so that even a single listed row is spread over the
 // chip; with more than one chunk the k best of each chunk go to `partial` as keys and
 // canon_rows_merge_kernel picks the k best of a row's chunks.
-template <int R, int METRIC>
-__global__ __launch_bounds__(256) void canon_rows_kernel(const float* __restrict__ A,
-                                                         const float* __restrict__ B, int64_t nb,
-                                                         int d, int k, int tot, int64_t chunk_cols0,
-                                                         int nchunk0, int64_t cap_keys,
-                                                         u64* __restrict__ partial, SelectOut out,
-                                                         const int* __restrict__ fb_count,
-                                                         const int* __restrict__ fb_rows,
-                                                         PrepInfo* __restrict__ adapt, int64_t na) {
-  extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
-  u64* slots = reinterpret_cast<u64*>(smem);                    // 4 * tot
-  float* qs = reinterpret_cast<float*>(slots + 4 * tot);        // d
-  const int wave = threadIdx.x >> 6;
-  const bool vec = (d & 3) == 0;
-  const int count = *fb_count;
-  if (blockIdx.x == 0 && threadIdx.x == 0 && count > 0) {
-    atomicAdd(&g_fallback_total, (unsigned long long)count);
-    // heads alone did not do for calls of this kind on this operand: so many rows had to be redone
-    // here (more than one in 512) that it cost more than the two matrix products saved: a redone row
-    // costs some hundred times its share of a sweep -- from the next call on the sweeps use all three
-    const u32 bit = k == 1 ? 1u : 2u;
-    if (adapt && (adapt->heads_only & bit) && count >= 8 && (int64_t)count * 512 > na) atomicAnd(&adapt->heads_only, ~bit);
-  }
-  const FallbackSplit fs = fallback_split(count, nb, k, chunk_cols0, nchunk0, cap_keys);
-  const int64_t chunk_cols = fs.chunk_cols;
-  const int nchunk = fs.nchunk;
-  const int64_t tasks = (int64_t)count * nchunk;
-  for (int64_t task = blockIdx.x; task < tasks; task += gridDim.x) {
-    const int64_t f = task / nchunk;
-    const int ch = (int)(task - f * nchunk);
-    const int64_t row = fb_rows[f];
-    const int64_t c_begin = ch * chunk_cols, c_end = min(nb, c_begin + chunk_cols);
-    __syncthreads();
-    for (int t = threadIdx.x; t < d; t += 256) qs[t] = A[row * d + t];
-    WaveSelect<R> ws;
-    ws.init(slots + wave * tot, tot, k);
-    __syncthreads();
-    for (int64_t c0 = c_begin; c0 < c_end; c0 += 256) {
-      const int64_t c = c0 + threadIdx.x;
-      const bool valid = c < c_end;
-      const float val = valid ? canon_row<METRIC>(qs, B + c * d, d, vec) : 0.f;
-      ws.push(valid, make_key(val, (u32)c, METRIC));
-    }
-    ws.finish();
-    __syncthreads();
-    KeySink sink;
-    sink.idmap = nullptr; sink.metric = METRIC;
-    if (nchunk == 1) {
-      sink.keys = nullptr; sink.val = out.val; sink.id64 = out.id64; sink.idx32 = out.idx32;
-      block_rank_merge(slots, tot, 4, k, sink, row * (int64_t)k);
-    } else {
-      sink.keys = partial; sink.val = nullptr; sink.id64 = nullptr; sink.idx32 = nullptr;
-      block_rank_merge(slots, tot, 4, k, sink, task * (int64_t)k);
-    }
-  }
-}
-
-// The same fallback for d a multiple of 32 (every shape the matrix-core route serves), with the
-// columns staged through LDS: one row of B per lane read straight from memory makes every load
-// instruction touch 64 cache lines and the chain wait for each of them (6 us per redone row at
+// The columns are staged through LDS: one row of B per lane read straight from memory makes every
+// load instruction touch 64 cache lines and the chain wait for each of them (6 us per redone row at
 // 65536 x 96).  Here a tile of 256 rows of B x 32 dimensions is fetched with 8 lanes per row (128
 // consecutive bytes per request), written to LDS with a row stride of 36 floats (16-byte aligned,
 // conflict-free for the 16-byte reads that follow), and lane r continues the canon chain of row r
-// over those 32 dimensions -- the same values in the same order as canon_row, hence the same bits.
+// over those 32 dimensions -- the same values in the same order as canon_row, hence the same bits
+// (dimensions past d are zeros on both sides: fma(0, 0, acc) = acc).
 // The next tile chunk is in flight (registers) while the current one is summed.
 template <int R, int METRIC>
 __global__ __launch_bounds__(256) void canon_rows_tiled_kernel(const float* __restrict__ A,
@@ -1163,7 +1107,9 @@ __global__ __launch_bounds__(256) void canon_rows_tiled_kernel(const float* __re
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
   u64* slots = reinterpret_cast<u64*>(smem);                    // 4 * tot
   float* qs = reinterpret_cast<float*>(slots + 4 * tot);        // d
-  float* tile = qs + d;                                         // 2 x TR x LD
+  const int dp = (d + DC - 1) / DC * DC;
+  const bool vec = (d & 3) == 0;
+  float* tile = qs + dp;                                        // 2 x TR x LD
   const int tid = threadIdx.x, wave = tid >> 6;
   const int r_ld = tid >> 3, c_ld = tid & 7;                    // fetch: 8 lanes per row, 32 rows per pass
   const int count = *fb_count;
@@ -1185,15 +1131,23 @@ __global__ __launch_bounds__(256) void canon_rows_tiled_kernel(const float* __re
     const int64_t row = fb_rows[f];
     const int64_t c_begin = ch * chunk_cols, c_end = min(nb, c_begin + chunk_cols);
     __syncthreads();                                            // the task before is done with qs, tile and slots
-    for (int t = tid; t < d; t += 256) qs[t] = A[row * d + t];
+    for (int t = tid; t < dp; t += 256) qs[t] = t < d ? A[row * d + t] : 0.f;
     WaveSelect<R> ws;
     ws.init(slots + wave * tot, tot, k);
     u32x4 stg[8];
     auto fetch = [&](int64_t i0, int c0) {
+      const int c = c0 + c_ld * 4;
 #pragma unroll
       for (int j = 0; j < 8; ++j) {
         const int64_t r = min(i0 + j * 32 + r_ld, c_end - 1);   // rows past the end: masked at the push
-        stg[j] = *reinterpret_cast<const u32x4*>(B + r * d + c0 + c_ld * 4);
+        const float* __restrict__ src = B + r * d + c;
+        u32x4 w = {0u, 0u, 0u, 0u};
+        if (vec) { if (c < d) w = *reinterpret_cast<const u32x4*>(src); }
+        else {
+#pragma unroll
+          for (int e = 0; e < 4; ++e) if (c + e < d) w[e] = __float_as_uint(src[e]);
+        }
+        stg[j] = w;
       }
     };
     auto stash = [&](int buf) {
@@ -1294,8 +1248,11 @@ __global__ __launch_bounds__(64) void canon_rows_merge_kernel(const u64* __restr
 
 int64_t mfma_padded_rows(int64_t n) { return (n + 63) / 64 * 64; }
 
+int mfma_padded_dim(int d) { return (d + 31) / 32 * 32; }
+
+// (rows of at most 16 floats -- sub-vectors -- would be mostly padding)
 bool mfma_knn_supported(int d, int k) {
-  return d >= 32 && d % 32 == 0 && d <= 2048 && k <= 150;
+  return d > 16 && d <= 2048 && k <= 150;
 }
 
 int mfma_knn_kp(int k) {
@@ -1313,19 +1270,21 @@ bool stationary_d(int d) { return d == 32 || d == 64 || d == 96 || d == 128; }
 }  // namespace
 
 void launch_prep(const float* x, int64_t n, int d, unsigned short* hi, unsigned short* lo,
-                 float* norm, PrepInfo* info, hipStream_t st, bool try_heads_only) {
-  hipLaunchKernelGGL(prep_info_init_kernel, dim3(1), dim3(1), 0, st, info, try_heads_only ? 1u : 0u);
+                 float* norm, PrepInfo* info, hipStream_t st, bool try_heads_only, bool write_f16, bool keep_heads) {
+  hipLaunchKernelGGL(prep_info_init_kernel, dim3(1), dim3(1), 0, st, info, try_heads_only ? 1u : 0u, keep_heads ? 1u : 0u);
   if (n <= 0) return;
   const int64_t n_pad = mfma_padded_rows(n);
-  if (!stationary_d(d)) {                            // the tiled kernel reads panels
-    hipLaunchKernelGGL(prep_panel_kernel, dim3((unsigned)std::min<int64_t>(n_pad / 32, 4096)), dim3(256), 0,
-                       st, x, n, n_pad, d, hi, lo, norm, info);
+  const int dp = mfma_padded_dim(d);
+  const int rpb = 2048 / dp;                         // rows per group of the row-major kernel
+  if (!stationary_d(dp)) {                           // the tiled kernel reads panels
+    const dim3 grid((unsigned)std::min<int64_t>(n_pad / 32, 4096));
+    if (write_f16) hipLaunchKernelGGL((prep_panel_kernel<true>), grid, dim3(256), 0, st, x, n, n_pad, d, dp, hi, lo, norm, info);
+    else hipLaunchKernelGGL((prep_panel_kernel<false>), grid, dim3(256), 0, st, x, n, n_pad, d, dp, hi, lo, norm, info);
     return;
   }
-  const int rpb = 2048 / d;                          // d % 8 == 0
-  const int64_t ngroups = (n_pad + rpb - 1) / rpb;
-  hipLaunchKernelGGL(prep_kernel, dim3((unsigned)std::min<int64_t>(ngroups, 4096)), dim3(256), 0, st, x, n,
-                     n_pad, d, rpb, hi, lo, norm, info);
+  const dim3 grid((unsigned)std::min<int64_t>((n_pad + rpb - 1) / rpb, 4096));
+  if (write_f16) hipLaunchKernelGGL((prep_kernel<true>), grid, dim3(256), 0, st, x, n, n_pad, d, dp, rpb, hi, lo, norm, info);
+  else hipLaunchKernelGGL((prep_kernel<false>), grid, dim3(256), 0, st, x, n, n_pad, d, dp, rpb, hi, lo, norm, info);
 }
 
 namespace {
@@ -1344,7 +1303,7 @@ __host__ __device__ inline int heads_only_bit(int k) { return k == 1 ? 1 : 2; }
 
 MfmaPlan make_plan(int64_t na, int64_t nb, int k, int d) {
   MfmaPlan p;
-  p.kc = !stationary_d(d);
+  p.kc = !stationary_d(mfma_padded_dim(d));
   const int bm = p.kc ? 256 : 128, bn = p.kc ? 256 : 64;      // tile of one workgroup step
   p.kp = mfma_knn_kp(k);
   p.hbit = heads_only_bit(k);
@@ -1561,6 +1520,7 @@ static void launch_sweep(const MfmaPlan& p, const MfmaOperand& A, const MfmaOper
                          int metric, char* work, hipStream_t st) {
   if (p.kc) {   // both operand-precision variants, as below
     const bool one = !certainly_three(A, B), three = !certainly_one(A, B), f16 = B.try_heads_only && three;
+    d = mfma_padded_dim(d);
     if (metric == 0) {
       if (f16) launch_sweep_kc_t<0, MODE, 3>(p, A, B, d, work, st);
       if (one) launch_sweep_kc_t<0, MODE, 0>(p, A, B, d, work, st);
@@ -1577,7 +1537,7 @@ static void launch_sweep(const MfmaPlan& p, const MfmaOperand& A, const MfmaOper
     if (metric == 0) launch_sweep_k<KS, 0, MODE>(p, A, B, work, st);                \
     else             launch_sweep_k<KS, 1, MODE>(p, A, B, work, st);                \
   } while (0)
-  switch (d / 16) {
+  switch (mfma_padded_dim(d) / 16) {
     case 2: GO(2); break;
     case 4: GO(4); break;
     case 6: GO(6); break;
@@ -1622,24 +1582,30 @@ void launch_rerank(const MfmaOperand& A, const MfmaOperand& B, int d, int metric
   else        { if (metric == 0) RR(4, 0); else RR(4, 1); }
 #undef RR
   // rows whose shortlist could not be proven sufficient: canon over all columns
+  launch_canon_rows(A.x, A.n, B.x, B.n, d, metric, k, out, fb_count, fb_rows, fb_partial,
+                    eps_scale < 0.f ? nullptr : const_cast<PrepInfo*>(B.info), st);
+}
+
+void launch_canon_rows(const float* A, int64_t na, const float* B, int64_t nb, int d, int metric, int k,
+                       const SelectOut& out, const int* fb_count, const int* fb_rows, u64* fb_partial,
+                       PrepInfo* adapt, hipStream_t st) {
   const int tot = select_slots_for_k(k);
-  const bool tiled = d % 32 == 0;
-  const size_t sh2 = (size_t)4 * tot * sizeof(u64) + (size_t)d * sizeof(float) +
-                     (tiled ? (size_t)2 * 256 * 36 * sizeof(float) : 0);
-  const FallbackPlan fp = fallback_plan(A.n, B.n, k);
-  const int grid = (int)std::min<int64_t>(A.n * (fp.cap_keys > 0 ? 64 : fp.nchunk), 2048);   // (idle workgroups leave at once)
+  const size_t sh2 = (size_t)4 * tot * sizeof(u64) + (size_t)mfma_padded_dim(d) * sizeof(float) +
+                     (size_t)2 * 256 * 36 * sizeof(float);
+  const FallbackPlan fp = fallback_plan(na, nb, k);
+  const int grid = (int)std::min<int64_t>(na * (fp.cap_keys > 0 ? 64 : fp.nchunk), 2048);   // (idle workgroups leave at once)
 #define CR(RV, MET)                                                                              \
   do {                                                                                           \
-    auto kern = tiled ? &canon_rows_tiled_kernel<RV, MET> : &canon_rows_kernel<RV, MET>;         \
+    auto kern = &canon_rows_tiled_kernel<RV, MET>;                                               \
     if (sh2 > 48 * 1024)                                                                         \
       (void)hipFuncSetAttribute(reinterpret_cast<const void*>(kern),                             \
                                 hipFuncAttributeMaxDynamicSharedMemorySize, (int)sh2);           \
-    hipLaunchKernelGGL(kern, dim3(grid), dim3(256), sh2, st, A.x, B.x, B.n, d,                   \
+    hipLaunchKernelGGL(kern, dim3(grid), dim3(256), sh2, st, A, B, nb, d,                        \
                        k, tot, fp.chunk_cols, fp.nchunk, fp.cap_keys, fb_partial, out, fb_count, fb_rows, \
-                       eps_scale < 0.f ? nullptr : const_cast<PrepInfo*>(B.info), A.n);          \
+                       adapt, na);                                                               \
     if (fp.nchunk > 1 || fp.cap_keys > 0)                                                        \
-      hipLaunchKernelGGL((canon_rows_merge_kernel<RV, MET>), dim3((unsigned)std::min<int64_t>(A.n, 1024)), \
-                         dim3(64), (size_t)tot * sizeof(u64), st, fb_partial, B.n, fp.chunk_cols, \
+      hipLaunchKernelGGL((canon_rows_merge_kernel<RV, MET>), dim3((unsigned)std::min<int64_t>(na, 1024)), \
+                         dim3(64), (size_t)tot * sizeof(u64), st, fb_partial, nb, fp.chunk_cols, \
                          fp.nchunk, fp.cap_keys, k, tot, out, fb_count, fb_rows);                \
   } while (0)
   const int R2 = select_regs_for_slots(tot);
