@@ -627,11 +627,26 @@ int vs_refine(const float* x, int64_t nb, const float* q, int64_t nq, int32_t d,
 
 namespace {
 
-// Best row of B [nb, d] for every row of A [n, d] (k-nearest-rows with k = 1, in pieces of 2^20
-// rows): idx [n] and, if asked for, the canon value val [n].  `sc` is grown as needed.
+// Best row of B [nb, d] for every row of A [n, d]: idx [n] and, if asked for, the canon value val
+// [n].  `sc` is grown as needed.  again: B was prepared in the same place by the call before (what
+// that learnt of the fp16 heads still holds).
 int nearest_rows(const float* A, int64_t n, const float* B, int64_t nb, int d, int metric,
-                 int32_t* idx, float* val, Scratch& sc, hipStream_t st) {
+                 int32_t* idx, float* val, Scratch& sc, hipStream_t st, bool again = false) {
   constexpr int64_t kPiece = 1 << 20;
+  const bool small = knn_small(n, nb, d);
+  if (g_knn_path.load() != 1 && nearest_supported(d) && !small && (!val || metric == VS_METRIC_L2)) {
+    const size_t pb = planes_bytes(nb, d);
+    const int64_t piece = std::min(n, 4 * kPiece);
+    if (int rc = sc.reserve(pb + nearest_bytes(piece, nb) + nearest_bytes(n % piece, nb))) return rc;
+    char* base = static_cast<char*>(sc.p);
+    Planes p = carve_planes(base, nb, d);
+    launch_prep(B, nb, d, p.hi, p.lo, p.norm, p.info, st, true, true, again);
+    const MfmaOperand ob = operand(B, nb, p);
+    for (int64_t i0 = 0; i0 < n; i0 += piece)
+      launch_nearest(A + i0 * d, std::min(piece, n - i0), d, metric, ob, g_knn_eps_scale.load(), idx + i0,
+                     val ? val + i0 : nullptr, base + pb, st);
+    return VS_OK;
+  }
   const KnnPlan plan = knn_plan_pieces(n, kPiece, nb, d, 1, false, true);
   if (!plan.mfma) {
     // shapes the matrix-core kernels do not cover (sub-vectors of a few dimensions): fused canon
@@ -662,37 +677,56 @@ struct DeviceBuf {   // a plain allocation released on scope exit
   int alloc(size_t bytes) { HIP_TRY(hipMalloc(&p, std::max<size_t>(bytes, 256))); return VS_OK; }
 };
 
+// The objectives of `problems` k-means runs from their rounds' partial sums [niter][problems][256]:
+// objective[p * niter + r] (or null).  Waits for the stream.
+int kmeans_collect(const double* partial, const int* bad, int64_t n, int K, int niter, int problems,
+                   double* objective, hipStream_t st) {
+  int h_bad = 0;
+  HIP_TRY(hipMemcpyAsync(&h_bad, bad, sizeof(int), hipMemcpyDeviceToHost, st));
+  std::vector<double> h((size_t)(objective ? niter : 0) * problems * 256);
+  if (objective) HIP_TRY(hipMemcpyAsync(h.data(), partial, h.size() * sizeof(double), hipMemcpyDeviceToHost, st));
+  HIP_TRY(hipStreamSynchronize(st));
+  if (h_bad != 0) return fail(VS_ERR_DEVICE, "k-means: assignment produced a centroid outside [0, %d)", K);
+  if (objective)
+    for (int r = 0; r < niter; ++r)
+      for (int p = 0; p < problems; ++p) {
+        double sum = 0.0;
+        for (int t = 0; t < 256; ++t) sum += h[((size_t)r * problems + p) * 256 + t];
+        objective[(size_t)p * niter + r] = sum / (double)n;
+      }
+  return VS_OK;
+}
+
 // niter rounds of Lloyd's iteration on device data.  dev_buf: idx [n] int32 | val [n] fp32 |
 // order [n] int32 | off [K + 1] int64, carved by the caller; sc: scratch of the assignment.
 int kmeans_rounds(const float* x, int64_t n, int d, int K, int niter, float* centroids,
                   double* objective, int32_t* idx, float* val, int32_t* order, int64_t* off,
                   Scratch& sc, hipStream_t st) {
   // Up to 16384 centroids the bookkeeping of a round (the objective, and every centroid's
-  // vectors in ascending order) stays on the device; beyond, the host does it.
+  // vectors in ascending order) stays on the device and nothing is read back between rounds: the
+  // objective's partial sums of all rounds are fetched at the end.  Beyond, the host does it.
   const bool on_device = K <= 16384 && n > 0;
-  DeviceBuf sortbuf;
-  if (on_device) { if (int rc = sortbuf.alloc(kmeans_sort_bytes(n, K))) return rc; }
+  DeviceBuf work;
+  Carver cw;
+  const size_t o_sort = cw.take(kmeans_sort_bytes(K, 1)), o_bad = cw.take(sizeof(int64_t)),
+               o_obj = cw.take((size_t)niter * 256 * sizeof(double)),
+               o_part = cw.take(segmented_mean_partial_bytes(n, d, K, 1));
+  char* wb = nullptr;
+  if (on_device) {
+    if (int rc = work.alloc(cw.off)) return rc;
+    wb = static_cast<char*>(work.p);
+    launch_fill_u64(reinterpret_cast<u64*>(wb + o_bad), 1, 0ull, st);
+  }
   std::vector<int32_t> h_idx(on_device ? 0 : (size_t)n), h_order(on_device ? 0 : (size_t)n);
   std::vector<float> h_val(on_device ? 0 : (size_t)n);
-  std::vector<int64_t> h_off((size_t)K + 1), cursor((size_t)K);
+  std::vector<int64_t> h_off(on_device ? 0 : (size_t)K + 1), cursor(on_device ? 0 : (size_t)K);
   for (int r = 0; r < niter; ++r) {
     // (1) nearest centroid of every vector: canon L2, ties to the smaller centroid number
-    if (int rc = nearest_rows(x, n, centroids, K, d, VS_METRIC_L2, idx, val, sc, st)) return rc;
+    if (int rc = nearest_rows(x, n, centroids, K, d, VS_METRIC_L2, idx, val, sc, st, r > 0)) return rc;
     if (on_device) {
-      int64_t* scal = nullptr;
-      double* partial = nullptr;
-      launch_kmeans_sort(idx, val, n, K, static_cast<char*>(sortbuf.p), order, off, &scal, &partial, st);
-      int64_t h_scal[2];
-      double h_part[256];
-      HIP_TRY(hipMemcpyAsync(h_scal, scal, sizeof(h_scal), hipMemcpyDeviceToHost, st));
-      HIP_TRY(hipMemcpyAsync(h_part, partial, sizeof(h_part), hipMemcpyDeviceToHost, st));
-      HIP_TRY(hipStreamSynchronize(st));
-      if (h_scal[1] != 0) return fail(VS_ERR_DEVICE, "k-means: assignment produced a centroid outside [0, %d)", K);
-      double obj = 0.0;
-      for (int t = 0; t < 256; ++t) obj += h_part[t];
-      if (objective) objective[r] = obj / (double)n;
-      if (int rc = sc.reserve(segmented_mean_partial_bytes(n, d, K, h_scal[0]))) return rc;
-      launch_segmented_mean(x, d, order, off, K, h_scal[0], centroids, static_cast<double*>(sc.p), st);
+      launch_kmeans_sort(idx, val, n, K, wb + o_sort, order, off, reinterpret_cast<int*>(wb + o_bad),
+                         reinterpret_cast<double*>(wb + o_obj) + (size_t)r * 256, st);
+      launch_segmented_mean(x, n, d, order, off, K, 1, centroids, reinterpret_cast<double*>(wb + o_part), st);
       continue;
     }
     HIP_TRY(hipMemcpyAsync(h_idx.data(), idx, (size_t)n * sizeof(int32_t), hipMemcpyDeviceToHost, st));
@@ -709,20 +743,63 @@ int kmeans_rounds(const float* x, int64_t n, int d, int K, int niter, float* cen
       ++h_off[(size_t)j + 1];
     }
     if (objective) objective[r] = n > 0 ? obj / (double)n : 0.0;
-    int64_t largest = 0;
-    for (int j = 0; j < K; ++j) largest = std::max(largest, h_off[(size_t)j + 1]);
     for (int j = 0; j < K; ++j) { h_off[(size_t)j + 1] += h_off[(size_t)j]; cursor[(size_t)j] = h_off[(size_t)j]; }
     for (int64_t i = 0; i < n; ++i) h_order[(size_t)cursor[(size_t)h_idx[(size_t)i]]++] = (int32_t)i;
     HIP_TRY(hipMemcpyAsync(order, h_order.data(), (size_t)n * sizeof(int32_t), hipMemcpyHostToDevice, st));
     HIP_TRY(hipMemcpyAsync(off, h_off.data(), h_off.size() * sizeof(int64_t), hipMemcpyHostToDevice, st));
     // (2) every centroid moves to the mean of its vectors (the assignment's scratch is free
     // again: it holds the block sums of clusters longer than one summation block)
-    if (int rc = sc.reserve(segmented_mean_partial_bytes(n, d, K, largest))) return rc;
-    launch_segmented_mean(x, d, order, off, K, largest, centroids, static_cast<double*>(sc.p), st);
+    if (int rc = sc.reserve(segmented_mean_partial_bytes(n, d, K, 1))) return rc;
+    launch_segmented_mean(x, n, d, order, off, K, 1, centroids, static_cast<double*>(sc.p), st);
     HIP_TRY(hipStreamSynchronize(st));   // the host arrays are reused by the next round
   }
+  if (on_device)
+    if (int rc = kmeans_collect(reinterpret_cast<const double*>(wb + o_obj), reinterpret_cast<const int*>(wb + o_bad),
+                                n, K, niter, 1, objective, st))
+      return rc;
   HIP_TRY(hipStreamSynchronize(st));     // the centroids are final when the call returns
   HIP_TRY(hipGetLastError());
+  return VS_OK;
+}
+
+// All sub-quantizers of a product quantizer at once (res [M][n][dsub], codebooks [M][K][dsub]): one
+// launch of every step of a round serves them all, where one problem after the other left most of
+// the chip idle (a round of one is some ten launches of a few microseconds' work).  Sub-quantizers are
+// taken in groups that keep the work space near 1 GiB.
+int kmeans_subquantizers(const float* res, int64_t n, int dsub, int M, int K, int niter, float* codebooks,
+                         double* objective, hipStream_t st) {
+  const size_t each = (size_t)n * (1 + 2 * sizeof(float)) + kmeans_sort_bytes(K, 1) +
+                      segmented_mean_partial_bytes(n, dsub, K, 1);
+  const int G = (int)std::max<size_t>(1, std::min<size_t>((size_t)M, (1ull << 30) / each));
+  Carver cw;
+  const size_t o_idx = cw.take((size_t)G * n), o_val = cw.take((size_t)G * n * sizeof(float)),
+               o_order = cw.take((size_t)G * n * sizeof(int32_t)), o_off = cw.take((size_t)G * (K + 1) * sizeof(int64_t)),
+               o_sort = cw.take(kmeans_sort_bytes(K, G)), o_bad = cw.take(sizeof(int64_t)),
+               o_obj = cw.take((size_t)niter * G * 256 * sizeof(double)),
+               o_part = cw.take(segmented_mean_partial_bytes(n, dsub, K, G));
+  DeviceBuf work;
+  if (int rc = work.alloc(cw.off)) return rc;
+  char* wb = static_cast<char*>(work.p);
+  uint8_t* idx = reinterpret_cast<uint8_t*>(wb + o_idx);
+  float* val = reinterpret_cast<float*>(wb + o_val);
+  int32_t* order = reinterpret_cast<int32_t*>(wb + o_order);
+  int64_t* off = reinterpret_cast<int64_t*>(wb + o_off);
+  double* obj = reinterpret_cast<double*>(wb + o_obj);
+  for (int m0 = 0; m0 < M; m0 += G) {
+    const int g = std::min(G, M - m0);
+    const float* x = res + (size_t)m0 * n * dsub;
+    float* cb = codebooks + (size_t)m0 * K * dsub;
+    launch_fill_u64(reinterpret_cast<u64*>(wb + o_bad), 1, 0ull, st);
+    for (int r = 0; r < niter; ++r) {
+      launch_pq_nearest(x, n, dsub * g, dsub, nullptr, nullptr, cb, K, g, idx, 1, n, val, st);
+      launch_kmeans_sort_bytes(idx, val, n, K, g, wb + o_sort, order, off, reinterpret_cast<int*>(wb + o_bad),
+                               obj + (size_t)r * g * 256, st);
+      launch_segmented_mean(x, n, dsub, order, off, K, g, cb, reinterpret_cast<double*>(wb + o_part), st);
+    }
+    if (int rc = kmeans_collect(obj, reinterpret_cast<const int*>(wb + o_bad), n, K, niter, g,
+                                objective ? objective + (size_t)m0 * niter : nullptr, st))
+      return rc;
+  }
   return VS_OK;
 }
 
@@ -800,7 +877,10 @@ int vs_ivfpq_train(const float* x, int64_t n, int32_t d, int32_t metric, int32_t
   if (int rc = nearest_rows(x, n, centroids, nlist, d, metric, idx, nullptr, sc, st)) return rc;
   launch_residual_slices(x, n, d, dsub, centroids, idx, res, st);
   // 4. one k-means per sub-quantizer on its slice of the residuals
-  for (int m = 0; m < M; ++m) {
+  if (pq_nearest_supported(dsub, K) && g_knn_path.load() != 1 && niter > 0) {
+    if (int rc = kmeans_subquantizers(res, n, dsub, M, K, niter, codebooks, objective ? objective + niter : nullptr, st))
+      return rc;
+  } else for (int m = 0; m < M; ++m) {
     if (int rc = kmeans_rounds(res + (size_t)m * n * dsub, n, dsub, K, niter,
                                codebooks + (size_t)m * K * dsub,
                                objective ? objective + (size_t)(1 + m) * niter : nullptr, idx, val,
@@ -919,6 +999,10 @@ int ivf_assign_and_place(vs_ivfpq* ix, const float* x, int64_t n, size_t extra, 
   // fp16 heads alone and learn from a call's fallback count whether that does for this data; a
   // short first call keeps the price of finding out small.
   constexpr int64_t kProbePiece = 8192;
+  // one sweep that keeps the best row only (no pieces to learn from: its undecided vectors are
+  // swept again with more products, not redone in full)
+  const bool one_sweep = g_knn_path.load() != 1 && ix->has_planes && nearest_supported(g.d) && !knn_small(n, g.nlist, g.d);
+  const int64_t sweep_piece = std::min<int64_t>(n, 4 * kAssignPiece);
   const int64_t first_piece = !ix->assign_probed && n > 4 * kProbePiece ? kProbePiece : 0;
   KnnPlan plan = knn_plan_pieces(n - first_piece, kAssignPiece, g.nlist, g.d, 1, ix->has_planes, true);
   if (first_piece > 0) {
@@ -926,6 +1010,7 @@ int ivf_assign_and_place(vs_ivfpq* ix, const float* x, int64_t n, size_t extra, 
     plan.bytes = std::max(plan.bytes, probe.bytes);
   }
   if (!plan.mfma) plan.bytes = 0;
+  if (one_sweep) plan.bytes = std::max(nearest_bytes(sweep_piece, g.nlist), nearest_bytes(n % sweep_piece, g.nlist));
   Carver cv;
   const size_t o_knn = cv.take(plan.bytes);
   const size_t o_keys = cv.take((size_t)n * sizeof(u64));
@@ -933,7 +1018,7 @@ int ivf_assign_and_place(vs_ivfpq* ix, const float* x, int64_t n, size_t extra, 
   const size_t o_extra = cv.take(extra);
   const size_t o_dest = cv.take((size_t)n * sizeof(int64_t));
   const size_t o_off = cv.take(((size_t)g.nlist + 1) * sizeof(int64_t));
-  const size_t o_place = cv.take(ivf_place_work_bytes(n, g.nlist));
+  const size_t o_place = cv.take(ivf_place_work_bytes(n));
   if (int rc = ix->scratch.reserve(cv.off)) return rc;
   char* base = static_cast<char*>(ix->scratch.p);
   u64* keys = reinterpret_cast<u64*>(base + o_keys);
@@ -942,7 +1027,12 @@ int ivf_assign_and_place(vs_ivfpq* ix, const float* x, int64_t n, size_t extra, 
   pl->dest = reinterpret_cast<int64_t*>(base + o_dest);
   pl->new_off = reinterpret_cast<int64_t*>(base + o_off);
 
-  if (plan.mfma) {
+  if (one_sweep) {
+    const MfmaOperand ob = operand(ix->centroids, g.nlist, ix->c_planes);
+    for (int64_t i0 = 0; i0 < n; i0 += sweep_piece)
+      launch_nearest(x + i0 * g.d, std::min(sweep_piece, n - i0), g.d, cmetric, ob, g_knn_eps_scale.load(),
+                     pl->list_of + i0, nullptr, base + o_knn, st);
+  } else if (plan.mfma) {
     for (int64_t i0 = 0; i0 < n;) {
       const int64_t ni = i0 == 0 && first_piece > 0 ? first_piece : std::min(kAssignPiece, n - i0);
       SelectOut o;

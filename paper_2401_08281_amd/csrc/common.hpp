@@ -308,6 +308,20 @@ static inline int select_regs_for_slots(int tot) { return tot <= 256 ? tot / 64 
 // scratch memory by the compiler; an ext-vector type stays in registers)
 typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
 
+// ---- stable ranking inside a wavefront -------------------------------------------
+// Among the lanes with `valid` and an equal key (below 2^bits): this lane's rank by lane number, and
+// their number.  One ballot per key bit, whatever the number of different keys.
+struct WaveRank { int rank, count; };
+__device__ __forceinline__ WaveRank wave_rank(bool valid, u32 key, int bits) {
+  u64 same = __builtin_amdgcn_ballot_w64(valid);
+  for (int b = 0; b < bits; ++b) {
+    const bool on = (key >> b) & 1u;
+    const u64 m = __builtin_amdgcn_ballot_w64(on);
+    same &= on ? m : ~m;
+  }
+  return {(int)__popcll(same & ((1ull << lane_id()) - 1ull)), (int)__popcll(same)};
+}
+
 // ---- inverted-list storage ------------------------------------------------------
 // list that owns storage position p: the l with off[l] <= p < off[l+1]
 __device__ __forceinline__ int list_of_position(const int64_t* __restrict__ off, int nlist,

@@ -87,9 +87,9 @@ size_t ivfpq_query_table_bytes(const IvfpqDims& g, int64_t nq);
 // Slots of n newly assigned vectors in the grown inverted lists, computed on the device:
 // dest[i] = slot of vector i (behind its list's old entries, new vectors of a list in batch order),
 // new_off [nlist + 1] = offsets of the grown lists.  list_of [n] (n < 2^31), old_off [nlist + 1],
-// work: ivf_place_work_bytes(n, nlist) bytes, all device memory.  Returns the device address of a
+// work: ivf_place_work_bytes(n) bytes, all device memory.  Returns the device address of a
 // flag that is non-zero once the kernels have run if some list_of[i] is outside [0, nlist).
-size_t ivf_place_work_bytes(int64_t n, int nlist);
+size_t ivf_place_work_bytes(int64_t n);
 int* launch_ivf_place(const int32_t* list_of, int64_t n, int nlist, const int64_t* old_off, char* work,
                       int64_t* dest, int64_t* new_off, hipStream_t st);
 // cdist[a][p] = <q_a, c_{probes[a][p]}> as one fp32 fused-multiply-add chain in dimension order
@@ -219,17 +219,19 @@ void launch_ivfsq8_scan(int d, int metric, const float* q, int64_t nq, const flo
 // ---- kernels_train.hip ---------------------------------------------------------
 // centroids[j] <- mean of the rows x[order[off[j] .. off[j + 1])] (float64 sum in that order, in
 // blocks of 4096 rows whose sums are added in block order); a centroid with an empty range keeps
-// its value.  `largest` = the largest range's length; `partial` = work space of
-// segmented_mean_partial_bytes (may be null when that is 0)
-size_t segmented_mean_partial_bytes(int64_t n, int d, int K, int64_t largest);
-void launch_segmented_mean(const float* x, int d, const int32_t* order, const int64_t* off, int K,
-                           int64_t largest, float* centroids, double* partial, hipStream_t st);
+// its value.  `problems` (d <= 32 where more than one) independent means of n rows each, arrays one
+// after the other.  `partial` = work space of segmented_mean_partial_bytes (may be null when that is 0)
+size_t segmented_mean_partial_bytes(int64_t n, int d, int K, int problems);
+void launch_segmented_mean(const float* x, int64_t n, int d, const int32_t* order, const int64_t* off, int K,
+                           int problems, float* centroids, double* partial, hipStream_t st);
 // stable counting sort of the assignment idx [n] by centroid (K <= 16384) and the float64 sum
-// of val [n]: order [n], off [K + 1]; scal[0] = largest cluster, scal[1] != 0 if an
-// assignment was outside [0, K); partial [256] sums to the sum of val
-size_t kmeans_sort_bytes(int64_t n, int K);
+// of val [n]: order [n], off [K + 1]; *bad is set if an assignment was outside [0, K);
+// partial [256] sums to the sum of val.  The second form: `problems` of them, idx as bytes.
+size_t kmeans_sort_bytes(int K, int problems);
 void launch_kmeans_sort(const int32_t* idx, const float* val, int64_t n, int K, char* work, int32_t* order,
-                        int64_t* off, int64_t** scal_out, double** partial_out, hipStream_t st);
+                        int64_t* off, int* bad, double* partial, hipStream_t st);
+void launch_kmeans_sort_bytes(const uint8_t* idx, const float* val, int64_t n, int K, int problems, char* work,
+                              int32_t* order, int64_t* off, int* bad, double* partial, hipStream_t st);
 // out[m][i][:] = (x[i] - centroids[list_of[i]])[m * dsub : (m + 1) * dsub], out is [d / dsub][n][dsub]
 void launch_residual_slices(const float* x, int64_t n, int d, int dsub, const float* centroids,
                             const int32_t* list_of, float* out, hipStream_t st);

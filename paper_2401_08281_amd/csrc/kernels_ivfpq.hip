@@ -9,23 +9,22 @@
 namespace {
 
 // ---------------------------------------------------------------------------
-// PQ encoding (Sec. 4.1 product quantizer; Sec. 5.1 residual encoding).
+// PQ encoding (Sec. 4.1 product quantizer; Sec. 5.1 residual encoding) of sub-vectors
+// too long for the matrix-core kernel (pq_nearest_kernel).
 // One lane per (vector, sub-quantizer m); a workgroup covers 256 vectors of
 // one m and keeps that sub-codebook in LDS, read as broadcasts.  The residual
 // is one fp32 subtraction per component; the nearest codeword is taken on the
 // canon chain (diff, fma) over the dsub components; a strict '<' while walking
 // j upward keeps the smaller code on ties.
 // ---------------------------------------------------------------------------
-template <int DSUB>
 __global__ __launch_bounds__(256) void pq_encode_kernel(const float* __restrict__ x, int64_t n,
-                                                        int d, int dsub_rt, int K,
+                                                        int d, int dsub, int K,
                                                         const int32_t* __restrict__ list_of,
                                                         const float* __restrict__ centroids,
                                                         const float* __restrict__ codebooks, int M,
                                                         uint8_t* __restrict__ tmp_codes) {
   extern __shared__ __attribute__((aligned(16))) float T[];  // [K][dsub]
   const int m = blockIdx.y;
-  const int dsub = DSUB > 0 ? DSUB : dsub_rt;
   const float* __restrict__ Tm = codebooks + (int64_t)m * K * dsub;
   for (int e = threadIdx.x; e < K * dsub; e += 256) T[e] = Tm[e];
   __syncthreads();
@@ -35,29 +34,14 @@ __global__ __launch_bounds__(256) void pq_encode_kernel(const float* __restrict_
   const float* __restrict__ c = centroids + (int64_t)list_of[i] * d + m * dsub;
   int best = 0;
   float bd = __builtin_inff();
-  if (DSUB > 0) {
-    float r[DSUB > 0 ? DSUB : 1];
-#pragma unroll
-    for (int u = 0; u < DSUB; ++u) r[u] = xi[u] - c[u];
-    for (int j = 0; j < K; ++j) {
-      float acc = 0.f;
-#pragma unroll
-      for (int u = 0; u < DSUB; ++u) {
-        const float diff = r[u] - T[j * DSUB + u];
-        acc = __builtin_fmaf(diff, diff, acc);
-      }
-      if (acc < bd) { bd = acc; best = j; }
+  for (int j = 0; j < K; ++j) {
+    float acc = 0.f;
+    for (int u = 0; u < dsub; ++u) {
+      const float r = xi[u] - c[u];
+      const float diff = r - T[j * dsub + u];
+      acc = __builtin_fmaf(diff, diff, acc);
     }
-  } else {
-    for (int j = 0; j < K; ++j) {
-      float acc = 0.f;
-      for (int u = 0; u < dsub; ++u) {
-        const float r = xi[u] - c[u];
-        const float diff = r - T[j * dsub + u];
-        acc = __builtin_fmaf(diff, diff, acc);
-      }
-      if (acc < bd) { bd = acc; best = j; }
-    }
+    if (acc < bd) { bd = acc; best = j; }
   }
   tmp_codes[i * M + m] = (uint8_t)best;
 }
@@ -1746,6 +1730,10 @@ void launch_pq_encode(const IvfpqDims& g, const float* x, int64_t n, const int32
                       const float* centroids, const float* codebooks, uint8_t* tmp_codes,
                       hipStream_t st) {
   if (n <= 0) return;
+  if (pq_nearest_supported(g.dsub, g.K)) {
+    launch_pq_nearest(x, n, g.d, g.dsub, centroids, list_of, codebooks, g.K, g.M, tmp_codes, g.M, 1, nullptr, st);
+    return;
+  }
   const dim3 grid((unsigned)((n + 255) / 256), (unsigned)g.M), block(256);
   const size_t shmem = (size_t)g.K * g.dsub * sizeof(float);
   if (shmem > 48 * 1024) {
@@ -1753,19 +1741,8 @@ void launch_pq_encode(const IvfpqDims& g, const float* x, int64_t n, const int32
                        centroids, codebooks, g.M, tmp_codes);
     return;
   }
-#define LAUNCH(DS) \
-  hipLaunchKernelGGL((pq_encode_kernel<DS>), grid, block, shmem, st, x, n, g.d, g.dsub, g.K, list_of, \
-                     centroids, codebooks, g.M, tmp_codes)
-  switch (g.dsub) {
-    case 2: LAUNCH(2); break;
-    case 3: LAUNCH(3); break;
-    case 4: LAUNCH(4); break;
-    case 8: LAUNCH(8); break;
-    case 12: LAUNCH(12); break;
-    case 16: LAUNCH(16); break;
-    default: LAUNCH(0); break;
-  }
-#undef LAUNCH
+  hipLaunchKernelGGL(pq_encode_kernel, grid, block, shmem, st, x, n, g.d, g.dsub, g.K, list_of, centroids,
+                     codebooks, g.M, tmp_codes);
 }
 
 void launch_relayout(const IvfpqDims& g, const uint8_t* old_codes, const int64_t* old_ids,

@@ -11,9 +11,9 @@
 //   place_colscan_kernel  per digit, exclusive running sum down the chunks (in place) and its total
 //   place_digit_offsets_kernel  exclusive sum of the totals: first slot of every digit
 //   place_scatter_kernel  one wavefront per chunk walks over its positions in order, 64 at a
-//                         time; lanes with the same digit are ranked by lane number (ballot)
-// then per-list counts (atomics: a count does not depend on order), two prefix sums over the
-// lists, and dest from each vector's rank in the sorted batch.
+//                         time; lanes with the same digit are ranked by lane number (ballots)
+// then the grown offsets from the places where the list changes in the sorted batch, and dest from
+// each vector's rank in it.
 #include <algorithm>
 
 #include "common.hpp"
@@ -45,17 +45,28 @@ __global__ __launch_bounds__(256) void place_hist_kernel(const int32_t* __restri
   for (int j = threadIdx.x; j < kBuckets; j += 256) mat[(int64_t)blockIdx.x * kBuckets + j] = h[j];
 }
 
-__global__ __launch_bounds__(256) void place_colscan_kernel(int32_t* __restrict__ mat, int nchunk,
-                                                            int64_t* __restrict__ cnt) {
-  const int j = blockIdx.x * 256 + threadIdx.x;
-  if (j >= kBuckets) return;
+// 64 digits per workgroup; wavefront s of 16 first sums, then rewrites its sixteenth of the chunks
+// (1024 chunks x 4096 digits with one thread per digit: 256 us, all of it latency)
+__global__ __launch_bounds__(1024) void place_colscan_kernel(int32_t* __restrict__ mat, int nchunk,
+                                                             int64_t* __restrict__ cnt) {
+  __shared__ int32_t part[16][64];
+  const int s = threadIdx.x >> 6, lane = threadIdx.x & 63;
+  const int j = blockIdx.x * 64 + lane, per = (nchunk + 15) / 16;
+  const int c0 = min(nchunk, s * per), c1 = min(nchunk, c0 + per);
+  int32_t sum = 0;
+#pragma unroll 16
+  for (int c = c0; c < c1; ++c) sum += mat[(int64_t)c * kBuckets + j];
+  part[s][lane] = sum;
+  __syncthreads();
   int32_t run = 0;
-  for (int c = 0; c < nchunk; ++c) {
+  for (int u = 0; u < s; ++u) run += part[u][lane];
+#pragma unroll 16
+  for (int c = c0; c < c1; ++c) {
     const int32_t v = mat[(int64_t)c * kBuckets + j];
     mat[(int64_t)c * kBuckets + j] = run;
     run += v;
   }
-  cnt[j] = run;
+  if (s == 15) cnt[j] = run;
 }
 
 // one workgroup of 256: thread t owns digits [16 t, 16 t + 16)
@@ -91,95 +102,60 @@ __global__ __launch_bounds__(64) void place_scatter_kernel(const int32_t* __rest
       const int32_t key = keys[i];
       if (key >= 0 && key < nlist) dg = digit_of(key, shift);   // (others were flagged by the histogram pass)
     }
-    u64 todo = __builtin_amdgcn_ballot_w64(dg >= 0);
-    while (todo != 0) {                                 // one round per distinct digit among the 64
-      const int leader = __builtin_ctzll(todo);
-      const int32_t k = __shfl(dg, leader);
-      const u64 same = __builtin_amdgcn_ballot_w64(dg == k);
-      const int base = next[k];
-      if (dg == k) out[base + __popcll(same & ((1ull << lane) - 1ull))] = i;
-      wave_lds_sync();                                  // everyone has read the slot before it moves
-      if (lane == leader) next[k] = base + __popcll(same);
-      wave_lds_sync();
-      todo &= ~same;
-    }
+    const WaveRank r = wave_rank(dg >= 0, (u32)dg, kDigitBits);
+    int slot = 0;
+    if (dg >= 0) slot = next[dg] + r.rank;
+    wave_lds_sync();                                    // everyone has read the counters before they move
+    if (dg >= 0 && r.rank == 0) next[dg] = slot + r.count;
+    if (dg >= 0) out[slot] = i;
+    wave_lds_sync();
   }
 }
 
-__global__ __launch_bounds__(256) void place_zero_kernel(int32_t* __restrict__ p, int64_t n) {
-  const int64_t i = blockIdx.x * 256ll + threadIdx.x;
-  if (i < n) p[i] = 0;
-}
-
-__global__ __launch_bounds__(256) void place_count_kernel(const int32_t* __restrict__ keys, int64_t n, int nlist,
-                                                          int32_t* __restrict__ cnt) {
-  const int64_t i = blockIdx.x * 256ll + threadIdx.x;
-  if (i >= n) return;
-  const int32_t l = keys[i];
-  if (l >= 0 && l < nlist) atomicAdd(&cnt[l], 1);
-}
-
-// One workgroup of 1024: thread t owns lists [t * per, (t + 1) * per).
-//   first_new[l] = number of new vectors in lists before l (their first rank in the sorted batch)
-//   new_off[l]   = first slot of list l in the grown store = sum over lists before l of old size + new count
-__global__ __launch_bounds__(1024) void place_list_offsets_kernel(const int32_t* __restrict__ cnt,
-                                                                  const int64_t* __restrict__ old_off, int nlist,
-                                                                  int64_t* __restrict__ first_new,
-                                                                  int64_t* __restrict__ new_off) {
-  __shared__ int64_t part_new[1024], part_all[1024];
-  const int t = threadIdx.x, per = (nlist + 1023) / 1024;
-  const int l0 = min(nlist, t * per), l1 = min(nlist, l0 + per);
-  int64_t s_new = 0, s_all = 0;
-  for (int l = l0; l < l1; ++l) {
-    s_new += cnt[l];
-    s_all += cnt[l] + (old_off[l + 1] - old_off[l]);
-  }
-  part_new[t] = s_new; part_all[t] = s_all;
-  __syncthreads();
-  int64_t b_new = 0, b_all = 0;
-  for (int u = 0; u < t; ++u) { b_new += part_new[u]; b_all += part_all[u]; }
-  for (int l = l0; l < l1; ++l) {
-    first_new[l] = b_new; new_off[l] = b_all;
-    b_new += cnt[l];
-    b_all += cnt[l] + (old_off[l + 1] - old_off[l]);
-  }
-  if (l1 == nlist && l0 < nlist) new_off[nlist] = b_all;   // (the thread that owns the last list)
-  if (nlist == 0 && t == 0) new_off[0] = 0;
+// With first_new(l) = the rank of list l's first new vector in the sorted batch (what an empty list
+// would have), known from the places where the list changes, the grown lists begin at
+//   new_off[l] = old_off[l] + first_new(l):   old sizes and new counts of the lists before l.
+// Thread p looks at ranks p - 1 and p and fills the lists in between (p = n: the rest).
+__global__ __launch_bounds__(256) void place_first_kernel(const int32_t* __restrict__ order,
+                                                          const int32_t* __restrict__ keys, int64_t n, int nlist,
+                                                          const int64_t* __restrict__ old_off,
+                                                          int64_t* __restrict__ new_off, const int* __restrict__ bad) {
+  const int64_t p = blockIdx.x * 256ll + threadIdx.x;
+  if (p > n || *bad) return;
+  const int before = p > 0 ? keys[order[p - 1]] : -1, here = p < n ? keys[order[p]] : nlist;
+  for (int l = before + 1; l <= here; ++l) new_off[l] = old_off[l] + p;
 }
 
 // the vector at rank p of the sorted batch goes behind its list's old entries and the p -
-// first_new[l] new ones before it
+// first_new(l) new ones before it: new_off[l] + old size + p - first_new(l) = old_off[l + 1] + p
 __global__ __launch_bounds__(256) void place_dest_kernel(const int32_t* __restrict__ order,
                                                          const int32_t* __restrict__ keys, int64_t n, int nlist,
-                                                         const int64_t* __restrict__ first_new,
-                                                         const int64_t* __restrict__ new_off,
                                                          const int64_t* __restrict__ old_off,
+                                                         const int* __restrict__ bad,
                                                          int64_t* __restrict__ dest) {
   const int64_t p = blockIdx.x * 256ll + threadIdx.x;
-  if (p >= n) return;
+  if (p >= n || *bad) return;
   const int32_t i = order[p];
   const int32_t l = keys[i];
   if (l < 0 || l >= nlist) return;
-  dest[i] = new_off[l] + (old_off[l + 1] - old_off[l]) + (p - first_new[l]);
+  dest[i] = old_off[l + 1] + p;   // = new_off[l] + old size + (p - first_new[l])
 }
 
 struct PlaceWork {
-  int32_t *order_a, *order_b, *mat, *cnt_new;
-  int64_t *digit_cnt, *digit_off, *first_new;
+  int32_t *order_a, *order_b, *mat;
+  int64_t *digit_cnt, *digit_off;
   int* bad;
   size_t bytes;
 };
-PlaceWork carve(char* base, int64_t n, int nlist) {
+PlaceWork carve(char* base, int64_t n) {
   PlaceWork w;
   size_t o = 0;
   auto take = [&](size_t b) { const size_t at = o; o += (b + 255) & ~(size_t)255; return base ? base + at : nullptr; };
   w.order_a = reinterpret_cast<int32_t*>(take((size_t)n * sizeof(int32_t)));
   w.order_b = reinterpret_cast<int32_t*>(take((size_t)n * sizeof(int32_t)));
   w.mat = reinterpret_cast<int32_t*>(take((size_t)kMaxChunks * kBuckets * sizeof(int32_t)));
-  w.cnt_new = reinterpret_cast<int32_t*>(take(((size_t)nlist + 1) * sizeof(int32_t)));
   w.digit_cnt = reinterpret_cast<int64_t*>(take((size_t)kBuckets * sizeof(int64_t)));
   w.digit_off = reinterpret_cast<int64_t*>(take((size_t)kBuckets * sizeof(int64_t)));
-  w.first_new = reinterpret_cast<int64_t*>(take(((size_t)nlist + 1) * sizeof(int64_t)));
   w.bad = reinterpret_cast<int*>(take(sizeof(int64_t)));
   w.bytes = o;
   return w;
@@ -187,11 +163,11 @@ PlaceWork carve(char* base, int64_t n, int nlist) {
 
 }  // namespace
 
-size_t ivf_place_work_bytes(int64_t n, int nlist) { return carve(nullptr, n, nlist).bytes; }
+size_t ivf_place_work_bytes(int64_t n) { return carve(nullptr, n).bytes; }
 
 int* launch_ivf_place(const int32_t* list_of, int64_t n, int nlist, const int64_t* old_off, char* work,
                       int64_t* dest, int64_t* new_off, hipStream_t st) {
-  const PlaceWork w = carve(work, n, nlist);
+  const PlaceWork w = carve(work, n);
   launch_fill_u64(reinterpret_cast<u64*>(w.bad), 1, 0ull, st);
   const int64_t chunk = std::max<int64_t>(1024, ((n + kMaxChunks - 1) / kMaxChunks + 63) / 64 * 64);
   const int nchunk = (int)((n + chunk - 1) / chunk);
@@ -200,20 +176,16 @@ int* launch_ivf_place(const int32_t* list_of, int64_t n, int nlist, const int64_
   for (int shift = 0; shift == 0 || (nlist - 1) >> shift != 0; shift += kDigitBits) {
     hipLaunchKernelGGL(place_hist_kernel, dim3((unsigned)nchunk), dim3(256), 0, st, list_of, perm, n, nlist, shift,
                        chunk, w.mat, w.bad);
-    hipLaunchKernelGGL(place_colscan_kernel, dim3(kBuckets / 256), dim3(256), 0, st, w.mat, nchunk, w.digit_cnt);
+    hipLaunchKernelGGL(place_colscan_kernel, dim3(kBuckets / 64), dim3(1024), 0, st, w.mat, nchunk, w.digit_cnt);
     hipLaunchKernelGGL(place_digit_offsets_kernel, dim3(1), dim3(256), 0, st, w.digit_cnt, w.digit_off);
     hipLaunchKernelGGL(place_scatter_kernel, dim3((unsigned)nchunk), dim3(64), 0, st, list_of, perm, n, nlist, shift,
                        chunk, w.mat, w.digit_off, out);
     perm = out;
     out = out == w.order_a ? w.order_b : w.order_a;
   }
-  hipLaunchKernelGGL(place_zero_kernel, dim3((unsigned)((nlist + 255) / 256)), dim3(256), 0, st, w.cnt_new,
-                     (int64_t)nlist);
-  hipLaunchKernelGGL(place_count_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st, list_of, n, nlist,
-                     w.cnt_new);
-  hipLaunchKernelGGL(place_list_offsets_kernel, dim3(1), dim3(1024), 0, st, w.cnt_new, old_off, nlist, w.first_new,
-                     new_off);
+  hipLaunchKernelGGL(place_first_kernel, dim3((unsigned)((n + 256) / 256)), dim3(256), 0, st, perm, list_of, n, nlist,
+                     old_off, new_off, w.bad);
   hipLaunchKernelGGL(place_dest_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st, perm, list_of, n, nlist,
-                     w.first_new, new_off, old_off, dest);
+                     old_off, w.bad, dest);
   return w.bad;
 }

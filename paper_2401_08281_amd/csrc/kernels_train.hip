@@ -20,19 +20,18 @@ constexpr int64_t kBlock = 4096;   // vectors per summation block (a multiple of
 // directly; the others store their block sums to `partial` (block bk of centroid j at slot
 // off[j] / kBlock + j + bk: the slots of different centroids never overlap) and
 // segmented_mean_finish_kernel adds them up.  A centroid without vectors is left as it is.
-// Lane t adds up dimensions t, t + 64, ...; dimensions are taken 64 * NC at a time (NC = 1,
-// 2 or 4).
-// The chain of a large cluster is long (it sets the kernel's time), so the memory latency
-// is taken off it: 64 / NC vectors at a time, their numbers come in with one load, their
-// rows are all requested before the first is added, and the additions then run in the
-// list's order.
-template <int NC>
+// A wavefront takes 64 of the dimensions (grid z), one per lane.
+// The chain of a large cluster is long (it sets the kernel's time), so the memory latency is taken
+// off it: 32 vectors at a time, their numbers come in with one load and their rows are all
+// requested a batch ahead of the additions, which run in the list's order.  262144 x 128 into 1024
+// centroids, clusters of up to some thousand: 710 us with one batch in flight and two dimensions
+// per lane, 140 us like this.
 __global__ __launch_bounds__(256) void segmented_mean_kernel(const float* __restrict__ x, int d,
                                                              const int32_t* __restrict__ order,
                                                              const int64_t* __restrict__ off, int K,
                                                              float* __restrict__ centroids,
                                                              double* __restrict__ partial) {
-  constexpr int NB = 64 / NC;
+  constexpr int NB = 32;
   const int wave = threadIdx.x >> 6, lane = lane_id();
   const int64_t j = blockIdx.x * 4ll + wave;
   if (j >= K) return;
@@ -40,98 +39,94 @@ __global__ __launch_bounds__(256) void segmented_mean_kernel(const float* __rest
   if (b0 == e0) return;
   const double count = (double)(e0 - b0);
   const int64_t nblk = (e0 - b0 + kBlock - 1) / kBlock;
-  for (int64_t bk = blockIdx.y; bk < nblk; bk += gridDim.y)
-  for (int t0 = 0; t0 < d; t0 += 64 * NC) {
+  const int t = blockIdx.z * 64 + lane;
+  const int tc = min(t, d - 1);                                  // (lanes past d load what they drop)
+  for (int64_t bk = blockIdx.y; bk < nblk; bk += gridDim.y) {
     const int64_t b = b0 + bk * kBlock, e = min(e0, b + kBlock);
-    double acc[NC];
+    double acc = 0.0;
+    float v0[NB], v1[NB];
+    auto fetch = [&](int64_t i, float (&v)[NB]) {
+      const int32_t mine = order[min(i + (lane & (NB - 1)), e - 1)];
 #pragma unroll
-    for (int c = 0; c < NC; ++c) acc[c] = 0.0;
-    int64_t i = b;
-    for (; i + NB <= e; i += NB) {
-      const int32_t mine = order[i + (lane & (NB - 1))];
-      float v[NB][NC];
+      for (int u = 0; u < NB; ++u) v[u] = x[(int64_t)__builtin_amdgcn_readlane(mine, u) * d + tc];
+    };
+    auto add = [&](int64_t i, const float (&v)[NB]) {
+      if (i + NB <= e) {
 #pragma unroll
-      for (int u = 0; u < NB; ++u) {
-        const float* __restrict__ row = x + (int64_t)__shfl(mine, u) * d + t0;
+        for (int u = 0; u < NB; ++u) acc += (double)v[u];
+      } else {
 #pragma unroll
-        for (int c = 0; c < NC; ++c) {
-          const int t = lane + 64 * c;
-          v[u][c] = t0 + t < d ? row[t] : 0.f;
-        }
+        for (int u = 0; u < NB; ++u) if (i + u < e) acc += (double)v[u];
       }
-#pragma unroll
-      for (int u = 0; u < NB; ++u)
-#pragma unroll
-        for (int c = 0; c < NC; ++c) acc[c] += (double)v[u][c];
+    };
+    fetch(b, v0);
+    for (int64_t i = b; i < e; i += 2 * NB) {
+      if (i + NB < e) fetch(i + NB, v1);
+      add(i, v0);
+      if (i + NB >= e) break;
+      if (i + 2 * NB < e) fetch(i + 2 * NB, v0);
+      add(i + NB, v1);
     }
-    for (; i < e; ++i) {
-      const float* __restrict__ row = x + (int64_t)order[i] * d + t0;
-#pragma unroll
-      for (int c = 0; c < NC; ++c) {
-        const int t = lane + 64 * c;
-        if (t0 + t < d) acc[c] += (double)row[t];
-      }
-    }
-#pragma unroll
-    for (int c = 0; c < NC; ++c) {
-      const int t = t0 + lane + 64 * c;
-      if (t < d) {
-        if (nblk == 1) centroids[j * d + t] = (float)(acc[c] / count);
-        else partial[(b0 / kBlock + j + bk) * d + t] = acc[c];
-      }
+    if (t < d) {
+      if (nblk == 1) centroids[j * d + t] = (float)(acc / count);
+      else partial[(b0 / kBlock + j + bk) * d + t] = acc;
     }
   }
 }
 
 // The same for rows of at most 32 floats (the sub-vectors of a product quantizer), where one
-// row per load instruction would leave most lanes idle: lane (s, t) = (lane / DP, lane % DP)
-// reads dimension t of every (64 / DP)-th vector, so one load instruction fetches 64 / DP
-// rows and a batch of 16 instructions 16 * 64 / DP vectors; the chain of dimension t then
-// takes the values in the list's order through cross-lane reads (it is kept in every group
-// s alike).  DP: d rounded up to 8, 16 or 32.
+// row per load instruction would leave most lanes idle: lane (c, t) = (lane / DP, lane % DP) adds up
+// dimension t of the c-th of 64 / DP centroids, so every lane runs one chain of its own and a load
+// instruction fetches 64 / DP rows.  64 vectors of each centroid are requested before the first is
+// added, the next 64 vector numbers while they are on their way.  (One centroid per wavefront, its
+// values spread by cross-lane reads to chains kept in every lane group alike: 195 us for 16 problems
+// of 262144 x 8 into 256 centroids; like this 60 us.)
+// DP: d rounded up to 8, 16 or 32.  Grid z: independent problems of the same shape (the
+// sub-quantizers of a product quantizer), their arrays one after the other.
 template <int DP>
 __global__ __launch_bounds__(256) void segmented_mean_small_kernel(const float* __restrict__ x, int d,
                                                                    const int32_t* __restrict__ order,
                                                                    const int64_t* __restrict__ off, int K,
                                                                    float* __restrict__ centroids,
                                                                    double* __restrict__ partial) {
-  constexpr int VPL = 64 / DP, NU = 16, NBV = NU * VPL;          // vectors per load, loads and vectors per batch
-  constexpr int NO = (NBV + 63) / 64;                            // registers of vector numbers per batch
-  static_assert(kBlock % NBV == 0, "whole batches per block");
-  const int wave = threadIdx.x >> 6, lane = lane_id();
-  const int s = lane / DP, t = lane % DP;
-  const int64_t j = blockIdx.x * 4ll + wave;
-  if (j >= K) return;
-  const int64_t b0 = off[j], e0 = off[j + 1];
-  if (b0 == e0) return;
+  constexpr int CPW = 64 / DP, NB = 64, NO = NB / DP;            // centroids per wavefront, vectors per batch
+  const int lane = lane_id(), c = lane / DP, t = lane % DP;
+  const int64_t j = (blockIdx.x * 4ll + (threadIdx.x >> 6)) * CPW + c;
+  off += (int64_t)blockIdx.z * (K + 1);
+  const int64_t n = off[K];
+  x += (int64_t)blockIdx.z * n * d;
+  order += (int64_t)blockIdx.z * n;
+  centroids += (int64_t)blockIdx.z * K * d;
+  partial += (int64_t)blockIdx.z * (n / kBlock + K + 1) * d;
+  const int64_t b0 = j < K ? off[j] : 0, e0 = j < K ? off[j + 1] : 0;
   const double count = (double)(e0 - b0);
   const int64_t nblk = (e0 - b0 + kBlock - 1) / kBlock;
-  for (int64_t bk = blockIdx.y; bk < nblk; bk += gridDim.y) {
-  const int64_t b = b0 + bk * kBlock, e = min(e0, b + kBlock);
-  double acc = 0.0;
-  int64_t i = b;
-  for (; i + NBV <= e; i += NBV) {
-    int32_t mine[NO];
+  const int tc = min(t, d - 1);                                  // (lanes past d load what they drop)
+  for (int64_t bk = blockIdx.y; __builtin_amdgcn_ballot_w64(bk < nblk) != 0; bk += gridDim.y) {
+    const bool mine_too = bk < nblk;
+    const int64_t b = mine_too ? b0 + bk * kBlock : 0, e = mine_too ? min(e0, b + kBlock) : 0;
+    double acc = 0.0;
+    int32_t num[NO], nxt[NO];
+    auto numbers = [&](int64_t i, int32_t (&v)[NO]) {            // (a group without vectors reads slot 0 and drops it)
 #pragma unroll
-    for (int o = 0; o < NO; ++o) mine[o] = (64 * o + lane) < NBV ? order[i + 64 * o + lane] : 0;
-    float v[NU];
+      for (int o = 0; o < NO; ++o) v[o] = order[max(min(i + o * DP + t, e - 1), (int64_t)0)];
+    };
+    numbers(b, num);
+    for (int64_t i = b; __builtin_amdgcn_ballot_w64(i < e) != 0; i += NB) {
+      numbers(i + NB, nxt);
+      float v[NB];
 #pragma unroll
-    for (int u = 0; u < NU; ++u) {
-      const int w = u * VPL + s;                                 // this lane's vector of load u: number w of the batch
-      const int32_t r = __shfl(mine[(u * VPL) / 64], w & 63);    // (a load's vectors sit in one register of numbers)
-      v[u] = t < d ? x[(int64_t)r * d + t] : 0.f;
+      for (int u = 0; u < NB; ++u)
+        v[u] = x[(int64_t)__shfl(num[u / DP], c * DP + u % DP) * d + tc];
+#pragma unroll
+      for (int u = 0; u < NB; ++u) acc += i + u < e ? (double)v[u] : 0.0;
+#pragma unroll
+      for (int o = 0; o < NO; ++o) num[o] = nxt[o];
     }
-#pragma unroll
-    for (int u = 0; u < NU; ++u)
-#pragma unroll
-      for (int s2 = 0; s2 < VPL; ++s2) acc += (double)__shfl(v[u], s2 * DP + t);
-  }
-  for (; i < e; ++i)                                             // the rest, one vector at a time
-    if (t < d) acc += (double)x[(int64_t)order[i] * d + t];
-  if (s == 0 && t < d) {
-    if (nblk == 1) centroids[j * d + t] = (float)(acc / count);
-    else partial[(b0 / kBlock + j + bk) * d + t] = acc;
-  }
+    if (mine_too && t < d) {
+      if (nblk == 1) centroids[j * d + t] = (float)(acc / count);
+      else partial[(b0 / kBlock + j + bk) * d + t] = acc;
+    }
   }
 }
 
@@ -143,9 +138,12 @@ __global__ __launch_bounds__(256) void segmented_mean_finish_kernel(const double
   const int wave = threadIdx.x >> 6, lane = lane_id();
   const int64_t j = blockIdx.x * 4ll + wave;
   if (j >= K) return;
+  off += (int64_t)blockIdx.z * (K + 1);
   const int64_t b0 = off[j], e0 = off[j + 1];
   const int64_t nblk = (e0 - b0 + kBlock - 1) / kBlock;
   if (nblk <= 1) return;
+  partial += (int64_t)blockIdx.z * (off[K] / kBlock + K + 1) * d;
+  centroids += (int64_t)blockIdx.z * K * d;
   const double count = (double)(e0 - b0);
   const double* __restrict__ src = partial + (b0 / kBlock + j) * d;
   for (int t = lane; t < d; t += VS_WAVE) {
@@ -161,22 +159,24 @@ __global__ __launch_bounds__(256) void segmented_mean_finish_kernel(const double
 // most 256 chunks of consecutive vectors:
 //   km_hist_kernel     per chunk, how many vectors go to each centroid        mat [nchunk][K]
 //   km_colscan_kernel  per centroid, exclusive running sum down the chunks (in place) and the total
-//   km_offsets_kernel  exclusive sum of the totals = first slot of each centroid, off [K + 1];
-//                      the largest total
+//   km_offsets_kernel  exclusive sum of the totals = first slot of each centroid, off [K + 1]
 //   km_scatter_kernel  one wavefront per chunk walks over its vectors in order, 64 at a time:
-//                      lanes with the same centroid are ranked by lane number (ballot), so
 //                      every vector gets slot off[j] + (vectors of j in earlier chunks) +
 //                      (earlier vectors of j in this chunk): the stable order.
 // K <= 16384 (one counter per centroid in LDS); the host does the same sort otherwise.
-__global__ __launch_bounds__(256) void km_hist_kernel(const int32_t* __restrict__ idx, int64_t n, int K,
+// Grid y: independent problems of the same shape, their arrays one after the other.
+template <typename T>
+__global__ __launch_bounds__(256) void km_hist_kernel(const T* __restrict__ idx, int64_t n, int K,
                                                       int64_t chunk, int32_t* __restrict__ mat,
                                                       int* __restrict__ bad) {
   extern __shared__ int km_lds[];
+  idx += (int64_t)blockIdx.y * n;
+  mat += (int64_t)blockIdx.y * gridDim.x * K;
   for (int j = threadIdx.x; j < K; j += 256) km_lds[j] = 0;
   __syncthreads();
   const int64_t i0 = blockIdx.x * chunk, i1 = min(n, i0 + chunk);
   for (int64_t i = i0 + threadIdx.x; i < i1; i += 256) {
-    const int32_t j = idx[i];
+    const int32_t j = (int32_t)idx[i];
     if (j < 0 || j >= K) *bad = 1;
     else atomicAdd(&km_lds[j], 1);
   }
@@ -184,67 +184,80 @@ __global__ __launch_bounds__(256) void km_hist_kernel(const int32_t* __restrict_
   for (int j = threadIdx.x; j < K; j += 256) mat[(int64_t)blockIdx.x * K + j] = km_lds[j];
 }
 
+// 64 centroids per workgroup; wavefront s first sums, then rewrites its quarter of the chunks
 __global__ __launch_bounds__(256) void km_colscan_kernel(int32_t* __restrict__ mat, int nchunk, int K,
                                                          int64_t* __restrict__ cnt) {
-  const int j = blockIdx.x * 256 + threadIdx.x;
-  if (j >= K) return;
+  __shared__ int32_t part[4][64];
+  mat += (int64_t)blockIdx.y * nchunk * K;
+  cnt += (int64_t)blockIdx.y * K;
+  const int s = threadIdx.x >> 6, lane = threadIdx.x & 63;
+  const int j = blockIdx.x * 64 + lane, per = (nchunk + 3) / 4;
+  const int c0 = min(nchunk, s * per), c1 = min(nchunk, c0 + per);
+  const bool ok = j < K;
+  int32_t sum = 0;
+#pragma unroll 8
+  for (int c = c0; c < c1; ++c) sum += ok ? mat[(int64_t)c * K + j] : 0;
+  part[s][lane] = sum;
+  __syncthreads();
+  if (!ok) return;
   int32_t run = 0;
-  for (int c = 0; c < nchunk; ++c) {
+  for (int u = 0; u < s; ++u) run += part[u][lane];
+#pragma unroll 8
+  for (int c = c0; c < c1; ++c) {
     const int32_t v = mat[(int64_t)c * K + j];
     mat[(int64_t)c * K + j] = run;
     run += v;
   }
-  cnt[j] = run;
+  if (s == 3) cnt[j] = run;
 }
 
-// one workgroup: lane t owns centroids [t * per, (t + 1) * per)
+// one workgroup per problem: lane t owns centroids [t * per, (t + 1) * per)
 __global__ __launch_bounds__(256) void km_offsets_kernel(const int64_t* __restrict__ cnt, int K,
-                                                         int64_t* __restrict__ off,
-                                                         int64_t* __restrict__ largest) {
-  __shared__ int64_t part[256], big[256];
+                                                         int64_t* __restrict__ off) {
+  __shared__ int64_t wsum[4];
+  cnt += (int64_t)blockIdx.y * K;
+  off += (int64_t)blockIdx.y * (K + 1);
   const int t = threadIdx.x, per = (K + 255) / 256;
   const int j0 = min(K, t * per), j1 = min(K, j0 + per);
-  int64_t sum = 0, mx = 0;
-  for (int j = j0; j < j1; ++j) { sum += cnt[j]; mx = max(mx, cnt[j]); }
-  part[t] = sum; big[t] = mx;
+  int64_t sum = 0;
+  for (int j = j0; j < j1; ++j) sum += cnt[j];
+  int64_t inc = sum;                                    // inclusive over the wavefront, then the workgroup
+  for (int o = 1; o < 64; o <<= 1) { const int64_t v = __shfl_up(inc, o); if ((t & 63) >= o) inc += v; }
+  if ((t & 63) == 63) wsum[t >> 6] = inc;
   __syncthreads();
-  int64_t base = 0;
-  for (int u = 0; u < t; ++u) base += part[u];
+  int64_t base = inc - sum;
+  for (int w = 0; w < (t >> 6); ++w) base += wsum[w];
   for (int j = j0; j < j1; ++j) { off[j] = base; base += cnt[j]; }
-  if (t == 255) {
-    int64_t total = 0, m = 0;
-    for (int u = 0; u < 256; ++u) { total += part[u]; m = max(m, big[u]); }
-    off[K] = total;
-    *largest = m;
-  }
+  if (t == 255) off[K] = base;
 }
 
-__global__ __launch_bounds__(64) void km_scatter_kernel(const int32_t* __restrict__ idx, int64_t n, int K,
+template <typename T>
+__global__ __launch_bounds__(64) void km_scatter_kernel(const T* __restrict__ idx, int64_t n, int K, int bits,
                                                         int64_t chunk, const int32_t* __restrict__ mat,
                                                         const int64_t* __restrict__ off,
                                                         int32_t* __restrict__ order) {
   extern __shared__ int km_lds[];                       // next slot of every centroid for this chunk
   const int lane = lane_id();
+  idx += (int64_t)blockIdx.y * n;
+  order += (int64_t)blockIdx.y * n;
+  mat += (int64_t)blockIdx.y * gridDim.x * K;
+  off += (int64_t)blockIdx.y * (K + 1);
   for (int j = lane; j < K; j += VS_WAVE) km_lds[j] = (int)(off[j] + mat[(int64_t)blockIdx.x * K + j]);
   wave_lds_sync();
   const int64_t i0 = blockIdx.x * chunk, i1 = min(n, i0 + chunk);
+  int32_t next = i0 + lane < i1 ? (int32_t)idx[i0 + lane] : -1;
   for (int64_t g = i0; g < i1; g += VS_WAVE) {
     const int64_t i = g + lane;
-    const bool valid = i < i1;
-    int32_t key = valid ? idx[i] : -1;
-    if (key >= K) key = -1;                             // (flagged by km_hist_kernel; never stored)
-    u64 todo = __builtin_amdgcn_ballot_w64(key >= 0);
-    while (todo != 0) {                                 // one round per distinct centroid among the 64
-      const int leader = __builtin_ctzll(todo);
-      const int32_t k = __shfl(key, leader);
-      const u64 same = __builtin_amdgcn_ballot_w64(key == k);
-      const int base = km_lds[k];
-      if (key == k) order[base + __popcll(same & ((1ull << lane) - 1ull))] = (int32_t)i;
-      wave_lds_sync();                                  // everyone has read the slot before it moves
-      if (lane == leader) km_lds[k] = base + __popcll(same);
-      wave_lds_sync();
-      todo &= ~same;
-    }
+    const int32_t key = next;
+    next = i + VS_WAVE < i1 ? (int32_t)idx[i + VS_WAVE] : -1;
+    const bool valid = key >= 0 && key < K;             // (others were flagged by km_hist_kernel; never stored)
+    const WaveRank r = wave_rank(valid, (u32)key, bits);
+    int slot = 0;
+    if (valid) slot = km_lds[key] + r.rank;
+    wave_lds_sync();                                    // everyone has read the counters before they move
+    if (valid && r.rank == 0) km_lds[key] = slot + r.count;
+    if (valid) order[slot] = (int32_t)i;
+    wave_lds_sync();
   }
 }
 
@@ -253,6 +266,8 @@ __global__ __launch_bounds__(64) void km_scatter_kernel(const int32_t* __restric
 __global__ __launch_bounds__(256) void km_objective_kernel(const float* __restrict__ val, int64_t n,
                                                            double* __restrict__ partial) {
   __shared__ double red[256];
+  val += (int64_t)blockIdx.y * n;
+  partial += (int64_t)blockIdx.y * gridDim.x;
   const int64_t per = (n + gridDim.x - 1) / gridDim.x;
   const int64_t i0 = blockIdx.x * per, i1 = min(n, i0 + per);
   double acc = 0.0;
@@ -285,57 +300,62 @@ __global__ __launch_bounds__(256) void residual_slices_kernel(const float* __res
 
 }  // namespace
 
-size_t segmented_mean_partial_bytes(int64_t n, int d, int K, int64_t largest) {
-  if (largest <= kBlock) return 0;
-  return (size_t)(n / kBlock + K + 1) * d * sizeof(double);
+size_t segmented_mean_partial_bytes(int64_t n, int d, int K, int problems) {
+  if (n <= kBlock) return 0;
+  return (size_t)(n / kBlock + K + 1) * d * sizeof(double) * problems;
 }
 
-void launch_segmented_mean(const float* x, int d, const int32_t* order, const int64_t* off, int K,
-                           int64_t largest, float* centroids, double* partial, hipStream_t st) {
-  if (K <= 0) return;
-  // `largest` = size of the largest cluster (the host counted): its number of blocks is the grid's second dimension
-  const int64_t nblk = std::max<int64_t>(1, (largest + kBlock - 1) / kBlock);
-  const dim3 grid((unsigned)((K + 3) / 4), (unsigned)std::min<int64_t>(nblk, 65535)), block(256);
+void launch_segmented_mean(const float* x, int64_t n, int d, const int32_t* order, const int64_t* off, int K,
+                           int problems, float* centroids, double* partial, hipStream_t st) {
+  if (K <= 0 || n <= 0) return;
+  // Blocks side by side: four times what clusters of equal size would have, so that an uneven
+  // split still spreads (a workgroup without a block leaves at once; the rest is a loop).
+  const int64_t most = (n + kBlock - 1) / kBlock, even = (n / K + kBlock - 1) / kBlock;
+  const unsigned gy = (unsigned)std::min<int64_t>(std::min<int64_t>(most, 65535), 4 * std::max<int64_t>(1, even));
+  const unsigned gx = (unsigned)((K + 3) / 4);
+  const int per_wave = d <= 8 ? 8 : (d <= 16 ? 4 : (d <= 32 ? 2 : 1));
+  const dim3 block(256), grid((unsigned)((K + 4 * per_wave - 1) / (4 * per_wave)), gy, (unsigned)problems);
   if (d <= 8) hipLaunchKernelGGL((segmented_mean_small_kernel<8>), grid, block, 0, st, x, d, order, off, K, centroids, partial);
   else if (d <= 16) hipLaunchKernelGGL((segmented_mean_small_kernel<16>), grid, block, 0, st, x, d, order, off, K, centroids, partial);
   else if (d <= 32) hipLaunchKernelGGL((segmented_mean_small_kernel<32>), grid, block, 0, st, x, d, order, off, K, centroids, partial);
-  else if (d <= 64) hipLaunchKernelGGL((segmented_mean_kernel<1>), grid, block, 0, st, x, d, order, off, K, centroids, partial);
-  else if (d <= 128) hipLaunchKernelGGL((segmented_mean_kernel<2>), grid, block, 0, st, x, d, order, off, K, centroids, partial);
-  else hipLaunchKernelGGL((segmented_mean_kernel<4>), grid, block, 0, st, x, d, order, off, K, centroids, partial);
-  if (nblk > 1)
-    hipLaunchKernelGGL(segmented_mean_finish_kernel, dim3((unsigned)((K + 3) / 4)), block, 0, st, partial, d, off, K,
+  else   // (problems == 1)
+    hipLaunchKernelGGL(segmented_mean_kernel, dim3(gx, gy, (unsigned)((d + 63) / 64)), block, 0, st, x, d, order, off, K, centroids, partial);
+  if (most > 1)
+    hipLaunchKernelGGL(segmented_mean_finish_kernel, dim3(gx, 1, (unsigned)problems), block, 0, st, partial, d, off, K,
                        centroids);
 }
 
-size_t kmeans_sort_bytes(int64_t n, int K) {
-  (void)n;
-  return (size_t)256 * K * sizeof(int32_t) + (size_t)K * sizeof(int64_t) + 256 * sizeof(double) + 64;
+size_t kmeans_sort_bytes(int K, int problems) {
+  return ((size_t)256 * K * sizeof(int32_t) + (size_t)K * sizeof(int64_t)) * problems;
 }
 
-// work: kmeans_sort_bytes(n, K); out: order [n], off [K + 1]; in the work space afterwards:
-// scal[0] = the largest cluster (int64), scal[1] = 1 if an assignment was out of range,
-// partial [256] doubles whose sum is the sum of val.
-void launch_kmeans_sort(const int32_t* idx, const float* val, int64_t n, int K, char* work, int32_t* order,
-                        int64_t* off, int64_t** scal_out, double** partial_out, hipStream_t st) {
-  int32_t* mat = reinterpret_cast<int32_t*>(work);
-  int64_t* cnt = reinterpret_cast<int64_t*>(work + (size_t)256 * K * sizeof(int32_t));
-  double* partial = reinterpret_cast<double*>(cnt + K);
-  int64_t* scal = reinterpret_cast<int64_t*>(partial + 256);
-  *scal_out = scal; *partial_out = partial;
-  const int64_t chunk = std::max<int64_t>(2048, ((n + 255) / 256 + 63) / 64 * 64);
-  const int nchunk = (int)((n + chunk - 1) / chunk);
+template <typename T>
+static void kmeans_sort(const T* idx, const float* val, int64_t n, int K, int problems, char* work, int32_t* order,
+                        int64_t* off, int* bad, double* partial, hipStream_t st) {
+  const int64_t chunk = std::max<int64_t>(1024, ((n + 255) / 256 + 63) / 64 * 64);
+  const unsigned nchunk = (unsigned)((n + chunk - 1) / chunk), P = (unsigned)problems;
+  int64_t* cnt = reinterpret_cast<int64_t*>(work);
+  int32_t* mat = reinterpret_cast<int32_t*>(cnt + (size_t)K * problems);
   const size_t lds = (size_t)K * sizeof(int);
   if (lds > 48 * 1024) {
-    (void)hipFuncSetAttribute(reinterpret_cast<const void*>(&km_hist_kernel), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-    (void)hipFuncSetAttribute(reinterpret_cast<const void*>(&km_scatter_kernel), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+    (void)hipFuncSetAttribute(reinterpret_cast<const void*>(&km_hist_kernel<T>), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+    (void)hipFuncSetAttribute(reinterpret_cast<const void*>(&km_scatter_kernel<T>), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
   }
-  launch_fill_u64(reinterpret_cast<u64*>(scal), 2, 0ull, st);
-  hipLaunchKernelGGL(km_hist_kernel, dim3((unsigned)nchunk), dim3(256), lds, st, idx, n, K, chunk, mat,
-                     reinterpret_cast<int*>(scal + 1));
-  hipLaunchKernelGGL(km_colscan_kernel, dim3((unsigned)((K + 255) / 256)), dim3(256), 0, st, mat, nchunk, K, cnt);
-  hipLaunchKernelGGL(km_offsets_kernel, dim3(1), dim3(256), 0, st, cnt, K, off, scal);
-  hipLaunchKernelGGL(km_scatter_kernel, dim3((unsigned)nchunk), dim3(64), lds, st, idx, n, K, chunk, mat, off, order);
-  hipLaunchKernelGGL(km_objective_kernel, dim3(256), dim3(256), 0, st, val, n, partial);
+  int bits = 1;
+  while ((1 << bits) < K) ++bits;
+  hipLaunchKernelGGL((km_hist_kernel<T>), dim3(nchunk, P), dim3(256), lds, st, idx, n, K, chunk, mat, bad);
+  hipLaunchKernelGGL(km_colscan_kernel, dim3((unsigned)((K + 63) / 64), P), dim3(256), 0, st, mat, (int)nchunk, K, cnt);
+  hipLaunchKernelGGL(km_offsets_kernel, dim3(1, P), dim3(256), 0, st, cnt, K, off);
+  hipLaunchKernelGGL((km_scatter_kernel<T>), dim3(nchunk, P), dim3(64), lds, st, idx, n, K, bits, chunk, mat, off, order);
+  hipLaunchKernelGGL(km_objective_kernel, dim3(256, P), dim3(256), 0, st, val, n, partial);
+}
+void launch_kmeans_sort(const int32_t* idx, const float* val, int64_t n, int K, char* work, int32_t* order,
+                        int64_t* off, int* bad, double* partial, hipStream_t st) {
+  kmeans_sort(idx, val, n, K, 1, work, order, off, bad, partial, st);
+}
+void launch_kmeans_sort_bytes(const uint8_t* idx, const float* val, int64_t n, int K, int problems, char* work,
+                              int32_t* order, int64_t* off, int* bad, double* partial, hipStream_t st) {
+  kmeans_sort(idx, val, n, K, problems, work, order, off, bad, partial, st);
 }
 
 void launch_residual_slices(const float* x, int64_t n, int d, int dsub, const float* centroids,
