@@ -722,7 +722,8 @@ int kmeans_rounds(const float* x, int64_t n, int d, int K, int niter, float* cen
   std::vector<int64_t> h_off(on_device ? 0 : (size_t)K + 1), cursor(on_device ? 0 : (size_t)K);
   for (int r = 0; r < niter; ++r) {
     // (1) nearest centroid of every vector: canon L2, ties to the smaller centroid number
-    if (int rc = nearest_rows(x, n, centroids, K, d, VS_METRIC_L2, idx, val, sc, st, r > 0)) return rc;
+    // (on the host's side the centroids' sums of a round use the same scratch: nothing is left there to keep)
+    if (int rc = nearest_rows(x, n, centroids, K, d, VS_METRIC_L2, idx, val, sc, st, on_device && r > 0)) return rc;
     if (on_device) {
       launch_kmeans_sort(idx, val, n, K, wb + o_sort, order, off, reinterpret_cast<int*>(wb + o_bad),
                          reinterpret_cast<double*>(wb + o_obj) + (size_t)r * 256, st);

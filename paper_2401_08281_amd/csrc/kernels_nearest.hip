@@ -314,8 +314,10 @@ __global__ __launch_bounds__(256) void nearest_finish_kernel(
       eps += METRIC == 0 ? split * nn + sub + rounding : (bf ? 2.f : 1.f) * split * nn + sub + 2.f * rounding;
     }
     unsure = !(b1 - b2 > eps_scale * eps) || (!bf && (fl & VEC_LARGE)) || eps_scale < 0.f;
-    // (a vector beyond the fp16 range, or with a NaN, collects nothing and goes on to the canon chain)
-    from = (!bf && (fl & VEC_LARGE)) || eps_scale < 0.f ? __builtin_inff() : b1 - eps;
+    // (a vector beyond the fp16 range or with a NaN, and every vector where a norm overflows -- the
+    // score of a row with an infinity is a NaN that no threshold finds -- collects nothing and goes
+    // on to the canon chain)
+    from = (!bf && (fl & VEC_LARGE)) || eps_scale < 0.f || !(nn < __builtin_inff()) ? __builtin_inff() : b1 - eps;
     idx[e] = best;
   }
   // one atomic per workgroup (per wavefront they were most of the kernel: 45 us for 4096 of them)

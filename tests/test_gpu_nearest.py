@@ -1,0 +1,168 @@
+"""Nearest rows, nearest codewords and ragged exact search on the matrix cores against the canon
+tiles (option knn_path = 1) and the CPU oracle.  Every comparison of ids, codes and distances is exact:
+the matrix cores only shortlist, the canon chain decides.  Needs a real MI355X."""
+import numpy as np
+import pytest
+
+from test_gpu_parity import dev, host, say, vs  # noqa: F401  (vs: fixture)
+
+pytestmark = pytest.mark.gpu
+
+L2, IP = 0, 1
+
+
+def rows(kind, n, d, seed):
+    rng = np.random.default_rng(seed)
+    if kind == "sift":
+        return np.rint(np.clip(rng.uniform(0, 255, (50, d))[rng.integers(0, 50, n)] + 20 * rng.standard_normal((n, d)),
+                               0, 255)).astype(np.float32)
+    x = rng.standard_normal((n, d)).astype(np.float32)
+    return x * np.float32({"gauss": 1.0, "beyond_fp16": 3e5, "tiny": 1e-18}[kind])
+
+
+def both_routes(vs, call):
+    """call() by the canon tiles and by the default route."""
+    try:
+        vs.vs_set_option("knn_path", 1)
+        canon = [host(t).copy() for t in call()]
+    finally:
+        vs.vs_set_option("knn_path", 0)
+    return canon, [host(t).copy() for t in call()]
+
+
+# n * rows * d is above 6e8, the size from which the sweep is used.  d: both ends of the range, every
+# padded length, remainders of 4, 2 and 1; rows of B: one step and a remainder, one past a step, a
+# split; n: one past a tile, remainders.
+NEAREST_CASES = [
+    ("d17", 131_073, 300, 17, L2, "gauss"), ("d30_ip", 80_001, 300, 30, IP, "gauss"),
+    ("d32", 60_033, 321, 32, L2, "sift"), ("d64_ip", 30_001, 320, 64, IP, "gauss"),
+    ("d66", 40_960, 257, 66, L2, "gauss"), ("d96", 20_001, 350, 96, L2, "gauss"),
+    ("d100", 25_700, 256, 100, L2, "sift"), ("d128", 65_537, 129, 128, L2, "sift"),
+    ("d127_ip", 20_481, 260, 127, IP, "gauss"), ("b_split", 700, 8_193, 128, L2, "sift"),
+    ("few_rows", 600_001, 9, 128, L2, "gauss"),
+    ("beyond_fp16", 30_001, 333, 72, L2, "beyond_fp16"), ("beyond_fp16_ip", 30_001, 333, 128, IP, "beyond_fp16"),
+    ("tiny", 20_001, 300, 128, L2, "tiny"),
+]
+
+
+@pytest.mark.parametrize("name,n,nb,d,metric,kind", NEAREST_CASES, ids=[c[0] for c in NEAREST_CASES])
+@pytest.mark.parametrize("special", ["plain", "ties_and_nonfinite"])
+def test_nearest_row_sweep_equals_canon_tiles(vs, name, n, nb, d, metric, kind, special):
+    """List assignment.  Second variant: centroids that occur twice (the smaller one wins), vectors
+    that are a centroid, hold an infinity, a NaN or only zeros."""
+    say("nearest %s n=%d nb=%d d=%d metric=%d %s" % (name, n, nb, d, metric, special))
+    x = rows(kind, n, d, 1)
+    cent = rows(kind, nb, d, 2)
+    if special != "plain":
+        cent[nb // 2:] = cent[:nb - nb // 2]
+        x[5:5 + nb // 2:2] = cent[:len(x[5:5 + nb // 2:2])]
+        x[1, d - 1], x[2, 0], x[3] = np.inf, np.nan, 0.0
+    xd, cd = dev(x), dev(cent)
+
+    def call():
+        ix = vs.IVFFlat(d, metric, cd)
+        ix.add(xd[:n // 3])
+        ix.add(xd[n // 3:])
+        out = ix.list_sizes(), ix.storage()[0]
+        ix.close()
+        return out
+    canon, got = both_routes(vs, call)
+    for a, b in zip(canon, got):
+        np.testing.assert_array_equal(a, b)
+
+
+@pytest.mark.parametrize("kind", ["all_nan", "one_inf", "huge", "inf_among_few_ip"])
+def test_nearest_row_sweep_with_nonfinite_centroids(vs, kind):
+    say("nearest, centroids %s" % kind)
+    n, nb, metric = (1_100_000, 9, IP) if kind == "inf_among_few_ip" else (40_001, 257, L2)
+    x, cent = rows("gauss", n, 64, 3), rows("gauss", nb, 64, 4)
+    if kind == "all_nan":
+        cent[:] = np.nan
+    elif kind == "huge":
+        cent[::2] *= np.float32(1e19)
+    else:
+        cent[7, 3] = -np.inf
+    xd, cd = dev(x), dev(cent)
+
+    def call():
+        ix = vs.IVFFlat(64, metric, cd)
+        ix.add(xd)
+        return ix.list_sizes(), ix.storage()[0]
+    canon, got = both_routes(vs, call)
+    for a, b in zip(canon, got):
+        np.testing.assert_array_equal(a, b)
+
+
+@pytest.mark.parametrize("n,d,K", [(20_001, 128, 300), (130_001, 17, 300), (1_500, 32, 16_385)])
+def test_kmeans_sweep_equals_canon_tiles(vs, n, d, K):
+    """Three rounds: objective, assignment and centroids, with the bookkeeping on the device and
+    (K > 16384) on the host."""
+    say("kmeans n=%d d=%d K=%d" % (n, d, K))
+    x = rows("sift", n, d, 5)
+    init = np.resize(x, (K, d)) + (np.arange(K) // n)[:, None].astype(np.float32)
+    xd = dev(x)
+
+    def call():
+        c = dev(init)
+        obj, assign = vs.vs_kmeans(xd, c, 3, return_assign=True)
+        return c, assign, dev(np.array(obj))
+    canon, got = both_routes(vs, call)
+    for a, b in zip(canon, got):
+        np.testing.assert_array_equal(a, b)
+
+
+# dsub: one and two groups of eight dimensions, both with remainders; 17 takes the vector kernel.
+# n: below one group of 32 vectors, one past a workgroup's 128.
+@pytest.mark.parametrize("nbits", [4, 8])
+@pytest.mark.parametrize("dsub", [1, 2, 3, 4, 7, 8, 9, 12, 15, 16, 17])
+@pytest.mark.parametrize("n,M", [(19, 4), (4_225, 6)])
+def test_nearest_codewords_match_oracle(vs, oracle, n, M, dsub, nbits):
+    say("encode n=%d M=%d dsub=%d nbits=%d" % (n, M, dsub, nbits))
+    d, K = M * dsub, 1 << nbits
+    x, cent = rows("sift", n, d, 6), rows("sift", 7, d, 7)
+    cb = rows("sift", K, d, 8).reshape(K, M, dsub).transpose(1, 0, 2) - 128.0
+    cb[0, K // 2:] = cb[0, :K // 2]                    # every codeword of the first one twice
+    cb[1, 1:] *= np.float32(1e4)                       # one small codeword among large ones
+    cb = np.ascontiguousarray(cb, dtype=np.float32)
+    ix = vs.IVFPQ(d, L2, dev(cent), dev(cb), nbits)
+    ix.add(dev(x))
+    orc = oracle.OracleIVFPQ(d, L2, cent, cb, nbits)
+    orc.add(x)
+    np.testing.assert_array_equal(host(ix.codes()), orc.codes)
+
+
+@pytest.mark.parametrize("n,d,M,nbits,niter", [(5_003, 12, 4, 8, 3), (5_003, 24, 2, 4, 3), (9_001, 34, 2, 8, 2),
+                                               (3_000_001, 32, 32, 4, 2)])
+def test_subquantizers_together_equal_one_at_a_time(vs, n, d, M, nbits, niter):
+    """The last shape's work space is beyond one group of sub-quantizers; 17 dimensions are not taken
+    together."""
+    say("train n=%d d=%d M=%d nbits=%d" % (n, d, M, nbits))
+    import torch
+    g = torch.Generator(device="cuda")
+    g.manual_seed(9)
+    x = torch.randn((n, d), generator=g, device="cuda")
+    cent = x[:16].clone()
+    cb = torch.randn((M, 1 << nbits, d // M), generator=g, device="cuda")
+
+    def call():
+        c, b = cent.clone(), cb.clone()
+        obj = vs.vs_ivfpq_train(x, L2, c, b, nbits, niter)
+        return c, b, torch.tensor(obj, dtype=torch.float64, device="cuda")
+    canon, got = both_routes(vs, call)
+    for a, b in zip(canon, got):
+        np.testing.assert_array_equal(a, b)
+
+
+# rows of B on both sides of one canon tile (16384), lengths between the padded ones
+@pytest.mark.parametrize("nb,nq,d,k,metric", [
+    (16_384, 3, 100, 10, L2), (16_385, 3, 100, 10, L2), (20_003, 130, 17, 1, IP), (20_003, 65, 33, 100, L2),
+    (9_001, 700, 129, 10, IP), (4_097, 600, 257, 10, L2), (1_201, 700, 770, 150, L2)])
+def test_ragged_exact_search_equals_canon_tiles(vs, nb, nq, d, k, metric):
+    say("ragged flat nb=%d nq=%d d=%d k=%d metric=%d" % (nb, nq, d, k, metric))
+    x, q = dev(rows("gauss", nb, d, 10)), dev(rows("gauss", nq, d, 11))
+    ix = vs.Flat(d, metric)
+    ix.add(x)
+    for call in (lambda: vs.vs_flat_search(x, q, k, metric), lambda: ix.search(q, k)):
+        canon, got = both_routes(vs, call)
+        for a, b in zip(canon, got):
+            np.testing.assert_array_equal(a, b)
