@@ -439,9 +439,13 @@ int64_t vs_knn_workspace_bytes(int64_t na, int64_t nb, int32_t d, int32_t k, int
     return -1;
   }
   if (na == 0) return 0;
-  const KnnPlan p = piece > 0 ? knn_plan_pieces(na, piece, nb, d, k, b_prepared != 0, false)
-                              : knn_plan(na, nb, d, k, b_prepared != 0, false);
-  return (int64_t)p.bytes;
+  size_t bytes = 0;   // (of either route: the callers choose the canon tiles where a problem is small)
+  for (const bool small_canon : {false, true}) {
+    const KnnPlan p = piece > 0 ? knn_plan_pieces(na, piece, nb, d, k, b_prepared != 0, small_canon)
+                                : knn_plan(na, nb, d, k, b_prepared != 0, small_canon);
+    bytes = std::max(bytes, p.bytes);
+  }
+  return (int64_t)bytes;
 }
 
 int vs_counters_read(int64_t* counters) {
@@ -453,6 +457,24 @@ int vs_counters_read(int64_t* counters) {
   counters[1] = (int64_t)fb;
   return VS_OK;
 }
+
+namespace {
+
+// Work space of a flat search.  The matrix-core route holds the rows a second time as operand planes;
+// where that does not fit, rows of a ragged length go through the canon tiles, whose work space does
+// not grow with the rows.
+int reserve_flat(Scratch& sc, KnnPlan* plan, int64_t nq, int64_t nb, int d, int k, bool b_prepared) {
+  const size_t keys = (size_t)nq * k * sizeof(u64);
+  int rc = sc.reserve(plan->bytes + keys);
+  if (rc == VS_ERR_OOM && plan->mfma && d % 32 != 0) {
+    (void)hipGetLastError();
+    *plan = knn_plan(nq, nb, d, k, b_prepared, false, 0);
+    rc = sc.reserve(plan->bytes + keys);
+  }
+  return rc;
+}
+
+}  // namespace
 
 int vs_flat_search(const float* x, int64_t nb, const float* q, int64_t nq, int32_t d,
                    int32_t metric, int32_t k, float* out_dist, int64_t* out_ids,
@@ -469,10 +491,10 @@ int vs_flat_search(const float* x, int64_t nb, const float* q, int64_t nq, int32
   HIP_TRY(hipGetDevice(&dev));
   if (dev < 0 || dev >= 16) return fail(VS_ERR_UNSUPPORTED, "vs_flat_search: device %d", dev);
 
-  const KnnPlan plan = knn_plan(nq, nb, d, k, false, d % 32 != 0);
+  KnnPlan plan = knn_plan(nq, nb, d, k, false, d % 32 != 0);
   ScratchUse guard(g_flat_scratch[dev], st);
   Scratch& sc = g_flat_scratch[dev];
-  if (int rc = sc.reserve(plan.bytes + (size_t)nq * k * sizeof(u64))) return rc;
+  if (int rc = reserve_flat(sc, &plan, nq, nb, d, k, false)) return rc;
   char* base = static_cast<char*>(sc.p);
   SelectOut out;
   out.val = out_dist;
@@ -523,14 +545,21 @@ int vs_flat_add(vs_flat* ix, const float* x, int64_t n, void* hip_stream) {
   if (ix->ntotal + n >= (1ll << 31)) return fail(VS_ERR_INVALID_ARG, "vs_flat_add: ntotal must stay below 2^31");
   hipStream_t st = static_cast<hipStream_t>(hip_stream);
   const int d = ix->d;
-  const bool planes = mfma_knn_supported(d, 1);
+  bool planes = mfma_knn_supported(d, 1);
   const int64_t total = ix->ntotal + n;
   if (total > ix->cap) {   // grow both buffers (at least doubling), keep the stored rows
     const int64_t cap = std::max(total, 2 * ix->cap);
     float* nx = nullptr;
     void* np = nullptr;
     hipError_t e = hipMalloc(reinterpret_cast<void**>(&nx), (size_t)cap * d * sizeof(float));
-    if (e == hipSuccess && planes) e = hipMalloc(&np, planes_bytes(cap, d));
+    if (e == hipSuccess && planes) {
+      e = hipMalloc(&np, planes_bytes(cap, d));
+      if (e == hipErrorOutOfMemory && d % 32 != 0) {   // ragged rows do without (canon tiles)
+        (void)hipGetLastError();
+        np = nullptr;
+        e = hipSuccess;
+      }
+    }
     if (e == hipSuccess && ix->ntotal > 0)
       e = hipMemcpyAsync(nx, ix->x, (size_t)ix->ntotal * d * sizeof(float), hipMemcpyDeviceToDevice, st);
     if (e == hipSuccess) e = hipStreamSynchronize(st);
@@ -546,6 +575,8 @@ int vs_flat_add(vs_flat* ix, const float* x, int64_t n, void* hip_stream) {
   }
   HIP_TRY(hipMemcpyAsync(ix->x + ix->ntotal * d, x, (size_t)n * d * sizeof(float), hipMemcpyDeviceToDevice, st));
   ix->ntotal = total;
+  planes = planes && ix->plane_mem;
+  if (!planes) ix->has_planes = false;
   if (planes) {   // (the panel layout of the planes depends on the row count: prepared anew)
     ix->planes = carve_planes(static_cast<char*>(ix->plane_mem), total, d);
     launch_prep(ix->x, total, d, ix->planes.hi, ix->planes.lo, ix->planes.norm, ix->planes.info, st, true);
@@ -571,10 +602,11 @@ int vs_flat_index_search(const vs_flat* ix, const float* q, int64_t nq, int32_t 
   const int64_t nb = ix->ntotal;
   const int d = ix->d, metric = ix->metric;
   const Planes* bp = ix->has_planes ? &ix->planes : nullptr;
-  const KnnPlan plan = knn_plan(nq, nb, d, k, bp != nullptr, d % 32 != 0);
+  // (ragged rows whose planes did not fit the memory: canon tiles)
+  KnnPlan plan = knn_plan(nq, nb, d, k, bp != nullptr, d % 32 != 0, !bp && d % 32 != 0 ? 0 : -1);
   ScratchUse guard(g_flat_scratch[dev], st);
   Scratch& sc = g_flat_scratch[dev];
-  if (int rc = sc.reserve(plan.bytes + (size_t)nq * k * sizeof(u64))) return rc;
+  if (int rc = reserve_flat(sc, &plan, nq, nb, d, k, bp != nullptr)) return rc;
   char* base = static_cast<char*>(sc.p);
   SelectOut out;
   out.val = out_dist;
@@ -1244,7 +1276,9 @@ struct SearchLayout {
   bool list_major = false;      // the scan runs list-major (see ivfpq_scan_listmajor_kernel)
   int lm_first = 0, lm_cap = 0;
 };
-void search_layout(const vs_ivfpq* ix, int64_t nq, int k, int nprobe, SearchLayout* out, bool allow_list_major = true) {
+// coarse_route: as knn_plan's route.
+void search_layout(const vs_ivfpq* ix, int64_t nq, int k, int nprobe, SearchLayout* out, bool allow_list_major = true,
+                   int coarse_route = -1) {
   SearchLayout& L = *out;
   const IvfpqDims& g = ix->g;
   L.npr = std::min<int>(nprobe, g.nlist);
@@ -1269,7 +1303,7 @@ void search_layout(const vs_ivfpq* ix, int64_t nq, int k, int nprobe, SearchLayo
   }
   const int ppb = (L.npr + L.nsplit - 1) / L.nsplit;
   L.nsplit = (L.npr + ppb - 1) / ppb;
-  L.plan = knn_plan(nq, g.nlist, g.d, L.npr, ix->has_planes, true);
+  L.plan = knn_plan(nq, g.nlist, g.d, L.npr, ix->has_planes, true, coarse_route);
   Carver cv;
   L.o_knn = cv.take(L.plan.bytes);
   L.o_pr = cv.take((size_t)nq * L.npr * sizeof(int32_t));
@@ -1393,8 +1427,14 @@ int vs_ivfpq_search_static(const vs_ivfpq* ix, const float* q, int64_t nq, int32
                            float* out_dist, int64_t* out_ids, void* hip_stream) {
   if (int rc = search_check_args("vs_ivfpq_search_static", ix, q, nq, k, nprobe, out_dist, out_ids)) return rc;
   if (nq == 0) return VS_OK;
-  SearchLayout L;
-  search_layout(ix, nq, k, nprobe, &L, false);   // (the list-major scan's buffers are not for a fixed work space)
+  // (the list-major scan's buffers are not for a fixed work space)
+  // What fits is decided on the route that a shape takes whatever the batch: the matrix cores for
+  // whole blocks of 32 dimensions, the canon tiles for the rest.  The choice by size (canon tiles
+  // for small problems: up to 75 MB of them at d = 32) is followed where it fits too.
+  SearchLayout L, chosen;
+  search_layout(ix, nq, k, nprobe, &L, false, ix->g.d % 32 == 0 ? 1 : 0);
+  search_layout(ix, nq, k, nprobe, &chosen, false);
+  if (L.bytes <= kStaticScratchBytes && chosen.bytes <= kStaticScratchBytes) L = chosen;
   if (L.bytes > kStaticScratchBytes)
     return fail(VS_ERR_INVALID_ARG,
                 "vs_ivfpq_search_static: %lld queries with k = %d, nprobe = %d need %zu bytes of work space, "

@@ -135,7 +135,8 @@ struct PrepInfo {
   // while the sweeps of such calls may use the fp16 heads alone on operands that are not exactly
   // bf16 (one matrix product instead of three, with the wider error bound that goes with it).  A
   // bit is cleared for good by the exact fallback once more than one row in 512 of a call failed
-  // the sufficiency test under that bound.
+  // the sufficiency test under that bound (k > 1), or by the one-sweep route once more than half of a
+  // call's vectors had to be swept again (k = 1).
   u32 heads_only;
 };
 struct MfmaOperand {

@@ -166,3 +166,51 @@ def test_ragged_exact_search_equals_canon_tiles(vs, nb, nq, d, k, metric):
         canon, got = both_routes(vs, call)
         for a, b in zip(canon, got):
             np.testing.assert_array_equal(a, b)
+
+
+def test_static_search_accepts_what_fits_by_the_matrix_core_route(vs):
+    """The canon tiles of a small problem can be larger than the fixed work space (600 x 16384 scores:
+    40 MiB) where the matrix-core route's shortlist fits it: the call is served, with the same results."""
+    import ctypes
+    import torch
+    d, nlist, M, nq = 32, 16384, 8, 600
+    say("static search nlist=%d nq=%d d=%d" % (nlist, nq, d))
+    x = dev(rows("gauss", 40_000, d, 5))
+    q = dev(rows("gauss", nq, d, 6))
+    ix = vs.IVFPQ(d, L2, x[:nlist].contiguous(), x[:256].view(256, M, d // M).permute(1, 0, 2).contiguous(), 8)
+    ix.add(x)
+    D, I = ix.search(q, 3, 1)
+    d2, i2 = torch.empty_like(D), torch.empty_like(I)
+    p = lambda t: ctypes.c_void_p(t.data_ptr())
+    rc = vs.lib().vs_ivfpq_search_static(ix.h, p(q), nq, 3, 1, p(d2), p(i2),
+                                         ctypes.c_void_p(torch.cuda.current_stream().cuda_stream))
+    assert rc == 0
+    np.testing.assert_array_equal(host(I), host(i2))
+    np.testing.assert_array_equal(host(D), host(d2))
+
+
+def test_ragged_rows_that_leave_no_room_for_planes_use_canon_tiles(vs):
+    """Operand planes of 1M x 100 take 768 MB; with less than that free the search and the index still work."""
+    import torch
+    n, d, nq, k = 1_000_000, 100, 40, 5
+    say("ragged rows n=%d d=%d with little memory free" % (n, d))
+    g = torch.Generator(device="cuda").manual_seed(7)
+    x = torch.randn((n, d), generator=g, device="cuda")
+    q = torch.randn((nq, d), generator=g, device="cuda")
+    want = [host(t).copy() for t in vs.vs_flat_search(x, q, k, L2)]
+    vs.vs_trim()
+    torch.cuda.empty_cache()
+    hold = torch.empty(max(0, torch.cuda.mem_get_info()[0] - (700 << 20)), dtype=torch.uint8, device="cuda")
+    try:
+        once = [host(t).copy() for t in vs.vs_flat_search(x, q, k, L2)]
+        vs.vs_trim()
+        ix = vs.Flat(d, L2)
+        ix.add(x)
+        kept = [host(t).copy() for t in ix.search(q, k)]
+    finally:
+        del hold
+        torch.cuda.empty_cache()
+        vs.vs_trim()
+    for got in (once, kept):
+        for a, b in zip(want, got):
+            np.testing.assert_array_equal(a, b)
