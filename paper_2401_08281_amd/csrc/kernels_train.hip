@@ -77,10 +77,11 @@ __global__ __launch_bounds__(256) void segmented_mean_kernel(const float* __rest
 // The same for rows of at most 32 floats (the sub-vectors of a product quantizer), where one
 // row per load instruction would leave most lanes idle: lane (c, t) = (lane / DP, lane % DP) adds up
 // dimension t of the c-th of 64 / DP centroids, so every lane runs one chain of its own and a load
-// instruction fetches 64 / DP rows.  64 vectors of each centroid are requested before the first is
-// added, the next 64 vector numbers while they are on their way.  (One centroid per wavefront, its
-// values spread by cross-lane reads to chains kept in every lane group alike: 195 us for 16 problems
-// of 262144 x 8 into 256 centroids; like this 60 us.)
+// instruction fetches 64 / DP rows.  Rows are requested 32 vectors ahead of the additions and their
+// numbers 64 ahead, so that waiting for a number never waits for the rows just requested.  16
+// problems of 262144 x 8 descriptors' residuals into 256 centroids: 209 us with one batch of 64 in
+// flight, 183 us like this.  The largest clusters' chains set the time: keeping a problem on one XCD
+// (180 us) and 32-bit offsets (186 us) changed nothing.
 // DP: d rounded up to 8, 16 or 32.  Grid z: independent problems of the same shape (the
 // sub-quantizers of a product quantizer), their arrays one after the other.
 template <int DP>
@@ -89,7 +90,7 @@ __global__ __launch_bounds__(256) void segmented_mean_small_kernel(const float* 
                                                                    const int64_t* __restrict__ off, int K,
                                                                    float* __restrict__ centroids,
                                                                    double* __restrict__ partial) {
-  constexpr int CPW = 64 / DP, NB = 64, NO = NB / DP;            // centroids per wavefront, vectors per batch
+  constexpr int CPW = 64 / DP, NB = 32, NO = NB / DP;            // centroids per wavefront, vectors per batch
   const int lane = lane_id(), c = lane / DP, t = lane % DP;
   const int64_t j = (blockIdx.x * 4ll + (threadIdx.x >> 6)) * CPW + c;
   off += (int64_t)blockIdx.z * (K + 1);
@@ -106,22 +107,32 @@ __global__ __launch_bounds__(256) void segmented_mean_small_kernel(const float* 
     const bool mine_too = bk < nblk;
     const int64_t b = mine_too ? b0 + bk * kBlock : 0, e = mine_too ? min(e0, b + kBlock) : 0;
     double acc = 0.0;
-    int32_t num[NO], nxt[NO];
-    auto numbers = [&](int64_t i, int32_t (&v)[NO]) {            // (a group without vectors reads slot 0 and drops it)
+    int32_t n0[NO], n1[NO];
+    float v0[NB], v1[NB];
+    auto numbers = [&](int64_t i, int32_t (&num)[NO]) {          // (a group without vectors reads slot 0 and drops it)
 #pragma unroll
-      for (int o = 0; o < NO; ++o) v[o] = order[max(min(i + o * DP + t, e - 1), (int64_t)0)];
+      for (int o = 0; o < NO; ++o) num[o] = order[max(min(i + o * DP + t, e - 1), (int64_t)0)];
     };
-    numbers(b, num);
-    for (int64_t i = b; __builtin_amdgcn_ballot_w64(i < e) != 0; i += NB) {
-      numbers(i + NB, nxt);
-      float v[NB];
+    auto request = [&](const int32_t (&num)[NO], float (&v)[NB]) {
 #pragma unroll
       for (int u = 0; u < NB; ++u)
         v[u] = x[(int64_t)__shfl(num[u / DP], c * DP + u % DP) * d + tc];
+    };
+    auto add = [&](int64_t i, const float (&v)[NB]) {
 #pragma unroll
       for (int u = 0; u < NB; ++u) acc += i + u < e ? (double)v[u] : 0.0;
-#pragma unroll
-      for (int o = 0; o < NO; ++o) num[o] = nxt[o];
+    };
+    numbers(b, n0);
+    numbers(b + NB, n1);
+    request(n0, v0);
+    for (int64_t i = b; __builtin_amdgcn_ballot_w64(i < e) != 0; i += 2 * NB) {
+      numbers(i + 2 * NB, n0);
+      request(n1, v1);
+      add(i, v0);
+      if (__builtin_amdgcn_ballot_w64(i + NB < e) == 0) break;
+      numbers(i + 3 * NB, n1);
+      request(n0, v0);
+      add(i + NB, v1);
     }
     if (mine_too && t < d) {
       if (nblk == 1) centroids[j * d + t] = (float)(acc / count);
