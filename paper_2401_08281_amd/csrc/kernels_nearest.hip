@@ -86,6 +86,9 @@ enum { VEC_INT = 1, VEC_EXACT = 2, VEC_NONNEG = 4, VEC_LARGE = 8 };
 template <int KSTEPS, bool BF> constexpr int kNearestBlocks = BF && KSTEPS > 4 ? 1 : 2;
 
 constexpr int kCandidates = 16;
+// Threshold of a vector (or of a lane past the list) that collects nothing: no score compares with a
+// NaN, while the scores of a vector beyond the fp16 range reach +infinity themselves.
+__device__ __forceinline__ float collects_nothing() { return __builtin_nanf(""); }
 __device__ __forceinline__ bool heads_alone(const PrepInfo* info) {
   return (info->heads_only & 1u) != 0u && info->max_norm_bits <= 0x4E800000u;   // 2^30
 }
@@ -185,7 +188,7 @@ __global__ __launch_bounds__(256, 2) void nearest_kernel(
   for (int rb = 0; rb < RB; ++rb) {
     top[rb].init();
     const int64_t e = e0 + wave * (32 * RB) + rb * 32 + (lane & 31);
-    th_e[rb] = COLLECT && e < total ? thr[e] : __builtin_inff();
+    th_e[rb] = COLLECT && e < total ? thr[e] : collects_nothing();
   }
   if (c_begin < c_end) { fetch(c_begin); stash(0, c_begin); }
   wait_all_global_loads();
@@ -242,7 +245,7 @@ __global__ __launch_bounds__(256, 2) void nearest_kernel(
               const int64_t c = ct + cb * 32 + block_row(v, half);
               if (c < c_end) {
                 const int pos = atomicAdd(&cnt[e], 1);
-                if (pos < kCandidates) cand[e * kCandidates + pos] = (int)c;
+                if ((u32)pos < (u32)kCandidates) cand[e * kCandidates + pos] = (int)c;
               }
             }
         } else {
@@ -314,10 +317,10 @@ __global__ __launch_bounds__(256) void nearest_finish_kernel(
       eps += METRIC == 0 ? split * nn + sub + rounding : (bf ? 2.f : 1.f) * split * nn + sub + 2.f * rounding;
     }
     unsure = !(b1 - b2 > eps_scale * eps) || (!bf && (fl & VEC_LARGE)) || eps_scale < 0.f;
-    // (a vector beyond the fp16 range or with a NaN, and every vector where a norm overflows -- the
-    // score of a row with an infinity is a NaN that no threshold finds -- collects nothing and goes
-    // on to the canon chain)
-    from = (!bf && (fl & VEC_LARGE)) || eps_scale < 0.f || !(nn < __builtin_inff()) ? __builtin_inff() : b1 - eps;
+    // (a vector beyond the fp16 range or with a NaN, and every vector where a norm overflows -- their
+    // scores are infinities and NaNs that say nothing -- collects nothing and goes on to the canon
+    // chain)
+    from = (!bf && (fl & VEC_LARGE)) || eps_scale < 0.f || !(nn < __builtin_inff()) ? collects_nothing() : b1 - eps;
     idx[e] = best;
   }
   // one atomic per workgroup (per wavefront they were most of the kernel: 45 us for 4096 of them)

@@ -93,6 +93,37 @@ def test_nearest_row_sweep_with_nonfinite_centroids(vs, kind):
         np.testing.assert_array_equal(a, b)
 
 
+# Ordinary centroids (fp16 heads) next to vectors of which one, a few or all components are beyond the
+# fp16 range: only 12 rows of B have positive partners of these components (score +infinity), the
+# others have zeros (NaN).  The last vector is among them and n leaves lanes past the list's end.
+@pytest.mark.parametrize("metric", [L2, IP])
+@pytest.mark.parametrize("d", [32, 96, 100, 128])
+@pytest.mark.parametrize("which", ["one", "few", "all", "infinite"])
+def test_vectors_beyond_the_fp16_range_next_to_ordinary_centroids(vs, which, d, metric):
+    say("nearest, %s component(s) beyond fp16, d=%d metric=%d" % (which, d, metric))
+    n, nb = 701, 16_500                                 # (more than 16384 rows of B: always the sweep)
+    x, cent = rows("gauss", n, d, 12), rows("gauss", nb, d, 13)
+    cols = np.arange(d) if which == "all" else np.arange(3, d, d // 5)[:{"one": 1, "few": 5, "infinite": 1}[which]]
+    some = np.random.default_rng(14).choice(nb, 12, replace=False)
+    positive = np.abs(cent[some][:, cols])
+    if which != "all":
+        cent[:, cols] = 0.0
+    cent[np.ix_(some, cols)] = positive
+    large = np.arange(n) if which == "all" else np.arange(n - 1, 0, -3)
+    x[np.ix_(large, cols)] = np.inf if which == "infinite" else 1e5
+    xd, cd = dev(x), dev(cent)
+
+    def call():
+        ix = vs.IVFFlat(d, metric, cd)
+        ix.add(xd)
+        out = ix.list_sizes(), ix.storage()[0]
+        ix.close()
+        return out
+    canon, got = both_routes(vs, call)
+    for a, b in zip(canon, got):
+        np.testing.assert_array_equal(a, b)
+
+
 @pytest.mark.parametrize("n,d,K", [(20_001, 128, 300), (130_001, 17, 300), (1_500, 32, 16_385)])
 def test_kmeans_sweep_equals_canon_tiles(vs, n, d, K):
     """Three rounds: objective, assignment and centroids, with the bookkeeping on the device and
