@@ -677,6 +677,7 @@ int nearest_rows(const float* A, int64_t n, const float* B, int64_t nb, int d, i
     for (int64_t i0 = 0; i0 < n; i0 += piece)
       launch_nearest(A + i0 * d, std::min(piece, n - i0), d, metric, ob, g_knn_eps_scale.load(), idx + i0,
                      val ? val + i0 : nullptr, base + pb, st);
+    g_knn_mfma_rows += n;
     return VS_OK;
   }
   const KnnPlan plan = knn_plan_pieces(n, kPiece, nb, d, 1, false, true);
@@ -1065,6 +1066,7 @@ int ivf_assign_and_place(vs_ivfpq* ix, const float* x, int64_t n, size_t extra, 
     for (int64_t i0 = 0; i0 < n; i0 += sweep_piece)
       launch_nearest(x + i0 * g.d, std::min(sweep_piece, n - i0), g.d, cmetric, ob, g_knn_eps_scale.load(),
                      pl->list_of + i0, nullptr, base + o_knn, st);
+    g_knn_mfma_rows += n;
   } else if (plan.mfma) {
     for (int64_t i0 = 0; i0 < n;) {
       const int64_t ni = i0 == 0 && first_piece > 0 ? first_piece : std::min(kAssignPiece, n - i0);

@@ -345,14 +345,15 @@ __global__ __launch_bounds__(256) void nearest_finish_kernel(
 
 // The canon best among a listed vector's candidates: 16 lanes per vector, one candidate each.
 // Vectors whose candidates did not fit (or that have none) go to the list of the exact fallback.
+// learn: this call's counts may clear B's heads_only (not where every vector is listed on request).
 template <int METRIC>
 __global__ __launch_bounds__(256) void nearest_decide_kernel(
     const float* __restrict__ x, int64_t n, int d, const float* __restrict__ B, int64_t nb,
     PrepInfo* __restrict__ Binfo, const int* __restrict__ list, const int* __restrict__ list_count,
     const int* __restrict__ cnt, const int* __restrict__ cand, int32_t* __restrict__ idx,
-    int* __restrict__ fb_count, int* __restrict__ fb_rows) {
+    int* __restrict__ fb_count, int* __restrict__ fb_rows, bool learn) {
   const int total = (int)min((int64_t)*list_count, n);
-  if (blockIdx.x == 0 && threadIdx.x == 0 && total >= 64 && 2ll * total > n && heads_alone(Binfo)) {
+  if (learn && blockIdx.x == 0 && threadIdx.x == 0 && total >= 64 && 2ll * total > n && heads_alone(Binfo)) {
     // the fp16 heads decided fewer than half of the vectors: later calls use more products
     // (every kernel of this call that asks has run)
     atomicAnd(&Binfo->heads_only, ~1u);
@@ -692,7 +693,7 @@ void launch_nearest(const float* x, int64_t n, int d, int metric, const MfmaOper
 #define DECIDE(MET)                                                                                        \
   hipLaunchKernelGGL((nearest_decide_kernel<MET>), dim3((unsigned)std::min<int64_t>((n + 15) / 16, 4096)), \
                      dim3(256), 0, st, x, n, d, B.x, B.n, const_cast<PrepInfo*>(B.info), list, counts, cnt, \
-                     reinterpret_cast<const int*>(work + p.o_cand), idx, counts + 1, fb_rows)
+                     reinterpret_cast<const int*>(work + p.o_cand), idx, counts + 1, fb_rows, eps_scale >= 0.f)
   if (metric == 0) DECIDE(0); else DECIDE(1);
 #undef DECIDE
   SelectOut out;

@@ -124,6 +124,44 @@ def test_vectors_beyond_the_fp16_range_next_to_ordinary_centroids(vs, which, d, 
         np.testing.assert_array_equal(a, b)
 
 
+def well_separated(n, nb, d, seed, far=3):
+    """Vectors near centroids that are far apart, so that the first sweep is certain of every one, but for
+    the first `far`: their first component, which only centroid 5 has, is beyond what the fp16 heads
+    may hold, while bf16 products are certain of them.  The number of exact fallbacks thus tells which
+    products a call used: `far` by fp16 heads, none by bf16."""
+    cent = 10 * rows("gauss", nb, d, seed)
+    cent[:, 0] = 0.0
+    x = cent[np.random.default_rng(seed).integers(6, nb, n)] + rows("gauss", n, d, seed + 1)
+    x[:, 0] = 0.0
+    cent[5, 0] = 1000.0
+    x[:far, 0] = 40_000.0
+    return dev(x), dev(cent)
+
+
+def add_and_count(vs, ix, x):
+    vs.vs_counters_read()
+    ix.add(x)
+    return vs.vs_counters_read()
+
+
+def test_counters_cover_the_one_sweep_route_and_forced_fallbacks_teach_nothing(vs):
+    n, nb, d = 25_000, 300, 96
+    say("counters of the sweep n=%d nb=%d d=%d" % (n, nb, d))
+    x, cent = well_separated(n, nb, d, 20)
+    ix = vs.IVFFlat(d, L2, cent)
+    assert add_and_count(vs, ix, x) == (n, 3)
+    try:
+        vs.vs_set_option("knn_eps_scale", -1.0)
+        assert add_and_count(vs, ix, x) == (n, n)
+    finally:
+        vs.vs_set_option("knn_eps_scale", 1.0)
+    assert add_and_count(vs, ix, x) == (n, 3)          # (0 had the forced call moved the index to bf16)
+    c = cent.clone()
+    vs.vs_kmeans(x, c, 2)
+    assert vs.vs_counters_read()[0] == 2 * n
+    ix.close()
+
+
 @pytest.mark.parametrize("n,d,K", [(20_001, 128, 300), (130_001, 17, 300), (1_500, 32, 16_385)])
 def test_kmeans_sweep_equals_canon_tiles(vs, n, d, K):
     """Three rounds: objective, assignment and centroids, with the bookkeeping on the device and
