@@ -147,7 +147,7 @@ struct StageTimer {
 constexpr size_t kTileBytes = 128ull << 20;
 
 // ---- run-time options (vs_set_option) -----------------------------------------
-std::atomic<int> g_knn_path{0};          // 0 auto, 1 canon tiles only, 2 MFMA shortlist whenever supported
+std::atomic<int> g_knn_path{0};          // 0 auto, 1 canon tiles only, 2 matrix cores whenever supported
 // List-major IVF-PQ scan: 0 where it pays (large batch, long code store), 1 wherever the shape
 // allows it, -1 never; and its two sizes: probes scanned query-major first, candidates per query.
 std::atomic<int> g_list_major{0};
@@ -227,14 +227,17 @@ struct KnnPlan {
 // cost in full.  Measured on 256 - 65536 columns of 32 - 768 dimensions, 1 - 1000 rows: the canon
 // route is ahead up to about 6e8 multiply-adds (4096 x 128, 1000 rows: 63 against 74 us; 1 row: 35
 // against 60) while the columns fit one tile (65536 x 96, 1 row: 168 against 80).
-bool knn_small(int64_t na, int64_t nb, int d) { return nb <= 16384 && (double)na * nb * d <= 6e8; }
+// (not with knn_path = 2, which takes the matrix cores wherever there is a kernel)
+bool knn_small(int64_t na, int64_t nb, int d) {
+  return g_knn_path.load() == 0 && nb <= 16384 && (double)na * nb * d <= 6e8;
+}
 // route: 1 / 0 = the matrix-core / the canon route (a plan made before for a larger piece of the
 // same rows), -1 = choose; small_canon: choose the canon route for problems that are small.
 KnnPlan knn_plan(int64_t na, int64_t nb, int d, int k, bool b_prepared, bool small_canon, int route = -1) {
   KnnPlan p;
   const int path = g_knn_path.load();
   p.mfma = path != 1 && nb > 0 && mfma_knn_supported(d, k) &&
-           (route < 0 ? !(small_canon && path == 0 && knn_small(na, nb, d)) : route == 1);
+           (route < 0 ? !(small_canon && knn_small(na, nb, d)) : route == 1);
   if (p.mfma) {
     size_t b = planes_bytes(na, d);
     if (!b_prepared) b += planes_bytes(nb, d);

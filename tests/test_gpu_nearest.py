@@ -20,19 +20,31 @@ def rows(kind, n, d, seed):
     return x * np.float32({"gauss": 1.0, "beyond_fp16": 3e5, "tiny": 1e-18}[kind])
 
 
-def both_routes(vs, call):
-    """call() by the canon tiles and by the default route."""
-    try:
-        vs.vs_set_option("knn_path", 1)
-        canon = [host(t).copy() for t in call()]
-    finally:
-        vs.vs_set_option("knn_path", 0)
-    return canon, [host(t).copy() for t in call()]
+def both_routes(vs, call, counted=None):
+    """call() by the canon tiles, and by the matrix cores: where the library chooses them and wherever there
+    is a kernel (the results of these two agree).  counted: the rows that the latter has to count."""
+    def by(path):
+        try:
+            vs.vs_set_option("knn_path", path)
+            vs.vs_counters_read()
+            out = [host(t).copy() for t in call()]
+            return out, vs.vs_counters_read()[0]
+        finally:
+            vs.vs_set_option("knn_path", 0)
+    canon, rows_canon = by(1)
+    chosen, _ = by(0)
+    forced, rows_forced = by(2)
+    assert rows_canon == 0
+    if counted is not None:
+        assert rows_forced == counted
+    for a, b in zip(chosen, forced):
+        np.testing.assert_array_equal(a, b)
+    return canon, forced
 
 
-# n * rows * d is above 6e8, the size from which the sweep is used.  d: both ends of the range, every
-# padded length, remainders of 4, 2 and 1; rows of B: one step and a remainder, one past a step, a
-# split; n: one past a tile, remainders.
+# Each part of an add is above 6e8 = n * rows * d, the size from which the sweep is chosen, or is taken to
+# the sweep by knn_path = 2.  d: both ends of the range, every padded length, remainders of 4, 2 and 1;
+# rows of B: one step and a remainder, one past a step, a split; n: one past a tile, remainders.
 NEAREST_CASES = [
     ("d17", 131_073, 300, 17, L2, "gauss"), ("d30_ip", 80_001, 300, 30, IP, "gauss"),
     ("d32", 60_033, 321, 32, L2, "sift"), ("d64_ip", 30_001, 320, 64, IP, "gauss"),
@@ -48,15 +60,16 @@ NEAREST_CASES = [
 @pytest.mark.parametrize("name,n,nb,d,metric,kind", NEAREST_CASES, ids=[c[0] for c in NEAREST_CASES])
 @pytest.mark.parametrize("special", ["plain", "ties_and_nonfinite"])
 def test_nearest_row_sweep_equals_canon_tiles(vs, name, n, nb, d, metric, kind, special):
-    """List assignment.  Second variant: centroids that occur twice (the smaller one wins), vectors
-    that are a centroid, hold an infinity, a NaN or only zeros."""
+    """List assignment, in two parts.  Second variant: centroids that occur twice (the smaller one wins), and
+    in both parts vectors that are a centroid, hold an infinity, a NaN or only zeros, the last one too."""
     say("nearest %s n=%d nb=%d d=%d metric=%d %s" % (name, n, nb, d, metric, special))
     x = rows(kind, n, d, 1)
     cent = rows(kind, nb, d, 2)
     if special != "plain":
         cent[nb // 2:] = cent[:nb - nb // 2]
-        x[5:5 + nb // 2:2] = cent[:len(x[5:5 + nb // 2:2])]
-        x[1, d - 1], x[2, 0], x[3] = np.inf, np.nan, 0.0
+        for part in (x[:n // 3], x[n // 3:]):
+            part[5:5 + nb // 2:2] = cent[:len(part[5:5 + nb // 2:2])]
+            part[1, d - 1], part[2, 0], part[3], part[-1, 0] = np.inf, np.nan, 0.0, -np.inf
     xd, cd = dev(x), dev(cent)
 
     def call():
@@ -66,9 +79,47 @@ def test_nearest_row_sweep_equals_canon_tiles(vs, name, n, nb, d, metric, kind, 
         out = ix.list_sizes(), ix.storage()[0]
         ix.close()
         return out
-    canon, got = both_routes(vs, call)
+    canon, got = both_routes(vs, call, n)
     for a, b in zip(canon, got):
         np.testing.assert_array_equal(a, b)
+
+
+@pytest.mark.parametrize("d", [17, 31, 32, 33, 48, 63, 64, 65, 80, 96, 97, 112, 127, 128])
+def test_small_sweeps_equal_canon_tiles(vs, d):
+    """Fewer vectors than a wavefront, a workgroup, a tile has, and one more; rows of B around one step of 64,
+    and enough for splits of several sizes; fp16 heads, bf16 (values beyond fp16), exact operands."""
+    for n in (1, 31, 65, 256, 257, 641):
+        for nb, kind, metric in ((1, "gauss", L2), (2, "sift", IP), (63, "beyond_fp16", L2), (64, "gauss", IP),
+                                 (65, "sift", L2), (513, "gauss", L2), (2_000, "beyond_fp16", IP), (2_049, "gauss", L2)):
+            say("small sweep n=%d nb=%d d=%d metric=%d %s" % (n, nb, d, metric, kind))
+            x, cent = rows(kind, n, d, 15), rows(kind, nb, d, 16)
+            cent[nb // 2:] = cent[:nb - nb // 2]
+            x[-1] = cent[-1]
+            xd, cd = dev(x), dev(cent)
+
+            def call():
+                ix = vs.IVFFlat(d, metric, cd)
+                ix.add(xd)
+                out = ix.list_sizes(), ix.storage()[0]
+                ix.close()
+                return out
+            canon, got = both_routes(vs, call, n)
+            for a, b in zip(canon, got):
+                np.testing.assert_array_equal(a, b)
+
+
+def test_knn_path_2_takes_small_assignments_to_the_matrix_cores(vs):
+    x, cent = dev(rows("gauss", 100, 64, 17)), dev(rows("gauss", 50, 64, 18))
+    ix = vs.IVFFlat(64, L2, cent)
+    try:
+        for path, rows_counted in ((0, 0), (2, 100), (1, 0)):
+            vs.vs_set_option("knn_path", path)
+            assert add_and_count(vs, ix, x)[0] == rows_counted
+            vs.vs_kmeans(x, cent.clone(), 3)
+            assert vs.vs_counters_read()[0] == 3 * rows_counted
+    finally:
+        vs.vs_set_option("knn_path", 0)
+    ix.close()
 
 
 @pytest.mark.parametrize("kind", ["all_nan", "one_inf", "huge", "inf_among_few_ip"])
