@@ -1032,12 +1032,12 @@ int ivf_assign_and_place(vs_ivfpq* ix, const float* x, int64_t n, size_t extra, 
   // scratch: work space of the MFMA assignment (pieces of at most kAssignPiece vectors) |
   // best keys [n] | list_of [n] | caller's extra | dest [n] | new offsets | work space of the placement
   constexpr int64_t kAssignPiece = 1 << 20;
-  // The first piece of an index's first large add is a short one: the sweeps start out on the
-  // fp16 heads alone and learn from a call's fallback count whether that does for this data; a
+  // On the k-nearest-rows route (d above 128) the first piece of an index's first large add is a short
+  // one: the sweeps start out on the fp16 heads alone and learn from a call's fallback count whether that does for this data; a
   // short first call keeps the price of finding out small.
   constexpr int64_t kProbePiece = 8192;
-  // one sweep that keeps the best row only (no pieces to learn from: its undecided vectors are
-  // swept again with more products, not redone in full)
+  // one sweep that keeps the best row only (no short first piece: the vectors that its fp16 heads leave
+  // with too many candidates are swept with three products in the same call, not redone in full)
   const bool one_sweep = g_knn_path.load() != 1 && ix->has_planes && nearest_supported(g.d) && !knn_small(n, g.nlist, g.d);
   const int64_t sweep_piece = std::min<int64_t>(n, 4 * kAssignPiece);
   const int64_t first_piece = !ix->assign_probed && n > 4 * kProbePiece ? kProbePiece : 0;

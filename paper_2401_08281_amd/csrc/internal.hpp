@@ -130,13 +130,15 @@ struct PrepInfo {
   u32 all_bf16;       // every value is exactly representable in bf16
   u32 max_norm_bits;  // bits of the largest squared row norm (non-negative float)
   u32 all_nonneg;     // no value is negative
-  // Of the column operand of a k-nearest-rows call only, and only where that operand outlives the
-  // call (an index's centroids or vectors): bit 0 (calls with k = 1) and bit 1 (k > 1) are set
-  // while the sweeps of such calls may use the fp16 heads alone on operands that are not exactly
-  // bf16 (one matrix product instead of three, with the wider error bound that goes with it).  A
-  // bit is cleared for good by the exact fallback once more than one row in 512 of a call failed
-  // the sufficiency test under that bound (k > 1), or by the one-sweep route once more than half of a
-  // call's vectors had to be swept again (k = 1).
+  // Of the column operand of a k-nearest-rows or one-sweep call only, and only where that operand
+  // outlives the call (an index's centroids or vectors, the centroids of a k-means run): a bit for each
+  // kind of call -- k = 1, k > 1, one sweep -- is set while the sweeps of such calls may use the fp16
+  // heads alone on operands that are not exactly bf16 (one matrix product instead of three, with the
+  // wider error bound that goes with it).  The bit is cleared for good by the exact fallback once more
+  // than one row in 512 of a call failed the sufficiency test under that bound, and by the one-sweep
+  // route (which takes the rows that fail through three products within the call) once more than half of
+  // a call's vectors had to be swept again.
+  static constexpr u32 kHeadsOne = 1u, kHeadsMany = 2u, kHeadsSweep = 4u, kHeadsAll = 7u;
   u32 heads_only;
 };
 struct MfmaOperand {

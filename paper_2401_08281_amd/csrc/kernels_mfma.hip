@@ -258,7 +258,7 @@ __global__ __launch_bounds__(256) void prep_panel_kernel(const float* __restrict
 
 __global__ void prep_info_init_kernel(PrepInfo* info, u32 heads_only, u32 keep_heads) {
   info->all_int = 1u; info->all_bf16 = 1u; info->max_norm_bits = 0u; info->all_nonneg = 1u;
-  if (!keep_heads) info->heads_only = heads_only ? 3u : 0u;
+  if (!keep_heads) info->heads_only = heads_only ? PrepInfo::kHeadsAll : 0u;
 }
 
 // ---------------------------------------------------------------------------
@@ -1118,7 +1118,7 @@ __global__ __launch_bounds__(256) void canon_rows_tiled_kernel(const float* __re
     // heads alone did not do for calls of this kind on this operand: so many rows had to be redone
     // here (more than one in 512) that it cost more than the two matrix products saved -- from the
     // next call on the sweeps use all three
-    const u32 bit = k == 1 ? 1u : 2u;
+    const u32 bit = k == 1 ? PrepInfo::kHeadsOne : PrepInfo::kHeadsMany;
     if (adapt && (adapt->heads_only & bit) && count >= 8 && (int64_t)count * 512 > na) atomicAnd(&adapt->heads_only, ~bit);
   }
   const FallbackSplit fs = fallback_split(count, nb, k, chunk_cols0, nchunk0, cap_keys);
@@ -1299,7 +1299,7 @@ struct MfmaPlan {
 size_t up256(size_t v) { return (v + 255) / 256 * 256; }
 // Calls for the single nearest row (list assignment) and calls for the k > 1 nearest (probes, flat
 // search) learn separately whether the heads alone do: their margins differ.
-__host__ __device__ inline int heads_only_bit(int k) { return k == 1 ? 1 : 2; }
+__host__ __device__ inline int heads_only_bit(int k) { return (int)(k == 1 ? PrepInfo::kHeadsOne : PrepInfo::kHeadsMany); }
 
 MfmaPlan make_plan(int64_t na, int64_t nb, int k, int d) {
   MfmaPlan p;

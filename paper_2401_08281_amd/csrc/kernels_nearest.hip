@@ -73,12 +73,14 @@ enum { VEC_INT = 1, VEC_EXACT = 2, VEC_NONNEG = 4, VEC_LARGE = 8 };
 // registers, and walks over a range of B in steps of 64 rows staged through LDS (double
 // buffered, padded rows: conflict-free 128-bit reads), each tile read by all four wavefronts.
 // BF == false: one product on the fp16 heads.  BF == true: bf16 heads, and the products with the
-// tails of either side where that side is not exactly bf16.  Both are launched; B's PrepInfo says
-// which one works: the heads alone until they are out of range or have failed too often.
-// COLLECT: the second sweep.  thr [e] = the score from which a row may still be the best; passing
-// rows go to cand [e][kCandidates] and are counted in cnt [e].
+// tails of either side where that side is not exactly bf16.  A call launches both, one pass after the
+// other, and NearestState says what each has to do (pass_vectors): where B's rows are in range and the
+// heads have not failed too often they take all vectors, and the bf16 pass those that the heads left
+// with too many candidates; else the bf16 pass takes all.
+// COLLECT: the second sweep of a pass.  thr [e] = the score from which a row may still be the best;
+// passing rows go to cand [e][kCandidates] and are counted in cnt [e].
 // Per 32 x 32 block: KSTEPS products of 32 cycles against 16 x 3 selection instructions of 4.
-// rows / count: null, or the list of vectors to do and its length (device memory).
+// rows: the numbers of the vectors to do, where they are not all.
 // Assignment of 1M integer vectors to 4096 rows at d = 128 (two sweeps, threshold, re-rank and
 // operand preparation before): 6.1 -> 1.4 ms (first sweep 1.13, second 0.22).
 // ---------------------------------------------------------------------------
@@ -89,16 +91,32 @@ constexpr int kCandidates = 16;
 // Threshold of a vector (or of a lane past the list) that collects nothing: no score compares with a
 // NaN, while the scores of a vector beyond the fp16 range reach +infinity themselves.
 __device__ __forceinline__ float collects_nothing() { return __builtin_nanf(""); }
-__device__ __forceinline__ bool heads_alone(const PrepInfo* info) {
-  return (info->heads_only & 1u) != 0u && info->max_norm_bits <= 0x4E800000u;   // 2^30
+
+// What a call's kernels tell each other (device memory).  listed: vectors whose best row a pass was
+// not certain of; left: those that its candidates did not decide.
+struct NearestState {
+  int heads;                  // the fp16 heads take all vectors first
+  int listed[2], left[2];     // of the fp16 pass and of the bf16 pass
+};
+// Few vectors that the heads left go straight to the canon chain, which spreads a single one over the
+// chip; a bf16 sweep costs about what redoing one vector in 512 costs (the rule of the k-nearest-rows
+// route's fallback).
+__device__ __forceinline__ bool sweep_left(const NearestState* s, int64_t n) {
+  return s->left[0] >= 8 && (int64_t)s->left[0] * 512 > n;
+}
+// vectors of the first sweep of a pass: all (null) or the ones left by the pass before
+__device__ __forceinline__ int64_t pass_vectors(const NearestState* s, int64_t n, bool bf, const int*& rows) {
+  if (!bf) { rows = nullptr; return s->heads ? n : 0; }
+  if (!s->heads) { rows = nullptr; return n; }
+  return sweep_left(s, n) ? min((int64_t)s->left[0], n) : 0;
 }
 
 template <int KSTEPS, int METRIC, bool BF, bool COLLECT>
 __global__ __launch_bounds__(256, 2) void nearest_kernel(
     const float* __restrict__ x, int64_t n, int d, const unsigned short* __restrict__ Bh,
-    const unsigned short* __restrict__ Bl, const float* __restrict__ Bnorm, PrepInfo* __restrict__ Binfo,
-    int64_t nb, int64_t tiles, int64_t cols_per_split, const int* __restrict__ rows,
-    const int* __restrict__ count, float* __restrict__ out_b1, float* __restrict__ out_b2,
+    const unsigned short* __restrict__ Bl, const float* __restrict__ Bnorm, const PrepInfo* __restrict__ Binfo,
+    int64_t nb, int64_t tiles, int64_t cols_per_split, const int* rows,
+    const NearestState* __restrict__ state, float* __restrict__ out_b1, float* __restrict__ out_b2,
     int* __restrict__ out_idx, float* __restrict__ out_norm, unsigned char* __restrict__ out_flags,
     const float* __restrict__ thr, int* __restrict__ cnt, int* __restrict__ cand) {
   constexpr int D = KSTEPS * 16, BN = 64, LDB = D + 8, NPL = BF ? 2 : 1, RB = kNearestBlocks<KSTEPS, BF>;
@@ -108,11 +126,10 @@ __global__ __launch_bounds__(256, 2) void nearest_kernel(
   float* nrm_s = reinterpret_cast<float*>(bt + 2 * NPL * BN * LDB);   // [2][BN] starting values
   const int tid = threadIdx.x, wave = tid >> 6, lane = lane_id(), half = lane >> 5;
   const int64_t split = blockIdx.x / tiles, tile = blockIdx.x - split * tiles;
-  const int64_t total = count ? min((int64_t)*count, n) : n;
+  const int64_t total = COLLECT ? min((int64_t)state->listed[BF], n) : pass_vectors(state, n, BF, rows);
   const int64_t e0 = tile * 128 * RB;
   if (e0 >= total) return;
   const int64_t c_begin = split * cols_per_split, c_end = min(nb, c_begin + cols_per_split);
-  if (heads_alone(Binfo) == BF) return;                           // the other precision does the work
   const bool use_bl = BF && Binfo->all_bf16 == 0u;
   const bool vec = (d & 3) == 0;
 
@@ -278,18 +295,25 @@ __global__ __launch_bounds__(256, 2) void nearest_kernel(
 }
 
 // Merges the splits, writes every vector's best row and puts those that are not certain on the
-// list, each with the score down to which a row may still be the best.
-template <int METRIC>
+// list, each with the score down to which a row may still be the best.  left: the vectors that the
+// fp16 pass left (for the bf16 pass).
+template <int METRIC, bool BF>
 __global__ __launch_bounds__(256) void nearest_finish_kernel(
     int64_t n, int d, int nsplit, const float* __restrict__ in_b1, const float* __restrict__ in_b2,
     const int* __restrict__ in_idx, const float* __restrict__ norm, const unsigned char* __restrict__ flags,
-    const PrepInfo* __restrict__ Binfo, float eps_scale, int32_t* __restrict__ idx, int* __restrict__ list_count,
-    int* __restrict__ list, float* __restrict__ thr, int* __restrict__ cnt) {
+    const PrepInfo* __restrict__ Binfo, float eps_scale, int32_t* __restrict__ idx, const int* __restrict__ left,
+    NearestState* __restrict__ state, int* __restrict__ list, float* __restrict__ thr, int* __restrict__ cnt) {
   const int64_t e = blockIdx.x * 256ll + threadIdx.x;
-  const bool bf = !heads_alone(Binfo);
+  constexpr bool bf = BF;
+  const int* rows = left;
+  const int64_t total = pass_vectors(state, n, BF, rows);
+  if (BF && e == 0 && total == 0) state->left[1] = state->left[0];   // (no second pass: its list stands)
+  if (blockIdx.x * 256ll >= total) return;
   bool unsure = false;
   float from = 0.f;
-  if (e < n) {
+  int row = 0;
+  if (e < total) {
+    row = rows ? rows[e] : (int)e;
     float b1 = -__builtin_inff(), b2 = b1;
     int best = 0;
     for (int s = 0; s < nsplit; ++s) {
@@ -318,10 +342,10 @@ __global__ __launch_bounds__(256) void nearest_finish_kernel(
     }
     unsure = !(b1 - b2 > eps_scale * eps) || (!bf && (fl & VEC_LARGE)) || eps_scale < 0.f;
     // (a vector beyond the fp16 range or with a NaN, and every vector where a norm overflows -- their
-    // scores are infinities and NaNs that say nothing -- collects nothing and goes on to the canon
-    // chain)
+    // scores are infinities and NaNs that say nothing -- collects nothing: it is left to the next pass
+    // or the canon chain)
     from = (!bf && (fl & VEC_LARGE)) || eps_scale < 0.f || !(nn < __builtin_inff()) ? collects_nothing() : b1 - eps;
-    idx[e] = best;
+    idx[row] = best;
   }
   // one atomic per workgroup (per wavefront they were most of the kernel: 45 us for 4096 of them)
   __shared__ int wave_count[4], base_s;
@@ -331,32 +355,33 @@ __global__ __launch_bounds__(256) void nearest_finish_kernel(
   __syncthreads();
   if (threadIdx.x == 0) {
     const int all = wave_count[0] + wave_count[1] + wave_count[2] + wave_count[3];
-    base_s = all > 0 ? atomicAdd(list_count, all) : 0;
+    base_s = all > 0 ? atomicAdd(&state->listed[BF], all) : 0;
   }
   __syncthreads();
   if (unsure) {
     int at = base_s + __popcll(mask & ((1ull << lane) - 1ull));
     for (int w = 0; w < wave; ++w) at += wave_count[w];
-    list[at] = (int)e;
+    list[at] = row;
     thr[at] = from;
     cnt[at] = 0;
   }
 }
 
 // The canon best among a listed vector's candidates: 16 lanes per vector, one candidate each.
-// Vectors whose candidates did not fit (or that have none) go to the list of the exact fallback.
+// Vectors whose candidates did not fit (or that have none) are left to the bf16 pass or, after it, to
+// the canon chain over all rows.
 // learn: this call's counts may clear B's heads_only (not where every vector is listed on request).
-template <int METRIC>
+template <int METRIC, bool BF>
 __global__ __launch_bounds__(256) void nearest_decide_kernel(
     const float* __restrict__ x, int64_t n, int d, const float* __restrict__ B, int64_t nb,
-    PrepInfo* __restrict__ Binfo, const int* __restrict__ list, const int* __restrict__ list_count,
+    PrepInfo* __restrict__ Binfo, const int* __restrict__ list, NearestState* __restrict__ state,
     const int* __restrict__ cnt, const int* __restrict__ cand, int32_t* __restrict__ idx,
-    int* __restrict__ fb_count, int* __restrict__ fb_rows, bool learn) {
-  const int total = (int)min((int64_t)*list_count, n);
-  if (learn && blockIdx.x == 0 && threadIdx.x == 0 && total >= 64 && 2ll * total > n && heads_alone(Binfo)) {
-    // the fp16 heads decided fewer than half of the vectors: later calls use more products
-    // (every kernel of this call that asks has run)
-    atomicAnd(&Binfo->heads_only, ~1u);
+    int* __restrict__ left, bool learn) {
+  const int total = (int)min((int64_t)state->listed[BF], n);
+  if (!BF && learn && blockIdx.x == 0 && threadIdx.x == 0 && total >= 64 && 2ll * total > n) {
+    // the fp16 heads decided fewer than half of the vectors: later calls begin with bf16 (the heads
+    // cost one product, the second sweep and three products for what they leave)
+    atomicAnd(&Binfo->heads_only, ~PrepInfo::kHeadsSweep);
   }
   const bool vec = (d & 3) == 0;
   const int lane = lane_id(), sub = lane & 15;
@@ -364,7 +389,7 @@ __global__ __launch_bounds__(256) void nearest_decide_kernel(
     if (e >= total) continue;
     const int row = list[e], c = cnt[e];
     if (c < 1 || c > kCandidates) {
-      if (sub == 0) fb_rows[atomicAdd(fb_count, 1)] = row;
+      if (sub == 0) left[atomicAdd(&state->left[BF], 1)] = row;
       continue;
     }
     u64 key = KEY_EMPTY;
@@ -423,7 +448,10 @@ __global__ __launch_bounds__(64) void row_values_kernel(const float* __restrict_
   if (i0 + lane < n) val[i0 + lane] = acc;
 }
 
-__global__ void nearest_counts_kernel(int* counts) { if (threadIdx.x < 2) counts[threadIdx.x] = 0; }
+__global__ void nearest_state_kernel(const PrepInfo* __restrict__ Binfo, NearestState* __restrict__ s) {
+  s->heads = (Binfo->heads_only & PrepInfo::kHeadsSweep) != 0u && Binfo->max_norm_bits <= 0x4E800000u;   // 2^30
+  s->listed[0] = s->listed[1] = s->left[0] = s->left[1] = 0;
+}
 
 // ---------------------------------------------------------------------------
 // Nearest codeword of every sub-vector (at most 16 dimensions, 256 or 16 codewords).
@@ -602,7 +630,7 @@ __global__ __launch_bounds__(256, NP == 1 ? 4 : 2) void pq_nearest_kernel(
   }
 }
 
-struct NearestPlan { int nsplit; int64_t cols_per_split; size_t o_b2, o_idx, o_norm, o_flags, o_counts, o_list, o_thr, o_cnt, o_cand, o_fbrows, o_fb, bytes; };
+struct NearestPlan { int nsplit; int64_t cols_per_split; size_t o_b2, o_idx, o_norm, o_flags, o_state, o_list, o_thr, o_cnt, o_cand, o_left, o_fb, bytes; };
 NearestPlan nearest_plan(int64_t n, int64_t nb) {
   NearestPlan p;
   const int64_t tiles = (n + 255) / 256;
@@ -620,12 +648,12 @@ NearestPlan nearest_plan(int64_t n, int64_t nb) {
   p.o_idx = take((size_t)p.nsplit * n * sizeof(int));
   p.o_norm = take((size_t)n * sizeof(float));
   p.o_flags = take((size_t)n);
-  p.o_counts = take(2 * sizeof(int));
+  p.o_state = take(sizeof(NearestState));
   p.o_list = take((size_t)n * sizeof(int));
   p.o_thr = take((size_t)n * sizeof(float));
   p.o_cnt = take((size_t)n * sizeof(int));
   p.o_cand = take((size_t)n * kCandidates * sizeof(int));
-  p.o_fbrows = take((size_t)n * sizeof(int));
+  p.o_left = take((size_t)n * sizeof(int));
   p.o_fb = take(mfma_knn_fallback_bytes(n, nb, 1));
   p.bytes = o;
   return p;
@@ -641,20 +669,19 @@ void launch_nearest_t(const NearestPlan& p, const float* x, int64_t n, int d, co
   constexpr int64_t per_tile = 128 * kNearestBlocks<KSTEPS, BF>;
   const int64_t tiles = (n + per_tile - 1) / per_tile;
   hipLaunchKernelGGL(kern, dim3((unsigned)(tiles * p.nsplit)), dim3(256), lds, st, x, n, d, BF ? B.hi : B.h16, B.lo,
-                     B.norm, const_cast<PrepInfo*>(B.info), B.n, tiles, p.cols_per_split,
-                     COLLECT ? reinterpret_cast<const int*>(w + p.o_list) : nullptr,
-                     COLLECT ? reinterpret_cast<const int*>(w + p.o_counts) : nullptr,
+                     B.norm, B.info, B.n, tiles, p.cols_per_split,
+                     reinterpret_cast<const int*>(w + (COLLECT ? p.o_list : p.o_left)),
+                     reinterpret_cast<const NearestState*>(w + p.o_state),
                      reinterpret_cast<float*>(w), reinterpret_cast<float*>(w + p.o_b2),
                      reinterpret_cast<int*>(w + p.o_idx), reinterpret_cast<float*>(w + p.o_norm),
                      reinterpret_cast<unsigned char*>(w + p.o_flags), reinterpret_cast<const float*>(w + p.o_thr),
                      reinterpret_cast<int*>(w + p.o_cnt), reinterpret_cast<int*>(w + p.o_cand));
 }
-template <bool COLLECT>
+template <bool BF, bool COLLECT>
 void launch_nearest_any(const NearestPlan& p, const float* x, int64_t n, int d, int metric, const MfmaOperand& B,
                         char* w, hipStream_t st) {
-#define GO2(KS, MET) do { launch_nearest_t<KS, MET, false, COLLECT>(p, x, n, d, B, w, st); \
-                          launch_nearest_t<KS, MET, true, COLLECT>(p, x, n, d, B, w, st); } while (0)
-#define GO(KS) do { if (metric == 0) GO2(KS, 0); else GO2(KS, 1); } while (0)
+#define GO(KS) do { if (metric == 0) launch_nearest_t<KS, 0, BF, COLLECT>(p, x, n, d, B, w, st); \
+                    else launch_nearest_t<KS, 1, BF, COLLECT>(p, x, n, d, B, w, st); } while (0)
   switch (mfma_padded_dim(d) / 16) {
     case 2: GO(2); break;
     case 4: GO(4); break;
@@ -662,7 +689,26 @@ void launch_nearest_any(const NearestPlan& p, const float* x, int64_t n, int d, 
     default: GO(8); break;
   }
 #undef GO
-#undef GO2
+}
+
+// One pass: sweep, list, second sweep over the listed vectors, decision.
+template <int METRIC, bool BF>
+void launch_nearest_pass(const NearestPlan& p, const float* x, int64_t n, int d, const MfmaOperand& B, float eps_scale,
+                         int32_t* idx, char* w, hipStream_t st) {
+  NearestState* state = reinterpret_cast<NearestState*>(w + p.o_state);
+  int* list = reinterpret_cast<int*>(w + p.o_list);
+  int* cnt = reinterpret_cast<int*>(w + p.o_cnt);
+  int* left = reinterpret_cast<int*>(w + p.o_left);
+  launch_nearest_any<BF, false>(p, x, n, d, METRIC, B, w, st);
+  hipLaunchKernelGGL((nearest_finish_kernel<METRIC, BF>), dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st, n, d,
+                     p.nsplit, reinterpret_cast<const float*>(w), reinterpret_cast<const float*>(w + p.o_b2),
+                     reinterpret_cast<const int*>(w + p.o_idx), reinterpret_cast<const float*>(w + p.o_norm),
+                     reinterpret_cast<const unsigned char*>(w + p.o_flags), B.info, eps_scale, idx, left, state, list,
+                     reinterpret_cast<float*>(w + p.o_thr), cnt);
+  launch_nearest_any<BF, true>(p, x, n, d, METRIC, B, w, st);
+  hipLaunchKernelGGL((nearest_decide_kernel<METRIC, BF>), dim3((unsigned)std::min<int64_t>((n + 15) / 16, 4096)),
+                     dim3(256), 0, st, x, n, d, B.x, B.n, const_cast<PrepInfo*>(B.info), list, state, cnt,
+                     reinterpret_cast<const int*>(w + p.o_cand), idx, left, eps_scale >= 0.f);
 }
 
 }  // namespace
@@ -675,30 +721,19 @@ void launch_nearest(const float* x, int64_t n, int d, int metric, const MfmaOper
                     int32_t* idx, float* val, char* work, hipStream_t st) {
   if (n <= 0) return;
   const NearestPlan p = nearest_plan(n, B.n);
-  int* counts = reinterpret_cast<int*>(work + p.o_counts);
-  hipLaunchKernelGGL(nearest_counts_kernel, dim3(1), dim3(64), 0, st, counts);
-  launch_nearest_any<false>(p, x, n, d, metric, B, work, st);
-  int* list = reinterpret_cast<int*>(work + p.o_list);
-  int* cnt = reinterpret_cast<int*>(work + p.o_cnt);
-  int* fb_rows = reinterpret_cast<int*>(work + p.o_fbrows);
-#define FINISH(MET)                                                                                        \
-  hipLaunchKernelGGL((nearest_finish_kernel<MET>), dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st, n, d, \
-                     p.nsplit, reinterpret_cast<const float*>(work), reinterpret_cast<const float*>(work + p.o_b2), \
-                     reinterpret_cast<const int*>(work + p.o_idx), reinterpret_cast<const float*>(work + p.o_norm), \
-                     reinterpret_cast<const unsigned char*>(work + p.o_flags), B.info, eps_scale, idx, counts, list, \
-                     reinterpret_cast<float*>(work + p.o_thr), cnt)
-  if (metric == 0) FINISH(0); else FINISH(1);
-#undef FINISH
-  launch_nearest_any<true>(p, x, n, d, metric, B, work, st);
-#define DECIDE(MET)                                                                                        \
-  hipLaunchKernelGGL((nearest_decide_kernel<MET>), dim3((unsigned)std::min<int64_t>((n + 15) / 16, 4096)), \
-                     dim3(256), 0, st, x, n, d, B.x, B.n, const_cast<PrepInfo*>(B.info), list, counts, cnt, \
-                     reinterpret_cast<const int*>(work + p.o_cand), idx, counts + 1, fb_rows, eps_scale >= 0.f)
-  if (metric == 0) DECIDE(0); else DECIDE(1);
-#undef DECIDE
+  NearestState* state = reinterpret_cast<NearestState*>(work + p.o_state);
+  hipLaunchKernelGGL(nearest_state_kernel, dim3(1), dim3(1), 0, st, B.info, state);
+  if (metric == 0) {
+    launch_nearest_pass<0, false>(p, x, n, d, B, eps_scale, idx, work, st);
+    launch_nearest_pass<0, true>(p, x, n, d, B, eps_scale, idx, work, st);
+  } else {
+    launch_nearest_pass<1, false>(p, x, n, d, B, eps_scale, idx, work, st);
+    launch_nearest_pass<1, true>(p, x, n, d, B, eps_scale, idx, work, st);
+  }
   SelectOut out;
   out.idx32 = idx;
-  launch_canon_rows(x, n, B.x, B.n, d, metric, 1, out, counts + 1, fb_rows, reinterpret_cast<u64*>(work + p.o_fb), nullptr, st);
+  launch_canon_rows(x, n, B.x, B.n, d, metric, 1, out, &state->left[1], reinterpret_cast<const int*>(work + p.o_left),
+                    reinterpret_cast<u64*>(work + p.o_fb), nullptr, st);
   if (val) hipLaunchKernelGGL(row_values_kernel, dim3((unsigned)((n + 63) / 64)), dim3(64), 0, st, x, n, d, B.x, idx, val);
 }
 

@@ -213,6 +213,79 @@ def test_counters_cover_the_one_sweep_route_and_forced_fallbacks_teach_nothing(v
     ix.close()
 
 
+def tight_groups(n, d, size, share, seed):
+    """Groups of `size` centroids whose squared distances to the group's centre are 0, 0.95, 1.9, ..., the
+    centres some 100 times that apart, and vectors at the centres (`share` of them; the others are at
+    centroids that stand alone).  |a|^2 + max |b|^2 is about 200 d: the fp16 bound, 9.8e-4 of it (19 at
+    d = 96), takes in a whole group of 20, the bf16 bound, some 1.2e-4 of it, three or four."""
+    g = np.random.default_rng(seed)
+    centres = 10 * g.standard_normal((30, d))
+    centres *= 10 * np.sqrt(d) / np.linalg.norm(centres, axis=1, keepdims=True)
+    step = g.standard_normal((30, size, d))
+    step *= np.sqrt(0.95 * np.arange(size))[None, :, None] / np.linalg.norm(step, axis=2, keepdims=True)
+    alone = 10 * g.standard_normal((100, d))
+    alone *= 10 * np.sqrt(d) / np.linalg.norm(alone, axis=1, keepdims=True)
+    cent = np.concatenate([(centres[:, None] + step).reshape(-1, d), alone])
+    x = alone[g.integers(0, 100, n)]
+    at = g.random(n) < share
+    x[at] = centres[g.integers(0, 30, at.sum())]
+    x += 0.01 * g.standard_normal((n, d))
+    return dev(x.astype(np.float32)), dev(cent.astype(np.float32)), int(at.sum())
+
+
+@pytest.mark.parametrize("d,metric", [(96, L2), (96, IP), (60, L2)])
+def test_vectors_that_the_heads_leave_are_swept_with_more_products(vs, d, metric):
+    """40 % of the vectors have more rows within the fp16 bound than the candidate list holds: they are
+    not redone by the canon chain over all rows, in no call."""
+    n = 12_001
+    say("tight groups n=%d d=%d metric=%d" % (n, d, metric))
+    x, cent, tight = tight_groups(n, d, 20, 0.4, 24)
+    assert tight * 512 > n
+
+    def call():
+        ix = vs.IVFFlat(d, metric, cent)
+        ix.add(x)
+        out = ix.list_sizes(), ix.storage()[0]
+        ix.close()
+        return out
+    canon, got = both_routes(vs, call, n)
+    for a, b in zip(canon, got):
+        np.testing.assert_array_equal(a, b)
+    ix = vs.IVFFlat(d, metric, cent)
+    vs.vs_set_option("knn_path", 2)
+    try:
+        for _ in range(2):
+            rows_counted, redone = add_and_count(vs, ix, x)
+            assert rows_counted == n
+            if metric == L2 and d == 96:
+                assert redone * 512 <= n, redone
+    finally:
+        vs.vs_set_option("knn_path", 0)
+    ix.close()
+
+
+def test_a_search_with_one_probe_teaches_the_sweep_nothing(vs):
+    """A search at nprobe = 1 gives up the fp16 heads for its own kind after one row in 512 redone; the
+    one-sweep route, which has a rule of its own, still begins with them (3 vectors left, see above)."""
+    n, nb, d = 25_000, 300, 96
+    say("one-probe search, then an add: n=%d nb=%d d=%d" % (n, nb, d))
+    x, cent = well_separated(n, nb, d, 20)
+    q, tight, _ = tight_groups(2_000, d, 64, 1.0, 25)
+    import torch
+    cent = torch.cat([cent, tight + 0.0])
+    ix = vs.IVFFlat(d, L2, cent)
+    assert add_and_count(vs, ix, x)[1] == 3
+    vs.vs_set_option("knn_path", 2)
+    try:
+        vs.vs_counters_read()
+        ix.search(q, 1, 1)
+        assert vs.vs_counters_read()[1] * 512 > 2_000          # the rule's condition
+    finally:
+        vs.vs_set_option("knn_path", 0)
+    assert add_and_count(vs, ix, x)[1] == 3
+    ix.close()
+
+
 @pytest.mark.parametrize("n,d,K", [(20_001, 128, 300), (130_001, 17, 300), (1_500, 32, 16_385)])
 def test_kmeans_sweep_equals_canon_tiles(vs, n, d, K):
     """Three rounds: objective, assignment and centroids, with the bookkeeping on the device and
