@@ -115,15 +115,33 @@ __global__ __launch_bounds__(64) void place_scatter_kernel(const int32_t* __rest
 // With first_new(l) = the rank of list l's first new vector in the sorted batch (what an empty list
 // would have), known from the places where the list changes, the grown lists begin at
 //   new_off[l] = old_off[l] + first_new(l):   old sizes and new counts of the lists before l.
-// Thread p looks at ranks p - 1 and p and fills the lists in between (p = n: the rest).
-__global__ __launch_bounds__(256) void place_first_kernel(const int32_t* __restrict__ order,
-                                                          const int32_t* __restrict__ keys, int64_t n, int nlist,
-                                                          const int64_t* __restrict__ old_off,
-                                                          int64_t* __restrict__ new_off, const int* __restrict__ bad) {
-  const int64_t p = blockIdx.x * 256ll + threadIdx.x;
-  if (p > n || *bad) return;
-  const int before = p > 0 ? keys[order[p - 1]] : -1, here = p < n ? keys[order[p]] : nlist;
-  for (int l = before + 1; l <= here; ++l) new_off[l] = old_off[l] + p;
+// Thread p looks at ranks p - 1 and p and fills the lists in between (p = n: the rest).  Where many
+// lists get nothing (a few vectors added to many lists, or all of them to a few) the gaps are long:
+// those of more than kGap lists are filled by the whole workgroup, one after the other.  Adding one
+// vector to 65536 lists: 6802 us with a thread per gap, 18 us like this (100 vectors: 565 and 53).
+constexpr int kGap = 32;
+__global__ __launch_bounds__(1024) void place_first_kernel(const int32_t* __restrict__ order,
+                                                           const int32_t* __restrict__ keys, int64_t n, int nlist,
+                                                           const int64_t* __restrict__ old_off,
+                                                           int64_t* __restrict__ new_off, const int* __restrict__ bad) {
+  __shared__ int long_gaps, gap_first[1024], gap_last[1024], gap_p[1024];
+  if (*bad) return;
+  if (threadIdx.x == 0) long_gaps = 0;
+  __syncthreads();
+  const int64_t p = blockIdx.x * 1024ll + threadIdx.x;
+  if (p <= n) {
+    const int first = (p > 0 ? keys[order[p - 1]] : -1) + 1, last = p < n ? keys[order[p]] : nlist;
+    if (last - first >= kGap) {
+      const int at = atomicAdd(&long_gaps, 1);
+      gap_first[at] = first; gap_last[at] = last; gap_p[at] = (int)p;
+    } else {
+      for (int l = first; l <= last; ++l) new_off[l] = old_off[l] + p;
+    }
+  }
+  __syncthreads();
+  for (int g = 0; g < long_gaps; ++g)
+#pragma unroll 4
+    for (int l = gap_first[g] + threadIdx.x; l <= gap_last[g]; l += 1024) new_off[l] = old_off[l] + gap_p[g];
 }
 
 // the vector at rank p of the sorted batch goes behind its list's old entries and the p -
@@ -183,7 +201,7 @@ int* launch_ivf_place(const int32_t* list_of, int64_t n, int nlist, const int64_
     perm = out;
     out = out == w.order_a ? w.order_b : w.order_a;
   }
-  hipLaunchKernelGGL(place_first_kernel, dim3((unsigned)((n + 256) / 256)), dim3(256), 0, st, perm, list_of, n, nlist,
+  hipLaunchKernelGGL(place_first_kernel, dim3((unsigned)((n + 1024) / 1024)), dim3(1024), 0, st, perm, list_of, n, nlist,
                      old_off, new_off, w.bad);
   hipLaunchKernelGGL(place_dest_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st, perm, list_of, n, nlist,
                      old_off, w.bad, dest);

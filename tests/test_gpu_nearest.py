@@ -175,6 +175,28 @@ def test_vectors_beyond_the_fp16_range_next_to_ordinary_centroids(vs, which, d, 
         np.testing.assert_array_equal(a, b)
 
 
+# runs of lists that get nothing: as long as one lane fills, one shorter, one longer, and the whole table
+# before, between and behind the vectors of one or two lists; more ranks than one workgroup has
+@pytest.mark.parametrize("nlist,hit", [(1, [0]), (70_001, [0]), (70_001, [70_000]), (70_001, [40_000]),
+                                       (70_001, [3, 35, 66, 99, 131, 70_000]), (1_100, [0, 1_099] * 600),
+                                       (5_000, list(range(31, 5_000, 33)) * 9)])
+def test_offsets_of_adds_that_leave_most_lists_as_they_are(vs, nlist, hit):
+    say("placement, %d vectors into %d lists" % (len(hit), nlist))
+    cent = np.zeros((nlist, 2), dtype=np.float32)
+    cent[:, 0] = np.arange(nlist)
+    ix = vs.IVFFlat(2, L2, dev(cent))
+    lists, ids = [[] for _ in range(nlist)], 0
+    for batch in (hit, hit[:1], hit[::-1]):
+        ix.add(dev(cent[batch]))
+        for l in batch:
+            lists[l].append(ids)
+            ids += 1
+    np.testing.assert_array_equal(host(ix.list_sizes()), [len(l) for l in lists])
+    got = ix.storage()
+    np.testing.assert_array_equal(host(got[0]), [i for l in lists for i in l])
+    ix.close()
+
+
 def well_separated(n, nb, d, seed, far=3):
     """Vectors near centroids that are far apart, so that the first sweep is certain of every one, but for
     the first `far`: their first component, which only centroid 5 has, is beyond what the fp16 heads
