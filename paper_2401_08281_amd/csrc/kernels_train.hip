@@ -11,16 +11,41 @@ namespace {
 
 constexpr int64_t kBlock = 4096;   // vectors per summation block (a multiple of every batch below)
 
+// Block bk of centroid j has the number off[j] / kBlock + j + bk: the numbers of different centroids
+// never overlap, there are n / kBlock + K of them whatever the clusters' sizes, and they leave out at
+// most one per centroid.  So workgroups can be launched for all blocks of the largest cluster at once
+// without knowing on the host which one that is.
+// Four rounds of 262144 x 8 into 256 centroids of which one holds 90 %, with four times the blocks of
+// equal clusters side by side instead: 7.9 ms, and 1.3 like this; x 128 into 1024: 9.2 and 2.2.
+__device__ __forceinline__ int64_t first_block(const int64_t* __restrict__ off, int j) { return off[j] / kBlock + j; }
+
+// The centroid whose blocks number s belongs to: the last j with first_block(j) <= s.  Every group of W
+// lanes looks for an s of its own, W centroids at a time.
+template <int W>
+__device__ __forceinline__ int block_owner(const int64_t* __restrict__ off, int K, int64_t s) {
+  const int lane = lane_id(), t = lane % W, g0 = lane - t;
+  const u64 mask = W == 64 ? ~0ull : ((1ull << (W & 63)) - 1ull) << g0;
+  int lo = 0, len = K;
+  while (__builtin_amdgcn_ballot_w64(len > 1) != 0) {
+    const int step = (len + W - 1) / W;
+    const int j = t * step;
+    const bool before = j < len && first_block(off, lo + j) <= s;     // (t = 0: always)
+    const int last = __popcll(__builtin_amdgcn_ballot_w64(before) & mask) - 1;
+    lo += last * step;
+    len = min(step, len - last * step);
+  }
+  return lo;
+}
+
 // One wavefront per (centroid j, block of kBlock vectors).  order[off[j] .. off[j + 1])
 // lists the vectors assigned to centroid j in ascending order; they are summed in float64 in
 // blocks of kBlock: a block from 0 in the list's order, the block sums in block order -- a
 // fixed order, so the sum has one value however the kernels are scheduled, and the blocks of
 // a large cluster run side by side (sixteen centroids over millions of sub-vectors would
 // otherwise be sixteen chains).  A centroid of one block stores sum / count rounded to fp32
-// directly; the others store their block sums to `partial` (block bk of centroid j at slot
-// off[j] / kBlock + j + bk: the slots of different centroids never overlap) and
+// directly; the others store their block sums to `partial`, by number, and
 // segmented_mean_finish_kernel adds them up.  A centroid without vectors is left as it is.
-// A wavefront takes 64 of the dimensions (grid z), one per lane.
+// A wavefront takes 64 of the dimensions (grid y), one per lane.
 // The chain of a large cluster is long (it sets the kernel's time), so the memory latency is taken
 // off it: 32 vectors at a time, their numbers come in with one load and their rows are all
 // requested a batch ahead of the additions, which run in the list's order.  262144 x 128 into 1024
@@ -33,16 +58,16 @@ __global__ __launch_bounds__(256) void segmented_mean_kernel(const float* __rest
                                                              double* __restrict__ partial) {
   constexpr int NB = 32;
   const int wave = threadIdx.x >> 6, lane = lane_id();
-  const int64_t j = blockIdx.x * 4ll + wave;
-  if (j >= K) return;
+  const int64_t s = blockIdx.x * 4ll + wave;
+  const int j = block_owner<64>(off, K, s);
   const int64_t b0 = off[j], e0 = off[j + 1];
-  if (b0 == e0) return;
   const double count = (double)(e0 - b0);
-  const int64_t nblk = (e0 - b0 + kBlock - 1) / kBlock;
-  const int t = blockIdx.z * 64 + lane;
-  const int tc = min(t, d - 1);                                  // (lanes past d load what they drop)
-  for (int64_t bk = blockIdx.y; bk < nblk; bk += gridDim.y) {
-    const int64_t b = b0 + bk * kBlock, e = min(e0, b + kBlock);
+  const int64_t nblk = (e0 - b0 + kBlock - 1) / kBlock, bk = s - first_block(off, j);
+  if (bk >= nblk) return;
+  const int64_t b = b0 + bk * kBlock, e = min(e0, b + kBlock);
+  for (int64_t t0 = blockIdx.y * 64ll; t0 < d; t0 += gridDim.y * 64ll) {
+    const int t = (int)t0 + lane;
+    const int tc = min(t, d - 1);                                // (lanes past d load what they drop)
     double acc = 0.0;
     float v0[NB], v1[NB];
     auto fetch = [&](int64_t i, float (&v)[NB]) {
@@ -69,7 +94,7 @@ __global__ __launch_bounds__(256) void segmented_mean_kernel(const float* __rest
     }
     if (t < d) {
       if (nblk == 1) centroids[j * d + t] = (float)(acc / count);
-      else partial[(b0 / kBlock + j + bk) * d + t] = acc;
+      else partial[s * d + t] = acc;
     }
   }
 }
@@ -92,52 +117,52 @@ __global__ __launch_bounds__(256) void segmented_mean_small_kernel(const float* 
                                                                    double* __restrict__ partial) {
   constexpr int CPW = 64 / DP, NB = 32, NO = NB / DP;            // centroids per wavefront, vectors per batch
   const int lane = lane_id(), c = lane / DP, t = lane % DP;
-  const int64_t j = (blockIdx.x * 4ll + (threadIdx.x >> 6)) * CPW + c;
+  const int64_t s = (blockIdx.x * 4ll + (threadIdx.x >> 6)) * CPW + c;
   off += (int64_t)blockIdx.z * (K + 1);
   const int64_t n = off[K];
   x += (int64_t)blockIdx.z * n * d;
   order += (int64_t)blockIdx.z * n;
   centroids += (int64_t)blockIdx.z * K * d;
   partial += (int64_t)blockIdx.z * (n / kBlock + K + 1) * d;
-  const int64_t b0 = j < K ? off[j] : 0, e0 = j < K ? off[j + 1] : 0;
+  const int j = block_owner<DP>(off, K, s);
+  const int64_t b0 = off[j], e0 = off[j + 1];
   const double count = (double)(e0 - b0);
-  const int64_t nblk = (e0 - b0 + kBlock - 1) / kBlock;
+  const int64_t nblk = (e0 - b0 + kBlock - 1) / kBlock, bk = s - first_block(off, j);
   const int tc = min(t, d - 1);                                  // (lanes past d load what they drop)
-  for (int64_t bk = blockIdx.y; __builtin_amdgcn_ballot_w64(bk < nblk) != 0; bk += gridDim.y) {
-    const bool mine_too = bk < nblk;
-    const int64_t b = mine_too ? b0 + bk * kBlock : 0, e = mine_too ? min(e0, b + kBlock) : 0;
-    double acc = 0.0;
-    int32_t n0[NO], n1[NO];
-    float v0[NB], v1[NB];
-    auto numbers = [&](int64_t i, int32_t (&num)[NO]) {          // (a group without vectors reads slot 0 and drops it)
+  const bool mine_too = bk < nblk;
+  const int64_t b = mine_too ? b0 + bk * kBlock : 0, e = mine_too ? min(e0, b + kBlock) : 0;
+  if (__builtin_amdgcn_ballot_w64(mine_too) == 0) return;
+  double acc = 0.0;
+  int32_t n0[NO], n1[NO];
+  float v0[NB], v1[NB];
+  auto numbers = [&](int64_t i, int32_t (&num)[NO]) {          // (a group without vectors reads slot 0 and drops it)
 #pragma unroll
-      for (int o = 0; o < NO; ++o) num[o] = order[max(min(i + o * DP + t, e - 1), (int64_t)0)];
-    };
-    auto request = [&](const int32_t (&num)[NO], float (&v)[NB]) {
+    for (int o = 0; o < NO; ++o) num[o] = order[max(min(i + o * DP + t, e - 1), (int64_t)0)];
+  };
+  auto request = [&](const int32_t (&num)[NO], float (&v)[NB]) {
 #pragma unroll
-      for (int u = 0; u < NB; ++u)
-        v[u] = x[(int64_t)__shfl(num[u / DP], c * DP + u % DP) * d + tc];
-    };
-    auto add = [&](int64_t i, const float (&v)[NB]) {
+    for (int u = 0; u < NB; ++u)
+      v[u] = x[(int64_t)__shfl(num[u / DP], c * DP + u % DP) * d + tc];
+  };
+  auto add = [&](int64_t i, const float (&v)[NB]) {
 #pragma unroll
-      for (int u = 0; u < NB; ++u) acc += i + u < e ? (double)v[u] : 0.0;
-    };
-    numbers(b, n0);
-    numbers(b + NB, n1);
+    for (int u = 0; u < NB; ++u) acc += i + u < e ? (double)v[u] : 0.0;
+  };
+  numbers(b, n0);
+  numbers(b + NB, n1);
+  request(n0, v0);
+  for (int64_t i = b; __builtin_amdgcn_ballot_w64(i < e) != 0; i += 2 * NB) {
+    numbers(i + 2 * NB, n0);
+    request(n1, v1);
+    add(i, v0);
+    if (__builtin_amdgcn_ballot_w64(i + NB < e) == 0) break;
+    numbers(i + 3 * NB, n1);
     request(n0, v0);
-    for (int64_t i = b; __builtin_amdgcn_ballot_w64(i < e) != 0; i += 2 * NB) {
-      numbers(i + 2 * NB, n0);
-      request(n1, v1);
-      add(i, v0);
-      if (__builtin_amdgcn_ballot_w64(i + NB < e) == 0) break;
-      numbers(i + 3 * NB, n1);
-      request(n0, v0);
-      add(i + NB, v1);
-    }
-    if (mine_too && t < d) {
-      if (nblk == 1) centroids[j * d + t] = (float)(acc / count);
-      else partial[(b0 / kBlock + j + bk) * d + t] = acc;
-    }
+    add(i + NB, v1);
+  }
+  if (mine_too && t < d) {
+    if (nblk == 1) centroids[j * d + t] = (float)(acc / count);
+    else partial[s * d + t] = acc;
   }
 }
 
@@ -319,20 +344,19 @@ size_t segmented_mean_partial_bytes(int64_t n, int d, int K, int problems) {
 void launch_segmented_mean(const float* x, int64_t n, int d, const int32_t* order, const int64_t* off, int K,
                            int problems, float* centroids, double* partial, hipStream_t st) {
   if (K <= 0 || n <= 0) return;
-  // Blocks side by side: four times what clusters of equal size would have, so that an uneven
-  // split still spreads (a workgroup without a block leaves at once; the rest is a loop).
-  const int64_t most = (n + kBlock - 1) / kBlock, even = (n / K + kBlock - 1) / kBlock;
-  const unsigned gy = (unsigned)std::min<int64_t>(std::min<int64_t>(most, 65535), 4 * std::max<int64_t>(1, even));
-  const unsigned gx = (unsigned)((K + 3) / 4);
+  const int64_t most = (n + kBlock - 1) / kBlock;
+  const int64_t blocks = n / kBlock + K;                         // block numbers, see first_block
+  const unsigned P = (unsigned)problems, gk = (unsigned)((K + 3) / 4);
   const int per_wave = d <= 8 ? 8 : (d <= 16 ? 4 : (d <= 32 ? 2 : 1));
-  const dim3 block(256), grid((unsigned)((K + 4 * per_wave - 1) / (4 * per_wave)), gy, (unsigned)problems);
-  if (d <= 8) hipLaunchKernelGGL((segmented_mean_small_kernel<8>), grid, block, 0, st, x, d, order, off, K, centroids, partial);
-  else if (d <= 16) hipLaunchKernelGGL((segmented_mean_small_kernel<16>), grid, block, 0, st, x, d, order, off, K, centroids, partial);
-  else if (d <= 32) hipLaunchKernelGGL((segmented_mean_small_kernel<32>), grid, block, 0, st, x, d, order, off, K, centroids, partial);
+  const unsigned gx = (unsigned)((blocks + 4 * per_wave - 1) / (4 * per_wave));
+  const dim3 block(256);
+  if (d <= 8) hipLaunchKernelGGL((segmented_mean_small_kernel<8>), dim3(gx, 1, P), block, 0, st, x, d, order, off, K, centroids, partial);
+  else if (d <= 16) hipLaunchKernelGGL((segmented_mean_small_kernel<16>), dim3(gx, 1, P), block, 0, st, x, d, order, off, K, centroids, partial);
+  else if (d <= 32) hipLaunchKernelGGL((segmented_mean_small_kernel<32>), dim3(gx, 1, P), block, 0, st, x, d, order, off, K, centroids, partial);
   else   // (problems == 1)
-    hipLaunchKernelGGL(segmented_mean_kernel, dim3(gx, gy, (unsigned)((d + 63) / 64)), block, 0, st, x, d, order, off, K, centroids, partial);
+    hipLaunchKernelGGL(segmented_mean_kernel, dim3(gx, (unsigned)std::min((d + 63) / 64, 65535)), block, 0, st, x, d, order, off, K, centroids, partial);
   if (most > 1)
-    hipLaunchKernelGGL(segmented_mean_finish_kernel, dim3(gx, 1, (unsigned)problems), block, 0, st, partial, d, off, K,
+    hipLaunchKernelGGL(segmented_mean_finish_kernel, dim3(gk, 1, P), block, 0, st, partial, d, off, K,
                        centroids);
 }
 

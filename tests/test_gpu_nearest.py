@@ -326,6 +326,33 @@ def test_kmeans_sweep_equals_canon_tiles(vs, n, d, K):
         np.testing.assert_array_equal(a, b)
 
 
+# d: both ends of the lanes of 8, 16 and 32 and of one and two wavefronts of dimensions
+@pytest.mark.parametrize("d", [1, 8, 9, 16, 17, 32, 33, 64, 65])
+@pytest.mark.parametrize("sizes", ["edges", "one_holds_most", "only_the_last", "many_centroids"])
+def test_means_of_clusters_of_all_sizes(vs, d, sizes):
+    """The mean of a cluster is its float64 sum in blocks of 4096 vectors, in their order, over its size;
+    a centroid without vectors keeps its place."""
+    say("means of clusters, %s d=%d" % (sizes, d))
+    size = {"edges": [0, 1, 31, 32, 33, 0, 4_095, 4_096, 4_097, 8_191, 8_192, 8_193, 12_289, 64, 0],
+            "one_holds_most": [3, 0, 70_001, 0, 0, 5] + [1] * 70, "only_the_last": [0] * 9 + [20_481],
+            "many_centroids": [0, 2, 0, 3] * 1_100 + [4_100] + [1] * 20}[sizes]
+    K, g = len(size), np.random.default_rng(31)
+    cent = np.zeros((K, d), dtype=np.float32)
+    cent[:, 0] = 1000.0 * np.arange(K)
+    own = g.permutation(np.repeat(np.arange(K), size))
+    x = (cent[own] + g.standard_normal((len(own), d))).astype(np.float32)
+    want = cent.copy()
+    for j in range(K):
+        mine = x[own == j].astype(np.float64)
+        if len(mine):
+            sums = [np.cumsum(mine[b:b + 4096], axis=0)[-1] for b in range(0, len(mine), 4096)]
+            want[j] = np.cumsum(sums, axis=0)[-1] / len(mine)
+    got = dev(cent)
+    _, assign = vs.vs_kmeans(dev(x), got, 1, return_assign=True)
+    np.testing.assert_array_equal(host(assign), own)
+    np.testing.assert_array_equal(host(got), want)
+
+
 # dsub: one and two groups of eight dimensions, both with remainders; 17 takes the vector kernel.
 # n: below one group of 32 vectors, one past a workgroup's 128.
 @pytest.mark.parametrize("nbits", [4, 8])
