@@ -802,20 +802,34 @@ int kmeans_rounds(const float* x, int64_t n, int d, int K, int niter, float* cen
 // All sub-quantizers of a product quantizer at once (res [M][n][dsub], codebooks [M][K][dsub]): one
 // launch of every step of a round serves them all, where one problem after the other left most of
 // the chip idle (a round of one is some ten launches of a few microseconds' work).  Sub-quantizers are
-// taken in groups that keep the work space near 1 GiB.
+// taken in groups that keep the work space near 1 GiB, or what of it is free; *done = false where not even
+// one finds room (nothing has been changed then).
 int kmeans_subquantizers(const float* res, int64_t n, int dsub, int M, int K, int niter, float* codebooks,
-                         double* objective, hipStream_t st) {
+                         double* objective, bool* done, hipStream_t st) {
+  *done = false;
   const size_t each = (size_t)n * (1 + 2 * sizeof(float)) + kmeans_sort_bytes(K, 1) +
                       segmented_mean_partial_bytes(n, dsub, K, 1);
-  const int G = (int)std::max<size_t>(1, std::min<size_t>((size_t)M, (1ull << 30) / each));
-  Carver cw;
-  const size_t o_idx = cw.take((size_t)G * n), o_val = cw.take((size_t)G * n * sizeof(float)),
-               o_order = cw.take((size_t)G * n * sizeof(int32_t)), o_off = cw.take((size_t)G * (K + 1) * sizeof(int64_t)),
-               o_sort = cw.take(kmeans_sort_bytes(K, G)), o_bad = cw.take(sizeof(int64_t)),
-               o_obj = cw.take((size_t)niter * G * 256 * sizeof(double)),
-               o_part = cw.take(segmented_mean_partial_bytes(n, dsub, K, G));
+  int G = (int)std::max<size_t>(1, std::min<size_t>((size_t)M, (1ull << 30) / each));
+  size_t o_idx, o_val, o_order, o_off, o_sort, o_bad, o_obj, o_part;
   DeviceBuf work;
-  if (int rc = work.alloc(cw.off)) return rc;
+  for (;; G = (G + 1) / 2) {
+    Carver cw;
+    o_idx = cw.take((size_t)G * n);
+    o_val = cw.take((size_t)G * n * sizeof(float));
+    o_order = cw.take((size_t)G * n * sizeof(int32_t));
+    o_off = cw.take((size_t)G * (K + 1) * sizeof(int64_t));
+    o_sort = cw.take(kmeans_sort_bytes(K, G));
+    o_bad = cw.take(sizeof(int64_t));
+    o_obj = cw.take((size_t)niter * G * 256 * sizeof(double));
+    o_part = cw.take(segmented_mean_partial_bytes(n, dsub, K, G));
+    const int rc = work.alloc(cw.off);
+    if (rc == VS_OK) break;
+    if (rc != VS_ERR_OOM) return rc;
+    (void)hipGetLastError();
+    work.p = nullptr;
+    if (G == 1) return VS_OK;
+  }
+  *done = true;
   char* wb = static_cast<char*>(work.p);
   uint8_t* idx = reinterpret_cast<uint8_t*>(wb + o_idx);
   float* val = reinterpret_cast<float*>(wb + o_val);
@@ -914,10 +928,12 @@ int vs_ivfpq_train(const float* x, int64_t n, int32_t d, int32_t metric, int32_t
   if (int rc = nearest_rows(x, n, centroids, nlist, d, metric, idx, nullptr, sc, st)) return rc;
   launch_residual_slices(x, n, d, dsub, centroids, idx, res, st);
   // 4. one k-means per sub-quantizer on its slice of the residuals
-  if (pq_nearest_supported(dsub, K) && g_knn_path.load() != 1 && niter > 0) {
-    if (int rc = kmeans_subquantizers(res, n, dsub, M, K, niter, codebooks, objective ? objective + niter : nullptr, st))
+  bool together = false;
+  if (pq_nearest_supported(dsub, K) && g_knn_path.load() != 1 && niter > 0)
+    if (int rc = kmeans_subquantizers(res, n, dsub, M, K, niter, codebooks, objective ? objective + niter : nullptr,
+                                      &together, st))
       return rc;
-  } else for (int m = 0; m < M; ++m) {
+  for (int m = 0; m < M && !together; ++m) {
     if (int rc = kmeans_rounds(res + (size_t)m * n * dsub, n, dsub, K, niter,
                                codebooks + (size_t)m * K * dsub,
                                objective ? objective + (size_t)(1 + m) * niter : nullptr, idx, val,

@@ -431,6 +431,37 @@ def test_static_search_accepts_what_fits_by_the_matrix_core_route(vs):
     np.testing.assert_array_equal(host(D), host(d2))
 
 
+@pytest.mark.parametrize("left", [300, 60, 14])
+def test_training_with_little_memory_free(vs, left):
+    """The work space of 32 sub-quantizers of 2M vectors is 576 MB together, 18 MB of one.  `left` MB more
+    than the coarse part needs leave room for half of them, for two, for none."""
+    import torch
+    n, d, M, nbits = 2_000_001, 32, 32, 4
+    say("train n=%d M=%d with %d MB to spare" % (n, M, left))
+    g = torch.Generator(device="cuda").manual_seed(9)
+    x = torch.randn((n, d), generator=g, device="cuda")
+    cent, cb = x[:16].clone(), torch.randn((M, 1 << nbits, 1), generator=g, device="cuda")
+
+    def call():
+        c, b = cent.clone(), cb.clone()
+        obj = vs.vs_ivfpq_train(x, L2, c, b, nbits, 2)
+        return [host(c).copy(), host(b).copy(), np.array(obj)]
+    want = call()
+    vs.vs_trim()
+    torch.cuda.empty_cache()
+    # the coarse part, per vector: three numbers, the residual, and 97 bytes of its assignment's scratch
+    need = n * (3 * 4 + 4 * d + 97) + (left << 20)
+    hold = torch.empty(max(0, torch.cuda.mem_get_info()[0] - need), dtype=torch.uint8, device="cuda")
+    try:
+        got = call()
+    finally:
+        del hold
+        torch.cuda.empty_cache()
+        vs.vs_trim()
+    for a, b in zip(want, got):
+        np.testing.assert_array_equal(a, b)
+
+
 def test_ragged_rows_that_leave_no_room_for_planes_use_canon_tiles(vs):
     """Operand planes of 1M x 100 take 768 MB; with less than that free the search and the index still work."""
     import torch
