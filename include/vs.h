@@ -146,8 +146,8 @@ VS_API int vs_refine(const float* x, int64_t nb, const float* q, int64_t nq, int
  *              training vectors to their centroid at step (1) of every round.
  *   assign     DEVICE [n] int32, or NULL: the centroid of every training vector at step (1)
  *              of the LAST round (the clusters whose means the returned centroids are).
- * Synchronises the stream before it returns (the objective's partial sums are read back once;
- * beyond 16384 centroids every round's assignment is, to be ordered on the host).
+ * Synchronises the stream before it returns and every 256 rounds (the objective's partial sums are read
+ * back; beyond 16384 centroids every round's assignment is, to be ordered on the host).
  * Errors: null pointers, d < 1, K < 1, niter < 0, n outside [0, 2^31).
  */
 VS_API int vs_kmeans(const float* x, int64_t n, int32_t d, int32_t K, int32_t niter,

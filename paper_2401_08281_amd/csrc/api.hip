@@ -713,18 +713,20 @@ struct DeviceBuf {   // a plain allocation released on scope exit
   int alloc(size_t bytes) { HIP_TRY(hipMalloc(&p, std::max<size_t>(bytes, 256))); return VS_OK; }
 };
 
-// The objectives of `problems` k-means runs from their rounds' partial sums [niter][problems][256]:
-// objective[p * niter + r] (or null).  Waits for the stream.
-int kmeans_collect(const double* partial, const int* bad, int64_t n, int K, int niter, int problems,
+// The objectives of `problems` k-means runs from the partial sums [rounds][problems][256] of some rounds:
+// objective[p * niter + r], r < rounds (or null).  Waits for the stream.  Sums are kept for at most
+// kSumRounds rounds: 2 KiB a round and problem.
+constexpr int kSumRounds = 256;
+int kmeans_collect(const double* partial, const int* bad, int64_t n, int K, int rounds, int niter, int problems,
                    double* objective, hipStream_t st) {
   int h_bad = 0;
   HIP_TRY(hipMemcpyAsync(&h_bad, bad, sizeof(int), hipMemcpyDeviceToHost, st));
-  std::vector<double> h((size_t)(objective ? niter : 0) * problems * 256);
+  std::vector<double> h((size_t)(objective ? rounds : 0) * problems * 256);
   if (objective) HIP_TRY(hipMemcpyAsync(h.data(), partial, h.size() * sizeof(double), hipMemcpyDeviceToHost, st));
   HIP_TRY(hipStreamSynchronize(st));
   if (h_bad != 0) return fail(VS_ERR_DEVICE, "k-means: assignment produced a centroid outside [0, %d)", K);
   if (objective)
-    for (int r = 0; r < niter; ++r)
+    for (int r = 0; r < rounds; ++r)
       for (int p = 0; p < problems; ++p) {
         double sum = 0.0;
         for (int t = 0; t < 256; ++t) sum += h[((size_t)r * problems + p) * 256 + t];
@@ -740,12 +742,12 @@ int kmeans_rounds(const float* x, int64_t n, int d, int K, int niter, float* cen
                   Scratch& sc, hipStream_t st) {
   // Up to 16384 centroids the bookkeeping of a round (the objective, and every centroid's
   // vectors in ascending order) stays on the device and nothing is read back between rounds: the
-  // objective's partial sums of all rounds are fetched at the end.  Beyond, the host does it.
+  // objective's partial sums are fetched at the end, and every kSumRounds.  Beyond, the host does it.
   const bool on_device = K <= 16384 && n > 0;
   DeviceBuf work;
   Carver cw;
   const size_t o_sort = cw.take(kmeans_sort_bytes(K, 1)), o_bad = cw.take(sizeof(int64_t)),
-               o_obj = cw.take((size_t)niter * 256 * sizeof(double)),
+               o_obj = cw.take((size_t)std::min(niter, kSumRounds) * 256 * sizeof(double)),
                o_part = cw.take(segmented_mean_partial_bytes(n, d, K, 1));
   char* wb = nullptr;
   if (on_device) {
@@ -762,8 +764,14 @@ int kmeans_rounds(const float* x, int64_t n, int d, int K, int niter, float* cen
     if (int rc = nearest_rows(x, n, centroids, K, d, VS_METRIC_L2, idx, val, sc, st, on_device && r > 0)) return rc;
     if (on_device) {
       launch_kmeans_sort(idx, val, n, K, wb + o_sort, order, off, reinterpret_cast<int*>(wb + o_bad),
-                         reinterpret_cast<double*>(wb + o_obj) + (size_t)r * 256, st);
+                         reinterpret_cast<double*>(wb + o_obj) + (size_t)(r % kSumRounds) * 256, st);
       launch_segmented_mean(x, n, d, order, off, K, 1, centroids, reinterpret_cast<double*>(wb + o_part), st);
+      if (r + 1 == niter || (r + 1) % kSumRounds == 0) {
+        const int r0 = r / kSumRounds * kSumRounds;
+        if (int rc = kmeans_collect(reinterpret_cast<const double*>(wb + o_obj), reinterpret_cast<const int*>(wb + o_bad),
+                                    n, K, r + 1 - r0, niter, 1, objective ? objective + r0 : nullptr, st))
+          return rc;
+      }
       continue;
     }
     HIP_TRY(hipMemcpyAsync(h_idx.data(), idx, (size_t)n * sizeof(int32_t), hipMemcpyDeviceToHost, st));
@@ -790,10 +798,6 @@ int kmeans_rounds(const float* x, int64_t n, int d, int K, int niter, float* cen
     launch_segmented_mean(x, n, d, order, off, K, 1, centroids, static_cast<double*>(sc.p), st);
     HIP_TRY(hipStreamSynchronize(st));   // the host arrays are reused by the next round
   }
-  if (on_device)
-    if (int rc = kmeans_collect(reinterpret_cast<const double*>(wb + o_obj), reinterpret_cast<const int*>(wb + o_bad),
-                                n, K, niter, 1, objective, st))
-      return rc;
   HIP_TRY(hipStreamSynchronize(st));     // the centroids are final when the call returns
   HIP_TRY(hipGetLastError());
   return VS_OK;
@@ -820,7 +824,7 @@ int kmeans_subquantizers(const float* res, int64_t n, int dsub, int M, int K, in
     o_off = cw.take((size_t)G * (K + 1) * sizeof(int64_t));
     o_sort = cw.take(kmeans_sort_bytes(K, G));
     o_bad = cw.take(sizeof(int64_t));
-    o_obj = cw.take((size_t)niter * G * 256 * sizeof(double));
+    o_obj = cw.take((size_t)std::min(niter, kSumRounds) * G * 256 * sizeof(double));
     o_part = cw.take(segmented_mean_partial_bytes(n, dsub, K, G));
     const int rc = work.alloc(cw.off);
     if (rc == VS_OK) break;
@@ -844,12 +848,15 @@ int kmeans_subquantizers(const float* res, int64_t n, int dsub, int M, int K, in
     for (int r = 0; r < niter; ++r) {
       launch_pq_nearest(x, n, dsub * g, dsub, nullptr, nullptr, cb, K, g, idx, 1, n, val, st);
       launch_kmeans_sort_bytes(idx, val, n, K, g, wb + o_sort, order, off, reinterpret_cast<int*>(wb + o_bad),
-                               obj + (size_t)r * g * 256, st);
+                               obj + (size_t)(r % kSumRounds) * g * 256, st);
       launch_segmented_mean(x, n, dsub, order, off, K, g, cb, reinterpret_cast<double*>(wb + o_part), st);
+      if (r + 1 == niter || (r + 1) % kSumRounds == 0) {
+        const int r0 = r / kSumRounds * kSumRounds;
+        if (int rc = kmeans_collect(obj, reinterpret_cast<const int*>(wb + o_bad), n, K, r + 1 - r0, niter, g,
+                                    objective ? objective + (size_t)m0 * niter + r0 : nullptr, st))
+          return rc;
+      }
     }
-    if (int rc = kmeans_collect(obj, reinterpret_cast<const int*>(wb + o_bad), n, K, niter, g,
-                                objective ? objective + (size_t)m0 * niter : nullptr, st))
-      return rc;
   }
   return VS_OK;
 }

@@ -431,6 +431,43 @@ def test_static_search_accepts_what_fits_by_the_matrix_core_route(vs):
     np.testing.assert_array_equal(host(D), host(d2))
 
 
+@pytest.mark.parametrize("niter", [255, 256, 257, 600])
+def test_objective_of_many_rounds(vs, niter):
+    """The sums of the objective are kept for 256 rounds: a long run's objective is that of its parts."""
+    import torch
+    say("objective of %d rounds" % niter)
+    n, d, K, first = 700, 6, 90, 100
+    x = dev(rows("gauss", n, d, 33))
+    whole, parts = x[:K].clone(), x[:K].clone()
+    obj = vs.vs_kmeans(x, whole, niter)
+    want = list(vs.vs_kmeans(x, parts, first)) + list(vs.vs_kmeans(x, parts, niter - first))
+    np.testing.assert_array_equal(obj, want)
+    np.testing.assert_array_equal(host(whole), host(parts))
+    cent = torch.zeros((1, d), device="cuda")
+    cb = x[:16].reshape(16, 2, 3).permute(1, 0, 2).contiguous()
+    got = vs.vs_ivfpq_train(x, L2, cent, cb.clone(), 4, niter)
+    res = (x - cent).reshape(n, 2, 3)
+    for m in range(2):
+        np.testing.assert_array_equal(np.array(got)[1 + m], vs.vs_kmeans(res[:, m].contiguous(), cb[m].clone(), niter))
+
+
+def hold_memory(need):
+    """Tensors that leave `need` bytes of device memory (what the driver reports as free is not all there is)."""
+    import torch
+    chunk, held = 16 << 20, []
+    free = torch.cuda.mem_get_info()[0]
+    if free > need + (4 << 30):
+        held.append(torch.empty(free - need - (4 << 30), dtype=torch.uint8, device="cuda"))
+    try:
+        while True:
+            held.append(torch.empty(chunk, dtype=torch.uint8, device="cuda"))
+    except torch.cuda.OutOfMemoryError:
+        pass
+    del held[-(-(-need // chunk)):]
+    torch.cuda.empty_cache()
+    return held
+
+
 @pytest.mark.parametrize("left", [300, 60, 14])
 def test_training_with_little_memory_free(vs, left):
     """The work space of 32 sub-quantizers of 2M vectors is 576 MB together, 18 MB of one.  `left` MB more
@@ -451,7 +488,8 @@ def test_training_with_little_memory_free(vs, left):
     torch.cuda.empty_cache()
     # the coarse part, per vector: three numbers, the residual, and 97 bytes of its assignment's scratch
     need = n * (3 * 4 + 4 * d + 97) + (left << 20)
-    hold = torch.empty(max(0, torch.cuda.mem_get_info()[0] - need), dtype=torch.uint8, device="cuda")
+    hold = hold_memory(need)
+    say("driver reports %d MB free of %d" % (torch.cuda.mem_get_info()[0] >> 20, need >> 20))
     try:
         got = call()
     finally:
