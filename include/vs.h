@@ -426,14 +426,14 @@ VS_API int vs_profile_read(double* stage_ms, int64_t* launches);
 /* ---- run-time options and counters ----------------------------------------- */
 
 /* "knn_path": how exact k-nearest-row problems (coarse quantizer, list
- *   assignment, flat search) are evaluated.  0 (default): matrix-core shortlist
+ *   assignment, flat search, nearest codewords) are evaluated.  0 (default): matrix-core shortlist
  *   + exact re-rank where a kernel exists (16 < d <= 2048, k <= 150) and the problem is
  *   not so small that canon distance tiles are faster, canon tiles otherwise; 1: canon
  *   tiles only; 2: the matrix cores wherever a kernel exists.
  *   All routes return identical results.
  * "knn_eps_scale": multiplies the error bound used to prove a shortlist
- *   sufficient (default 1; a negative value sends every row to the exact
- *   fallback -- for tests).
+ *   sufficient or a nearest codeword certain (default 1; a negative value sends
+ *   every row to the exact fallback -- for tests).
  * "list_major": whether vs_ivfpq_search scans a batch list by list instead of query by query
  *   (Sec. 4.3 "Compressed-domain search"; L2 indexes with residual tables of PQ8x8 on d = 32,
  *   PQ16x8 on d = 128 and PQ32x8 on d = 96): every list is then read from memory once per batch

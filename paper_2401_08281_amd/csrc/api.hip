@@ -846,7 +846,7 @@ int kmeans_subquantizers(const float* res, int64_t n, int dsub, int M, int K, in
     float* cb = codebooks + (size_t)m0 * K * dsub;
     launch_fill_u64(reinterpret_cast<u64*>(wb + o_bad), 1, 0ull, st);
     for (int r = 0; r < niter; ++r) {
-      launch_pq_nearest(x, n, dsub * g, dsub, nullptr, nullptr, cb, K, g, idx, 1, n, val, st);
+      launch_pq_nearest(x, n, dsub * g, dsub, nullptr, nullptr, cb, K, g, g_knn_eps_scale.load(), idx, 1, n, val, st);
       launch_kmeans_sort_bytes(idx, val, n, K, g, wb + o_sort, order, off, reinterpret_cast<int*>(wb + o_bad),
                                obj + (size_t)(r % kSumRounds) * g * 256, st);
       launch_segmented_mean(x, n, dsub, order, off, K, g, cb, reinterpret_cast<double*>(wb + o_part), st);
@@ -1165,7 +1165,8 @@ int vs_ivfpq_add(vs_ivfpq* ix, const float* x, int64_t n, const int64_t* ids, vo
     return rc;
   uint8_t* tmp_codes = reinterpret_cast<uint8_t*>(pl.extra);
   float* tmp_norms = with_norms ? reinterpret_cast<float*>(pl.extra + code_bytes) : nullptr;
-  launch_pq_encode(g, x, n, pl.list_of, ix->centroids, ix->codebooks, tmp_codes, st);
+  launch_pq_encode(g, x, n, pl.list_of, ix->centroids, ix->codebooks, g_knn_path.load() != 1, g_knn_eps_scale.load(),
+                   tmp_codes, st);
   if (with_norms)
     launch_pq_norms(g, tmp_codes, n, pl.list_of, ix->centroids, ix->codebooks, tmp_norms, st);
 

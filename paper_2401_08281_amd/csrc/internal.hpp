@@ -42,8 +42,8 @@ struct IvfpqDims {
 };
 // tmp_codes[i][m] = PQ code of sub-vector m of the residual of x_i (one byte per m)
 void launch_pq_encode(const IvfpqDims& g, const float* x, int64_t n, const int32_t* list_of,
-                      const float* centroids, const float* codebooks, uint8_t* tmp_codes,
-                      hipStream_t st);
+                      const float* centroids, const float* codebooks, bool matrix_cores, float eps_scale,
+                      uint8_t* tmp_codes, hipStream_t st);
 // move old entries to their new offsets and scatter the new ones
 // norms / old_norms / tmp_norms: the stored norms of Sec. 4.3's decomposition, or all null
 void launch_relayout(const IvfpqDims& g, const uint8_t* old_codes, const int64_t* old_ids,
@@ -193,8 +193,8 @@ void launch_nearest(const float* x, int64_t n, int d, int metric, const MfmaOper
 // val [M][n] = its canon distance where not null.  dsub up to 16, K = 16 or 256.
 bool pq_nearest_supported(int dsub, int K);
 void launch_pq_nearest(const float* x, int64_t n, int d, int dsub, const float* centroids, const int32_t* list_of,
-                       const float* codebooks, int K, int M, uint8_t* codes, int64_t stride_i, int64_t stride_m,
-                       float* val, hipStream_t st);
+                       const float* codebooks, int K, int M, float eps_scale, uint8_t* codes, int64_t stride_i,
+                       int64_t stride_m, float* val, hipStream_t st);
 
 // ---- kernels_ivfflat.hip -------------------------------------------------------
 void launch_ivfflat_relayout(int d, int nlist, const float* old_rows, const int64_t* old_ids,

@@ -10,7 +10,7 @@ namespace {
 
 // ---------------------------------------------------------------------------
 // PQ encoding (Sec. 4.1 product quantizer; Sec. 5.1 residual encoding) of sub-vectors
-// too long for the matrix-core kernel (pq_nearest_kernel).
+// too long for the matrix-core kernel (pq_nearest_kernel), and where that is not wanted.
 // One lane per (vector, sub-quantizer m); a workgroup covers 256 vectors of
 // one m and keeps that sub-codebook in LDS, read as broadcasts.  The residual
 // is one fp32 subtraction per component; the nearest codeword is taken on the
@@ -1727,11 +1727,12 @@ static int bank_slots_for_k(int k, int ppb) {
 }
 
 void launch_pq_encode(const IvfpqDims& g, const float* x, int64_t n, const int32_t* list_of,
-                      const float* centroids, const float* codebooks, uint8_t* tmp_codes,
-                      hipStream_t st) {
+                      const float* centroids, const float* codebooks, bool matrix_cores, float eps_scale,
+                      uint8_t* tmp_codes, hipStream_t st) {
   if (n <= 0) return;
-  if (pq_nearest_supported(g.dsub, g.K)) {
-    launch_pq_nearest(x, n, g.d, g.dsub, centroids, list_of, codebooks, g.K, g.M, tmp_codes, g.M, 1, nullptr, st);
+  if (matrix_cores && pq_nearest_supported(g.dsub, g.K)) {
+    launch_pq_nearest(x, n, g.d, g.dsub, centroids, list_of, codebooks, g.K, g.M, eps_scale, tmp_codes, g.M, 1,
+                      nullptr, st);
     return;
   }
   const dim3 grid((unsigned)((n + 255) / 256), (unsigned)g.M), block(256);

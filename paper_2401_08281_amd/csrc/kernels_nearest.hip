@@ -463,7 +463,8 @@ __global__ void nearest_state_kernel(const PrepInfo* __restrict__ Binfo, Nearest
 // (NP groups of each kind for 8 NP dimensions), so the score <r, t> - |t|^2 / 2 comes out finished
 // and costs only the selection: 3 vector instructions per (sub-vector, codeword) where the canon
 // chain costs 2 per dimension.  Sub-vectors whose best two are within the error bound are decided
-// by the canon chain over all codewords, 64 codewords at a time (about one in a hundred).
+// by the canon chain over all codewords, 64 codewords at a time (about one in a hundred;
+// all of them where eps_scale, which scales the bound, is negative).
 // RES: sub-vector m of x_i minus its list's centroid; else x is [M][n][dsub].
 // Encoding 1M vectors of 16 x 8 dimensions: 1.29 -> 0.72 ms.
 // ---------------------------------------------------------------------------
@@ -473,7 +474,8 @@ template <int NP, int KB, bool RES, bool VEC>
 __global__ __launch_bounds__(256, NP == 1 ? 4 : 2) void pq_nearest_kernel(
     const float* __restrict__ x, int64_t n, int d, int dsub, const float* __restrict__ centroids,
     const int32_t* __restrict__ list_of, const float* __restrict__ codebooks, int K, int M, int64_t chunks,
-    int groups, uint8_t* __restrict__ codes, int64_t stride_i, int64_t stride_m, float* __restrict__ val) {
+    int groups, float eps_scale, uint8_t* __restrict__ codes, int64_t stride_i, int64_t stride_m,
+    float* __restrict__ val) {
   constexpr int NG = 3 * NP + 1, S = (NG + 1) / 2, DP = 8 * NP;
   extern __shared__ __attribute__((aligned(16))) float T[];       // [K][dsub]
   const int tid = threadIdx.x, wave = tid >> 6, lane = lane_id(), half = lane >> 5;
@@ -596,7 +598,7 @@ __global__ __launch_bounds__(256, NP == 1 ? 4 : 2) void pq_nearest_kernel(
     // |t| <= |r| + its distance, whose square is at most |r|^2 - 2 b2 up to that error.
     const float dist = sqrtf(fmaxf(rr - 2.f * b2, 0.f)), tmax = sqrtf(rr) + 1.01f * dist;
     // (+ 1e-30: the tags alone tell scores of zero apart, and products of tiny numbers vanish)
-    const bool unsure = !(b1 - b2 > 4e-5f * (rr + tmax * tmax) + 1e-30f);
+    const bool unsure = !(b1 - b2 > eps_scale * (4e-5f * (rr + tmax * tmax) + 1e-30f)) || eps_scale < 0.f;
     u32 todo = (u32)__builtin_amdgcn_ballot_w64(unsure);          // (both halves agree)
     while (todo != 0) {
       const int src = __builtin_ctz(todo);
@@ -740,8 +742,8 @@ void launch_nearest(const float* x, int64_t n, int d, int metric, const MfmaOper
 bool pq_nearest_supported(int dsub, int K) { return dsub >= 1 && dsub <= 16 && (K == 16 || K == 256); }
 
 void launch_pq_nearest(const float* x, int64_t n, int d, int dsub, const float* centroids, const int32_t* list_of,
-                       const float* codebooks, int K, int M, uint8_t* codes, int64_t stride_i, int64_t stride_m,
-                       float* val, hipStream_t st) {
+                       const float* codebooks, int K, int M, float eps_scale, uint8_t* codes, int64_t stride_i,
+                       int64_t stride_m, float* val, hipStream_t st) {
   if (n <= 0) return;
   // groups of 32 vectors per wavefront: as many as leave about eight workgroups per compute unit
   // (the fragments of 256 codewords cost as much as one or two groups)
@@ -753,7 +755,7 @@ void launch_pq_nearest(const float* x, int64_t n, int d, int dsub, const float* 
                    (reinterpret_cast<uintptr_t>(x) & 15) == 0;
 #define GO(NP, KB, RES, VEC) \
   hipLaunchKernelGGL((pq_nearest_kernel<NP, KB, RES, VEC>), grid, block, lds, st, x, n, d, dsub, centroids, list_of, \
-                     codebooks, K, M, chunks, groups, codes, stride_i, stride_m, val)
+                     codebooks, K, M, chunks, groups, eps_scale, codes, stride_i, stride_m, val)
 #define GO2(NP, KB) do { if (centroids) { if (vec) GO(NP, KB, true, true); else GO(NP, KB, true, false); } \
                          else { if (vec) GO(NP, KB, false, true); else GO(NP, KB, false, false); } } while (0)
   if (dsub <= 8) { if (K == 256) GO2(1, 8); else GO2(1, 1); }

@@ -373,6 +373,50 @@ def test_nearest_codewords_match_oracle(vs, oracle, n, M, dsub, nbits):
     np.testing.assert_array_equal(host(ix.codes()), orc.codes)
 
 
+@pytest.mark.parametrize("nbits", [4, 8])
+@pytest.mark.parametrize("dsub", [2, 5, 8, 12, 16])
+@pytest.mark.parametrize("kind", ["gauss", "tiny", "huge", "nonfinite_vectors"])
+def test_nearest_codewords_on_all_routes(vs, kind, dsub, nbits):
+    """Codes by the canon chain alone (knn_path = 1), by the matrix cores, and by their canon branch for every
+    sub-vector (knn_eps_scale < 0); training likewise."""
+    say("codes on all routes, %s dsub=%d nbits=%d" % (kind, dsub, nbits))
+    n, M, K = 1_061, 4, 1 << nbits
+    d = M * dsub
+    scale = np.float32({"tiny": 1e-20, "huge": 3e18}.get(kind, 1.0))
+    x, cent = rows("gauss", n, d, 40) * scale, rows("gauss", 5, d, 41) * scale
+    cb = np.ascontiguousarray(rows("gauss", K, d, 42).reshape(K, M, dsub).transpose(1, 0, 2)) * scale
+    cb[0, K // 2] = cb[0, 1]
+    if kind == "nonfinite_vectors":
+        x[5, 0], x[6, 1], x[7, d - 1], x[8] = np.nan, np.inf, -np.inf, np.nan
+    xd, cd, bd = dev(x), dev(cent), dev(cb)
+
+    def codes():
+        ix = vs.IVFPQ(d, L2, cd, bd, nbits)
+        ix.add(xd)
+        out = host(ix.codes()).copy(), host(ix.list_sizes()).copy()
+        ix.close()
+        return out
+
+    def trained():
+        c, b = cd.clone(), bd.clone()
+        vs.vs_ivfpq_train(xd, L2, c, b, nbits, 2)
+        return host(c).copy(), host(b).copy()
+    calls = [codes] + ([trained] if "nonfinite" not in kind else [])
+    for call in calls:
+        got = {}
+        for path, eps in ((0, 1.0), (1, 1.0), (0, -1.0)):
+            try:
+                vs.vs_set_option("knn_path", path)
+                vs.vs_set_option("knn_eps_scale", eps)
+                got[path, eps] = call()
+            finally:
+                vs.vs_set_option("knn_path", 0)
+                vs.vs_set_option("knn_eps_scale", 1.0)
+        for other in ((0, 1.0), (0, -1.0)):
+            for a, b in zip(got[1, 1.0], got[other]):
+                np.testing.assert_array_equal(a, b)
+
+
 @pytest.mark.parametrize("n,d,M,nbits,niter", [(5_003, 12, 4, 8, 3), (5_003, 24, 2, 4, 3), (9_001, 34, 2, 8, 2),
                                                (3_000_001, 32, 32, 4, 2)])
 def test_subquantizers_together_equal_one_at_a_time(vs, n, d, M, nbits, niter):
