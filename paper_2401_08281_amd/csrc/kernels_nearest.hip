@@ -489,6 +489,7 @@ __global__ __launch_bounds__(256, NP == 1 ? 4 : 2) void pq_nearest_kernel(
   for (int e = tid; e < K * dsub; e += 256) T[e] = Tm[e];
   __syncthreads();
 
+  bool odd = false;   // a codeword with a NaN or a norm that overflows: its scores say nothing
   // codeword fragments: lane = codeword (row of the block), half = which group of a step
   u16x8 af[KB][S];
 #pragma unroll
@@ -507,6 +508,7 @@ __global__ __launch_bounds__(256, NP == 1 ? 4 : 2) void pq_nearest_kernel(
         th[p][u] = h;
         tl[p][u] = bf16_bits(v - bf16_value(h));
       }
+    odd = odd || !(tt < __builtin_inff());
     const float hn = j < K ? -0.5f * tt : kPadScore;
     const unsigned short n1 = bf16_bits(hn);
     const float r1 = hn - bf16_value(n1);
@@ -524,6 +526,7 @@ __global__ __launch_bounds__(256, NP == 1 ? 4 : 2) void pq_nearest_kernel(
       for (int u = 0; u < 8; ++u) af[b][s][u] = half ? hi[u] : lo[u];
     }
   }
+  const bool all_unsure = __builtin_amdgcn_ballot_w64(odd) != 0 || eps_scale < 0.f;
   const floatx16 fzero = {0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0};
   const int64_t base = (chunk * 4 + wave) * 32ll * groups;
   for (int g = 0; g < groups; ++g) {
@@ -598,7 +601,7 @@ __global__ __launch_bounds__(256, NP == 1 ? 4 : 2) void pq_nearest_kernel(
     // |t| <= |r| + its distance, whose square is at most |r|^2 - 2 b2 up to that error.
     const float dist = sqrtf(fmaxf(rr - 2.f * b2, 0.f)), tmax = sqrtf(rr) + 1.01f * dist;
     // (+ 1e-30: the tags alone tell scores of zero apart, and products of tiny numbers vanish)
-    const bool unsure = !(b1 - b2 > eps_scale * (4e-5f * (rr + tmax * tmax) + 1e-30f)) || eps_scale < 0.f;
+    const bool unsure = !(b1 - b2 > eps_scale * (4e-5f * (rr + tmax * tmax) + 1e-30f)) || all_unsure;
     u32 todo = (u32)__builtin_amdgcn_ballot_w64(unsure);          // (both halves agree)
     while (todo != 0) {
       const int src = __builtin_ctz(todo);
@@ -612,12 +615,14 @@ __global__ __launch_bounds__(256, NP == 1 ? 4 : 2) void pq_nearest_kernel(
 #pragma unroll
         for (int t = 0; t < DP; ++t)
           if (t < dsub) { const float diff = rs[t] - T[j * dsub + t]; acc = __builtin_fmaf(diff, diff, acc); }
-        const u64 kk = make_key(acc, (u32)j, 0);
+        // (encoding never chose a codeword at a distance that is not finite; training orders a NaN's bits
+        // like the keys of the nearest-row routes)
+        const u64 kk = RES && !(acc < __builtin_inff()) ? KEY_EMPTY : make_key(acc, (u32)j, 0);
         key = kk < key ? kk : key;
       }
 #pragma unroll
       for (int off = 1; off < 64; off <<= 1) { const u64 o = __shfl_xor(key, off); key = o < key ? o : key; }
-      if ((lane & 31) == src) best = (int)min(key_index(key), (u32)(K - 1));
+      if ((lane & 31) == src) best = RES && key == KEY_EMPTY ? 0 : (int)min(key_index(key), (u32)(K - 1));
     }
     if (half == 0 && i0 + lane < n) {
       codes[(i0 + lane) * stride_i + m * stride_m] = (uint8_t)best;

@@ -375,7 +375,7 @@ def test_nearest_codewords_match_oracle(vs, oracle, n, M, dsub, nbits):
 
 @pytest.mark.parametrize("nbits", [4, 8])
 @pytest.mark.parametrize("dsub", [2, 5, 8, 12, 16])
-@pytest.mark.parametrize("kind", ["gauss", "tiny", "huge", "nonfinite_vectors"])
+@pytest.mark.parametrize("kind", ["gauss", "tiny", "huge", "nonfinite_vectors", "nonfinite_codewords"])
 def test_nearest_codewords_on_all_routes(vs, kind, dsub, nbits):
     """Codes by the canon chain alone (knn_path = 1), by the matrix cores, and by their canon branch for every
     sub-vector (knn_eps_scale < 0); training likewise."""
@@ -388,6 +388,10 @@ def test_nearest_codewords_on_all_routes(vs, kind, dsub, nbits):
     cb[0, K // 2] = cb[0, 1]
     if kind == "nonfinite_vectors":
         x[5, 0], x[6, 1], x[7, d - 1], x[8] = np.nan, np.inf, -np.inf, np.nan
+    if kind == "nonfinite_codewords":
+        cb[0, 3, 0], cb[0, 0, 1], cb[1, 0, 0], cb[1, K - 1, 1] = np.nan, np.inf, np.nan, -np.inf
+        cb[2, :, 0] = np.inf
+        cb[2, 0, 0] = np.nan
     xd, cd, bd = dev(x), dev(cent), dev(cb)
 
     def codes():
@@ -401,8 +405,7 @@ def test_nearest_codewords_on_all_routes(vs, kind, dsub, nbits):
         c, b = cd.clone(), bd.clone()
         vs.vs_ivfpq_train(xd, L2, c, b, nbits, 2)
         return host(c).copy(), host(b).copy()
-    calls = [codes] + ([trained] if "nonfinite" not in kind else [])
-    for call in calls:
+    for call in (codes, trained):
         got = {}
         for path, eps in ((0, 1.0), (1, 1.0), (0, -1.0)):
             try:
