@@ -375,6 +375,16 @@ __device__ __forceinline__ float canon_row(const float* __restrict__ qs, const f
   return acc;
 }
 
+// The canon value of the nearest-row routes, whose tiles hold whole blocks of 32 dimensions: the zeros
+// behind a ragged row leave every sum as it is but for -0 (a product that underflowed in the last
+// dimension of an inner product), which they make +0.
+template <int METRIC>
+__device__ __forceinline__ float canon_row_padded(const float* __restrict__ qs, const float* __restrict__ b,
+                                                  int d, bool vec) {
+  const float v = canon_row<METRIC>(qs, b, d, vec);
+  return METRIC != 0 && (d & 31) != 0 ? v + 0.f : v;
+}
+
 // The same value for 64 rows at once, one per lane of a wavefront, with memory read in runs of
 // 128 bytes (d a multiple of 32): per chunk of 32 dimensions eight lanes fetch the 128 bytes
 // of one row (8 rows per load instruction), the chunk goes through a wavefront-private LDS

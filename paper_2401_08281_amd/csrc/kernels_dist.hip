@@ -7,7 +7,7 @@
 //     IP: acc = fma(a[t], b[t], acc)
 // starting from acc = +0.  Each accumulator below is such a chain; tiling is
 // across pairs only, never across t, so the result is independent of the
-// tiling.  Padding dimensions contribute fma(0, 0, acc) = acc exactly.
+// tiling.  Padding dimensions contribute fma(0, 0, acc) = acc (+0 where acc is -0).
 //
 // Work decomposition: a workgroup of 256 lanes (4 wavefronts) owns a 64 x 64
 // tile of pairs; each lane owns a 4 x 4 register block.  Both operand tiles

@@ -990,7 +990,7 @@ __global__ __launch_bounds__(64) void rerank_kernel(
     const u64 ak = e < kp ? ws.s[e] : KEY_EMPTY;
     if (ak == KEY_EMPTY) { v[r] = KEY_EMPTY; continue; }
     const u32 idx = key_index(ak);
-    v[r] = make_key(canon_row<METRIC>(qs, B + (int64_t)idx * d, d, vec), idx, METRIC);
+    v[r] = make_key(canon_row_padded<METRIC>(qs, B + (int64_t)idx * d, d, vec), idx, METRIC);
   }
   wave_sort_regs(v);
   wave_lds_sync();
@@ -1091,8 +1091,7 @@ __device__ __forceinline__ FallbackSplit fallback_split(int count, int64_t nb, i
 // 65536 x 96).  Here a tile of 256 rows of B x 32 dimensions is fetched with 8 lanes per row (128
 // consecutive bytes per request), written to LDS with a row stride of 36 floats (16-byte aligned,
 // conflict-free for the 16-byte reads that follow), and lane r continues the canon chain of row r
-// over those 32 dimensions -- the same values in the same order as canon_row, hence the same bits
-// (dimensions past d are zeros on both sides: fma(0, 0, acc) = acc).
+// over those 32 dimensions -- the same values in the same order as canon_row_padded, hence the same bits.
 // The next tile chunk is in flight (registers) while the current one is summed.
 template <int R, int METRIC>
 __global__ __launch_bounds__(256) void canon_rows_tiled_kernel(const float* __restrict__ A,

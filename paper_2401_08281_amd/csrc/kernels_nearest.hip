@@ -395,7 +395,7 @@ __global__ __launch_bounds__(256) void nearest_decide_kernel(
     u64 key = KEY_EMPTY;
     if (sub < c) {
       const int j = cand[(int64_t)e * kCandidates + sub];
-      key = make_key(canon_row<METRIC>(x + (int64_t)row * d, B + (int64_t)j * d, d, vec), (u32)j, METRIC);
+      key = make_key(canon_row_padded<METRIC>(x + (int64_t)row * d, B + (int64_t)j * d, d, vec), (u32)j, METRIC);
     }
 #pragma unroll
     for (int off = 1; off < 16; off <<= 1) { const u64 o = __shfl_xor(key, off); key = o < key ? o : key; }

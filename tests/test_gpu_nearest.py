@@ -457,6 +457,44 @@ def test_ragged_exact_search_equals_canon_tiles(vs, nb, nq, d, k, metric):
             np.testing.assert_array_equal(a, b)
 
 
+@pytest.mark.parametrize("d", [33, 50, 64])
+def test_products_that_underflow_tie_alike_on_all_routes(vs, d):
+    """Inner products of +0 and, in some rows, of a product that underflows to -0 in the last dimension, far
+    ahead of all others: where rows are padded to whole blocks of 32 the zeros make both +0 (a tie)."""
+    say("underflowing products d=%d" % d)
+    nb, nq = 20_003, 40
+    x, q = np.zeros((nb, d), dtype=np.float32), np.zeros((nq, d), dtype=np.float32)
+    x[:, 0] = -1.0
+    special = np.arange(100, 112)
+    x[special, 0] = 0.0
+    x[special, d - 1] = np.where(special % 2 == 0, np.float32(-1e-23), np.float32(1e-23))
+    q[:, 0], q[:, d - 1] = 1.0, 1e-23
+    xd, qd = dev(x), dev(q)
+
+    def assigned():
+        ix = vs.IVFFlat(d, IP, xd)
+        ix.add(qd)
+        out = (ix.list_sizes(),)
+        ix.close()
+        return out
+    for call in (lambda: vs.vs_flat_search(xd, qd, 8, IP), assigned):
+        canon, got = both_routes(vs, call)
+        for a, b in zip(canon, got):
+            np.testing.assert_array_equal(a, b)
+
+
+@pytest.mark.parametrize("d", [33, 64, 100])
+@pytest.mark.parametrize("metric", [L2, IP])
+@pytest.mark.parametrize("scale", [1e-18, 1e-19, 1e-20, 1e-22])
+def test_exact_search_of_tiny_values(vs, scale, d, metric):
+    """Products near and below the smallest normal number, which the matrix cores may drop."""
+    say("tiny values %g d=%d metric=%d" % (scale, d, metric))
+    x, q = dev(rows("gauss", 5_001, d, 45) * np.float32(scale)), dev(rows("gauss", 300, d, 46) * np.float32(scale))
+    canon, got = both_routes(vs, lambda: vs.vs_flat_search(x, q, 10, metric))
+    for a, b in zip(canon, got):
+        np.testing.assert_array_equal(a, b)
+
+
 def test_static_search_accepts_what_fits_by_the_matrix_core_route(vs):
     """The canon tiles of a small problem can be larger than the fixed work space (600 x 16384 scores:
     40 MiB) where the matrix-core route's shortlist fits it: the call is served, with the same results."""
