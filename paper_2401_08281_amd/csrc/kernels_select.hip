@@ -89,7 +89,11 @@ void launch_row_select(const float* mat, int64_t ld, int64_t nrows, int64_t ncol
                        int metric, int k, u64* keys, bool first, bool last, const SelectOut& out,
                        hipStream_t st) {
   if (nrows <= 0) return;
-  const int tot = select_slots_for_k(k);
+  // (close below 64 a list of 128 slots has hardly room for the candidates of one step and is sorted at
+  // nearly every step.  1000 rows of 16384 values at d = 32, tiles and selection: k = 64 273 us with 128
+  // slots and 107 with 256, k = 49 124 and 102; k = 48 with 128: 121)
+  int tot = select_slots_for_k(k);
+  if (tot == 128 && k > 48) tot = 256;
   const size_t shmem = (size_t)5 * tot * sizeof(u64);
   const dim3 grid((unsigned)nrows), block(256);
 #define LAUNCH(RR)                                                                                 \

@@ -457,6 +457,19 @@ def test_ragged_exact_search_equals_canon_tiles(vs, nb, nq, d, k, metric):
             np.testing.assert_array_equal(a, b)
 
 
+# both list sizes of the canon tiles' selection and the values of k between which they change
+@pytest.mark.parametrize("k", [47, 48, 49, 63, 64, 65, 127, 128, 129])
+@pytest.mark.parametrize("nb", [40, 64, 3_001, 16_500])
+def test_selection_at_the_sizes_of_its_lists(vs, nb, k):
+    say("selection nb=%d k=%d" % (nb, k))
+    x, q = rows("sift", nb, 40, 47), dev(rows("sift", 70, 40, 48))
+    x[nb // 2:] = x[:nb - nb // 2]                      # ties
+    xd = dev(x)
+    canon, got = both_routes(vs, lambda: vs.vs_flat_search(xd, q, k, L2))
+    for a, b in zip(canon, got):
+        np.testing.assert_array_equal(a, b)
+
+
 @pytest.mark.parametrize("d", [33, 50, 64])
 def test_products_that_underflow_tie_alike_on_all_routes(vs, d):
     """Inner products of +0 and, in some rows, of a product that underflows to -0 in the last dimension, far
