@@ -224,12 +224,20 @@ struct KnnPlan {
 };
 // A problem so small that the launches of the matrix-core route (prepare, two sweeps, threshold,
 // re-rank, fallback: up to a dozen kernels) cost more than one canon tile pass and one selection
-// cost in full.  Measured on 256 - 65536 columns of 32 - 768 dimensions, 1 - 1000 rows: the canon
-// route is ahead up to about 6e8 multiply-adds (4096 x 128, 1000 rows: 63 against 74 us; 1 row: 35
-// against 60) while the columns fit one tile (65536 x 96, 1 row: 168 against 80).
+// cost in full.  Measured on 256 - 65536 columns of 32 - 768 dimensions, 1 - 10000 rows, k = 1 - 150
+// (profiles/small_problems_routes.txt): the canon route is ahead up to about 6e8 multiply-adds (4096 x 128,
+// 1000 rows, k = 16: 65 against 74 us; 1 row: 35 against 59), while there are not too many values to
+// select from (d = 32, k = 64: 10000 rows of 1024 184 against 167 us, 1000 of 16384 107 against 87) and the
+// columns fit one tile (65536 x 96, 1 row: 169 against 81).
 // (not with knn_path = 2, which takes the matrix cores wherever there is a kernel)
 bool knn_small(int64_t na, int64_t nb, int d) {
-  return g_knn_path.load() == 0 && nb <= 16384 && (double)na * nb * d <= 6e8;
+  return g_knn_path.load() == 0 && nb <= 16384 && na * nb <= 8000000 && (double)na * nb * d <= 6e8;
+}
+// The same for nearest rows in one sweep, against the canon tiles that keep the best row only.  One round
+// of k-means: 1.2e9 multiply-adds 5 - 15 % longer in one sweep, 2e9 about equal from 128 rows of B on, 4e9
+// 20 - 35 % shorter (up to 64 rows of B the two stay within 15 % of each other whatever the number of vectors).
+bool nearest_small(int64_t n, int64_t nb, int d) {
+  return g_knn_path.load() == 0 && nb <= 16384 && (double)n * nb * d <= 2e9;
 }
 // route: 1 / 0 = the matrix-core / the canon route (a plan made before for a larger piece of the
 // same rows), -1 = choose; small_canon: choose the canon route for problems that are small.
@@ -668,8 +676,8 @@ namespace {
 int nearest_rows(const float* A, int64_t n, const float* B, int64_t nb, int d, int metric,
                  int32_t* idx, float* val, Scratch& sc, hipStream_t st, bool again = false) {
   constexpr int64_t kPiece = 1 << 20;
-  const bool small = knn_small(n, nb, d);
-  if (g_knn_path.load() != 1 && nearest_supported(d) && !small && (!val || metric == VS_METRIC_L2)) {
+  const bool one_best = nearest_supported(d) && (!val || metric == VS_METRIC_L2), small = nearest_small(n, nb, d);
+  if (g_knn_path.load() != 1 && one_best && !small) {
     const size_t pb = planes_bytes(nb, d);
     const int64_t piece = std::min(n, 4 * kPiece);
     if (int rc = sc.reserve(pb + nearest_bytes(piece, nb) + nearest_bytes(n % piece, nb))) return rc;
@@ -683,10 +691,11 @@ int nearest_rows(const float* A, int64_t n, const float* B, int64_t nb, int d, i
     g_knn_mfma_rows += n;
     return VS_OK;
   }
-  const KnnPlan plan = knn_plan_pieces(n, kPiece, nb, d, 1, false, true);
+  KnnPlan plan;
+  if (!(one_best && small)) plan = knn_plan_pieces(n, kPiece, nb, d, 1, false, true);
   if (!plan.mfma) {
-    // shapes the matrix-core kernels do not cover (sub-vectors of a few dimensions): fused canon
-    // distance + arg-best tiles, one 64-bit key (value, row of B) per row of A
+    // small problems and shapes the matrix-core kernels do not cover (sub-vectors of a few dimensions):
+    // fused canon distance + arg-best tiles, one 64-bit key (value, row of B) per row of A
     if (int rc = sc.reserve((size_t)n * sizeof(u64))) return rc;
     u64* keys = static_cast<u64*>(sc.p);
     launch_fill_u64(keys, n, 0xFFFFFFFFFFFFFFFFull, st);
@@ -1056,17 +1065,19 @@ int ivf_assign_and_place(vs_ivfpq* ix, const float* x, int64_t n, size_t extra, 
   // best keys [n] | list_of [n] | caller's extra | dest [n] | new offsets | work space of the placement
   constexpr int64_t kAssignPiece = 1 << 20;
   // On the k-nearest-rows route (d above 128) the first piece of an index's first large add is a short
-  // one: the sweeps start out on the fp16 heads alone and learn from a call's fallback count whether that does for this data; a
-  // short first call keeps the price of finding out small.
+  // one: the sweeps start out on the fp16 heads alone and learn from a call's fallback count whether
+  // that does for this data; a short first call keeps the price of finding out small.
   constexpr int64_t kProbePiece = 8192;
   // one sweep that keeps the best row only (no short first piece: the vectors that its fp16 heads leave
   // with too many candidates are swept with three products in the same call, not redone in full)
-  const bool one_sweep = g_knn_path.load() != 1 && ix->has_planes && nearest_supported(g.d) && !knn_small(n, g.nlist, g.d);
+  const bool one_best = ix->has_planes && nearest_supported(g.d), small = nearest_small(n, g.nlist, g.d);
+  const bool one_sweep = g_knn_path.load() != 1 && one_best && !small;
   const int64_t sweep_piece = std::min<int64_t>(n, 4 * kAssignPiece);
   const int64_t first_piece = !ix->assign_probed && n > 4 * kProbePiece ? kProbePiece : 0;
-  KnnPlan plan = knn_plan_pieces(n - first_piece, kAssignPiece, g.nlist, g.d, 1, ix->has_planes, true);
-  if (first_piece > 0) {
-    const KnnPlan probe = knn_plan(first_piece, g.nlist, g.d, 1, ix->has_planes, false, plan.mfma ? 1 : 0);
+  KnnPlan plan;
+  if (!one_best) plan = knn_plan_pieces(n - first_piece, kAssignPiece, g.nlist, g.d, 1, ix->has_planes, true);
+  if (plan.mfma && first_piece > 0) {
+    const KnnPlan probe = knn_plan(first_piece, g.nlist, g.d, 1, ix->has_planes, false, 1);
     plan.bytes = std::max(plan.bytes, probe.bytes);
   }
   if (!plan.mfma) plan.bytes = 0;

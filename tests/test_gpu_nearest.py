@@ -42,9 +42,9 @@ def both_routes(vs, call, counted=None):
     return canon, forced
 
 
-# Each part of an add is above 6e8 = n * rows * d, the size from which the sweep is chosen, or is taken to
-# the sweep by knn_path = 2.  d: both ends of the range, every padded length, remainders of 4, 2 and 1;
-# rows of B: one step and a remainder, one past a step, a split; n: one past a tile, remainders.
+# Parts of an add below n * rows * d = 2e9, where the canon tiles are chosen, go to the sweep by knn_path = 2.
+# d: both ends of the range, every padded length, remainders of 4, 2 and 1; rows of B: one step and a
+# remainder, one past a step, a split; n: one past a tile, remainders.
 NEAREST_CASES = [
     ("d17", 131_073, 300, 17, L2, "gauss"), ("d30_ip", 80_001, 300, 30, IP, "gauss"),
     ("d32", 60_033, 321, 32, L2, "sift"), ("d64_ip", 30_001, 320, 64, IP, "gauss"),
@@ -218,7 +218,7 @@ def add_and_count(vs, ix, x):
 
 
 def test_counters_cover_the_one_sweep_route_and_forced_fallbacks_teach_nothing(vs):
-    n, nb, d = 25_000, 300, 96
+    n, nb, d = 75_000, 300, 96
     say("counters of the sweep n=%d nb=%d d=%d" % (n, nb, d))
     x, cent = well_separated(n, nb, d, 20)
     ix = vs.IVFFlat(d, L2, cent)
@@ -289,7 +289,7 @@ def test_vectors_that_the_heads_leave_are_swept_with_more_products(vs, d, metric
 def test_a_search_with_one_probe_teaches_the_sweep_nothing(vs):
     """A search at nprobe = 1 gives up the fp16 heads for its own kind after one row in 512 redone; the
     one-sweep route, which has a rule of its own, still begins with them (3 vectors left, see above)."""
-    n, nb, d = 25_000, 300, 96
+    n, nb, d = 75_000, 300, 96
     say("one-probe search, then an add: n=%d nb=%d d=%d" % (n, nb, d))
     x, cent = well_separated(n, nb, d, 20)
     q, tight, _ = tight_groups(2_000, d, 64, 1.0, 25)
@@ -575,7 +575,7 @@ def test_training_with_little_memory_free(vs, left):
     say("train n=%d M=%d with %d MB to spare" % (n, M, left))
     g = torch.Generator(device="cuda").manual_seed(9)
     x = torch.randn((n, d), generator=g, device="cuda")
-    cent, cb = x[:16].clone(), torch.randn((M, 1 << nbits, 1), generator=g, device="cuda")
+    cent, cb = x[:64].clone(), torch.randn((M, 1 << nbits, 1), generator=g, device="cuda")
 
     def call():
         c, b = cent.clone(), cb.clone()
