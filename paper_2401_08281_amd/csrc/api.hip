@@ -223,15 +223,21 @@ struct KnnPlan {
   size_t bytes = 0;               // scratch needed
 };
 // A problem so small that the launches of the matrix-core route (prepare, two sweeps, threshold,
-// re-rank, fallback: up to a dozen kernels) cost more than one canon tile pass and one selection
-// cost in full.  Measured on 256 - 65536 columns of 32 - 768 dimensions, 1 - 10000 rows, k = 1 - 150
-// (profiles/small_problems_routes.txt): the canon route is ahead up to about 6e8 multiply-adds (4096 x 128,
-// 1000 rows, k = 16: 65 against 74 us; 1 row: 35 against 59), while there are not too many values to
-// select from (d = 32, k = 64: 10000 rows of 1024 184 against 167 us, 1000 of 16384 107 against 87) and the
-// columns fit one tile (65536 x 96, 1 row: 169 against 81).
+// re-rank, fallback: up to a dozen kernels) cost more than the canon tiles and their selection cost in
+// full.  Measured on 256 - 131072 columns of 17 - 769 dimensions, 1 - 10000 rows, k = 1 - 150
+// (profiles/small_problems_routes.txt).  With columns prepared before, the canon route is ahead up to about
+// 6e8 multiply-adds (4096 x 128, 1000 rows, k = 16: 65 against 74 us; 1 row: 35 against 59), while there
+// are not too many values to select from (d = 32, k = 64: 10000 rows of 1024 184 against 167 us, 1000 of
+// 16384 107 against 87) and the columns fit one round of tiles (65536 x 96, 1 row: 169 against 81), or
+// two for a few short rows (20000 x 33, 1 row: 63 against 80).  Columns that come with the call have to be
+// prepared first, 30 to 60 us and a pass over them: 40000 x 100, 30 rows 115 against 132, 1000 rows of
+// 10000 x 200 165 against 177, 65536 x 100, 1 row 170 against 152.
 // (not with knn_path = 2, which takes the matrix cores wherever there is a kernel)
-bool knn_small(int64_t na, int64_t nb, int d) {
-  return g_knn_path.load() == 0 && nb <= 16384 && na * nb <= 8000000 && (double)na * nb * d <= 6e8;
+bool knn_small(int64_t na, int64_t nb, int d, bool b_prepared) {
+  const double pairs = (double)na * nb;
+  if (g_knn_path.load() != 0) return false;
+  if (!b_prepared) return nb <= 49152 && pairs <= 1e7 && pairs * d <= 2e9;
+  return (nb <= 16384 || (nb <= 24576 && na <= 64 && d < 64)) && pairs <= 8e6 && pairs * d <= 6e8;
 }
 // The same for nearest rows in one sweep, against the canon tiles that keep the best row only.  One round
 // of k-means: 1.2e9 multiply-adds 5 - 15 % longer in one sweep, 2e9 about equal from 128 rows of B on, 4e9
@@ -245,7 +251,7 @@ KnnPlan knn_plan(int64_t na, int64_t nb, int d, int k, bool b_prepared, bool sma
   KnnPlan p;
   const int path = g_knn_path.load();
   p.mfma = path != 1 && nb > 0 && mfma_knn_supported(d, k) &&
-           (route < 0 ? !(small_canon && knn_small(na, nb, d)) : route == 1);
+           (route < 0 ? !(small_canon && knn_small(na, nb, d, b_prepared)) : route == 1);
   if (p.mfma) {
     size_t b = planes_bytes(na, d);
     if (!b_prepared) b += planes_bytes(nb, d);
