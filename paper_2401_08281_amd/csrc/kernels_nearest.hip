@@ -526,7 +526,8 @@ __global__ __launch_bounds__(256, NP == 1 ? 4 : 2) void pq_nearest_kernel(
       for (int u = 0; u < 8; ++u) af[b][s][u] = half ? hi[u] : lo[u];
     }
   }
-  const bool all_unsure = __builtin_amdgcn_ballot_w64(odd) != 0 || eps_scale < 0.f;
+  // (no difference of scores is larger than a NaN: every sub-vector goes through the canon branch)
+  const float bound = __builtin_amdgcn_ballot_w64(odd) != 0 || eps_scale < 0.f ? __builtin_nanf("") : eps_scale * 4e-5f;
   const floatx16 fzero = {0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0};
   const int64_t base = (chunk * 4 + wave) * 32ll * groups;
   for (int g = 0; g < groups; ++g) {
@@ -601,7 +602,7 @@ __global__ __launch_bounds__(256, NP == 1 ? 4 : 2) void pq_nearest_kernel(
     // |t| <= |r| + its distance, whose square is at most |r|^2 - 2 b2 up to that error.
     const float dist = sqrtf(fmaxf(rr - 2.f * b2, 0.f)), tmax = sqrtf(rr) + 1.01f * dist;
     // (+ 1e-30: the tags alone tell scores of zero apart, and products of tiny numbers vanish)
-    const bool unsure = !(b1 - b2 > eps_scale * (4e-5f * (rr + tmax * tmax) + 1e-30f)) || all_unsure;
+    const bool unsure = !(b1 - b2 > bound * (rr + tmax * tmax) + 1e-30f);
     u32 todo = (u32)__builtin_amdgcn_ballot_w64(unsure);          // (both halves agree)
     while (todo != 0) {
       const int src = __builtin_ctz(todo);
