@@ -87,6 +87,9 @@ VS_API int vs_flat_search(const float* x, int64_t nb, const float* q, int64_t nq
  *                    database again: its cost grows with ntotal, add in large pieces.
  *                    Synchronises the stream.  ntotal stays below 2^31.
  *   vs_flat_index_search  same results as vs_flat_search(stored rows, ...), bit for bit.
+ *                    Takes 4 * d bytes per row, and 6 * d' + 4 more (d' = d rounded up to a
+ *                    multiple of 32, 16 < d <= 2048) for the operand planes; where these do
+ *                    not fit, rows whose d is not a multiple of 32 go without.
  *   vs_flat_ntotal   number of stored rows (-1 for a null handle).
  *   vs_flat_destroy  frees the index (null is a no-op); the caller makes sure that no
  *                    search on it is still running.
@@ -102,7 +105,9 @@ VS_API int vs_flat_index_search(const vs_flat* ix, const float* q, int64_t nq, i
 
 /*
  * vs_flat_search, vs_kmeans and vs_ivfpq_train keep one grow-only work buffer per device
- * (operand planes, candidate lists, ...; for a 10M x 768 database about 30 GB).  vs_trim
+ * (operand planes, candidate lists, ...; for a 10M x 768 database about 50 GB).  The planes
+ * take 6 * d' + 4 bytes per database row, d' = d rounded up to a multiple of 32 (d > 16);
+ * where they do not fit, rows whose d is not a multiple of 32 are searched without.  vs_trim
  * waits for the current device to go idle and frees that buffer; the next call allocates
  * what it needs again.  Indexes own their buffers and release them in their destroy call.
  */
@@ -164,7 +169,8 @@ VS_API int vs_kmeans(const float* x, int64_t n, int32_t d, int32_t K, int32_t ni
  *   centroids [nlist, d], codebooks [M, 2^nbits, d / M]: DEVICE, in = initial, out = trained.
  *   objective HOST pointer to (1 + M) * niter doubles, or NULL: row 0 the coarse k-means,
  *             row 1 + m sub-quantizer m.
- * Needs n * d floats of device memory for the residuals.  Blocks until done.
+ * Needs n * d floats of device memory for the residuals, and up to 1 GiB of what is free to train
+ * several sub-quantizers at a time (9 bytes per vector and sub-quantizer).  Blocks until done.
  * Errors: as vs_ivfpq_create for the shape; n outside [1, 2^31); niter < 0; null pointers.
  */
 VS_API int vs_ivfpq_train(const float* x, int64_t n, int32_t d, int32_t metric, int32_t nlist,

@@ -226,12 +226,12 @@ struct KnnPlan {
 // re-rank, fallback: up to a dozen kernels) cost more than the canon tiles and their selection cost in
 // full.  Measured on 256 - 131072 columns of 17 - 769 dimensions, 1 - 10000 rows, k = 1 - 150
 // (profiles/small_problems_routes.txt).  With columns prepared before, the canon route is ahead up to about
-// 6e8 multiply-adds (4096 x 128, 1000 rows, k = 16: 65 against 74 us; 1 row: 35 against 59), while there
-// are not too many values to select from (d = 32, k = 64: 10000 rows of 1024 184 against 167 us, 1000 of
-// 16384 107 against 87) and the columns fit one round of tiles (65536 x 96, 1 row: 169 against 81), or
-// two for a few short rows (20000 x 33, 1 row: 63 against 80).  Columns that come with the call have to be
-// prepared first, 30 to 60 us and a pass over them: 40000 x 100, 30 rows 115 against 132, 1000 rows of
-// 10000 x 200 165 against 177, 65536 x 100, 1 row 170 against 152.
+// 6e8 multiply-adds (4096 x 128, 1000 rows, k = 16: 66 against 75 us; 1 row: 34 against 59), while there
+// are not too many values to select from (d = 32, k = 64: 10000 rows of 1024 191 against 166 us, 1000 of
+// 16384 106 against 88) and the columns fit one round of tiles (65536 x 96, 1 row: 153 against 83), or
+// two for a few short rows (20000 x 33, 1 row: 58 against 78).  Columns that come with the call have to be
+// prepared first, 30 to 60 us and a pass over them: 40960 x 100, 30 rows 125 against 155, 1000 rows of
+// 10000 x 200 150 against 165, 65536 x 100, 1 row 170 against 156.
 // (not with knn_path = 2, which takes the matrix cores wherever there is a kernel)
 bool knn_small(int64_t na, int64_t nb, int d, bool b_prepared) {
   const double pairs = (double)na * nb;
@@ -240,8 +240,8 @@ bool knn_small(int64_t na, int64_t nb, int d, bool b_prepared) {
   return (nb <= 16384 || (nb <= 24576 && na <= 64 && d < 64)) && pairs <= 8e6 && pairs * d <= 6e8;
 }
 // The same for nearest rows in one sweep, against the canon tiles that keep the best row only.  One round
-// of k-means: 1.2e9 multiply-adds 5 - 15 % longer in one sweep, 2e9 about equal from 128 rows of B on, 4e9
-// 20 - 35 % shorter (up to 64 rows of B the two stay within 15 % of each other whatever the number of vectors).
+// of k-means, 1024 rows of B at d = 128: 6e8 multiply-adds 20 % longer in one sweep, 1.2e9 12 %, 2e9 equal, 3e9
+// 18 % shorter (up to 64 rows of B the two stay within 15 % of each other whatever the number of vectors).
 bool nearest_small(int64_t n, int64_t nb, int d) {
   return g_knn_path.load() == 0 && nb <= 16384 && (double)n * nb * d <= 2e9;
 }

@@ -71,12 +71,12 @@ __device__ __forceinline__ int precision_variant(const PrepInfo* a, const PrepIn
 // ---------------------------------------------------------------------------
 // Operand preparation: bf16 head / tail planes, fp32 squared norms, and the
 // facts needed to bound the approximation error (PrepInfo).
-// One lane per 8 consecutive elements (d % 8 == 0), 256 lanes per workgroup,
-// 2048 / d rows per group; a workgroup walks over groups and reports its flags
-// and largest norm once at the end.  Row sums are added in a fixed order.
 // The planes are [n_pad][dp] row-major, dp = d rounded up to a multiple of 32: the padding
 // dimensions hold zeros, which add nothing to any product or norm, so that every d goes
-// through the matrix cores.  F16: also write the fp16 heads.
+// through the matrix cores.  One lane per 8 consecutive elements of a plane, 256 lanes per
+// workgroup, 2048 / dp rows per group; a workgroup walks over groups and reports its flags
+// and largest norm once at the end.  Row sums are added in a fixed order.
+// F16: also write the fp16 heads.
 // ---------------------------------------------------------------------------
 template <bool F16>
 __global__ __launch_bounds__(256) void prep_kernel(const float* __restrict__ x, int64_t n,

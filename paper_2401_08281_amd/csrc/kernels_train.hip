@@ -50,7 +50,7 @@ __device__ __forceinline__ int block_owner(const int64_t* __restrict__ off, int 
 // off it: 32 vectors at a time, their numbers come in with one load and their rows are all
 // requested a batch ahead of the additions, which run in the list's order.  262144 x 128 into 1024
 // centroids, clusters of up to some thousand: 710 us with one batch in flight and two dimensions
-// per lane, 140 us like this.
+// per lane, 63 us like this.
 __global__ __launch_bounds__(256) void segmented_mean_kernel(const float* __restrict__ x, int d,
                                                              const int32_t* __restrict__ order,
                                                              const int64_t* __restrict__ off, int K,
@@ -105,8 +105,9 @@ __global__ __launch_bounds__(256) void segmented_mean_kernel(const float* __rest
 // instruction fetches 64 / DP rows.  Rows are requested 32 vectors ahead of the additions and their
 // numbers 64 ahead, so that waiting for a number never waits for the rows just requested.  16
 // problems of 262144 x 8 descriptors' residuals into 256 centroids: 209 us with one batch of 64 in
-// flight, 183 us like this.  The largest clusters' chains set the time: keeping a problem on one XCD
-// (180 us) and 32-bit offsets (186 us) changed nothing.
+// flight, 183 us like this with four times the workgroups and a loop over blocks, 135 us with one
+// block per group of lanes.  The largest clusters' chains set the time: keeping a problem on one XCD and
+// 32-bit offsets changed nothing.
 // DP: d rounded up to 8, 16 or 32.  Grid z: independent problems of the same shape (the
 // sub-quantizers of a product quantizer), their arrays one after the other.
 template <int DP>
