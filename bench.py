@@ -36,17 +36,31 @@ LOOKUP_PEAK_T = 256 * 4 * 16 * 2.4e9 / 1.5 / 1e12
 # Next to the published peaks the JSON line carries what THIS GPU reached in THIS run on a
 # read-only stream over 2 GiB and on a register-only loop of v_mfma_f32_32x32x16_bf16
 # (libvs_calibrate.so; --no-calibrate-peaks leaves them null).
-SCAN_SOURCES = ("kernels_ivfpq.hip", "common.hpp")   # what the scan kernels are compiled from
+SCAN_SOURCES = ("kernels_ivfpq.hip", "kernels_mscan.hip", "common.hpp")   # what the scan kernels are compiled from
 
 
 def log(msg):
     print("[bench] " + msg, file=sys.stderr, flush=True)
 
 
-def scan_kernel_name(cfg, search_type, list_major=False):
+MATRIX_SCAN_KERNEL = "ms_sweep_kernel"
+
+
+def matrix_scan(cfg, search_type, nq, npr, k):
+    """Whether the library scans the lists on the matrix cores (same rule as mscan_chosen in csrc/api.hip, for the
+    shapes of the workloads here: up to eight steps of 32 dimensions)."""
+    if cfg["d"] > 256 or cfg["M"] % 4 or k > 128:
+        return False
+    residual_tables = cfg["metric"] == 0 and search_type == "tables"
+    return nq * npr * (cfg["nb"] / cfg["nlist"]) >= (3e6 if residual_tables else 2e7) or (residual_tables and nq * npr >= 8192)
+
+
+def scan_kernel_name(cfg, search_type, list_major=False, on_matrix_cores=False):
     """The scan kernel the library picks for this shape (same rule as its launcher).  list_major:
     the search ran list by list (the call's statistics say so): the dominant kernel is that scan."""
     code_size = cfg["M"] * cfg["nbits"] // 8
+    if on_matrix_cores:
+        return MATRIX_SCAN_KERNEL
     if list_major:
         return "ivfpq_scan_listmajor_kernel"
     if cfg["nbits"] == 8 and (cfg["M"], cfg["d"] // cfg["M"]) in ((16, 8), (32, 3), (8, 4)):
@@ -143,6 +157,10 @@ def record_traffic(args):
                   nq_ * (npr_ - 4) >= 3 * cfg["nlist"] and cfg["nb"] * cfg["M"] >= (512 << 20) and
                   cfg["nb"] >= 1024 * cfg["nlist"])
     kernel = scan_kernel_name(cfg, args.search_type, list_major)
+    for path in glob.glob(os.path.join(args.record_traffic[0], "**", "*counter_collection.csv"), recursive=True):
+        with open(path, newline="") as f:   # a run whose lists were scanned on the matrix cores
+            if any(MATRIX_SCAN_KERNEL in r["Kernel_Name"] for r in csv.DictReader(f)):
+                kernel = MATRIX_SCAN_KERNEL
     GIB_KIB = float(1 << 20)
     got = {}
     for counter, folder in zip(("FETCH_SIZE", "WRITE_SIZE"), args.record_traffic):
@@ -351,6 +369,7 @@ def main():
     # a list-major search: stage "scan" is the list-major kernel alone, which visits the codes of
     # all probes but the first few of every query (those are stage "scan_first", query-major)
     list_major = stats["list_major_first_probes"] > 0
+    on_matrix_cores = not list_major and matrix_scan(cfg, args.search_type, nq, min(nprobe, cfg["nlist"]), k)
     scanned_dominant = scanned - stats["list_major_first_codes"]
     algo_bytes = scanned_dominant * code_size
     if list_major:
@@ -423,8 +442,8 @@ def main():
         "rows_matrix_core": stats["coarse_rows_matrix_core"],
         "rows_exact_fallback": stats_after["coarse_rows_fallback"],
         "rows_exact_fallback_first_call": stats["coarse_rows_fallback"], "traffic": None}
-    roofline = {"bound": "hbm", "kernel": scan_kernel_name(cfg, args.search_type, list_major), "achieved": achieved,
-                "peak": HBM_PEAK_GBS, "unit": "GB/s", "frac": achieved / HBM_PEAK_GBS,
+    roofline = {"bound": "hbm", "kernel": scan_kernel_name(cfg, args.search_type, list_major, on_matrix_cores),
+                "achieved": achieved, "peak": HBM_PEAK_GBS, "unit": "GB/s", "frac": achieved / HBM_PEAK_GBS,
                 "peak_measured_read_stream": read_now,
                 "frac_of_measured": achieved / read_now if read_now else None,
                 "traffic": traffic, "algorithmic_bytes_per_launch": algo_bytes,
@@ -455,6 +474,23 @@ def main():
                     "list_major": {"first_probes_per_query": stats["list_major_first_probes"],
                                    "codes_scanned_query_major_first": stats["list_major_first_codes"],
                                    "queries_rescanned": stats_after["list_major_rescanned"]}}
+    if on_matrix_cores:
+        # The lists' codes are decoded once per batch and multiplied with all queries that probe the list: 2 d flop per
+        # (query, code) pair in fp16.  (Stage "scan" is the sweep over all probed lists; the sweep that bounds the
+        # distances is part of "scan_first", the exact evaluation of the candidates of "merge".)
+        flop = 2.0 * float(scanned) * cfg["d"]
+        tf = flop / (scan_ms * 1e-3) / 1e12 if scan_ms > 0 else 0.0
+        roofline = {"bound": "mfma", "kernel": MATRIX_SCAN_KERNEL, "achieved": tf, "peak": BF16_MFMA_PEAK_TFLOPS,
+                    "unit": "TFLOP/s", "frac": tf / BF16_MFMA_PEAK_TFLOPS,
+                    "peak_measured_mfma_loop": peaks.get("mfma_loop_TFLOPs"),
+                    "algorithmic_flop_per_launch": flop, "traffic": traffic, "kernel_ms": scan_ms,
+                    "pairs_per_launch": pairs, "probed_nonempty_lists_per_launch": stats["probed_lists"],
+                    "hbm_equivalent": {"algorithmic_bytes_per_launch": algo_bytes, "achieved_GBps": achieved,
+                                       "frac_of_peak": achieved / HBM_PEAK_GBS,
+                                       "peak_measured_read_stream": read_now,
+                                       "note": "codes visited x code size over the kernel's time; a list comes from "
+                                               "memory about once per batch, so this is not an HBM rate"},
+                    "queries_rescanned": stats_after["list_major_rescanned"]}
     out = {
         "metric": "IVF-PQ queries/sec at fixed nprobe & recall@10; ADC-scan HBM GB/s vs peak",
         "value": qps, "unit": "queries/s", "n_gpus": 1, "steps": args.steps, "warmup": args.warmup,

@@ -210,6 +210,8 @@ VS_API int vs_ivfpq_create(vs_ivfpq** out, int32_t d, int32_t metric, int32_t nl
  * machine.  Code bytes: nbits == 8: byte m = c_m; nbits == 4: byte i =
  * c_{2i} | c_{2i+1} << 4.
  * The list storage is re-laid-out contiguously; the call synchronises.
+ * Shapes that the matrix-core scan serves (option "matrix_scan") also keep the codes in that scan's
+ * order, about their own size once more, while that is at most a quarter of the free memory.
  * n == 0 is a no-op.  The total number of stored vectors must stay < 2^32.
  */
 VS_API int vs_ivfpq_add(vs_ivfpq* ix, const float* x, int64_t n, const int64_t* ids, void* hip_stream);
@@ -224,9 +226,10 @@ VS_API int vs_ivfpq_add(vs_ivfpq* ix, const float* x, int64_t n, const int64_t* 
  * are returned best first with their stored ids.
  *   q [nq, d] fp32; out_dist [nq, k] fp32; out_ids [nq, k] int64.
  * Errors: null pointers (with nq > 0), k or nprobe < 1 or > VS_MAX_K.
- * Large batches on L2 indexes of the three fixed shapes are scanned list by list (option
- * "list_major" below): same results, one read of every probed list per batch; the work space then
- * also holds the candidate buffers, 8 bytes x "list_major_candidates" (default 1024) per query.
+ * Large batches are scanned list by list on the matrix cores (option "matrix_scan" below): same
+ * results, one read of every probed list per batch; the work space then also holds the candidate
+ * buffers, up to 64 bytes x "list_major_candidates" (default 1024) per query and about 1 GiB.
+ * Where it does not fit, and in batches that are too small, the lists are scanned query by query.
  * Work space: one grow-only buffer per index (the first call of a size allocates it; later
  * calls only enqueue kernels).  Searches of one index from several host threads or on several
  * streams are serialised on it: a call on another stream than the previous search's first waits,
@@ -247,9 +250,9 @@ VS_API int vs_ivfpq_search(const vs_ivfpq* ix, const float* q, int64_t nq, int32
  *   list_major_first_probes  0, or (the batch was scanned list by list, see vs_ivfpq_search) the
  *                            number of probes per query that were scanned query by query first
  *   list_major_first_codes   the part of scanned_codes that falls on those probes
- *   list_major_rescanned     queries whose candidate buffer overflowed in the list-major scan and
- *                            that were therefore scanned again query by query (their codes are
- *                            not counted twice in scanned_codes)
+ *   list_major_rescanned     queries whose candidate buffer overflowed in a scan list by list (on the
+ *                            matrix cores as well) and that were therefore scanned again query by
+ *                            query (their codes are not counted twice in scanned_codes)
  * Results, errors and work space are those of vs_ivfpq_search.  nq == 0 zeroes the block.
  */
 typedef struct vs_search_stats {
@@ -416,7 +419,7 @@ enum {
   VS_STAGE_FLAT_DIST = 4,     /* flat search: query x database distance tiles    */
   VS_STAGE_FLAT_SELECT = 5,   /* flat search: k-selection                        */
   VS_STAGE_REFINE = 6,        /* vs_refine: exact distances of a shortlist + selection */
-  VS_STAGE_SCAN_FIRST = 7,    /* list-major search: first probes query by query, pairs grouped by list */
+  VS_STAGE_SCAN_FIRST = 7,    /* search list by list: pairs grouped by list, distances bounded on the first probes */
   VS_NUM_STAGES = 8
 };
 
@@ -451,6 +454,13 @@ VS_API int vs_profile_read(double* stage_ms, int64_t* launches);
  *   own first; the k-th best distance found there is the bound under which the list-major scan
  *   keeps a code.  "list_major_candidates" (default 1024, 64..65536): codes kept per query; a
  *   query that finds more is scanned again query by query (vs_search_stats counts them).
+ * "matrix_scan": whether vs_ivfpq_search, vs_ivfflat_search and vs_ivfsq8_search scan a batch list by
+ *   list on the matrix cores: products in fp16 decide which stored vectors can be among a query's k
+ *   best, these are evaluated with the arithmetic of the other scans.  k <= 128; raw
+ *   vectors and scalar codes of 16 < d <= 256; PQ of up to 64 sub-quantizers, a multiple of four, each
+ *   of up to 8 dimensions.  0 (default): where
+ *   it pays, by the number of vectors visited; 1: wherever there is a kernel; -1: never.
+ *   "list_major" = 1 goes before it.  Results are identical either way.
  * Options are process-wide. */
 VS_API int vs_set_option(const char* name, double value);
 /* counters[0] = rows evaluated through the matrix-core route, counters[1] = rows

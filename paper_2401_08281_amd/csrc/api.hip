@@ -153,6 +153,8 @@ std::atomic<int> g_knn_path{0};          // 0 auto, 1 canon tiles only, 2 matrix
 std::atomic<int> g_list_major{0};
 std::atomic<int> g_lm_first{4};
 std::atomic<int> g_lm_cap{1024};
+// Matrix-core scan of inverted lists: 0 where it pays, 1 wherever there is a kernel, -1 never.
+std::atomic<int> g_matrix_scan{0};
 std::atomic<float> g_knn_eps_scale{1.f}; // multiplies the error bound of the MFMA shortlist test
 std::atomic<long long> g_knn_mfma_rows{0};
 
@@ -361,6 +363,10 @@ struct vs_ivfpq {
   int search_type = VS_ST_RESIDUAL_TABLES;
   int64_t* list_off = nullptr;  // device [nlist + 1]
   std::vector<int64_t> h_off;   // host copy
+  int64_t max_list = 0;         // the longest list's length
+  void* ms_mem = nullptr;       // what the matrix-core scan of the lists keeps (shapes that have one), behind centroids
+  void* ms_units = nullptr;     // the codes in that scan's order (IVF-PQ), behind codes
+  bool ms_units_apart = false;  // ... in memory of its own
   void* plane_mem = nullptr;    // bf16 head/tail planes + norms of the centroids (MFMA route)
   Planes c_planes;
   bool has_planes = false;
@@ -433,6 +439,11 @@ int vs_set_option(const char* name, double value) {
   if (!strcmp(name, "list_major")) {
     if (value != 0 && value != 1 && value != -1) return fail(VS_ERR_INVALID_ARG, "vs_set_option: list_major must be -1, 0 or 1");
     g_list_major = (int)value;
+    return VS_OK;
+  }
+  if (!strcmp(name, "matrix_scan")) {
+    if (value != 0 && value != 1 && value != -1) return fail(VS_ERR_INVALID_ARG, "vs_set_option: matrix_scan must be -1, 0 or 1");
+    g_matrix_scan = (int)value;
     return VS_OK;
   }
   if (!strcmp(name, "list_major_first")) {
@@ -967,6 +978,20 @@ int vs_ivfpq_train(const float* x, int64_t n, int32_t d, int32_t metric, int32_t
   return VS_OK;
 }
 
+// The centroids' memory, with room for what the matrix-core scan keeps of an index behind them (one allocation costs
+// what the rest of its preparation does).  Without memory for that the index goes without that scan.
+static hipError_t alloc_centroids(vs_ivfpq* ix, int kind, size_t bytes) {
+  const size_t own = align_up(bytes), more = mscan_index_bytes(kind, ix->g);
+  if (more != 0) {
+    if (hipMalloc(reinterpret_cast<void**>(&ix->centroids), own + more) == hipSuccess) {
+      ix->ms_mem = reinterpret_cast<char*>(ix->centroids) + own;
+      return hipSuccess;
+    }
+    (void)hipGetLastError();
+  }
+  return hipMalloc(reinterpret_cast<void**>(&ix->centroids), bytes);
+}
+
 int vs_ivfpq_create(vs_ivfpq** out, int32_t d, int32_t metric, int32_t nlist, int32_t M,
                     int32_t nbits, const float* centroids, const float* codebooks,
                     void* hip_stream) {
@@ -995,7 +1020,7 @@ int vs_ivfpq_create(vs_ivfpq** out, int32_t d, int32_t metric, int32_t nlist, in
   TRY_C(hipGetDevice(&ix->device));
   const size_t cb = (size_t)nlist * d * sizeof(float);
   const size_t tb = (size_t)M * ix->g.K * ix->g.dsub * sizeof(float);
-  TRY_C(hipMalloc(reinterpret_cast<void**>(&ix->centroids), cb));
+  TRY_C(alloc_centroids(ix, kMsPq, cb));
   // (the codebooks twice: [M, K, dsub] as given, and behind it [K, M, dsub], the order in which the
   // per-query tables of the wavefront-private scan are computed)
   TRY_C(hipMalloc(reinterpret_cast<void**>(&ix->codebooks), 2 * tb));
@@ -1005,6 +1030,7 @@ int vs_ivfpq_create(vs_ivfpq** out, int32_t d, int32_t metric, int32_t nlist, in
   launch_pq_codebooks_by_entry(ix->g, ix->codebooks, ix->codebooks + tb / sizeof(float), st);
   TRY_C(hipMalloc(reinterpret_cast<void**>(&ix->cnorm), (size_t)nlist * sizeof(float)));
   launch_row_norms(ix->centroids, nlist, d, ix->cnorm, st);
+  if (ix->ms_mem) launch_mscan_index(kMsPq, ix->g, ix->centroids, ix->codebooks, ix->ms_mem, st);
   TRY_C(hipMemsetAsync(ix->list_off, 0, ((size_t)nlist + 1) * sizeof(int64_t), st));
   if (mfma_knn_supported(d, 1)) {
     TRY_C(hipMalloc(&ix->plane_mem, planes_bytes(nlist, d)));
@@ -1034,6 +1060,7 @@ static void ivf_free_device_memory(vs_ivfpq* ix) {
   if (ix->norms) (void)hipFree(ix->norms);
   if (ix->cnorm) (void)hipFree(ix->cnorm);
   if (ix->list_tables) (void)hipFree(ix->list_tables);
+  if (ix->ms_units_apart) (void)hipFree(ix->ms_units);
   if (ix->plane_mem) (void)hipFree(ix->plane_mem);
   ix->scratch.release();
 }
@@ -1159,10 +1186,15 @@ int ivf_commit_storage(vs_ivfpq* ix, uint8_t* codes, int64_t* new_ids, float* ne
   if (ix->norms) (void)hipFree(ix->norms);
   ix->codes = codes; ix->ids = new_ids; ix->norms = new_norms; ix->ntotal = total;
   ix->h_off.swap(pl->h_new);
+  ix->max_list = 0;
+  for (int l = 0; l < ix->g.nlist; ++l) ix->max_list = std::max(ix->max_list, ix->h_off[l + 1] - ix->h_off[l]);
   return VS_OK;
 }
 
 }  // namespace
+
+// entries that a store is longer than its vectors: the matrix-core scan reads blocks of 16
+constexpr int64_t kStorePad = 16;
 
 int vs_ivfpq_add(vs_ivfpq* ix, const float* x, int64_t n, const int64_t* ids, void* hip_stream) {
   if (!ix) return fail(VS_ERR_INVALID_ARG, "vs_ivfpq_add: index is null");
@@ -1191,7 +1223,27 @@ int vs_ivfpq_add(vs_ivfpq* ix, const float* x, int64_t n, const int64_t* ids, vo
   uint8_t* codes = nullptr;
   int64_t* new_ids = nullptr;
   float* new_norms = nullptr;
-  HIP_TRY(hipMalloc(reinterpret_cast<void**>(&codes), (size_t)total * g.code_size));
+  // The codes, and behind them the codes in the matrix-core scan's order (one allocation: a second one takes the host
+  // about as long as the kernel that fills it).  Above 1 GiB they lie apart, so that they can go when an index outgrows
+  // the memory, and an index that they would leave little memory goes without.
+  const size_t own = align_up((size_t)(total + kStorePad) * g.code_size);
+  size_t more = ix->ms_mem ? mscan_units_bytes(g, total) : 0;
+  const bool apart = more > (1ull << 30);
+  void* units = nullptr;
+  if (more != 0 && !apart) {
+    if (hipMalloc(reinterpret_cast<void**>(&codes), own + more) == hipSuccess) units = codes + own;
+    else { (void)hipGetLastError(); codes = nullptr; }
+  }
+  if (!codes && hipMalloc(reinterpret_cast<void**>(&codes), own) != hipSuccess) {
+    (void)hipGetLastError();
+    if (ix->ms_units_apart) {
+      HIP_TRY(hipDeviceSynchronize());
+      (void)hipFree(ix->ms_units);
+      ix->ms_units = nullptr;
+      ix->ms_units_apart = false;
+    }
+    HIP_TRY(hipMalloc(reinterpret_cast<void**>(&codes), own));
+  }
   if (hipMalloc(reinterpret_cast<void**>(&new_ids), (size_t)total * sizeof(int64_t)) != hipSuccess ||
       (with_norms && hipMalloc(reinterpret_cast<void**>(&new_norms), (size_t)total * sizeof(float)) != hipSuccess)) {
     (void)hipFree(codes);
@@ -1200,7 +1252,22 @@ int vs_ivfpq_add(vs_ivfpq* ix, const float* x, int64_t n, const int64_t* ids, vo
   }
   launch_relayout(g, ix->codes, ix->ids, ix->norms, ix->ntotal, ix->list_off, pl.new_off, tmp_codes,
                   ids, ix->ntotal, tmp_norms, pl.dest, pl.list_of, n, codes, new_ids, new_norms, st);
-  return ivf_commit_storage(ix, codes, new_ids, new_norms, total, &pl, st, "vs_ivfpq_add");
+  if (apart) {
+    size_t room = 0, all = 0;
+    if (hipMemGetInfo(&room, &all) != hipSuccess || more > room / 4 || hipMalloc(&units, more) != hipSuccess) {
+      (void)hipGetLastError();
+      units = nullptr;
+    }
+  }
+  if (units) launch_mscan_units(g, codes, pl.new_off, total, units, st);
+  if (int rc = ivf_commit_storage(ix, codes, new_ids, new_norms, total, &pl, st, "vs_ivfpq_add")) {
+    if (apart && units) (void)hipFree(units);
+    return rc;
+  }
+  if (ix->ms_units_apart) (void)hipFree(ix->ms_units);
+  ix->ms_units = units;
+  ix->ms_units_apart = apart && units != nullptr;
+  return VS_OK;
 }
 
 int vs_ivfpq_set_search_type(vs_ivfpq* ix, int32_t search_type) {
@@ -1313,6 +1380,44 @@ int vs_ivfpq_coarse(const vs_ivfpq* ix, const float* q, int64_t nq, int32_t npro
 
 namespace {
 
+// An index as the matrix-core scan sees it.
+MscanIndex mscan_index(int kind, const vs_ivfpq* ix, const float* vmin = nullptr, const float* step = nullptr) {
+  MscanIndex m;
+  m.kind = kind; m.g = ix->g; m.ntotal = ix->ntotal; m.max_list = ix->max_list;
+  m.centroids = ix->centroids; m.list_off = ix->list_off; m.codes = ix->codes; m.codebooks = ix->codebooks;
+  m.mem = ix->ms_mem; m.units = ix->ms_units; m.cnorm = ix->cnorm; m.norms = ix->norms; m.list_tables = ix->list_tables;
+  m.vmin = vmin; m.step = step;
+  m.sigma_src = ix->has_planes ? &ix->c_planes.info->max_norm_bits : nullptr;
+  return m;
+}
+// tables of a search: 0 residual, 1 inner product, 2 stored norms, 3 precomputed
+int table_form(const vs_ivfpq* ix) {
+  if (ix->g.metric == VS_METRIC_IP) return 1;
+  if (ix->search_type == VS_ST_STORED_NORMS && ix->norms) return 2;
+  return ix->search_type == VS_ST_PRECOMPUTED_TABLES && ix->list_tables ? 3 : 0;
+}
+// Whether a search goes through the matrix-core scan.  Its ten or so launches and the sorting of the pairs take some
+// 70 us more than the query-major scan of a small problem, its cost per visited vector is a small part of that scan's.
+// Measured, query-major -> matrix cores:
+//   residual tables (built for every pair by the query-major scan): 2752 pairs 105 -> 123 us, 4239 pairs 109 -> 144,
+//   7992 pairs and 4.0e6 vectors visited 264 -> 194, 14,058 pairs 277 -> 164, 22,960 pairs 277 -> 175;
+//   tables per query (inner product, stored norms, precomputed): 6.4e6 vectors visited 218 -> 204, 6.7e6 200 -> 217,
+//   1.3e7 185 -> 177, 2.2e7 301 -> 299, 2.3e7 750 -> 418, 4.3e7 822 -> 341;
+//   raw vectors and scalar codes by 32-dimension steps: 7.6e5 109 -> 146, 1.0e6 93 -> 93, 1.6e6 72 -> 103, 1.0e7 438 ->
+//   344, 1.3e7 351 -> 163.
+bool mscan_chosen(const MscanIndex& m, int form, int64_t nq, int npr, int k, MscanPlan* plan) {
+  const int opt = g_matrix_scan.load();
+  if (opt < 0 || g_list_major.load() == 1) return false;
+  const double visited = (double)nq * npr * ((double)m.ntotal / m.g.nlist);
+  const bool pays = m.kind == kMsPq ? visited >= (form == 0 ? 3e6 : 2e7) || (form == 0 && nq * (int64_t)npr >= 8192)
+                                    : visited * ((m.g.d + 31) / 32) >= 4e6;
+  if (opt == 0 && !pays) return false;
+  // candidates per query: four times what the list-major scan keeps (it only sees those behind the first lists), less
+  // for batches beyond 16,384 queries so that they stay near 1 GiB
+  const int64_t cap = std::max<int64_t>(256, std::min<int64_t>(4 * (int64_t)g_lm_cap.load(), (1ll << 26) / nq));
+  return mscan_plan(m, nq, npr, k, (int)cap, plan);
+}
+
 // Work space of one search, carved from one buffer.
 struct SearchLayout {
   int npr = 0, nsplit = 1;
@@ -1321,10 +1426,13 @@ struct SearchLayout {
   bool query_tables = false;
   bool list_major = false;      // the scan runs list-major (see ivfpq_scan_listmajor_kernel)
   int lm_first = 0, lm_cap = 0;
+  bool mscan = false;           // the scan runs on the matrix cores
+  MscanPlan ms;
+  size_t o_ms = 0;
 };
 // coarse_route: as knn_plan's route.
 void search_layout(const vs_ivfpq* ix, int64_t nq, int k, int nprobe, SearchLayout* out, bool allow_list_major = true,
-                   int coarse_route = -1) {
+                   int coarse_route = -1, bool allow_mscan = true) {
   SearchLayout& L = *out;
   const IvfpqDims& g = ix->g;
   L.npr = std::min<int>(nprobe, g.nlist);
@@ -1334,11 +1442,15 @@ void search_layout(const vs_ivfpq* ix, int64_t nq, int k, int nprobe, SearchLayo
   // list is probed several times by the batch, the codes do not fit the caches anyway and the
   // lists are long (a list of one or two chunks leaves the list-major kernel, which builds two
   // tables and then scans, with nothing to overlap the builds with: measured slower at 244 codes).
+  if (allow_list_major && allow_mscan && mscan_chosen(mscan_index(kMsPq, ix), table_form(ix), nq, L.npr, k, &L.ms)) {
+    L.mscan = true;
+    L.nsplit = 1;
+  }
   const int lm = g_list_major.load();
   const int first = std::min(g_lm_first.load(), L.npr - 1);
   const bool residual_tables = !(ix->search_type == VS_ST_STORED_NORMS && ix->norms) &&
                                !(ix->search_type == VS_ST_PRECOMPUTED_TABLES && ix->list_tables);
-  if (allow_list_major && lm >= 0 && ivfpq_listmajor_shape(g) && residual_tables && first >= 1 &&
+  if (!L.mscan && allow_list_major && lm >= 0 && ivfpq_listmajor_shape(g) && residual_tables && first >= 1 &&
       ix->ntotal > 0 && nq * (int64_t)L.npr < (1ll << 32) &&
       (lm == 1 || (L.nsplit == 1 && L.npr >= 16 && nq * (int64_t)(L.npr - first) >= 3 * (int64_t)g.nlist &&
                    ix->ntotal * (int64_t)g.code_size >= (512ll << 20) && ix->ntotal >= 1024 * (int64_t)g.nlist))) {
@@ -1357,11 +1469,12 @@ void search_layout(const vs_ivfpq* ix, int64_t nq, int k, int nprobe, SearchLayo
   L.o_part = cv.take((size_t)nq * L.nsplit * k * sizeof(u64));
   L.o_cnt = cv.take(sizeof(u64));
   // (every table form but the residual tables: inner product, stored norms, precomputed tables)
-  L.query_tables = ivfpq_wave_scan_applies(g, ix->ntotal) &&
+  L.query_tables = !L.mscan && ivfpq_wave_scan_applies(g, ix->ntotal) &&
                    (g.metric == VS_METRIC_IP || (ix->search_type == VS_ST_STORED_NORMS && ix->norms) ||
                     (ix->search_type == VS_ST_PRECOMPUTED_TABLES && ix->list_tables));
   if (L.query_tables) L.o_qt = cv.take(ivfpq_query_table_bytes(g, nq));
   if (L.list_major) L.o_lm = cv.take(ivfpq_listmajor_bytes(g, nq, L.npr, L.lm_cap));
+  if (L.mscan) L.o_ms = cv.take(L.ms.bytes);
   L.bytes = cv.off;
 }
 
@@ -1399,6 +1512,33 @@ int search_run(const char* who, const vs_ivfpq* ix, const SearchLayout& L, char*
   const bool with_norms = ix->search_type == VS_ST_STORED_NORMS && ix->norms;
   const bool split = ix->search_type == VS_ST_PRECOMPUTED_TABLES && ix->list_tables;
   bool scanned = false;
+  if (L.mscan) {
+    const MscanIndex m = mscan_index(kMsPq, ix);
+    char* ms = base + L.o_ms;
+    const int form = table_form(ix);
+    auto part = [&](int which) {
+      launch_mscan(which, m, L.ms, q, probes, cdist, form, k, g_knn_eps_scale.load(), ms, ix->ids, out_dist, out_ids, st);
+    };
+    {
+      StageTimer t(timed ? VS_STAGE_SCAN_FIRST : -1, st);
+      part(0);
+    }
+    {
+      StageTimer t(timed ? VS_STAGE_SCAN : -1, st);
+      part(1);
+    }
+    StageTimer t(timed ? VS_STAGE_MERGE : -1, st);
+    part(2);
+    const Rescan rs = mscan_rescan(m, L.ms, ms, partial);
+    if (launch_ivfpq_scan(g, q, nq, ix->centroids, ix->codebooks, probes, cdist, L.npr, 1, ix->list_off, ix->codes,
+                          with_norms ? ix->norms : nullptr, ix->cnorm, split ? ix->list_tables : nullptr, nullptr,
+                          ix->ntotal, k, partial, counter, ix->ids, out_dist, out_ids, st, rs) != 0)
+      return fail(VS_ERR_UNSUPPORTED, "%s: look-up tables of M * 2^nbits = %d floats plus selection state for k = %d exceed the LDS", who, g.M * g.K, k);
+    launch_rescan_merge(rs, k, g.metric, ix->ids, out_dist, out_ids, st);
+    if (stats)
+      launch_search_stats_rescan(mscan_rescan_count(m, L.ms, ms), reinterpret_cast<long long*>(stats), st);
+    scanned = true;
+  }
   if (L.list_major) {   // (where its selection state does not fit the LDS: the query-major scan below)
     auto part = [&](int which) {
       return launch_ivfpq_scan_listmajor(which, g, q, nq, ix->centroids, ix->codebooks, probes, cdist, L.npr,
@@ -1439,6 +1579,18 @@ int search_run(const char* who, const vs_ivfpq* ix, const SearchLayout& L, char*
   return VS_OK;
 }
 
+// Work space of a search; without room for the matrix-core scan's candidates the search takes another scan.
+int reserve_search(const vs_ivfpq* ix, int64_t nq, int k, int nprobe, SearchLayout* L) {
+  int rc = ix->scratch.reserve(L->bytes);
+  if (rc == VS_ERR_OOM && L->mscan) {
+    (void)hipGetLastError();
+    *L = SearchLayout();
+    search_layout(ix, nq, k, nprobe, L, true, -1, false);
+    rc = ix->scratch.reserve(L->bytes);
+  }
+  return rc;
+}
+
 }  // namespace
 
 int vs_ivfpq_search(const vs_ivfpq* ix, const float* q, int64_t nq, int32_t k, int32_t nprobe,
@@ -1448,7 +1600,7 @@ int vs_ivfpq_search(const vs_ivfpq* ix, const float* q, int64_t nq, int32_t k, i
   SearchLayout L;
   search_layout(ix, nq, k, nprobe, &L);
   ScratchUse use(ix->scratch, static_cast<hipStream_t>(hip_stream));
-  if (int rc = ix->scratch.reserve(L.bytes)) return rc;
+  if (int rc = reserve_search(ix, nq, k, nprobe, &L)) return rc;
   return search_run("vs_ivfpq_search", ix, L, static_cast<char*>(ix->scratch.p), q, nq, k, out_dist, out_ids,
                     static_cast<hipStream_t>(hip_stream), true);
 }
@@ -1464,7 +1616,7 @@ int vs_ivfpq_search_stats(const vs_ivfpq* ix, const float* q, int64_t nq, int32_
   SearchLayout L;
   search_layout(ix, nq, k, nprobe, &L);
   ScratchUse use(ix->scratch, st);
-  if (int rc = ix->scratch.reserve(L.bytes)) return rc;
+  if (int rc = reserve_search(ix, nq, k, nprobe, &L)) return rc;
   return search_run("vs_ivfpq_search_stats", ix, L, static_cast<char*>(ix->scratch.p), q, nq, k, out_dist, out_ids,
                     st, true, stats);
 }
@@ -1519,7 +1671,7 @@ int vs_ivfflat_create(vs_ivfflat** out, int32_t d, int32_t metric, int32_t nlist
   } while (0)
   TRY_C(hipGetDevice(&ix->device));
   const size_t cb = (size_t)nlist * d * sizeof(float);
-  TRY_C(hipMalloc(reinterpret_cast<void**>(&ix->centroids), cb));
+  TRY_C(mfma_knn_supported(d, 1) ? alloc_centroids(ix, kMsFlat, cb) : hipMalloc(reinterpret_cast<void**>(&ix->centroids), cb));
   TRY_C(hipMalloc(reinterpret_cast<void**>(&ix->list_off), ((size_t)nlist + 1) * sizeof(int64_t)));
   TRY_C(hipMemcpyAsync(ix->centroids, centroids, cb, hipMemcpyDeviceToDevice, st));
   TRY_C(hipMemsetAsync(ix->list_off, 0, ((size_t)nlist + 1) * sizeof(int64_t), st));
@@ -1530,6 +1682,7 @@ int vs_ivfflat_create(vs_ivfflat** out, int32_t d, int32_t metric, int32_t nlist
                 ix->c_planes.info, st, true);
     ix->c_planes.try_heads_only = true;
     ix->has_planes = true;
+    if (ix->ms_mem) launch_mscan_index(kMsFlat, ix->g, ix->centroids, nullptr, ix->ms_mem, st);
   }
   TRY_C(hipStreamSynchronize(st));
   if (ix->has_planes) TRY_C(learn_planes(&ix->c_planes));
@@ -1560,7 +1713,7 @@ int vs_ivfflat_add(vs_ivfflat* fx, const float* x, int64_t n, const int64_t* ids
   const int64_t total = ix->ntotal + n;
   uint8_t* rows = nullptr;
   int64_t* new_ids = nullptr;
-  HIP_TRY(hipMalloc(reinterpret_cast<void**>(&rows), (size_t)total * g.code_size));
+  HIP_TRY(hipMalloc(reinterpret_cast<void**>(&rows), (size_t)(total + kStorePad) * g.code_size));
   if (hipMalloc(reinterpret_cast<void**>(&new_ids), (size_t)total * sizeof(int64_t)) != hipSuccess) {
     (void)hipFree(rows);
     return fail(VS_ERR_OOM, "vs_ivfflat_add: id storage allocation failed");
@@ -1590,16 +1743,48 @@ int vs_ivfflat_search(const vs_ivfflat* fx, const float* q, int64_t nq, int32_t 
   const int ppb = (npr + nsplit - 1) / nsplit;
   nsplit = (npr + ppb - 1) / ppb;
   const KnnPlan plan = knn_plan(nq, g.nlist, g.d, npr, ix->has_planes, true);
-  Carver cv;
-  const size_t o_knn = cv.take(plan.bytes);
-  const size_t o_pr = cv.take((size_t)nq * npr * sizeof(int32_t));
-  const size_t o_part = cv.take((size_t)nq * nsplit * k * sizeof(u64));
+  const MscanIndex m = mscan_index(kMsFlat, ix);
+  MscanPlan ms;
+  bool mscan = mscan_chosen(m, 0, nq, npr, k, &ms);
   ScratchUse use(ix->scratch, st);
-  if (int rc = ix->scratch.reserve(cv.off)) return rc;
+  size_t o_knn = 0, o_pr = 0, o_part = 0, o_ms = 0;
+  for (;; mscan = false) {   // (without room for the matrix-core scan's candidates: the query-major scan)
+    Carver cv;
+    o_knn = cv.take(plan.bytes);
+    o_pr = cv.take((size_t)nq * npr * sizeof(int32_t));
+    o_part = cv.take((size_t)nq * (mscan ? 1 : nsplit) * k * sizeof(u64));
+    if (mscan) o_ms = cv.take(ms.bytes);
+    const int rc = ix->scratch.reserve(cv.off);
+    if (rc == VS_OK) break;
+    if (rc != VS_ERR_OOM || !mscan) return rc;
+    (void)hipGetLastError();
+  }
   char* base = static_cast<char*>(ix->scratch.p);
   int32_t* probes = reinterpret_cast<int32_t*>(base + o_pr);
   u64* partial = reinterpret_cast<u64*>(base + o_part);
   if (int rc = coarse_select(ix, plan, base + o_knn, q, nq, npr, probes, nullptr, st)) return rc;
+  if (mscan) {
+    char* wm = base + o_ms;
+    auto part = [&](int which) {
+      launch_mscan(which, m, ms, q, probes, nullptr, 0, k, g_knn_eps_scale.load(), wm, ix->ids, out_dist, out_ids, st);
+    };
+    {
+      StageTimer t(VS_STAGE_SCAN_FIRST, st);
+      part(0);
+    }
+    {
+      StageTimer t(VS_STAGE_SCAN, st);
+      part(1);
+    }
+    StageTimer t(VS_STAGE_MERGE, st);
+    part(2);
+    const Rescan rs = mscan_rescan(m, ms, wm, partial);
+    launch_ivfflat_scan(g.d, g.metric, q, nq, probes, npr, 1, ix->list_off,
+                          reinterpret_cast<const float*>(ix->codes), k, partial, ix->ids, out_dist, out_ids, st, rs);
+    launch_rescan_merge(rs, k, g.metric, ix->ids, out_dist, out_ids, st);
+    HIP_TRY(hipGetLastError());
+    return VS_OK;
+  }
   {
     StageTimer t(VS_STAGE_SCAN, st);
     launch_ivfflat_scan(g.d, g.metric, q, nq, probes, npr, nsplit, ix->list_off,
@@ -1661,7 +1846,7 @@ int vs_ivfsq8_create(vs_ivfsq8** out, int32_t d, int32_t metric, int32_t nlist,
   } while (0)
   TRY_C(hipGetDevice(&ix->device));
   const size_t cb = (size_t)nlist * d * sizeof(float), pb = (size_t)d * sizeof(float);
-  TRY_C(hipMalloc(reinterpret_cast<void**>(&ix->centroids), cb));
+  TRY_C(mfma_knn_supported(d, 1) ? alloc_centroids(ix, kMsSq8, cb) : hipMalloc(reinterpret_cast<void**>(&ix->centroids), cb));
   TRY_C(hipMalloc(reinterpret_cast<void**>(&ix->list_off), ((size_t)nlist + 1) * sizeof(int64_t)));
   TRY_C(hipMalloc(reinterpret_cast<void**>(&sx->vmin), pb));
   TRY_C(hipMalloc(reinterpret_cast<void**>(&sx->step), pb));
@@ -1676,6 +1861,7 @@ int vs_ivfsq8_create(vs_ivfsq8** out, int32_t d, int32_t metric, int32_t nlist,
                 ix->c_planes.info, st, true);
     ix->c_planes.try_heads_only = true;
     ix->has_planes = true;
+    if (ix->ms_mem) launch_mscan_index(kMsSq8, ix->g, ix->centroids, nullptr, ix->ms_mem, st);
   }
   TRY_C(hipStreamSynchronize(st));
   if (ix->has_planes) TRY_C(learn_planes(&ix->c_planes));
@@ -1710,7 +1896,7 @@ int vs_ivfsq8_add(vs_ivfsq8* sx, const float* x, int64_t n, const int64_t* ids, 
   const int64_t total = ix->ntotal + n;
   uint8_t* codes = nullptr;
   int64_t* new_ids = nullptr;
-  HIP_TRY(hipMalloc(reinterpret_cast<void**>(&codes), (size_t)total * g.code_size));
+  HIP_TRY(hipMalloc(reinterpret_cast<void**>(&codes), (size_t)(total + kStorePad) * g.code_size));
   if (hipMalloc(reinterpret_cast<void**>(&new_ids), (size_t)total * sizeof(int64_t)) != hipSuccess) {
     (void)hipFree(codes);
     return fail(VS_ERR_OOM, "vs_ivfsq8_add: id storage allocation failed");
@@ -1738,16 +1924,48 @@ int vs_ivfsq8_search(const vs_ivfsq8* sx, const float* q, int64_t nq, int32_t k,
   const int ppb = (npr + nsplit - 1) / nsplit;
   nsplit = (npr + ppb - 1) / ppb;
   const KnnPlan plan = knn_plan(nq, g.nlist, g.d, npr, ix->has_planes, true);
-  Carver cv;
-  const size_t o_knn = cv.take(plan.bytes);
-  const size_t o_pr = cv.take((size_t)nq * npr * sizeof(int32_t));
-  const size_t o_part = cv.take((size_t)nq * nsplit * k * sizeof(u64));
+  const MscanIndex m = mscan_index(kMsSq8, ix, sx->vmin, sx->step);
+  MscanPlan ms;
+  bool mscan = mscan_chosen(m, 0, nq, npr, k, &ms);
   ScratchUse use(ix->scratch, st);
-  if (int rc = ix->scratch.reserve(cv.off)) return rc;
+  size_t o_knn = 0, o_pr = 0, o_part = 0, o_ms = 0;
+  for (;; mscan = false) {   // (without room for the matrix-core scan's candidates: the query-major scan)
+    Carver cv;
+    o_knn = cv.take(plan.bytes);
+    o_pr = cv.take((size_t)nq * npr * sizeof(int32_t));
+    o_part = cv.take((size_t)nq * (mscan ? 1 : nsplit) * k * sizeof(u64));
+    if (mscan) o_ms = cv.take(ms.bytes);
+    const int rc = ix->scratch.reserve(cv.off);
+    if (rc == VS_OK) break;
+    if (rc != VS_ERR_OOM || !mscan) return rc;
+    (void)hipGetLastError();
+  }
   char* base = static_cast<char*>(ix->scratch.p);
   int32_t* probes = reinterpret_cast<int32_t*>(base + o_pr);
   u64* partial = reinterpret_cast<u64*>(base + o_part);
   if (int rc = coarse_select(ix, plan, base + o_knn, q, nq, npr, probes, nullptr, st)) return rc;
+  if (mscan) {
+    char* wm = base + o_ms;
+    auto part = [&](int which) {
+      launch_mscan(which, m, ms, q, probes, nullptr, 0, k, g_knn_eps_scale.load(), wm, ix->ids, out_dist, out_ids, st);
+    };
+    {
+      StageTimer t(VS_STAGE_SCAN_FIRST, st);
+      part(0);
+    }
+    {
+      StageTimer t(VS_STAGE_SCAN, st);
+      part(1);
+    }
+    StageTimer t(VS_STAGE_MERGE, st);
+    part(2);
+    const Rescan rs = mscan_rescan(m, ms, wm, partial);
+    launch_ivfsq8_scan(g.d, g.metric, q, nq, sx->vmin, sx->step, probes, npr, 1, ix->list_off, ix->codes, k, partial,
+                         ix->ids, out_dist, out_ids, st, rs);
+    launch_rescan_merge(rs, k, g.metric, ix->ids, out_dist, out_ids, st);
+    HIP_TRY(hipGetLastError());
+    return VS_OK;
+  }
   {
     StageTimer t(VS_STAGE_SCAN, st);
     launch_ivfsq8_scan(g.d, g.metric, q, nq, sx->vmin, sx->step, probes, npr, nsplit, ix->list_off,

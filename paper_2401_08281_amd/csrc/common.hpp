@@ -4,6 +4,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include "internal.hpp"
+
 typedef unsigned long long u64;
 typedef unsigned int u32;
 
@@ -495,4 +497,21 @@ __device__ __forceinline__ void block_rank_merge(const u64* __restrict__ base, i
     for (int w = 0; w < nl; ++w) total += count_less(base + w * stride, k, KEY_EMPTY);
     for (int r = total + threadIdx.x; r < k; r += nthreads) sink.put(at0 + r, KEY_EMPTY);
   }
+}
+
+// ---- work items of the query-major scans ------------------------------------------
+// What workgroup `item` of a query-major scan works on: a query and a split of its probes, or (rs.list) a piece of a
+// listed query.  none: nothing.
+struct ScanItem { int64_t qi, out; int split, ppb; bool none, piece; };
+__device__ __forceinline__ ScanItem scan_item(const Rescan& rs, int64_t item, int nsplit, int ppb, int nprobe) {
+  if (rs.list == nullptr) return {item / nsplit, item, (int)(item % nsplit), ppb, false, false};
+  const u32 s = rs.split();
+  if (item >= (int64_t)*rs.count * s) return {0, 0, 0, 0, true, false};
+  const int64_t qi = rs.list[item / s];
+  return {qi, s > 1 ? item : qi, (int)(item % s), (nprobe + (int)s - 1) / (int)s, false, s > 1};
+}
+__device__ __forceinline__ KeySink scan_sink(const Rescan& rs, const ScanItem& it, const KeySink& sink) {
+  KeySink o = sink;
+  if (it.piece) { o.keys = rs.partial; o.val = nullptr; o.id64 = nullptr; o.idx32 = nullptr; o.idmap = nullptr; }
+  return o;
 }

@@ -36,6 +36,20 @@ void launch_keys_to_probes(const u64* keys, int64_t n, int metric, int32_t* out_
                            float* out_val, hipStream_t st);
 void launch_keys_to_index32(const u64* keys, int64_t n, int32_t* out_idx, hipStream_t st);
 
+// ---- queries that a list-by-list scan leaves to the query-major one --------------------
+// The listed queries (list and their number in device memory) are scanned query by query; while they are few, in
+// `pieces` pieces each -- one query is a long scan for one workgroup -- whose k best keys go to `partial`
+// [limit][k] and are merged by launch_rescan_merge.
+struct Rescan {
+  const u32* list = nullptr;
+  const u32* count = nullptr;
+  u64* partial = nullptr;
+  u32 pieces = 1, limit = 0;
+  __device__ u32 split() const { return (u64)*count * pieces <= limit ? pieces : 1u; }
+};
+void launch_rescan_merge(const Rescan& rs, int k, int metric, const int64_t* ids, float* out_dist, int64_t* out_ids,
+                         hipStream_t st);
+
 // ---- IVF-PQ (kernels_ivfpq.hip) ----------------------------------------------
 struct IvfpqDims {
   int d, metric, nlist, M, nbits, K, dsub, code_size;
@@ -77,7 +91,9 @@ int launch_ivfpq_scan(const IvfpqDims& g, const float* q, int64_t nq, const floa
                       int nprobe, int nsplit, const int64_t* list_off, const uint8_t* codes,
                       const float* norms, const float* cnorm, const float* list_tables,
                       float* query_tables, int64_t ntotal, int k, u64* partial, u64* counter,
-                      const int64_t* ids, float* out_dist, int64_t* out_ids, hipStream_t st);
+                      const int64_t* ids, float* out_dist, int64_t* out_ids, hipStream_t st,
+                      const Rescan& rescan = Rescan());
+// (rescan, nsplit == 1: only the listed queries are scanned)
 // The wavefront-private scan (one wavefront per (query, probe split); every table form but the
 // residual tables) is used while the mean list is at most this long; it needs query_tables:
 // ivfpq_query_table_bytes() of device work space.
@@ -120,6 +136,46 @@ int launch_ivfpq_scan_listmajor(int part, const IvfpqDims& g, const float* q, in
                                 int p_first, int cap, const int64_t* list_off, const uint8_t* codes,
                                 int64_t ntotal, int k, u64* first, u64* counter, char* lm, const int64_t* ids,
                                 float* out_dist, int64_t* out_ids, hipStream_t st);
+// ---- matrix-core scan of inverted lists (kernels_mscan.hip) -----------------------
+enum { kMsPq = 0, kMsFlat = 1, kMsSq8 = 2 };
+// What the scan needs of an index (device pointers).
+struct MscanIndex {
+  int kind = kMsPq;
+  IvfpqDims g{};                       // kMsFlat, kMsSq8: d, metric, nlist (code_size bytes per vector)
+  int64_t ntotal = 0, max_list = 0;    // stored vectors, the longest list's
+  const float* centroids = nullptr;
+  const int64_t* list_off = nullptr;
+  const void* codes = nullptr;
+  const float* codebooks = nullptr;    // kMsPq
+  const void* mem = nullptr;           // launch_mscan_index's output
+  const void* units = nullptr;         // kMsPq: launch_mscan_units' output
+  const float *cnorm = nullptr, *norms = nullptr, *list_tables = nullptr;
+  const float *vmin = nullptr, *step = nullptr;   // kMsSq8
+  const u32* sigma_src = nullptr;      // kMsFlat, kMsSq8: bits of the centroids' largest squared norm
+};
+struct MscanPlan {
+  int64_t nq = 0;
+  int npr = 0, cap = 0, slots = 0;
+  u32 capcodes = 0, seg = 0, max_a = 0, max_b = 0, surv = 0;
+  size_t bytes = 0;                    // work space
+};
+// bytes of what an index keeps for the scan (0 where the shape has none), and its preparation
+size_t mscan_index_bytes(int kind, const IvfpqDims& g);
+void launch_mscan_index(int kind, const IvfpqDims& g, const float* centroids, const float* codebooks, void* out,
+                        hipStream_t st);
+size_t mscan_units_bytes(const IvfpqDims& g, int64_t ntotal);
+void launch_mscan_units(const IvfpqDims& g, const uint8_t* codes, const int64_t* list_off, int64_t ntotal, void* out,
+                        hipStream_t st);
+// plan of a search of npr probes per query, k results, cap candidates per query; false: not by this scan
+bool mscan_plan(const MscanIndex& ix, int64_t nq, int npr, int k, int cap, MscanPlan* out);
+// form: 0 residual tables (or no PQ), 1 inner product, 2 stored norms, 3 precomputed tables.  Parts 0, 1, 2 in
+// turn; then the queries of mscan_rescan are the caller's to scan query by query.
+void launch_mscan(int part, const MscanIndex& ix, const MscanPlan& p, const float* q, const int32_t* probes,
+                  const float* cdist, int form, int k, float eps_scale, char* ws, const int64_t* ids, float* out_dist,
+                  int64_t* out_ids, hipStream_t st);
+const unsigned* mscan_rescan_count(const MscanIndex& ix, const MscanPlan& p, const char* ws);
+// (partial: nq * k keys of work space)
+Rescan mscan_rescan(const MscanIndex& ix, const MscanPlan& p, const char* ws, u64* partial);
 void launch_ivfpq_merge(const u64* partial, int64_t nq, int nsplit, int k, int metric,
                         const int64_t* ids, float* out_dist, int64_t* out_ids, hipStream_t st);
 
@@ -208,7 +264,7 @@ size_t ivfflat_scan_lds_bytes(int d, int k);
 void launch_ivfflat_scan(int d, int metric, const float* q, int64_t nq, const int32_t* probes,
                          int nprobe, int nsplit, const int64_t* list_off, const float* rows, int k,
                          u64* partial, const int64_t* ids, float* out_dist, int64_t* out_ids,
-                         hipStream_t st);
+                         hipStream_t st, const Rescan& rescan = Rescan());
 
 // IVF-SQ8 (same file): 8-bit scalar-quantizer codes [n, d]; scan = IVF-Flat over reconstructions
 void launch_sq8_encode(const float* x, int64_t n, int d, const float* vmin, const float* step,
@@ -217,7 +273,8 @@ size_t ivfsq8_scan_lds_bytes(int d, int k);
 void launch_ivfsq8_scan(int d, int metric, const float* q, int64_t nq, const float* vmin,
                         const float* step, const int32_t* probes, int nprobe, int nsplit,
                         const int64_t* list_off, const uint8_t* codes, int k, u64* partial,
-                        const int64_t* ids, float* out_dist, int64_t* out_ids, hipStream_t st);
+                        const int64_t* ids, float* out_dist, int64_t* out_ids, hipStream_t st,
+                        const Rescan& rescan = Rescan());
 
 // ---- kernels_train.hip ---------------------------------------------------------
 // centroids[j] <- mean of the rows x[order[off[j] .. off[j + 1])] (float64 sum in that order, in

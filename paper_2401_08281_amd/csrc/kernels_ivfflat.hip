@@ -54,16 +54,18 @@ template <int R, int METRIC>
 __global__ __launch_bounds__(256) void ivfflat_scan_kernel(
     const float* __restrict__ q, int d, const int32_t* __restrict__ probes, int nprobe, int ppb,
     int nsplit, const int64_t* __restrict__ list_off, const float* __restrict__ rows, int k, int tot,
-    KeySink sink) {
+    KeySink sink, const Rescan again) {
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
   u64* slots = reinterpret_cast<u64*>(smem);                    // 4 * tot
   u64* bound = slots + 4 * tot;                                 // workgroup bound (+ pad)
   float* qs = reinterpret_cast<float*>(bound + 2);              // d
-  const int64_t qi = blockIdx.x / nsplit;
-  const int split = blockIdx.x % nsplit;
+  const ScanItem it = scan_item(again, blockIdx.x, nsplit, ppb, nprobe);
+  if (it.none) return;
+  const int64_t qi = it.qi;
+  const int split = it.split;
   const int wave = threadIdx.x >> 6;
-  const int p_begin = split * ppb;
-  const int p_end = min(nprobe, p_begin + ppb);
+  const int p_begin = split * it.ppb;
+  const int p_end = min(nprobe, p_begin + it.ppb);
   const bool vec = (d & 3) == 0;
 
   for (int t = threadIdx.x; t < d; t += 256) qs[t] = q[qi * d + t];
@@ -84,7 +86,7 @@ __global__ __launch_bounds__(256) void ivfflat_scan_kernel(
   }
   ws.finish();
   __syncthreads();
-  block_rank_merge(slots, tot, 4, k, sink, ((int64_t)qi * nsplit + split) * k);
+  block_rank_merge(slots, tot, 4, k, scan_sink(again, it, sink), it.out * k);
 }
 
 // The same scan with the rows staged through LDS, for d a multiple of 32.  Reading one row
@@ -98,17 +100,19 @@ template <int R, int METRIC>
 __global__ __launch_bounds__(256) void ivfflat_scan_tiled_kernel(
     const float* __restrict__ q, int d, const int32_t* __restrict__ probes, int nprobe, int ppb,
     int nsplit, const int64_t* __restrict__ list_off, const float* __restrict__ rows, int k, int tot,
-    KeySink sink) {
+    KeySink sink, const Rescan again) {
   constexpr int DC = 32, LD = 36, TR = 256;
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
   u64* slots = reinterpret_cast<u64*>(smem);                    // 4 * tot
   u64* bound = slots + 4 * tot;                                 // workgroup bound (+ pad)
   float* qs = reinterpret_cast<float*>(bound + 2);              // d
   float* tile = qs + d;                                         // 2 x TR x LD
-  const int64_t qi = blockIdx.x / nsplit;
-  const int split = blockIdx.x % nsplit;
+  const ScanItem it = scan_item(again, blockIdx.x, nsplit, ppb, nprobe);
+  if (it.none) return;
+  const int64_t qi = it.qi;
+  const int split = it.split;
   const int tid = threadIdx.x, wave = tid >> 6;
-  const int p_end = min(nprobe, split * ppb + ppb);
+  const int p_end = min(nprobe, split * it.ppb + it.ppb);
   const int r_ld = tid >> 3, c_ld = tid & 7;                    // fetch: 8 lanes per row, 32 rows per pass
 
   for (int t = tid; t < d; t += 256) qs[t] = q[qi * d + t];
@@ -151,7 +155,7 @@ __global__ __launch_bounds__(256) void ivfflat_scan_tiled_kernel(
       *reinterpret_cast<u32x4*>(tile + ((BUF) * TR + j_ * 32 + r_ld) * LD + c_ld * 4) = stg[j_]; \
   } while (0)
 
-  Pos cur = first_row_from(split * ppb);
+  Pos cur = first_row_from(split * it.ppb);
   if (cur.ok) { FETCH(cur); STASH(0); }
   __syncthreads();                                              // query, bound and the first chunk
   int buf = 0;
@@ -186,7 +190,7 @@ __global__ __launch_bounds__(256) void ivfflat_scan_tiled_kernel(
 #undef STASH
   ws.finish();
   block_sync_lds();
-  block_rank_merge(slots, tot, 4, k, sink, ((int64_t)qi * nsplit + split) * k);
+  block_rank_merge(slots, tot, 4, k, scan_sink(again, it, sink), it.out * k);
 }
 
 // ---------------------------------------------------------------------------
@@ -246,22 +250,24 @@ __global__ __launch_bounds__(256) void ivfsq8_scan_kernel(
     const float* __restrict__ q, int d, const float* __restrict__ vmin, const float* __restrict__ step,
     const int32_t* __restrict__ probes, int nprobe, int ppb, int nsplit,
     const int64_t* __restrict__ list_off, const uint8_t* __restrict__ codes, int k, int tot,
-    KeySink sink) {
+    KeySink sink, const Rescan again) {
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
   u64* slots = reinterpret_cast<u64*>(smem);
   u64* bound = slots + 4 * tot;
   float* qs = reinterpret_cast<float*>(bound + 2);              // per-query terms, 2 d floats (+ 1)
-  const int64_t qi = blockIdx.x / nsplit;
-  const int split = blockIdx.x % nsplit;
+  const ScanItem it = scan_item(again, blockIdx.x, nsplit, ppb, nprobe);
+  if (it.none) return;
+  const int64_t qi = it.qi;
+  const int split = it.split;
   const int wave = threadIdx.x >> 6;
-  const int p_end = min(nprobe, split * ppb + ppb);
+  const int p_end = min(nprobe, split * it.ppb + it.ppb);
   sq8_query_terms<METRIC>(q, qi, d, vmin, step, qs, qs + 2 * d);
   if (threadIdx.x == 0) *bound = KEY_EMPTY;
   WaveSelect<R> ws;
   ws.init(slots + wave * tot, tot, k, bound);
   __syncthreads();
   const float acc0 = METRIC == 1 ? qs[2 * d] : 0.f;
-  for (int p = split * ppb; p < p_end; ++p) {
+  for (int p = split * it.ppb; p < p_end; ++p) {
     const int l = probes[qi * nprobe + p];
     if (l < 0) continue;
     const int64_t begin = list_off[l], end = list_off[l + 1];
@@ -278,7 +284,7 @@ __global__ __launch_bounds__(256) void ivfsq8_scan_kernel(
   }
   ws.finish();
   __syncthreads();
-  block_rank_merge(slots, tot, 4, k, sink, ((int64_t)qi * nsplit + split) * k);
+  block_rank_merge(slots, tot, 4, k, scan_sink(again, it, sink), it.out * k);
 }
 
 // d a multiple of DC (64 or 32): tiles of 256 codes x DC components staged through LDS with
@@ -289,17 +295,19 @@ __global__ __launch_bounds__(256) void ivfsq8_scan_tiled_kernel(
     const float* __restrict__ q, int d, const float* __restrict__ vmin, const float* __restrict__ step,
     const int32_t* __restrict__ probes, int nprobe, int ppb, int nsplit,
     const int64_t* __restrict__ list_off, const uint8_t* __restrict__ codes, int k, int tot,
-    KeySink sink) {
+    KeySink sink, const Rescan again) {
   constexpr int LDB = DC + 16, TR = 256, LPR = DC / 16, NPASS = TR * LPR / 256;   // lanes per row, passes
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
   u64* slots = reinterpret_cast<u64*>(smem);
   u64* bound = slots + 4 * tot;
   float* qs = reinterpret_cast<float*>(bound + 2);              // per-query terms, 2 d floats (+ 4)
   unsigned char* tile = reinterpret_cast<unsigned char*>(qs + 2 * d + 4);   // 2 x TR x LDB bytes
-  const int64_t qi = blockIdx.x / nsplit;
-  const int split = blockIdx.x % nsplit;
+  const ScanItem it = scan_item(again, blockIdx.x, nsplit, ppb, nprobe);
+  if (it.none) return;
+  const int64_t qi = it.qi;
+  const int split = it.split;
   const int tid = threadIdx.x, wave = tid >> 6;
-  const int p_end = min(nprobe, split * ppb + ppb);
+  const int p_end = min(nprobe, split * it.ppb + it.ppb);
   const int r_ld = tid / LPR, c_ld = tid % LPR;
 
   sq8_query_terms<METRIC>(q, qi, d, vmin, step, qs, qs + 2 * d);
@@ -341,7 +349,7 @@ __global__ __launch_bounds__(256) void ivfsq8_scan_tiled_kernel(
       *reinterpret_cast<u32x4*>(tile + ((BUF) * TR + j_ * (256 / LPR) + r_ld) * LDB + c_ld * 16) = stg[j_]; \
   } while (0)
 
-  Pos cur = first_row_from(split * ppb);
+  Pos cur = first_row_from(split * it.ppb);
   if (cur.ok) { FETCH(cur); STASH(0); }
   __syncthreads();
   const float acc0 = METRIC == 1 ? qs[2 * d] : 0.f;
@@ -381,7 +389,7 @@ __global__ __launch_bounds__(256) void ivfsq8_scan_tiled_kernel(
 #undef STASH
   ws.finish();
   block_sync_lds();
-  block_rank_merge(slots, tot, 4, k, sink, ((int64_t)qi * nsplit + split) * k);
+  block_rank_merge(slots, tot, 4, k, scan_sink(again, it, sink), it.out * k);
 }
 
 }  // namespace
@@ -411,7 +419,7 @@ size_t ivfflat_scan_lds_bytes(int d, int k) {
 void launch_ivfflat_scan(int d, int metric, const float* q, int64_t nq, const int32_t* probes,
                          int nprobe, int nsplit, const int64_t* list_off, const float* rows, int k,
                          u64* partial, const int64_t* ids, float* out_dist, int64_t* out_ids,
-                         hipStream_t st) {
+                         hipStream_t st, const Rescan& rescan) {
   if (nq <= 0) return;
   KeySink sink;
   sink.metric = metric;
@@ -429,7 +437,7 @@ void launch_ivfflat_scan(int d, int metric, const float* q, int64_t nq, const in
       (void)hipFuncSetAttribute(reinterpret_cast<const void*>(kern),                             \
                                 hipFuncAttributeMaxDynamicSharedMemorySize, (int)shmem);         \
     hipLaunchKernelGGL(kern, grid, block, shmem, st, q, d, probes, nprobe, ppb, nsplit, list_off, \
-                       rows, k, tot, sink);                                                      \
+                       rows, k, tot, sink, rescan);                                                      \
   } while (0)
   switch (select_regs_for_slots(tot)) {
     case 2: if (metric == 0) GO(2, 0); else GO(2, 1); break;
@@ -457,7 +465,8 @@ size_t ivfsq8_scan_lds_bytes(int d, int k) {
 void launch_ivfsq8_scan(int d, int metric, const float* q, int64_t nq, const float* vmin,
                         const float* step, const int32_t* probes, int nprobe, int nsplit,
                         const int64_t* list_off, const uint8_t* codes, int k, u64* partial,
-                        const int64_t* ids, float* out_dist, int64_t* out_ids, hipStream_t st) {
+                        const int64_t* ids, float* out_dist, int64_t* out_ids, hipStream_t st,
+                        const Rescan& rescan) {
   if (nq <= 0) return;
   KeySink sink;
   sink.metric = metric;
@@ -477,7 +486,7 @@ void launch_ivfsq8_scan(int d, int metric, const float* q, int64_t nq, const flo
       (void)hipFuncSetAttribute(reinterpret_cast<const void*>(kern),                             \
                                 hipFuncAttributeMaxDynamicSharedMemorySize, (int)shmem);         \
     hipLaunchKernelGGL(kern, grid, block, shmem, st, q, d, vmin, step, probes, nprobe, ppb, nsplit, \
-                       list_off, codes, k, tot, sink);                                           \
+                       list_off, codes, k, tot, sink, rescan);                                           \
   } while (0)
   switch (select_regs_for_slots(tot)) {
     case 2: if (metric == 0) GO(2, 0); else GO(2, 1); break;

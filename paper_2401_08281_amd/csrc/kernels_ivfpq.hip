@@ -263,7 +263,7 @@ __global__ __launch_bounds__(256) void ivfpq_scan_kernel(
     const int32_t* __restrict__ probes, const float* __restrict__ cdist, int nprobe, int ppb,
     int nsplit, const int64_t* __restrict__ list_off, const uint8_t* __restrict__ codes,
     const float* __restrict__ norms, const float* __restrict__ cnorm, int cs, int k, int tot,
-    KeySink sink) {
+    KeySink sink, const Rescan again) {
   // mode 0: L2, one table of squared residual distances per (query, list); mode 1: inner
   // product, one table per query, cdist = <q, c_l>; mode 2: L2 through stored norms (Sec. 4.3):
   // one table -2 <q_m, T_m[j]> per query; per list |q|^2 - 2 <q, c_l> = |q - c_l|^2 - |c_l|^2,
@@ -279,12 +279,14 @@ __global__ __launch_bounds__(256) void ivfpq_scan_kernel(
       (u32)(uintptr_t)((__attribute__((address_space(3))) unsigned char*)smem) == 0u &&
       M * K * (int)sizeof(float) <= 65536;
 
-  const int64_t qi = blockIdx.x / nsplit;
-  const int split = blockIdx.x % nsplit;
+  const ScanItem it = scan_item(again, blockIdx.x, nsplit, ppb, nprobe);
+  if (it.none) return;
+  const int64_t qi = it.qi;
+  const int split = it.split;
   const int wave = threadIdx.x >> 6, lane = lane_id();
   const float* __restrict__ qv = q + qi * d;
-  const int p_begin = split * ppb;
-  const int p_end = min(nprobe, p_begin + ppb);
+  const int p_begin = split * it.ppb;
+  const int p_end = min(nprobe, p_begin + it.ppb);
 
   WaveSelect<R> ws;
   ws.init(slots + wave * tot, tot, k);
@@ -369,7 +371,7 @@ __global__ __launch_bounds__(256) void ivfpq_scan_kernel(
   }
   ws.finish();
   __syncthreads();
-  block_rank_merge(slots, tot, 4, k, sink, ((int64_t)qi * nsplit + split) * k);
+  block_rank_merge(slots, tot, 4, k, scan_sink(again, it, sink), it.out * k);
 }
 
 // ---------------------------------------------------------------------------
@@ -388,7 +390,7 @@ __global__ __launch_bounds__(256) void ivfpq_scan_pipe_kernel(
     const int32_t* __restrict__ probes, const float* __restrict__ cdist, int nprobe, int ppb,
     int nsplit, const int64_t* __restrict__ list_off, const uint8_t* __restrict__ codes,
     const float* __restrict__ norms, const float* __restrict__ cnorm, int64_t ntotal, int k, int tot,
-    KeySink sink) {
+    KeySink sink, const Rescan again) {
   constexpr int K = 1 << NBITS;
   constexpr int MPW = NBITS == 8 ? 16 : 32;                      // sub-quantizers per 16 code bytes
   const int metric = mode == 1 ? 1 : 0;                         // ordering of the keys
@@ -406,12 +408,14 @@ __global__ __launch_bounds__(256) void ivfpq_scan_pipe_kernel(
   u64* slots = reinterpret_cast<u64*>(                          // 4 * tot
       (reinterpret_cast<uintptr_t>(s_list + ppb) + 7) & ~(uintptr_t)7);
 
-  const int64_t qi = blockIdx.x / nsplit;
-  const int split = blockIdx.x % nsplit;
+  const ScanItem it = scan_item(again, blockIdx.x, nsplit, ppb, nprobe);
+  if (it.none) return;
+  const int64_t qi = it.qi;
+  const int split = it.split;
   const int tid = threadIdx.x, wave = tid >> 6;
   const float* __restrict__ qv = q + qi * d;
-  const int p_begin = split * ppb;
-  const int np = ntotal > 0 ? max(0, min(nprobe, p_begin + ppb) - p_begin) : 0;
+  const int p_begin = split * it.ppb;
+  const int np = ntotal > 0 ? max(0, min(nprobe, p_begin + it.ppb) - p_begin) : 0;
   const int cs = 16 * W16;
 
   WaveSelect<R> ws;
@@ -518,7 +522,7 @@ __global__ __launch_bounds__(256) void ivfpq_scan_pipe_kernel(
   }
   ws.finish();
   __syncthreads();
-  block_rank_merge(slots, tot, 4, k, sink, ((int64_t)qi * nsplit + split) * k);
+  block_rank_merge(slots, tot, 4, k, scan_sink(again, it, sink), it.out * k);
 }
 
 // ---------------------------------------------------------------------------
@@ -666,11 +670,8 @@ void ivfpq_scan_bank_kernel(
     const int64_t* __restrict__ list_off, const uint8_t* __restrict__ codes,
     const float* __restrict__ norms, const float* __restrict__ cnorm,
     const float* __restrict__ list_tables, int64_t ntotal, int k, int tot,
-    KeySink sink, unsigned long long* __restrict__ next_item, const u32* __restrict__ item_list,
-    const u32* __restrict__ item_count) {
-  // item_list / item_count: null, or (nsplit = 1 only) the queries to scan and how many they are,
-  // both in device memory: the second launch after a list-major scan, for the queries whose
-  // candidate buffer overflowed (usually none: every workgroup then leaves at its first look)
+    KeySink sink, unsigned long long* __restrict__ next_item, const Rescan again) {
+  // again: the queries that a list-by-list scan left (usually none: every workgroup then leaves at its first look)
   // METRIC 0: L2 with a table per (query, list); 1: inner product; 2: L2 through stored norms
   // (one table -2 <q_m, T_m[j]> per query; per list cdist - |c_l|^2 = |q|^2 - 2 <q, c_l>;
   // + |x'|^2 per code); 3: L2 with the table of a (query, list) pair formed as a per-query term
@@ -704,6 +705,7 @@ void ivfpq_scan_bank_kernel(
   unsigned long long* s_item = reinterpret_cast<unsigned long long*>(bound + 1);
   // (the kernel has no static LDS, so its dynamic LDS -- the tables first -- starts at LDS address
   // 0 and a table offset is an LDS address: the launcher checks this)
+  if (again.list != nullptr && *again.count == 0u) return;
   const int tid = threadIdx.x, wave = tid >> 6;
   const int m_own = tid & (M - 1), jg = tid / M;                // table build: codewords jg * EPL + i of m_own
   const int rep0 = jg & (REP - 1);                              // this lane's copy (build: the first it stores)
@@ -750,11 +752,12 @@ void ivfpq_scan_bank_kernel(
     if (tid == 0) *s_item = atomicAdd(next_item, 1ull);
     block_sync_lds();
     const int64_t item = (int64_t)*s_item;
-    if (item >= (item_count != nullptr ? (int64_t)*item_count : nitems)) break;
-    const int64_t qi = item_list != nullptr ? (int64_t)item_list[item] : item / nsplit;
-    const int split = (int)(item % nsplit);
-    const int p_begin = split * ppb;
-    const int np = ntotal > 0 ? min(nprobe, p_begin + ppb) - p_begin : 0;
+    if (again.list == nullptr && item >= nitems) break;
+    const ScanItem it = scan_item(again, item, nsplit, ppb, nprobe);
+    if (it.none) break;
+    const int64_t qi = it.qi;
+    const int p_begin = it.split * it.ppb;
+    const int np = ntotal > 0 ? max(0, min(nprobe, p_begin + it.ppb) - p_begin) : 0;
     float qm[DSUB];                                             // this lane's slice of the query
 #pragma unroll
     for (int u = 0; u < DSUB; ++u) qm[u] = q[qi * D + m_own * DSUB + u];
@@ -1001,7 +1004,7 @@ void ivfpq_scan_bank_kernel(
     }
     ws.finish();
     block_sync_lds();
-    block_rank_merge(slots, tot, NW, k, sink, (item_list != nullptr ? qi : item) * k);
+    block_rank_merge(slots, tot, NW, k, scan_sink(again, it, sink), it.out * k);
     block_sync_lds();   // the slots have been read; the next item may reset them
   }
 }
@@ -1598,18 +1601,12 @@ __global__ __launch_bounds__(MODE == 3 ? 64 : 64 * kWaveScanShare) void ivfpq_sc
 // (value, stored id).  Storage position -> id goes through the ids array
 // (Sec. 6.1: IVF indexes store the 64-bit id next to each code).
 template <int R>
-__global__ __launch_bounds__(64) void ivfpq_merge_kernel(const u64* __restrict__ partial,
-                                                         int nsplit, int k, int tot, int metric,
-                                                         const int64_t* __restrict__ ids,
-                                                         float* __restrict__ out_dist,
-                                                         int64_t* __restrict__ out_ids) {
-  extern __shared__ u64 mslots[];
-  const int64_t qi = blockIdx.x;
+__device__ __forceinline__ void merge_partial(const u64* __restrict__ src, int n, u64* mslots, int64_t qi, int k, int tot,
+                                              int metric, const int64_t* __restrict__ ids,
+                                              float* __restrict__ out_dist, int64_t* __restrict__ out_ids) {
   const int lane = lane_id();
   WaveSelect<R> ws;
   ws.init(mslots, tot, k);
-  const u64* __restrict__ src = partial + qi * (int64_t)nsplit * k;
-  const int n = nsplit * k;
   for (int j0 = 0; j0 < n; j0 += VS_WAVE) {
     const int j = j0 + lane;
     const u64 key = j < n ? src[j] : KEY_EMPTY;
@@ -1624,6 +1621,26 @@ __global__ __launch_bounds__(64) void ivfpq_merge_kernel(const u64* __restrict__
     out_dist[qi * k + j] = v;
     out_ids[qi * k + j] = id;
   }
+}
+template <int R>
+__global__ __launch_bounds__(64) void ivfpq_merge_kernel(const u64* __restrict__ partial,
+                                                         int nsplit, int k, int tot, int metric,
+                                                         const int64_t* __restrict__ ids,
+                                                         float* __restrict__ out_dist,
+                                                         int64_t* __restrict__ out_ids) {
+  extern __shared__ u64 mslots[];
+  const int64_t qi = blockIdx.x;
+  merge_partial<R>(partial + qi * (int64_t)nsplit * k, nsplit * k, mslots, qi, k, tot, metric, ids, out_dist, out_ids);
+}
+// the same for the queries scanned again in pieces
+template <int R>
+__global__ __launch_bounds__(64) void rescan_merge_kernel(const Rescan rs, int k, int tot, int metric,
+                                                          const int64_t* __restrict__ ids, float* __restrict__ out_dist,
+                                                          int64_t* __restrict__ out_ids) {
+  extern __shared__ u64 mslots[];
+  if (blockIdx.x >= *rs.count || rs.split() == 1u) return;
+  merge_partial<R>(rs.partial + (int64_t)blockIdx.x * rs.pieces * k, (int)rs.pieces * k, mslots, (int64_t)rs.list[blockIdx.x], k,
+                   tot, metric, ids, out_dist, out_ids);
 }
 
 }  // namespace
@@ -1843,8 +1860,7 @@ static int launch_scan_bank(const IvfpqDims& g, const float* q, int64_t nq, cons
                              int nprobe, int ppb, int nsplit, const int64_t* list_off,
                              const uint8_t* codes, const float* norms, const float* cnorm,
                              const float* list_tables, int64_t ntotal, int k, int tot, KeySink sink,
-                             u64* counter, hipStream_t st, const u32* item_list = nullptr,
-                             const u32* item_count = nullptr) {
+                             u64* counter, hipStream_t st, const Rescan& rescan = Rescan()) {
   const size_t shmem = bank_scan_lds_bytes(tot, ppb);
   constexpr int NT = kBankThreads;
   auto kern = &ivfpq_scan_bank_kernel<M, DSUB, METRIC, R, NT>;
@@ -1862,7 +1878,7 @@ static int launch_scan_bank(const IvfpqDims& g, const float* q, int64_t nq, cons
   launch_fill_u64(counter, 1, 0ull, st);
   hipLaunchKernelGGL(kern, dim3((unsigned)grid), dim3(NT), shmem, st, q, centroids, codebooks,
                      probes, cdist, nprobe, ppb, nsplit, nitems, list_off, codes, norms, cnorm, list_tables,
-                     ntotal, k, tot, sink, reinterpret_cast<unsigned long long*>(counter), item_list, item_count);
+                     ntotal, k, tot, sink, reinterpret_cast<unsigned long long*>(counter), rescan);
   return 0;
 }
 
@@ -1873,10 +1889,10 @@ static int launch_scan_bank_any(const IvfpqDims& g, const float* q, int64_t nq,
                                  int nsplit, const int64_t* list_off, const uint8_t* codes,
                                  const float* norms, const float* cnorm, const float* list_tables,
                                  int mode, int64_t ntotal, int k, int tot, KeySink sink, u64* counter,
-                                 hipStream_t st) {
+                                 hipStream_t st, const Rescan& rescan) {
 #define GO(MET, RR)                                                                               \
   return launch_scan_bank<M, DSUB, MET, RR>(g, q, nq, centroids, codebooks, probes, cdist, nprobe, ppb,  \
-                                            nsplit, list_off, codes, norms, cnorm, list_tables, ntotal, k, tot, sink, counter, st)
+                                            nsplit, list_off, codes, norms, cnorm, list_tables, ntotal, k, tot, sink, counter, st, rescan)
   const int r = tot <= 128 ? 2 : (tot <= 256 ? 4 : 0);   // register-sort width covering the slots
   if (mode == 1)      { if (r == 2) GO(1, 2); else if (r == 4) GO(1, 4); else GO(1, 0); }
   else if (mode == 2) { if (r == 2) GO(2, 2); else if (r == 4) GO(2, 4); else GO(2, 0); }
@@ -1928,14 +1944,14 @@ static void launch_scan_pipe(const IvfpqDims& g, const float* q, int64_t nq,
                              const int32_t* probes, const float* cdist, int nprobe, int ppb,
                              int nsplit, const int64_t* list_off, const uint8_t* codes,
                              const float* norms, const float* cnorm, int mode, int64_t ntotal, int k,
-                             int tot, size_t shmem, KeySink sink, hipStream_t st) {
+                             int tot, size_t shmem, KeySink sink, hipStream_t st, const Rescan& rescan) {
   auto kern = &ivfpq_scan_pipe_kernel<NBITS, R, W16>;
   if (shmem > 48 * 1024)
     (void)hipFuncSetAttribute(reinterpret_cast<const void*>(kern),
                               hipFuncAttributeMaxDynamicSharedMemorySize, (int)shmem);
   hipLaunchKernelGGL(kern, dim3((unsigned)(nq * nsplit)), dim3(256), shmem, st, q, g.d, mode,
                      g.M, g.dsub, centroids, codebooks, probes, cdist, nprobe, ppb, nsplit, list_off,
-                     codes, norms, cnorm, ntotal, k, tot, sink);
+                     codes, norms, cnorm, ntotal, k, tot, sink, rescan);
 }
 
 template <int NBITS, int R>
@@ -1944,14 +1960,14 @@ static void launch_scan_generic(const IvfpqDims& g, const float* q, int64_t nq,
                                 const int32_t* probes, const float* cdist, int nprobe, int ppb,
                                 int nsplit, const int64_t* list_off, const uint8_t* codes,
                                 const float* norms, const float* cnorm, int mode, int k, int tot,
-                                size_t shmem, KeySink sink, hipStream_t st) {
+                                size_t shmem, KeySink sink, hipStream_t st, const Rescan& rescan) {
   auto kern = &ivfpq_scan_kernel<NBITS, R>;
   if (shmem > 48 * 1024)
     (void)hipFuncSetAttribute(reinterpret_cast<const void*>(kern),
                               hipFuncAttributeMaxDynamicSharedMemorySize, (int)shmem);
   hipLaunchKernelGGL(kern, dim3((unsigned)(nq * nsplit)), dim3(256), shmem, st, q, g.d, mode,
                      g.M, g.dsub, centroids, codebooks, probes, cdist, nprobe, ppb, nsplit, list_off,
-                     codes, norms, cnorm, g.code_size, k, tot, sink);
+                     codes, norms, cnorm, g.code_size, k, tot, sink, rescan);
 }
 
 int launch_ivfpq_scan(const IvfpqDims& g, const float* q, int64_t nq, const float* centroids,
@@ -1959,7 +1975,7 @@ int launch_ivfpq_scan(const IvfpqDims& g, const float* q, int64_t nq, const floa
                       int nprobe, int nsplit, const int64_t* list_off, const uint8_t* codes,
                       const float* norms, const float* cnorm, const float* list_tables,
                       float* query_tables, int64_t ntotal, int k, u64* partial, u64* counter,
-                      const int64_t* ids, float* out_dist, int64_t* out_ids, hipStream_t st) {
+                      const int64_t* ids, float* out_dist, int64_t* out_ids, hipStream_t st, const Rescan& rescan) {
   if (nq <= 0) return 0;
   // table form: 1 inner product; 2 L2 through the stored norms (norms non-null; cnorm = the
   // centroids' squared norms); 0 L2 with one table of squared residual distances per (query, list)
@@ -1975,7 +1991,7 @@ int launch_ivfpq_scan(const IvfpqDims& g, const float* q, int64_t nq, const floa
   const size_t shmem = (size_t)4 * tot * sizeof(u64) + (size_t)g.M * g.K * sizeof(float) +
                        (size_t)(g.d + 2) * sizeof(float);
   if (shmem + 64 > 160 * 1024) return -1;
-  if (mode != 0 && query_tables && ivfpq_wave_scan_applies(g, ntotal)) {
+  if (mode != 0 && query_tables && !rescan.list && ivfpq_wave_scan_applies(g, ntotal)) {
     if (wave_scan_lds_bytes(g, mode, select_slots_for_k(k), ppb) > 160 * 1024) return -1;
 #define WAVE(MM, DS, MODE)                                                                             \
   return launch_scan_wave<MM, DS, MODE>(g, q, nq, codebooks, query_tables, list_tables, probes, cdist, nprobe, \
@@ -1990,7 +2006,8 @@ int launch_ivfpq_scan(const IvfpqDims& g, const float* q, int64_t nq, const floa
 #define BANK(MM, DS)                                                                              \
   if (g.M == MM && g.dsub == DS) {                                                                \
     return launch_scan_bank_any<MM, DS>(g, q, nq, centroids, codebooks, probes, cdist, nprobe, ppb, \
-                                        nsplit, list_off, codes, norms, cnorm, list_tables, mode, ntotal, k, btot, sink, counter, st); \
+                                        nsplit, list_off, codes, norms, cnorm, list_tables, mode, ntotal, k, btot, sink, counter, st, \
+                                        rescan); \
   }
     BANK(16, 8)   // PQ16x8 on d = 128
     BANK(32, 3)   // PQ32x8 on d = 96
@@ -2004,7 +2021,7 @@ int launch_ivfpq_scan(const IvfpqDims& g, const float* q, int64_t nq, const floa
   if ((g.code_size == 16 || g.code_size == 32 || g.code_size == 64) && pipe_shmem + 64 <= 160 * 1024) {
 #define PIPE3(NB, RR, WW)                                                                        \
   launch_scan_pipe<NB, RR, WW>(g, q, nq, centroids, codebooks, probes, cdist, nprobe, ppb, nsplit, \
-                               list_off, codes, norms, cnorm, mode, ntotal, k, tot, pipe_shmem, sink, st)
+                               list_off, codes, norms, cnorm, mode, ntotal, k, tot, pipe_shmem, sink, st, rescan)
 #define PIPE2(NB, RR)                                                                            \
   do {                                                                                           \
     if (g.code_size == 16) PIPE3(NB, RR, 1);                                                     \
@@ -2019,7 +2036,7 @@ int launch_ivfpq_scan(const IvfpqDims& g, const float* q, int64_t nq, const floa
   }
 #define GEN(NB, RR)                                                                              \
   launch_scan_generic<NB, RR>(g, q, nq, centroids, codebooks, probes, cdist, nprobe, ppb, nsplit, \
-                              list_off, codes, norms, cnorm, mode, k, tot, shmem, sink, st)
+                              list_off, codes, norms, cnorm, mode, k, tot, shmem, sink, st, rescan)
   if (g.nbits == 8) { if (r == 2) GEN(8, 2); else if (r == 4) GEN(8, 4); else GEN(8, 0); }
   else              { if (r == 2) GEN(4, 2); else if (r == 4) GEN(4, 4); else GEN(4, 0); }
 #undef GEN
@@ -2136,8 +2153,11 @@ static int launch_listmajor_t(int part, const IvfpqDims& g, const float* q, int6
   KeySink fin;
   fin.metric = 0; fin.keys = nullptr; fin.val = out_dist; fin.id64 = out_ids; fin.idx32 = nullptr; fin.idmap = ids;
   const int rb = tot_b <= 128 ? 2 : (tot_b <= 256 ? 4 : 0);
+  Rescan left;
+  left.list = rlist;
+  left.count = rcount;
 #define BANK_B(RR) launch_scan_bank<M, DSUB, 0, RR>(g, q, nq, centroids, codebooks, probes, cdist, nprobe, nprobe, 1, \
-                                                    list_off, codes, nullptr, nullptr, nullptr, ntotal, k, tot_b, fin, counter, st, rlist, rcount)
+                                                    list_off, codes, nullptr, nullptr, nullptr, ntotal, k, tot_b, fin, counter, st, left)
   return rb == 2 ? BANK_B(2) : (rb == 4 ? BANK_B(4) : BANK_B(0));
 #undef BANK_B
 }
@@ -2165,6 +2185,19 @@ int launch_ivfpq_scan_listmajor(int part, const IvfpqDims& g, const float* q, in
 // where the number of queries scanned again by the last part lies (one u32, device memory)
 const unsigned* ivfpq_listmajor_rescan_count(const IvfpqDims& g, int64_t nq, int nprobe, int cap, const char* lm) {
   return reinterpret_cast<const unsigned*>(lm + lm_layout(nq, nprobe, g.nlist, cap).o_rcount);
+}
+
+void launch_rescan_merge(const Rescan& rs, int k, int metric, const int64_t* ids, float* out_dist, int64_t* out_ids,
+                         hipStream_t st) {
+  const unsigned most = rs.limit / rs.pieces;      // listed queries that are scanned in pieces, at most
+  if (rs.pieces < 2 || most < 1) return;
+  const int tot = select_slots_for_k(k);
+  const size_t shmem = (size_t)tot * sizeof(u64);
+  switch (select_regs_for_slots(tot)) {
+    case 2: hipLaunchKernelGGL((rescan_merge_kernel<2>), dim3(most), dim3(64), shmem, st, rs, k, tot, metric, ids, out_dist, out_ids); break;
+    case 4: hipLaunchKernelGGL((rescan_merge_kernel<4>), dim3(most), dim3(64), shmem, st, rs, k, tot, metric, ids, out_dist, out_ids); break;
+    default: hipLaunchKernelGGL((rescan_merge_kernel<0>), dim3(most), dim3(64), shmem, st, rs, k, tot, metric, ids, out_dist, out_ids); break;
+  }
 }
 
 void launch_ivfpq_merge(const u64* partial, int64_t nq, int nsplit, int k, int metric,
