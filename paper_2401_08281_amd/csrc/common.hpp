@@ -387,6 +387,51 @@ __device__ __forceinline__ float canon_row_padded(const float* __restrict__ qs, 
   return METRIC != 0 && (d & 31) != 0 ? v + 0.f : v;
 }
 
+// canon_row_padded with 32 dimensions requested before the first of them is used (same chain).  For gathers of rows
+// that few lanes share: read four dimensions at a time, every one of the eight reads of a 128-byte line waits by itself.
+template <int METRIC>
+__device__ __forceinline__ float canon_row_ahead(const float* __restrict__ qs, const float* __restrict__ b,
+                                                 int d, bool vec) {
+  float acc = 0.f;
+  int t = 0;
+  if (vec) {
+    for (; t + 32 <= d; t += 32) {
+      float4 r[8];
+#pragma unroll
+      for (int i = 0; i < 8; ++i) r[i] = *reinterpret_cast<const float4*>(b + t + 4 * i);
+      __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+      for (int i = 0; i < 8; ++i) {
+        const float bb[4] = {r[i].x, r[i].y, r[i].z, r[i].w};
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+          const float a = qs[t + 4 * i + u];
+          if (METRIC == 0) { const float diff = a - bb[u]; acc = __builtin_fmaf(diff, diff, acc); }
+          else acc = __builtin_fmaf(a, bb[u], acc);
+        }
+      }
+    }
+  } else {
+    for (; t + 16 <= d; t += 16) {
+      float r[16];
+#pragma unroll
+      for (int i = 0; i < 16; ++i) r[i] = b[t + i];
+      __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+      for (int i = 0; i < 16; ++i) {
+        const float a = qs[t + i];
+        if (METRIC == 0) { const float diff = a - r[i]; acc = __builtin_fmaf(diff, diff, acc); }
+        else acc = __builtin_fmaf(a, r[i], acc);
+      }
+    }
+  }
+  for (; t < d; ++t) {
+    if (METRIC == 0) { const float diff = qs[t] - b[t]; acc = __builtin_fmaf(diff, diff, acc); }
+    else acc = __builtin_fmaf(qs[t], b[t], acc);
+  }
+  return METRIC != 0 && (d & 31) != 0 ? acc + 0.f : acc;
+}
+
 // The same value for 64 rows at once, one per lane of a wavefront, with memory read in runs of
 // 128 bytes (d a multiple of 32): per chunk of 32 dimensions eight lanes fetch the 128 bytes
 // of one row (8 rows per load instruction), the chunk goes through a wavefront-private LDS

@@ -930,7 +930,9 @@ __global__ __launch_bounds__(256) void tau_kernel(const float* __restrict__ mini
 // ---------------------------------------------------------------------------
 // Exact re-rank: one wavefront per row of A.
 // ---------------------------------------------------------------------------
-template <int R, int METRIC>
+// R: 64 * R slots for the listed columns; RF: the kp re-ranked ones fit 64 * RF (a sort of 64 values is less than half of
+// one of 128).
+template <int R, int RF, int METRIC>
 __global__ __launch_bounds__(64) void rerank_kernel(
     const u64* __restrict__ shortlist, const int* __restrict__ cnt, const float* __restrict__ tau,
     int nsplit, int cap, int kp, const float* __restrict__ A,
@@ -945,11 +947,23 @@ __global__ __launch_bounds__(64) void rerank_kernel(
   const bool vec = (d & 3) == 0;
   for (int t = lane; t < d; t += VS_WAVE) qs[t] = A[row * d + t];
 
-  // global kp best approximate keys of this row
+  // global kp best approximate keys of this row.  Sorting is most of this kernel's instructions, so a row whose lists
+  // hold no more than the slots (nearly every one) collects them as they are and sorts once; a longer one keeps
+  // the best as they come in, a sort whenever the slots are full.
   WaveSelect<R> ws;
   ws.init(slots, 64 * R, kp);
-  bool truncated = false;
-  int64_t total = 0;                                            // columns with m <= tau
+  int most = 0, sum = 0;
+  for (int sp = lane; sp < nsplit; sp += VS_WAVE) {
+    const int c = cnt[row * nsplit + sp];
+    most = max(most, c);
+    sum += min(c, 1 << 20);
+  }
+#pragma unroll
+  for (int off = 1; off < 64; off <<= 1) { most = max(most, __shfl_xor(most, off)); sum += __shfl_xor(sum, off); }
+  const bool truncated = most > cap;                            // a list was
+  const bool few = sum <= 64 * R && !truncated;
+  int64_t total = sum;                                          // columns with m <= tau
+  int held = 0;
   // (eight splits at a time: their counts and the first 64 slots of their lists -- cap >= 64,
   // the slots exist whether filled or not -- are requested together, one round trip instead
   // of sixteen; a handful of rows against many splits is bound by exactly these)
@@ -966,9 +980,13 @@ __global__ __launch_bounds__(64) void rerank_kernel(
     for (int u = 0; u < 8; ++u) {
       if (sp0 + u >= nsplit) break;
       const u64* __restrict__ src = shortlist + (row * nsplit + sp0 + u) * (int64_t)cap;
-      truncated = truncated || listed[u] > cap;
-      total += listed[u];
       const int n = min(listed[u], cap);
+      if (few) {
+        if (lane < n) ws.s[held + lane] = first[u];
+        for (int j = VS_WAVE + lane; j < n; j += VS_WAVE) ws.s[held + j] = src[j];
+        held += n;
+        continue;
+      }
       if (n > 0) ws.push(lane < n && first[u] != KEY_EMPTY, first[u]);
       for (int j0 = VS_WAVE; j0 < n; j0 += VS_WAVE) {
         const int j = j0 + lane;
@@ -977,25 +995,75 @@ __global__ __launch_bounds__(64) void rerank_kernel(
       }
     }
   }
-  ws.finish();
+  if (few) ws.cnt = held - kp;                                  // (trim() sorts the first k + cnt slots)
+  if (few) ws.trim(); else ws.finish();
   const u64 tkey = ws.s[kp - 1];                                // kp-th best approximate key
 
-  // canon value of every shortlisted row, then an exact sort
-  // (one row per lane, R rows in flight per lane: staging 64 rows at a time through an LDS
-  // tile, as the refinement kernel does, measured slower here)
-  u64 v[R];
+  const float na2 = Anorm[row], nb2 = __uint_as_float(Binfo->max_norm_bits);
+  // Integer data exactly representable in bf16: every number the sweeps and this kernel
+  // form is a multiple of 1/2 below 2^23 in magnitude, hence exact, when N = max|q|^2 +
+  // max|x|^2 satisfies 1.5 N < 2^23 (|<q,x>| <= N / 2, |tau| / 2 <= N), or N < 2^23 when
+  // no value is negative (0 <= <q,x>, -|q|^2 <= tau <= |x|^2).
+  const float nsum = __uint_as_float(Ainfo->max_norm_bits) + nb2;
+  const bool nonneg = Ainfo->all_nonneg && Binfo->all_nonneg;
+  const bool exact = Ainfo->all_int && Binfo->all_int && Ainfo->all_bf16 && Binfo->all_bf16 &&
+                     (nonneg ? nsum < 8388608.f : nsum < 5592405.f);
+  const bool inexact = !(Ainfo->all_bf16 && Binfo->all_bf16);
+  // |approx - canon| <= eps: bf16 head/tail split drops terms below 2^-15 |q||x| per product;
+  // fp32 accumulation and the canon chain each stay below d 2^-22 (|q|^2 + |x|^2); the
+  // collect sweep's own rounding (a few ulps of |tau| / 2 + |<q,x>|) is the last term.
+  // fp16 heads alone: qh_i = q_i + a_i with |a_i| <= u |q_i| + s, u = 2^-11 (rounding to 11
+  // significant bits) and s = 2^-25 (half the spacing of fp16 subnormals), likewise x, so
+  // |<q,x> - <qh,xh>| <= (2u + u^2) |q||x| + s (1 + u) sqrt(d) (|q| + |x|) + d s^2; with
+  // |q||x| <= N / 2 and |q| + |x| <= sqrt(2 N), N = |q|^2 + |x|^2, twice that on the distance:
+  // 9.78e-4 N + 6.0e-8 sqrt(2 d N) + 1.8e-15 d (inner product: the value is the product itself,
+  // half of each).
+  const bool f16 = precision_variant(Ainfo, Binfo, k == 1 ? 1 : 2, false) == 3;
+  const float nn = na2 + nb2;
+  constexpr float F16_S = METRIC == 0 ? 1.f : 0.5f;
+  const float split_term = !inexact ? 0.f : (f16 ? F16_S * 9.78e-4f : 6.2e-5f);
+  const float coef = split_term + (float)d * 4.8e-7f + 2e-6f;
+  const float abs_term = f16 ? F16_S * (6.0e-8f * sqrtf(2.f * (float)d * nn) + 1.8e-15f * (float)d) : 0.f;
+  const float eps = eps_scale * (coef * nn + abs_term);
+
+  // The listed values are formed from accumulators that started at tau: whole numbers too where it is one (that of a
+  // row with fewer than kp group minima is stretched and mostly is none) within the bounds above.
+  const float tau_v = tau[row];
+  const bool as_listed = METRIC == 0 && exact && tau_v == rintf(tau_v) && __builtin_fabsf(tau_v) <= (nonneg ? nsum : 2.f * nsum);
+
+  // Canon value of the shortlisted rows that can be among the k best, then an exact sort.  The gathers of rows (48 of
+  // 3 KB for each of 10,000 queries: 1.5 GB from the Infinity Cache) are what this kernel takes its time for, so
+  //   - nothing is read where the approximate values are the canon values (as_listed; squared distances only: the
+  //     sign of a zero product is the chain's);
+  //   - a row whose approximate value is beyond the k-th best by more than twice the error is left out: the k rows up
+  //     to there have canon values within one error of it.  (0.1 eps for the rounding of this test itself, which is
+  //     below 3e-7 of N and eps above 1.6e-5 N.)  An error that is not finite leaves nothing out.
+  // One row per lane, the next 64 behind them.
+  // Re-ranking for 10,000 queries with the single sort above: 16 of 4096 integer rows, d = 128, 51.6 -> 21.1 us; 64 of
+  // 65536 unit vectors, d = 96, 91 -> 71; 32 of 16384, d = 768, inner product, 267 -> 195.
+  // (staging 64 rows at a time through an LDS tile, as the refinement kernel does, measured slower here)
+  // (1e-36 d: products and sums below the smallest normal number, which the matrix cores may drop)
+  const float slack = 2.1f * fmaxf(eps_scale, 1.f) * (coef * nn + abs_term) + 1e-36f * (float)d;
+  const float cut = key_value(ws.s[k - 1], METRIC) + (METRIC == 0 ? slack : -slack);
+  u64 v[RF];
 #pragma unroll
-  for (int r = 0; r < R; ++r) {
-    const int e = lane * R + r;
+  for (int r = 0; r < RF; ++r) {
+    const int e = lane + 64 * r;
     const u64 ak = e < kp ? ws.s[e] : KEY_EMPTY;
-    if (ak == KEY_EMPTY) { v[r] = KEY_EMPTY; continue; }
+    v[r] = KEY_EMPTY;
+    if (ak == KEY_EMPTY) continue;
     const u32 idx = key_index(ak);
-    v[r] = make_key(canon_row_padded<METRIC>(qs, B + (int64_t)idx * d, d, vec), idx, METRIC);
+    const float approx = key_value(ak, METRIC);
+    if (as_listed) { v[r] = ak; continue; }
+    if (METRIC == 0 ? approx > cut : approx < cut) continue;
+    v[r] = make_key(canon_row_ahead<METRIC>(qs, B + (int64_t)idx * d, d, vec), idx, METRIC);
   }
-  wave_sort_regs(v);
-  wave_lds_sync();
+  if (!as_listed) {                                             // (else the slots are sorted as they are)
+    wave_sort_regs(v);
+    wave_lds_sync();
 #pragma unroll
-  for (int r = 0; r < R; ++r) slots[lane * R + r] = v[r];
+    for (int r = 0; r < RF; ++r) slots[lane * RF + r] = v[r];
+  }
   wave_lds_sync();
   const lds_u64_ptr sorted = to_lds(slots);
   const u64 vk = sorted[k - 1];                                 // k-th best canon key
@@ -1007,34 +1075,7 @@ __global__ __launch_bounds__(64) void rerank_kernel(
   if (vk == KEY_EMPTY) {
     ok = total >= nb;                    // fewer than k candidates: right only if every column is listed
   } else {
-    const float na2 = Anorm[row], nb2 = __uint_as_float(Binfo->max_norm_bits);
-    // Integer data exactly representable in bf16: every number the sweeps and this kernel
-    // form is a multiple of 1/2 below 2^23 in magnitude, hence exact, when N = max|q|^2 +
-    // max|x|^2 satisfies 1.5 N < 2^23 (|<q,x>| <= N / 2, |tau| / 2 <= N), or N < 2^23 when
-    // no value is negative (0 <= <q,x>, -|q|^2 <= tau <= |x|^2).
-    const float nsum = __uint_as_float(Ainfo->max_norm_bits) + nb2;
-    const bool nonneg = Ainfo->all_nonneg && Binfo->all_nonneg;
-    const bool exact = Ainfo->all_int && Binfo->all_int && Ainfo->all_bf16 && Binfo->all_bf16 &&
-                       (nonneg ? nsum < 8388608.f : nsum < 5592405.f);
     if (!exact) {   // (exact: approximate = canon bit for bit, so the k best listed keys are the answer)
-      const bool inexact = !(Ainfo->all_bf16 && Binfo->all_bf16);
-      // |approx - canon| <= eps: bf16 head/tail split drops terms below 2^-15 |q||x| per product;
-      // fp32 accumulation and the canon chain each stay below d 2^-22 (|q|^2 + |x|^2); the
-      // collect sweep's own rounding (a few ulps of |tau| / 2 + |<q,x>|) is the last term.
-      // fp16 heads alone: qh_i = q_i + a_i with |a_i| <= u |q_i| + s, u = 2^-11 (rounding to 11
-      // significant bits) and s = 2^-25 (half the spacing of fp16 subnormals), likewise x, so
-      // |<q,x> - <qh,xh>| <= (2u + u^2) |q||x| + s (1 + u) sqrt(d) (|q| + |x|) + d s^2; with
-      // |q||x| <= N / 2 and |q| + |x| <= sqrt(2 N), N = |q|^2 + |x|^2, twice that on the distance:
-      // 9.78e-4 N + 6.0e-8 sqrt(2 d N) + 1.8e-15 d (inner product: the value is the product itself,
-      // half of each).
-      const bool f16 = precision_variant(Ainfo, Binfo, k == 1 ? 1 : 2, false) == 3;
-      const float nn = na2 + nb2;
-      constexpr float F16_S = METRIC == 0 ? 1.f : 0.5f;
-      const float split_term = !inexact ? 0.f : (f16 ? F16_S * 9.78e-4f : 6.2e-5f);
-      const float coef = split_term + (float)d * 4.8e-7f + 2e-6f;
-      const float abs_term = f16 ? F16_S * (6.0e-8f * sqrtf(2.f * (float)d * nn) + 1.8e-15f * (float)d) : 0.f;
-      const float eps = eps_scale * (coef * nn + abs_term);
-      const float tau_v = tau[row];
       const float ub = METRIC == 0 ? na2 + tau_v : -tau_v;
       const float kv = key_value(vk, METRIC);
       float tv = ub;
@@ -1376,6 +1417,11 @@ MfmaPlan make_plan(int64_t na, int64_t nb, int k, int d) {
   if (p.stride == 1) {
     p.kp_tau = p.kp;
   } else {
+    // (the threshold lists more than kp columns here, and only those close to the k-th best are re-ranked: more
+    // candidates cost next to nothing, and rows whose kp-th is not provably beyond the k-th, each redone over all
+    // columns, become rare.  32 of 16384, d = 768, inner product, 10,000 rows: with 48 candidates a few rows took 101 us,
+    // with 64 none does)
+    if (k > 1) p.kp = std::max(p.kp, 64);
     const double ks = (double)k / p.stride;
     p.kp_tau = std::min(p.kp, (int)std::ceil(ks + 4.0 * std::sqrt(ks) + 2.0));
     // Room for the listed columns -- in EVERY split: when B is stored in cluster order a
@@ -1571,14 +1617,20 @@ void launch_rerank(const MfmaOperand& A, const MfmaOperand& B, int d, int metric
   const int kp = p.kp;
   const int* cnt = reinterpret_cast<const int*>(reinterpret_cast<const char*>(shortlist) + p.o_cnt);
   const float* tau = reinterpret_cast<const float*>(reinterpret_cast<const char*>(shortlist) + p.o_tau);
-  const int R = kp <= 64 ? 2 : 4;   // (fb_count was cleared by launch_mfma_shortlist's threshold kernel)
+  // (fb_count was cleared by launch_mfma_shortlist's threshold kernel)
+  // Slots for what a row usually lists: about kp columns, or stride * kp_tau of them where the threshold is a sample's.
+  const int R = kp <= 64 && p.stride == 1 ? 2 : 4;
   const size_t sh = (size_t)64 * R * sizeof(u64) + (size_t)d * sizeof(float);
-#define RR(RV, MET)                                                                               \
-  hipLaunchKernelGGL((rerank_kernel<RV, MET>), dim3((unsigned)A.n), dim3(64), sh, st, shortlist,  \
+#define RR(RV, RF, MET)                                                                           \
+  hipLaunchKernelGGL((rerank_kernel<RV, RF, MET>), dim3((unsigned)A.n), dim3(64), sh, st, shortlist,  \
                      cnt, tau, p.nsplit, p.cap, kp, A.x, B.x, B.n, d, k, A.norm, A.info, B.info,   \
                      eps_scale, out, fb_count, fb_rows)
-  if (R == 2) { if (metric == 0) RR(2, 0); else RR(2, 1); }
-  else        { if (metric == 0) RR(4, 0); else RR(4, 1); }
+#define RRM(RV, RF) do { if (metric == 0) RR(RV, RF, 0); else RR(RV, RF, 1); } while (0)
+  if (R == 2) RRM(2, 1);
+  else if (kp <= 64) RRM(4, 1);
+  else if (kp <= 128) RRM(4, 2);
+  else RRM(4, 4);
+#undef RRM
 #undef RR
   // rows whose shortlist could not be proven sufficient: canon over all columns
   launch_canon_rows(A.x, A.n, B.x, B.n, d, metric, k, out, fb_count, fb_rows, fb_partial,
