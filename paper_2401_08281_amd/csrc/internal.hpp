@@ -45,6 +45,7 @@ struct Rescan {
   const u32* count = nullptr;
   u64* partial = nullptr;
   u32 pieces = 1, limit = 0;
+  unsigned long long* cursor = nullptr;   // a work counter that is zero when the scan starts, or null
   __device__ u32 split() const { return (u64)*count * pieces <= limit ? pieces : 1u; }
 };
 void launch_rescan_merge(const Rescan& rs, int k, int metric, const int64_t* ids, float* out_dist, int64_t* out_ids,

@@ -747,9 +747,9 @@ void ivfpq_scan_bank_kernel(
 
   // Items are handed out through a counter in memory (*next_item starts at 0), one at a time: the
   // items of a batch differ in length (the sum of their lists), and with a fixed share per
-  // workgroup the launch would end with the unluckiest share.
-  for (;;) {
-    if (tid == 0) *s_item = atomicAdd(next_item, 1ull);
+  // workgroup the launch would end with the unluckiest share.  (next_item null: a workgroup per item)
+  for (unsigned long long own = blockIdx.x;; own = (unsigned long long)nitems) {
+    if (tid == 0) *s_item = next_item != nullptr ? atomicAdd(next_item, 1ull) : own;
     block_sync_lds();
     const int64_t item = (int64_t)*s_item;
     if (again.list == nullptr && item >= nitems) break;
@@ -1875,10 +1875,14 @@ static int launch_scan_bank(const IvfpqDims& g, const float* q, int64_t nq, cons
   if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kern, NT, shmem) != hipSuccess || per_cu < 1)
     per_cu = 1;
   const int64_t grid = std::min<int64_t>(nitems, 256ll * per_cu);
-  launch_fill_u64(counter, 1, 0ull, st);
+  // The counter costs a launch of its own (4 us of a query's 58) and is left out where every item has a workgroup;
+  // queries scanned again bring one that was cleared with their list.
+  const bool counted = rescan.list != nullptr || nitems > grid;
+  if (counted && rescan.cursor == nullptr) launch_fill_u64(counter, 1, 0ull, st);
+  unsigned long long* next_item = !counted ? nullptr : (rescan.cursor ? rescan.cursor : reinterpret_cast<unsigned long long*>(counter));
   hipLaunchKernelGGL(kern, dim3((unsigned)grid), dim3(NT), shmem, st, q, centroids, codebooks,
                      probes, cdist, nprobe, ppb, nsplit, nitems, list_off, codes, norms, cnorm, list_tables,
-                     ntotal, k, tot, sink, reinterpret_cast<unsigned long long*>(counter), rescan);
+                     ntotal, k, tot, sink, next_item, rescan);
   return 0;
 }
 

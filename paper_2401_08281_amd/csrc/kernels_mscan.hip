@@ -1483,6 +1483,7 @@ Rescan mscan_rescan(const MscanIndex& ix, const MscanPlan& p, const char* ws, u6
   Rescan rs;
   rs.list = reinterpret_cast<const u32*>(ws + ms_layout(ix, p).o_rlist);
   rs.count = mscan_rescan_count(ix, p, ws);
+  rs.cursor = reinterpret_cast<unsigned long long*>(const_cast<unsigned*>(rs.count) + 4);   // (cleared by part 0)
   rs.partial = partial;
   rs.pieces = (u32)std::min(p.npr, 16);
   rs.limit = (u32)std::min<int64_t>(p.nq, 65536);
