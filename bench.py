@@ -20,6 +20,7 @@ of the same queries.
 import argparse
 import json
 import os
+import re
 import sys
 import time
 
@@ -44,6 +45,7 @@ def log(msg):
 
 
 MATRIX_SCAN_KERNEL = "ms_sweep_kernel"
+MATRIX_SCAN_BOUND = re.compile(r"ms_sweep_kernel<.*, \d+, 0, \d+>")   # its MODE 0 (Side, METRIC, MODE, NT)
 
 
 def matrix_scan(cfg, search_type, nq, npr, k):
@@ -172,6 +174,8 @@ def record_traffic(args):
                 for r in csv.DictReader(f):
                     if r["Counter_Name"] != counter:
                         continue
+                    if kernel == MATRIX_SCAN_KERNEL and MATRIX_SCAN_BOUND.search(r["Kernel_Name"]):
+                        continue                     # the sweep over a query's first lists, another stage
                     if kernel in r["Kernel_Name"]:
                         vals["scan"].append(float(r["Counter_Value"]))
                     elif "vs_calibrate_copy_kernel" in r["Kernel_Name"]:
