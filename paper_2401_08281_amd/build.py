@@ -12,7 +12,7 @@ CALIBRATE_SOURCE = "calibrate.hip"
 SOURCES = ["api.hip", "kernels_dist.hip", "kernels_select.hip", "kernels_ivfpq.hip", "kernels_mfma.hip", "kernels_nearest.hip",
            "kernels_refine.hip", "kernels_train.hip",
            "kernels_ivfflat.hip", "kernels_mscan.hip", "kernels_place.hip"]
-HEADERS = ["common.hpp", "internal.hpp", os.path.join("..", "..", "include", "vs.h")]
+HEADERS = ["common.hpp", "internal.hpp", "survivors.hpp", os.path.join("..", "..", "include", "vs.h")]
 
 FLAGS = [
     "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-ffp-contract=off", "-fvisibility=hidden",

@@ -37,6 +37,7 @@
 
 #include "common.hpp"
 #include "internal.hpp"
+#include "survivors.hpp"
 
 namespace {
 
@@ -890,7 +891,7 @@ struct RerankArgs {
   u32* rescan_list;
   u32* rescan_count;
   uint4* surv;                                    // PQ: see ms_list_kernel
-  u32 *surv_count, *surv_first, *surv_number;
+  u32 *surv_count, *surv_unwritten, *surv_first, *surv_number;
   u32 surv_cap;
   float* surv_value;
   const void* codes;
@@ -973,7 +974,8 @@ __device__ __forceinline__ void ms_survivors(const RerankArgs& A, int64_t qi, u3
 
 // PQ, in three launches.  (1) One wavefront per query: the survivors of all queries in one list {storage position,
 // pair, list, position in the list}, a query's next to each other; 16 wavefronts share one addition to the list's
-// length.
+// length.  A query whose survivors do not all fit writes none of them and is scanned again; what it leaves empty of the
+// list goes to *surv_unwritten, so that nobody reads it.
 __global__ __launch_bounds__(1024) void ms_list_kernel(const RerankArgs A) {
   __shared__ u32 keep_s[16][256];
   __shared__ u32 count_s[16], base_s;
@@ -998,13 +1000,14 @@ __global__ __launch_bounds__(1024) void ms_list_kernel(const RerankArgs A) {
   __syncthreads();
   if (qi >= A.nq) return;
   u32 at = base_s + count_s[wave];
-  const bool full = mine > 0 && at + mine > A.surv_cap;         // no room in the list: to the query-major scan
+  const SurvivorPlace place = survivor_place(at, mine, A.surv_cap);
   if (lane == 0) {
     A.surv_first[qi] = at;
-    A.surv_number[qi] = left || full ? 0xFFFFFFFFu : mine;
-    if (full) A.rescan_list[atomicAdd(A.rescan_count, 1u)] = (u32)qi;
+    A.surv_number[qi] = left || place.full ? 0xFFFFFFFFu : mine;
+    if (place.full) A.rescan_list[atomicAdd(A.rescan_count, 1u)] = (u32)qi;
+    if (place.unwritten) *A.surv_unwritten = place.unwritten;   // (one query at most)
   }
-  if (mine == 0 || full) return;
+  if (mine == 0 || place.full) return;
   ms_survivors(A, qi, n, limit, keep_s[wave], [&](int num, u32 pos, u32 p) {
     const u32 pr = (u32)qi * (u32)A.npr + p;
     const int l = A.probes[pr];
@@ -1026,7 +1029,7 @@ __global__ __launch_bounds__(kSweepThreads) void ms_eval_pq_kernel(const RerankA
   float* cbs = reinterpret_cast<float*>(smem);                  // [M][K][dsub]
   const int wave = threadIdx.x >> 6, lane = lane_id(), nw = kSweepThreads / VS_WAVE;
   float* ent = reinterpret_cast<float*>(smem + pq_eval_cb_bytes(M, K, dsub)) + (size_t)wave * B * LE;
-  const u32 total = min(*A.surv_count, A.surv_cap);
+  const u32 total = survivors_written(*A.surv_count, A.surv_cap, *A.surv_unwritten);
   if (blockIdx.x * (u32)(nw * B) >= total) return;              // (uniform)
   for (int i = threadIdx.x; i < M * K * dsub / 4; i += kSweepThreads)
     reinterpret_cast<f32x4*>(cbs)[i] = reinterpret_cast<const f32x4*>(A.codebooks)[i];
@@ -1637,6 +1640,7 @@ void launch_mscan(int part, const MscanIndex& ix, const MscanPlan& p, const floa
   B.cand_count = A.cand_count; B.cand = A.cand;
   B.rescan_list = reinterpret_cast<u32*>(ws + L.o_rlist); B.rescan_count = ctr + 4;
   B.surv = reinterpret_cast<uint4*>(ws + L.o_surv); B.surv_count = ctr + 5;
+  B.surv_unwritten = ctr + 6;
   B.surv_first = reinterpret_cast<u32*>(ws + L.o_sfirst); B.surv_number = reinterpret_cast<u32*>(ws + L.o_snum);
   B.surv_cap = p.surv;
   B.surv_value = reinterpret_cast<float*>(ws + L.o_sval);
