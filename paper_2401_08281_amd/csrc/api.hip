@@ -206,10 +206,9 @@ MfmaOperand operand(const float* x, int64_t n, const Planes& p) {
 }
 // After the preparation of an index's own operand has completed: tell the host whether the
 // rows are exactly bf16, so that searches enqueue only the sweep variant that will run.
-hipError_t learn_planes(Planes* p) {
-  PrepInfo h;
-  const hipError_t e = hipMemcpy(&h, p->info, sizeof(PrepInfo), hipMemcpyDeviceToHost);
-  if (e == hipSuccess) p->known_bf16 = h.all_bf16 ? 1 : 0;
+hipError_t learn_planes(Planes* p, PrepInfo* h) {
+  const hipError_t e = hipMemcpy(h, p->info, sizeof(PrepInfo), hipMemcpyDeviceToHost);
+  if (e == hipSuccess) p->known_bf16 = h->all_bf16 ? 1 : 0;
   return e;
 }
 
@@ -612,7 +611,8 @@ int vs_flat_add(vs_flat* ix, const float* x, int64_t n, void* hip_stream) {
     ix->has_planes = true;
   }
   HIP_TRY(hipStreamSynchronize(st));
-  if (planes) HIP_TRY(learn_planes(&ix->planes));
+  PrepInfo info;
+  if (planes) HIP_TRY(learn_planes(&ix->planes, &info));
   HIP_TRY(hipGetLastError());
   return VS_OK;
 }
@@ -992,6 +992,16 @@ static hipError_t alloc_centroids(vs_ivfpq* ix, int kind, size_t bytes) {
   return hipMalloc(reinterpret_cast<void**>(&ix->centroids), bytes);
 }
 
+// After an index's preparation has completed: what the host wants to know of its centroids (learn_planes), and whether
+// the data are of a size that the matrix-core scan's bounds hold for; other indexes go without that scan.
+static hipError_t learn_index(vs_ivfpq* ix, int kind) {
+  if (!ix->has_planes) return hipSuccess;
+  PrepInfo h;
+  const hipError_t e = learn_planes(&ix->c_planes, &h);
+  if (e == hipSuccess && !mscan_scale_fits(kind, kind == kMsPq ? h.codebook_max_bits : h.max_norm_bits)) ix->ms_mem = nullptr;
+  return e;
+}
+
 int vs_ivfpq_create(vs_ivfpq** out, int32_t d, int32_t metric, int32_t nlist, int32_t M,
                     int32_t nbits, const float* centroids, const float* codebooks,
                     void* hip_stream) {
@@ -1020,7 +1030,7 @@ int vs_ivfpq_create(vs_ivfpq** out, int32_t d, int32_t metric, int32_t nlist, in
   TRY_C(hipGetDevice(&ix->device));
   const size_t cb = (size_t)nlist * d * sizeof(float);
   const size_t tb = (size_t)M * ix->g.K * ix->g.dsub * sizeof(float);
-  TRY_C(alloc_centroids(ix, kMsPq, cb));
+  TRY_C(mfma_knn_supported(d, 1) ? alloc_centroids(ix, kMsPq, cb) : hipMalloc(reinterpret_cast<void**>(&ix->centroids), cb));
   // (the codebooks twice: [M, K, dsub] as given, and behind it [K, M, dsub], the order in which the
   // per-query tables of the wavefront-private scan are computed)
   TRY_C(hipMalloc(reinterpret_cast<void**>(&ix->codebooks), 2 * tb));
@@ -1030,7 +1040,6 @@ int vs_ivfpq_create(vs_ivfpq** out, int32_t d, int32_t metric, int32_t nlist, in
   launch_pq_codebooks_by_entry(ix->g, ix->codebooks, ix->codebooks + tb / sizeof(float), st);
   TRY_C(hipMalloc(reinterpret_cast<void**>(&ix->cnorm), (size_t)nlist * sizeof(float)));
   launch_row_norms(ix->centroids, nlist, d, ix->cnorm, st);
-  if (ix->ms_mem) launch_mscan_index(kMsPq, ix->g, ix->centroids, ix->codebooks, ix->ms_mem, st);
   TRY_C(hipMemsetAsync(ix->list_off, 0, ((size_t)nlist + 1) * sizeof(int64_t), st));
   if (mfma_knn_supported(d, 1)) {
     TRY_C(hipMalloc(&ix->plane_mem, planes_bytes(nlist, d)));
@@ -1039,9 +1048,10 @@ int vs_ivfpq_create(vs_ivfpq** out, int32_t d, int32_t metric, int32_t nlist, in
                 ix->c_planes.info, st, true);
     ix->c_planes.try_heads_only = true;
     ix->has_planes = true;
+    if (ix->ms_mem) launch_mscan_index(kMsPq, ix->g, ix->centroids, ix->codebooks, ix->c_planes.info, ix->ms_mem, st);
   }
   TRY_C(hipStreamSynchronize(st));
-  if (ix->has_planes) TRY_C(learn_planes(&ix->c_planes));
+  TRY_C(learn_index(ix, kMsPq));
 #undef TRY_C
   {   // set-up for vs_ivfpq_search_static: this device's address of the static work space
     char* unused = nullptr;
@@ -1387,7 +1397,7 @@ MscanIndex mscan_index(int kind, const vs_ivfpq* ix, const float* vmin = nullptr
   m.centroids = ix->centroids; m.list_off = ix->list_off; m.codes = ix->codes; m.codebooks = ix->codebooks;
   m.mem = ix->ms_mem; m.units = ix->ms_units; m.cnorm = ix->cnorm; m.norms = ix->norms; m.list_tables = ix->list_tables;
   m.vmin = vmin; m.step = step;
-  m.sigma_src = ix->has_planes ? &ix->c_planes.info->max_norm_bits : nullptr;
+  if (ix->has_planes) m.sigma_src = kind == kMsPq ? &ix->c_planes.info->codebook_max_bits : &ix->c_planes.info->max_norm_bits;
   return m;
 }
 // tables of a search: 0 residual, 1 inner product, 2 stored norms, 3 precomputed
@@ -1682,10 +1692,10 @@ int vs_ivfflat_create(vs_ivfflat** out, int32_t d, int32_t metric, int32_t nlist
                 ix->c_planes.info, st, true);
     ix->c_planes.try_heads_only = true;
     ix->has_planes = true;
-    if (ix->ms_mem) launch_mscan_index(kMsFlat, ix->g, ix->centroids, nullptr, ix->ms_mem, st);
+    if (ix->ms_mem) launch_mscan_index(kMsFlat, ix->g, ix->centroids, nullptr, ix->c_planes.info, ix->ms_mem, st);
   }
   TRY_C(hipStreamSynchronize(st));
-  if (ix->has_planes) TRY_C(learn_planes(&ix->c_planes));
+  TRY_C(learn_index(ix, kMsFlat));
 #undef TRY_C
   *out = fx;
   return VS_OK;
@@ -1861,10 +1871,10 @@ int vs_ivfsq8_create(vs_ivfsq8** out, int32_t d, int32_t metric, int32_t nlist,
                 ix->c_planes.info, st, true);
     ix->c_planes.try_heads_only = true;
     ix->has_planes = true;
-    if (ix->ms_mem) launch_mscan_index(kMsSq8, ix->g, ix->centroids, nullptr, ix->ms_mem, st);
+    if (ix->ms_mem) launch_mscan_index(kMsSq8, ix->g, ix->centroids, nullptr, ix->c_planes.info, ix->ms_mem, st);
   }
   TRY_C(hipStreamSynchronize(st));
-  if (ix->has_planes) TRY_C(learn_planes(&ix->c_planes));
+  TRY_C(learn_index(ix, kMsSq8));
 #undef TRY_C
   *out = sx;
   return VS_OK;

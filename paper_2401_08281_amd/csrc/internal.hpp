@@ -152,7 +152,7 @@ struct MscanIndex {
   const void* units = nullptr;         // kMsPq: launch_mscan_units' output
   const float *cnorm = nullptr, *norms = nullptr, *list_tables = nullptr;
   const float *vmin = nullptr, *step = nullptr;   // kMsSq8
-  const u32* sigma_src = nullptr;      // kMsFlat, kMsSq8: bits of the centroids' largest squared norm
+  const u32* sigma_src = nullptr;      // bits of the codebooks' largest magnitude (kMsPq), of the centroids' largest squared norm
 };
 struct MscanPlan {
   int64_t nq = 0;
@@ -162,8 +162,12 @@ struct MscanPlan {
 };
 // bytes of what an index keeps for the scan (0 where the shape has none), and its preparation
 size_t mscan_index_bytes(int kind, const IvfpqDims& g);
-void launch_mscan_index(int kind, const IvfpqDims& g, const float* centroids, const float* codebooks, void* out,
-                        hipStream_t st);
+// (info: of the centroids' preparation, launched before; PQ: receives codebook_max_bits)
+struct PrepInfo;
+void launch_mscan_index(int kind, const IvfpqDims& g, const float* centroids, const float* codebooks, PrepInfo* info,
+                        void* out, hipStream_t st);
+// Whether the scan's bounds hold for an index: bits of the number that its scale is taken from (sigma_src)
+bool mscan_scale_fits(int kind, u32 bits);
 size_t mscan_units_bytes(const IvfpqDims& g, int64_t ntotal);
 void launch_mscan_units(const IvfpqDims& g, const uint8_t* codes, const int64_t* list_off, int64_t ntotal, void* out,
                         hipStream_t st);
@@ -197,6 +201,7 @@ struct PrepInfo {
   // a call's vectors had to be swept again.
   static constexpr u32 kHeadsOne = 1u, kHeadsMany = 2u, kHeadsSweep = 4u, kHeadsAll = 7u;
   u32 heads_only;
+  u32 codebook_max_bits;   // of an IVF-PQ index with a matrix-core scan: bits of the codebooks' largest magnitude
 };
 struct MfmaOperand {
   const float* x;             // [n, d] original fp32 rows

@@ -32,8 +32,15 @@
 // The kernels use kappa = 1.02 u + phi, 4 u for 3 u, and absolute terms of 2^-26 d in scaled units (which also
 // cover subnormal squares that the dot product instruction may drop).  Where a value has no finite fp16
 // image (overflow, NaN), the vector or the query passes every test and is decided exactly.
+//   The exact evaluation knows no scale: it must not leave fp32's range where the scaled bounds stay inside theirs,
+// or it ties what they tell apart (an infinite or vanishing distance, a NaN).  The scan therefore serves indexes whose
+// scale is within 2^-40 .. 2^40 (mscan_scale_fits): components with an fp16 image are then below 2^56, sums of 512
+// of their squares below 2^121, and what underflows is below 2^-149 512 2^80 in scaled units, far below the absolute
+// terms.  Terms that are not such sums (|c|^2, <q, c>, the cells of scalar codes) have a limit each in the sweep.
 #include <algorithm>
 #include <cmath>
+#include <cstdlib>
+#include <cstring>
 
 #include "common.hpp"
 #include "internal.hpp"
@@ -251,13 +258,13 @@ struct SweepArgs {
 };
 
 // power of two that scales the data: a vector of the norm (or a component of the size) `v` becomes 2^exp
+// (nothing but zeros: as it is)
 __device__ __forceinline__ float scale_of(u32 bits, int exp, int is_square) {
   const float v = __uint_as_float(bits);
-  if (!(v > 0.f) || !(v < 3.0e38f)) return 1.f;
-  const float r = is_square ? sqrtf(v) : v;
+  if (!(v > 0.f)) return 1.f;
   int e;
-  (void)frexpf(r, &e);
-  return ldexpf(1.f, max(-100, min(100, exp - e)));
+  (void)frexpf(is_square ? sqrtf(v) : v, &e);
+  return ldexpf(1.f, exp - e);
 }
 
 // -- PQ codes.  A lane row g of the wavefront holds sub-quantizers g * MG .. g * MG + MG - 1 of its code: MG (or
@@ -286,7 +293,7 @@ struct PqSide {
   // d / M = 3: the fourth half of a granule holds -|t|^2 / 2 and meets a constant on the query's side, so that the
   // product contains the stored vector's norm
   static constexpr bool NORM = ROT && MG == 8;
-  static constexpr bool CHECK = false;                          // a finite codebook has finite fp16 images
+  static constexpr bool CHECK = false;                          // every codeword has a finite image (mscan_scale_fits)
   struct Raw { u32 w[NW]; };
   const uint8_t* units;                                         // this lane's bytes of unit 0
   const unsigned char* lut;                                     // this lane row's granules in LDS
@@ -512,7 +519,6 @@ void ms_sweep_kernel(const SweepArgs A) {
   side.init(A, smem, col, g);
   const bool vec = S::KIND == kMsFlat ? (A.map.d & 3) == 0 : (A.map.d & 7) == 0;
   const float sigma = scale_of(*A.sigma_src, A.sigma_exp, A.sigma_sqrt), sigma2 = sigma * sigma;
-  const bool finite = (*A.sigma_src & 0x7F800000u) != 0x7F800000u;   // (else every query passes everything)
   const u32 nitems = *A.nitems;
   const float inf = __builtin_inff();
 
@@ -594,9 +600,13 @@ void ms_sweep_kernel(const SweepArgs A) {
       float arow, brow = 0.f;
       const u32 qi = pr[t] / (u32)A.npr;
       float ex = A.abs_err;
-      bool bad = !(a2[t] < 1.0e30f) || !finite;
+      bool bad = !(a2[t] < 1.0e30f);
+      if (S::KIND == kMsSq8) bad = bad || !(extra < 0x1p40f);   // (cells far beyond what they code: middle and width below 2^60)
       if (METRIC == 0) {
-        if (S::KIND == kMsPq && A.form >= 2) ex += A.phi2 * (6.f * A.cnorm[l] + 4.f * A.cdist[pr[t]]) * sigma2;
+        if (S::KIND == kMsPq && A.form >= 2) {
+          ex += A.phi2 * (6.f * A.cnorm[l] + 4.f * A.cdist[pr[t]]) * sigma2;
+          bad = bad || !(A.cnorm[l] < 0x1p119f);                // (|x'|^2 and the sums it enters stay finite)
+        }
         if (S::KIND == kMsSq8) ex += 0x1p-31f * extra;
         bad = bad || !(ex < 1.0e30f);
         if (MODE == 0) arow = __builtin_fmaf(1.f + A.c4u + A.kappa, a2[t], ex);
@@ -610,7 +620,9 @@ void ms_sweep_kernel(const SweepArgs A) {
           ex += 2.f * A.phi * an * sqrtf(c2);
           if (S::KIND == kMsSq8) ex += 2.f * A.phi * an * sqrtf(extra);
         } else {
-          c = A.cdist[pr[t]] * sigma2;
+          c = A.cdist[pr[t]];
+          bad = bad || !(fabsf(c) < 0x1p119f);
+          c *= sigma2;
         }
         ex += A.phi * fabsf(c);
         bad = bad || !(fabsf(c) < 1.0e30f) || !(ex < 1.0e30f);
@@ -1215,7 +1227,7 @@ __global__ __launch_bounds__(256) void ms_rerank_sq8_kernel(const RerankArgs A) 
 
 // ---- what an index keeps for the scan --------------------------------------------------------------------
 // The fp16 codebook as granules [m][part][entry] of gh halfs, scaled by the power of two that puts the largest
-// component (its bits go to *maxbits) at 2^exp -- every workgroup finds the largest for itself --, and the
+// component (its bits go to *maxbits; a NaN is larger than any) at 2^exp -- every workgroup finds the largest for itself --, and the
 // centroids in fragment order.
 __global__ __launch_bounds__(512) void ms_codebook_kernel(const float* __restrict__ codebooks, int M, int K, int dsub,
                                                           int parts, int gh, int exp, u32* __restrict__ maxbits,
@@ -1356,8 +1368,23 @@ int pq_lanes(int M) { return M <= 8 ? 8 : (M <= 16 ? 16 : (M <= 32 ? 32 : 64)); 
   X(4, 1, 8, 8, false) X(8, 1, 8, 8, false) X(16, 1, 8, 8, false)                                           \
   X(8, 1, 4, 4, false) X(16, 1, 4, 4, false) X(4, 1, 8, 4, false) X(8, 1, 8, 4, false) X(16, 1, 8, 4, false)
 
-// What an index keeps: PQ: fp16 codebook | its largest component | centroids [nlist][kp] fp32 in fragment order; raw
-// vectors and scalar codes: centroids [nlist][kp] fp16
+// Whether the data that an index's scale is taken from -- bits of the codebooks' largest magnitude (PQ) or of the
+// centroids' largest squared norm -- lies where the scan's bounds hold (see the head of this file).  A codeword or a
+// centroid that is not finite does not.
+constexpr int kPqExp = 6, kRowsExp = 4, kScaleRange = 40;
+bool mscan_scale_fits(int kind, u32 bits) {
+  float v;
+  static_assert(sizeof(v) == sizeof(bits), "");
+  std::memcpy(&v, &bits, sizeof(v));
+  if (v == 0.f) return true;
+  if (!(v > 0.f) || !std::isfinite(v)) return false;
+  int e;
+  (void)std::frexp(kind == kMsPq ? v : std::sqrt(v), &e);
+  return std::abs((kind == kMsPq ? kPqExp : kRowsExp) - e) <= kScaleRange;
+}
+
+// What an index keeps: PQ: fp16 codebook | centroids [nlist][kp] fp32 in fragment order; raw vectors and scalar
+// codes: centroids [nlist][kp] fp16
 size_t mscan_index_bytes(int kind, const IvfpqDims& g) {
   if (kind != kMsPq) {
     if (flat_ksteps(g.d) > 8) return 0;
@@ -1372,7 +1399,7 @@ size_t mscan_index_bytes(int kind, const IvfpqDims& g) {
   VS_MS_PQ_FORMS(X)
 #undef X
   if (!found || s.cb16 > 128 * 1024 || pq_eval_bytes(g.M, g.K, g.dsub, pq_lanes(g.M), 8) > 160 * 1024) return 0;
-  return up256(s.cb16) + 256 + up256((size_t)g.nlist * s.ks * 32 * 4);
+  return up256(s.cb16) + up256((size_t)g.nlist * s.ks * 32 * 4);
 }
 
 // The codes once more, in units of 32 (PQ): bytes, and their preparation from the list-contiguous store
@@ -1387,16 +1414,16 @@ void launch_mscan_units(const IvfpqDims& g, const uint8_t* codes, const int64_t*
                      static_cast<uint8_t*>(out));
 }
 
-void launch_mscan_index(int kind, const IvfpqDims& g, const float* centroids, const float* codebooks, void* out,
-                        hipStream_t st) {
+void launch_mscan_index(int kind, const IvfpqDims& g, const float* centroids, const float* codebooks, PrepInfo* info,
+                        void* out, hipStream_t st) {
   const MsShape s = ms_shape(kind, g);
   const int kp = 32 * s.ks;
   const unsigned grid = (unsigned)std::min<int64_t>(1024, ((int64_t)g.nlist * kp + 2047) / 2048 + 16);
   char* o = static_cast<char*>(out);
   if (kind == kMsPq)
     hipLaunchKernelGGL(ms_codebook_kernel, dim3(grid), dim3(512), 0, st, codebooks, g.M, g.K, g.dsub, s.map.parts,
-                       s.map.gh, 6, reinterpret_cast<u32*>(o + up256(s.cb16)), reinterpret_cast<_Float16*>(o), centroids,
-                       (int64_t)g.nlist, kp, s.map, norm_slot(g), reinterpret_cast<float*>(o + up256(s.cb16) + 256));
+                       s.map.gh, kPqExp, &info->codebook_max_bits, reinterpret_cast<_Float16*>(o), centroids,
+                       (int64_t)g.nlist, kp, s.map, norm_slot(g), reinterpret_cast<float*>(o + up256(s.cb16)));
   else
     hipLaunchKernelGGL(ms_centroids16_kernel, dim3(grid), dim3(256), 0, st, centroids, (int64_t)g.nlist, kp, s.map,
                        reinterpret_cast<_Float16*>(o));
@@ -1444,7 +1471,7 @@ MsLayout ms_layout(const MscanIndex& ix, const MscanPlan& p) {
 }  // namespace
 
 bool mscan_supported(const MscanIndex& ix, int k) {
-  return k >= 1 && k <= 128 && ix.mem != nullptr && (ix.kind == kMsPq ? ix.units != nullptr : ix.sigma_src != nullptr);
+  return k >= 1 && k <= 128 && ix.mem != nullptr && (ix.kind != kMsPq || ix.units != nullptr);
 }
 
 // Sizes of a search.  slots: groups of four codes that give a query's threshold; seg: codes of a list per work item.
@@ -1552,15 +1579,10 @@ SweepArgs sweep_args(const MscanIndex& ix, const MscanPlan& p, const MsShape& s,
   A.codes = ix.codes; A.units = static_cast<const uint8_t*>(ix.units);
   const char* mem = static_cast<const char*>(ix.mem);
   A.cb16 = reinterpret_cast<const f16x2*>(mem); A.cb16_bytes = s.cb16;
-  A.cperm = ix.kind == kMsPq ? mem + up256((size_t)s.cb16) + 256 : mem;
+  A.cperm = ix.kind == kMsPq ? mem + up256((size_t)s.cb16) : mem;
   A.vmin = ix.vmin; A.step = ix.step;
-  if (ix.kind == kMsPq) {
-    A.sigma_src = reinterpret_cast<const u32*>(mem + up256((size_t)s.cb16));
-    A.sigma_exp = 6; A.sigma_sqrt = 0;
-  } else {
-    A.sigma_src = ix.sigma_src;
-    A.sigma_exp = 4; A.sigma_sqrt = 1;
-  }
+  A.sigma_src = ix.sigma_src;
+  A.sigma_exp = ix.kind == kMsPq ? kPqExp : kRowsExp; A.sigma_sqrt = ix.kind != kMsPq;
   A.form = form; A.cdist = cdist; A.cnorm = ix.cnorm;
   A.qbound = reinterpret_cast<float*>(ws + L.o_bound);
   A.gmin = reinterpret_cast<float*>(ws + L.o_gmin);

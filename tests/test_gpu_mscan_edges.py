@@ -64,3 +64,73 @@ def test_survivors_beyond_their_list(vs, d, M, nbits, what):
         assert 0 < n <= nq, n        # (some had no room and were scanned again)
     finally:
         ix.close()
+
+
+# 32 x 3 holds |t|^2 / 2 of a codeword in its table, 16 x 8 and 20 x 5 its components only
+@pytest.mark.parametrize("d,M,big", [(96, 32, 400.0), (128, 16, 1e5), (100, 20, 1e5)])
+@pytest.mark.parametrize("metric", [L2, IP])
+@pytest.mark.parametrize("bad", [np.nan, np.inf, -np.inf])
+def test_codewords_that_are_not_finite(vs, d, M, big, metric, bad):
+    """Such a codeword is never chosen; a large finite one beside it is, and its vectors are found."""
+    rng = np.random.default_rng(d + M)
+    cent, x = lists_of(rng, d, [150] * 16)
+    cb = rng.standard_normal((M, 256, d // M)).astype(np.float32)
+    cb[:, 0] = big
+    cb[0, 1, 0] = bad
+    x[:200] = cent[rng.integers(0, 16, 200)] + big             # coded with the large codewords
+    ix = vs.IVFPQ(d, metric, dev(cent), dev(cb), nbits=8)
+    try:
+        ix.add(dev(x))
+        q = np.concatenate([x[:60], x[300:400]]) + 0.1 * rng.standard_normal((160, d))
+        D, I = both_scans(vs, ix, dev(q.astype(np.float32)), 20, 16)
+        assert (I[:60, 0] < 200).float().mean() > 0.9          # (they are among the results)
+    finally:
+        ix.close()
+
+
+# sizes at which squares overflow or vanish, sums of codewords do, or the scale itself leaves its range
+@pytest.mark.parametrize("size", [1e-30, 1e-22, 1e-13, 1e-6, 1e12, 3e14, 1e19, 1e24, 1e36])
+@pytest.mark.parametrize("metric", [L2, IP])
+@pytest.mark.parametrize("kind,d,M,form", [("pq", 96, 32, 0), ("pq", 128, 16, 1), ("pq", 100, 20, 0), ("flat", 64, 0, 0),
+                                           ("sq8", 64, 0, 0)])
+def test_data_of_any_size(vs, kind, d, M, form, metric, size):
+    """Distances that are infinite, vanish or are not numbers in the exact arithmetic: the same ties."""
+    if form and metric == IP:
+        pytest.skip("stored norms serve L2")
+    rng = np.random.default_rng(d)
+    cent, x = lists_of(rng, d, [100] * 12)
+    with np.errstate(over="ignore", under="ignore"):
+        cent, x = (cent * np.float32(size)).astype(np.float32), (x * np.float32(size)).astype(np.float32)
+        q = (x[rng.integers(0, len(x), 150)] * rng.uniform(0.99, 1.01, (150, d))).astype(np.float32)
+    if kind == "pq":
+        cb = (rng.standard_normal((M, 256, d // M)) * size).astype(np.float32)
+        ix = vs.IVFPQ(d, metric, dev(cent), dev(cb), nbits=8)
+    else:
+        ix = make(vs, kind, d, M, 8, metric, cent, x, rng)
+    try:
+        if form:
+            ix.set_search_type(form)
+        ix.add(dev(x))
+        both_scans(vs, ix, dev(q), 10, 6)
+    finally:
+        ix.close()
+
+
+@pytest.mark.parametrize("kind,d,M", [("pq", 128, 16), ("pq", 100, 20), ("flat", 64, 0), ("sq8", 96, 0)])
+def test_centroids_far_larger_than_residuals(vs, kind, d, M):
+    """Stored norms and inner products whose terms are near the end of fp32 while residuals are of ordinary size."""
+    rng = np.random.default_rng(d)
+    for metric in (L2, IP):
+        for size in (1e4, 1e12, 1e17, 4e18, 1e25):
+            cent = (size * rng.standard_normal((12, d))).astype(np.float32)
+            x = (cent[rng.integers(0, 12, 1200)] * rng.uniform(1 - 1e-6, 1 + 1e-6, (1200, d))).astype(np.float32)
+            q = (x[rng.integers(0, 1200, 150)] * rng.uniform(1 - 1e-6, 1 + 1e-6, (150, d))).astype(np.float32)
+            ix = make(vs, kind, d, M, 8, metric, cent, x, rng)
+            try:
+                ix.add(dev(x))
+                for form in (0, 1) if kind == "pq" and metric == L2 else (0,):
+                    if form:
+                        ix.set_search_type(form)
+                    both_scans(vs, ix, dev(q), 10, 6, (metric, size, form))
+            finally:
+                ix.close()
