@@ -1594,7 +1594,7 @@ SweepArgs sweep_args(const MscanIndex& ix, const MscanPlan& p, const MsShape& s,
   const double u = 0x1p-11, chain = 2.0 * ix.g.d + ix.g.M + 64.0, es = std::max(0.f, eps_scale);
   const double phi = chain * 0x1p-22;
   const double phi2 = ix.kind == kMsPq && form >= 2 ? chain * 0x1p-23 : 0.0;
-  A.phi = (float)(phi * es);
+  A.phi = (float)std::max(1e-30, phi * es);   // (not zero: it meets infinite thresholds)
   A.phi2 = (float)(phi2 * es);
   A.kappa = (float)((1.02 * u + phi + 4.0 * phi2) * es);
   A.c4u = (float)(4.0 * u * es);

@@ -134,3 +134,19 @@ def test_centroids_far_larger_than_residuals(vs, kind, d, M):
                     both_scans(vs, ix, dev(q), 10, 6, (metric, size, form))
             finally:
                 ix.close()
+
+
+@pytest.mark.parametrize("kind,d,M", [("pq", 128, 16), ("pq", 100, 20), ("flat", 64, 0), ("sq8", 96, 0)])
+@pytest.mark.parametrize("metric", [L2, IP])
+def test_no_error_bound_and_no_threshold(vs, kind, d, M, metric):
+    """Fewer vectors than k in the probed lists: every one is a result, also where the error bounds are scaled to nothing."""
+    rng = np.random.default_rng(d)
+    cent, x = lists_of(rng, d, [20] * 12)
+    ix = make(vs, kind, d, M, 8, metric, cent, x, rng)
+    try:
+        ix.add(dev(x))
+        vs.vs_set_option("knn_eps_scale", 0.0)
+        D, I = both_scans(vs, ix, dev(x[:100]), 100, 4)
+        assert ((I >= 0).sum(1) == 80).all()
+    finally:
+        ix.close()
