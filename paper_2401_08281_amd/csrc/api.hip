@@ -157,6 +157,7 @@ std::atomic<int> g_lm_cap{1024};
 std::atomic<int> g_matrix_scan{0};
 std::atomic<float> g_knn_eps_scale{1.f}; // multiplies the error bound of the MFMA shortlist test
 std::atomic<long long> g_knn_mfma_rows{0};
+std::atomic<int> g_trims{0};             // calls of vs_trim
 
 void tile_shape(int64_t na, int64_t nb, int64_t* rows, int64_t* cols) {
   int64_t c = std::min<int64_t>(nb, 16384);
@@ -372,6 +373,16 @@ struct vs_ivfpq {
   bool assign_probed = false;   // an add has run its assignment through the matrix-core route
   int coarse_metric = -1;       // metric of list assignment and probing; -1: the index metric (g.metric)
   mutable Scratch scratch;
+  // The smallest work space of a matrix-core scan that there was no memory for.  Searches that need as much leave that
+  // scan out from then on -- tried again in every call it would cost a free and two allocations, each waiting for the
+  // device, where a call is to enqueue kernels only -- until the index grows or vs_trim is called.
+  mutable std::atomic<size_t> ms_refused{SIZE_MAX};
+  mutable std::atomic<int> ms_refused_at{0};   // g_trims at that time
+  bool ms_has_room(size_t bytes) const { return ms_refused_at != g_trims || bytes < ms_refused; }
+  void ms_no_room(size_t bytes) const {
+    if (ms_has_room(bytes)) ms_refused = bytes;
+    ms_refused_at = g_trims.load();
+  }
 };
 
 // IVF-Flat shares the lists, the coarse quantizer and the bookkeeping of the IVF-PQ index
@@ -659,6 +670,7 @@ int vs_trim(void) {
   std::lock_guard<std::mutex> lock(g_flat_scratch[dev].mu);
   HIP_TRY(hipDeviceSynchronize());   // nothing may still be using the buffer
   g_flat_scratch[dev].release();
+  ++g_trims;
   return VS_OK;
 }
 
@@ -1196,6 +1208,7 @@ int ivf_commit_storage(vs_ivfpq* ix, uint8_t* codes, int64_t* new_ids, float* ne
   if (ix->norms) (void)hipFree(ix->norms);
   ix->codes = codes; ix->ids = new_ids; ix->norms = new_norms; ix->ntotal = total;
   ix->h_off.swap(pl->h_new);
+  ix->ms_refused = SIZE_MAX;
   ix->max_list = 0;
   for (int l = 0; l < ix->g.nlist; ++l) ix->max_list = std::max(ix->max_list, ix->h_off[l + 1] - ix->h_off[l]);
   return VS_OK;
@@ -1415,7 +1428,7 @@ int table_form(const vs_ivfpq* ix) {
 //   1.3e7 185 -> 177, 2.2e7 301 -> 299, 2.3e7 750 -> 418, 4.3e7 822 -> 341;
 //   raw vectors and scalar codes by 32-dimension steps: 7.6e5 109 -> 146, 1.0e6 93 -> 93, 1.6e6 72 -> 103, 1.0e7 438 ->
 //   344, 1.3e7 351 -> 163.
-bool mscan_chosen(const MscanIndex& m, int form, int64_t nq, int npr, int k, MscanPlan* plan) {
+bool mscan_chosen(const vs_ivfpq* ix, const MscanIndex& m, int form, int64_t nq, int npr, int k, MscanPlan* plan) {
   const int opt = g_matrix_scan.load();
   if (opt < 0 || g_list_major.load() == 1) return false;
   const double visited = (double)nq * npr * ((double)m.ntotal / m.g.nlist);
@@ -1425,7 +1438,7 @@ bool mscan_chosen(const MscanIndex& m, int form, int64_t nq, int npr, int k, Msc
   // candidates per query: four times what the list-major scan keeps (it only sees those behind the first lists), less
   // for batches beyond 16,384 queries so that they stay near 1 GiB
   const int64_t cap = std::max<int64_t>(256, std::min<int64_t>(4 * (int64_t)g_lm_cap.load(), (1ll << 26) / nq));
-  return mscan_plan(m, nq, npr, k, (int)cap, plan);
+  return mscan_plan(m, nq, npr, k, (int)cap, plan) && ix->ms_has_room(plan->bytes);
 }
 
 // Work space of one search, carved from one buffer.
@@ -1452,7 +1465,7 @@ void search_layout(const vs_ivfpq* ix, int64_t nq, int k, int nprobe, SearchLayo
   // list is probed several times by the batch, the codes do not fit the caches anyway and the
   // lists are long (a list of one or two chunks leaves the list-major kernel, which builds two
   // tables and then scans, with nothing to overlap the builds with: measured slower at 244 codes).
-  if (allow_list_major && allow_mscan && mscan_chosen(mscan_index(kMsPq, ix), table_form(ix), nq, L.npr, k, &L.ms)) {
+  if (allow_list_major && allow_mscan && mscan_chosen(ix, mscan_index(kMsPq, ix), table_form(ix), nq, L.npr, k, &L.ms)) {
     L.mscan = true;
     L.nsplit = 1;
   }
@@ -1594,6 +1607,7 @@ int reserve_search(const vs_ivfpq* ix, int64_t nq, int k, int nprobe, SearchLayo
   int rc = ix->scratch.reserve(L->bytes);
   if (rc == VS_ERR_OOM && L->mscan) {
     (void)hipGetLastError();
+    ix->ms_no_room(L->ms.bytes);
     *L = SearchLayout();
     search_layout(ix, nq, k, nprobe, L, true, -1, false);
     rc = ix->scratch.reserve(L->bytes);
@@ -1755,7 +1769,7 @@ int vs_ivfflat_search(const vs_ivfflat* fx, const float* q, int64_t nq, int32_t 
   const KnnPlan plan = knn_plan(nq, g.nlist, g.d, npr, ix->has_planes, true);
   const MscanIndex m = mscan_index(kMsFlat, ix);
   MscanPlan ms;
-  bool mscan = mscan_chosen(m, 0, nq, npr, k, &ms);
+  bool mscan = mscan_chosen(ix, m, 0, nq, npr, k, &ms);
   ScratchUse use(ix->scratch, st);
   size_t o_knn = 0, o_pr = 0, o_part = 0, o_ms = 0;
   for (;; mscan = false) {   // (without room for the matrix-core scan's candidates: the query-major scan)
@@ -1768,6 +1782,7 @@ int vs_ivfflat_search(const vs_ivfflat* fx, const float* q, int64_t nq, int32_t 
     if (rc == VS_OK) break;
     if (rc != VS_ERR_OOM || !mscan) return rc;
     (void)hipGetLastError();
+    ix->ms_no_room(ms.bytes);
   }
   char* base = static_cast<char*>(ix->scratch.p);
   int32_t* probes = reinterpret_cast<int32_t*>(base + o_pr);
@@ -1936,7 +1951,7 @@ int vs_ivfsq8_search(const vs_ivfsq8* sx, const float* q, int64_t nq, int32_t k,
   const KnnPlan plan = knn_plan(nq, g.nlist, g.d, npr, ix->has_planes, true);
   const MscanIndex m = mscan_index(kMsSq8, ix, sx->vmin, sx->step);
   MscanPlan ms;
-  bool mscan = mscan_chosen(m, 0, nq, npr, k, &ms);
+  bool mscan = mscan_chosen(ix, m, 0, nq, npr, k, &ms);
   ScratchUse use(ix->scratch, st);
   size_t o_knn = 0, o_pr = 0, o_part = 0, o_ms = 0;
   for (;; mscan = false) {   // (without room for the matrix-core scan's candidates: the query-major scan)
@@ -1949,6 +1964,7 @@ int vs_ivfsq8_search(const vs_ivfsq8* sx, const float* q, int64_t nq, int32_t k,
     if (rc == VS_OK) break;
     if (rc != VS_ERR_OOM || !mscan) return rc;
     (void)hipGetLastError();
+    ix->ms_no_room(ms.bytes);
   }
   char* base = static_cast<char*>(ix->scratch.p);
   int32_t* probes = reinterpret_cast<int32_t*>(base + o_pr);

@@ -150,3 +150,54 @@ def test_no_error_bound_and_no_threshold(vs, kind, d, M, metric):
         assert ((I >= 0).sum(1) == 80).all()
     finally:
         ix.close()
+
+
+@pytest.mark.parametrize("kind,d,M", [("pq", 96, 32), ("flat", 64, 0), ("sq8", 96, 0)])
+def test_no_memory_for_the_candidates(vs, kind, d, M):
+    """With too little memory for a batch's candidates, about 1 GB, the query-major scan serves it: the first call finds
+    out, the next ones only enqueue kernels (they can be captured).  vs_trim and a larger index try again."""
+    from test_gpu_nearest import hold_memory
+    rng = np.random.default_rng(d)
+    nq, k, nprobe = 30_000, 10, 8
+    cent, x = lists_of(rng, d, [100] * 40)
+    q = dev((x[rng.integers(0, len(x), nq)] + 0.1 * rng.standard_normal((nq, d))).astype(np.float32))
+    ix = make(vs, kind, d, M, 8, L2, cent, x, rng)
+    vs.vs_set_option("matrix_scan", 1)
+
+    def route():
+        vs.vs_profile_enable(1)
+        vs.vs_profile_read()
+        D, I = ix.search(q, k, nprobe)
+        torch.cuda.synchronize()
+        n = vs.vs_profile_read()
+        vs.vs_profile_enable(0)
+        return D, I, n
+
+    try:
+        ix.add(dev(x))
+        vs.vs_trim()
+        torch.cuda.empty_cache()
+        print("little memory", kind, flush=True)
+        hold = hold_memory(400 << 20)
+        try:
+            D0, I0 = [t.clone() for t in ix.search(q, k, nprobe)]
+            torch.cuda.synchronize()
+            g = torch.cuda.CUDAGraph()
+            with torch.cuda.graph(g):
+                D1, I1 = ix.search(q, k, nprobe)
+            for _ in range(3):
+                D1.zero_()
+                g.replay()
+                torch.cuda.synchronize()
+                assert same(D0, D1) and same(I0, I1)
+            del g, D1, I1
+        finally:
+            del hold
+            torch.cuda.empty_cache()
+        D2, I2, n = route()
+        assert same(D0, D2) and same(I0, I2) and not n["scan_first"][1]
+        vs.vs_trim()
+        D2, I2, n = route()
+        assert same(D0, D2) and same(I0, I2) and n["scan_first"][1]
+    finally:
+        ix.close()
