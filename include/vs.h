@@ -211,7 +211,9 @@ VS_API int vs_ivfpq_create(vs_ivfpq** out, int32_t d, int32_t metric, int32_t nl
  * c_{2i} | c_{2i+1} << 4.
  * The list storage is re-laid-out contiguously; the call synchronises.
  * Shapes that the matrix-core scan serves (option "matrix_scan") also keep the codes in that scan's
- * order, about their own size once more, while that is at most a quarter of the free memory.
+ * order, about their own size once more: up to 128 MiB wherever there is room, more than that while it
+ * is at most a quarter of the free memory.  An add that does not find the memory gives that copy up
+ * (searches then scan the lists query by query) before it fails.
  * n == 0 is a no-op.  The total number of stored vectors must stay < 2^32.
  */
 VS_API int vs_ivfpq_add(vs_ivfpq* ix, const float* x, int64_t n, const int64_t* ids, void* hip_stream);

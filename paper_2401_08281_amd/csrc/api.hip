@@ -1247,37 +1247,42 @@ int vs_ivfpq_add(vs_ivfpq* ix, const float* x, int64_t n, const int64_t* ids, vo
   int64_t* new_ids = nullptr;
   float* new_norms = nullptr;
   // The codes, and behind them the codes in the matrix-core scan's order (one allocation: a second one takes the host
-  // about as long as the kernel that fills it).  Above 1 GiB they lie apart, so that they can go when an index outgrows
-  // the memory, and an index that they would leave little memory goes without.
+  // about as long as the kernel that fills it).  Above 128 MiB they lie apart, so that they can go when an index outgrows
+  // the memory, and an index that they would leave little memory goes without.  Wherever memory is short the copy is
+  // what is given up: an add succeeds if it would without one.
   const size_t own = align_up((size_t)(total + kStorePad) * g.code_size);
-  size_t more = ix->ms_mem ? mscan_units_bytes(g, total) : 0;
-  const bool apart = more > (1ull << 30);
-  void* units = nullptr;
-  if (more != 0 && !apart) {
-    if (hipMalloc(reinterpret_cast<void**>(&codes), own + more) == hipSuccess) units = codes + own;
-    else { (void)hipGetLastError(); codes = nullptr; }
-  }
-  if (!codes && hipMalloc(reinterpret_cast<void**>(&codes), own) != hipSuccess) {
+  const size_t more = ix->ms_mem ? mscan_units_bytes(g, total) : 0;
+  const bool apart = more > (128ull << 20);
+  auto allocate = [&](size_t behind) {
+    if (hipMalloc(reinterpret_cast<void**>(&codes), own + behind) == hipSuccess &&
+        hipMalloc(reinterpret_cast<void**>(&new_ids), (size_t)total * sizeof(int64_t)) == hipSuccess &&
+        (!with_norms || hipMalloc(reinterpret_cast<void**>(&new_norms), (size_t)total * sizeof(float)) == hipSuccess))
+      return true;
     (void)hipGetLastError();
-    if (ix->ms_units_apart) {
-      HIP_TRY(hipDeviceSynchronize());
-      (void)hipFree(ix->ms_units);
-      ix->ms_units = nullptr;
-      ix->ms_units_apart = false;
-    }
-    HIP_TRY(hipMalloc(reinterpret_cast<void**>(&codes), own));
-  }
-  if (hipMalloc(reinterpret_cast<void**>(&new_ids), (size_t)total * sizeof(int64_t)) != hipSuccess ||
-      (with_norms && hipMalloc(reinterpret_cast<void**>(&new_norms), (size_t)total * sizeof(float)) != hipSuccess)) {
-    (void)hipFree(codes);
+    if (codes) (void)hipFree(codes);
     if (new_ids) (void)hipFree(new_ids);
-    return fail(VS_ERR_OOM, "vs_ivfpq_add: id / norm storage allocation failed");
+    codes = nullptr;
+    new_ids = nullptr;
+    new_norms = nullptr;
+    return false;
+  };
+  void* units = nullptr;
+  bool room = allocate(apart ? 0 : more);
+  if (room && more != 0 && !apart) units = codes + own;
+  if (!room && more != 0 && !apart) room = allocate(0);
+  if (!room && ix->ms_units_apart) {
+    HIP_TRY(hipDeviceSynchronize());
+    (void)hipFree(ix->ms_units);
+    ix->ms_units = nullptr;
+    ix->ms_units_apart = false;
+    room = allocate(0);
   }
+  if (!room) return fail(VS_ERR_OOM, "vs_ivfpq_add: code / id / norm storage allocation failed");
   launch_relayout(g, ix->codes, ix->ids, ix->norms, ix->ntotal, ix->list_off, pl.new_off, tmp_codes,
                   ids, ix->ntotal, tmp_norms, pl.dest, pl.list_of, n, codes, new_ids, new_norms, st);
   if (apart) {
-    size_t room = 0, all = 0;
-    if (hipMemGetInfo(&room, &all) != hipSuccess || more > room / 4 || hipMalloc(&units, more) != hipSuccess) {
+    size_t left = 0, all = 0;
+    if (hipMemGetInfo(&left, &all) != hipSuccess || more > left / 4 || hipMalloc(&units, more) != hipSuccess) {
       (void)hipGetLastError();
       units = nullptr;
     }

@@ -201,3 +201,46 @@ def test_no_memory_for_the_candidates(vs, kind, d, M):
         assert same(D0, D2) and same(I0, I2) and n["scan_first"][1]
     finally:
         ix.close()
+
+
+def test_an_add_that_has_no_room_for_the_copy_of_the_codes(vs):
+    """6M codes of 16 bytes take 144 MB with their ids, their copy for the matrix cores about 98 MB more: with some 210
+    MB free the codes and the copy fit, the ids then do not, and the copy goes."""
+    from test_gpu_nearest import hold_memory
+    n, d, M, nlist = 3_000_000, 128, 16, 64
+    g = torch.Generator(device="cuda").manual_seed(3)
+    x = torch.randn((n, d), generator=g, device="cuda")
+    cb = torch.randn((M, 256, d // M), generator=g, device="cuda")
+    q = x[:500] + 0.1
+    ix = vs.IVFPQ(d, L2, x[:nlist].contiguous(), cb, nbits=8)
+    vs.vs_set_option("matrix_scan", 1)
+    try:
+        ix.add(x)
+        vs.vs_trim()
+        torch.cuda.synchronize()
+        torch.cuda.empty_cache()
+        print("adding with little memory", flush=True)
+        hold = hold_memory(200 << 20)
+        try:
+            ix.add(x)
+        finally:
+            del hold
+            torch.cuda.empty_cache()
+        assert ix.ntotal == 2 * n
+        D, I = [t.clone() for t in ix.search(q, 20, 4)]
+        vs.vs_set_option("matrix_scan", -1)
+        D0, I0 = ix.search(q, 20, 4)
+        torch.cuda.synchronize()
+        assert same(D, D0) and same(I, I0)
+        vs.vs_set_option("matrix_scan", 1)
+        ix.add(x[:1000].contiguous())                           # with room again, the copy is back
+        assert (both_scans(vs, ix, q, 20, 4)[1] >= 0).all()
+        vs.vs_profile_enable(1)
+        vs.vs_profile_read()
+        ix.search(q, 20, 4)
+        torch.cuda.synchronize()
+        n_first = vs.vs_profile_read()["scan_first"][1]
+        vs.vs_profile_enable(0)
+        assert n_first
+    finally:
+        ix.close()
