@@ -356,7 +356,7 @@ struct vs_ivfpq {
   float* codebooks = nullptr;   // [M, K, dsub]
   int64_t ntotal = 0;
   uint8_t* codes = nullptr;     // [ntotal, code_size], list-contiguous
-  int64_t* ids = nullptr;       // [ntotal]
+  int64_t* ids = nullptr;       // [ntotal], behind codes
   float* norms = nullptr;       // [ntotal] squared norms of the decoded vectors, search_type 1 only
   float* cnorm = nullptr;       // [nlist] squared norms of the centroids (IVF-PQ only)
   float* list_tables = nullptr; // [nlist, K, M] per-list terms of the split tables (search type 2, once computed)
@@ -365,10 +365,9 @@ struct vs_ivfpq {
   std::vector<int64_t> h_off;   // host copy
   int64_t max_list = 0;         // the longest list's length
   void* ms_mem = nullptr;       // what the matrix-core scan of the lists keeps (shapes that have one), behind centroids
-  void* ms_units = nullptr;     // the codes in that scan's order (IVF-PQ), behind codes
+  void* ms_units = nullptr;     // the codes in that scan's order (IVF-PQ), behind codes and ids
   bool ms_units_apart = false;  // ... in memory of its own
-  void* plane_mem = nullptr;    // bf16 head/tail planes + norms of the centroids (MFMA route)
-  Planes c_planes;
+  Planes c_planes;              // bf16 head/tail planes + norms of the centroids (MFMA route), behind centroids
   bool has_planes = false;
   bool assign_probed = false;   // an add has run its assignment through the matrix-core route
   int coarse_metric = -1;       // metric of list assignment and probing; -1: the index metric (g.metric)
@@ -990,18 +989,27 @@ int vs_ivfpq_train(const float* x, int64_t n, int32_t d, int32_t metric, int32_t
   return VS_OK;
 }
 
-// The centroids' memory, with room for what the matrix-core scan keeps of an index behind them (one allocation costs
-// what the rest of its preparation does).  Without memory for that the index goes without that scan.
+// The centroids' memory, and behind them their operand planes and what the matrix-core scan keeps of an index: one
+// allocation, as each of 2 MB or more takes the host 12 to 25 us to make and 12 to give back (4096 x 128: all three are
+// that large; below, an allocation takes 1 us).  Without memory for the last the index goes without that scan.
 static hipError_t alloc_centroids(vs_ivfpq* ix, int kind, size_t bytes) {
-  const size_t own = align_up(bytes), more = mscan_index_bytes(kind, ix->g);
-  if (more != 0) {
-    if (hipMalloc(reinterpret_cast<void**>(&ix->centroids), own + more) == hipSuccess) {
-      ix->ms_mem = reinterpret_cast<char*>(ix->centroids) + own;
-      return hipSuccess;
-    }
+  const bool planes = mfma_knn_supported(ix->g.d, 1);
+  const size_t at = align_up(bytes), own = at + (planes ? align_up(planes_bytes(ix->g.nlist, ix->g.d)) : 0);
+  size_t more = planes ? mscan_index_bytes(kind, ix->g) : 0;
+  hipError_t e = hipMalloc(reinterpret_cast<void**>(&ix->centroids), own + more);
+  if (e != hipSuccess && more != 0) {
     (void)hipGetLastError();
+    more = 0;
+    e = hipMalloc(reinterpret_cast<void**>(&ix->centroids), own);
   }
-  return hipMalloc(reinterpret_cast<void**>(&ix->centroids), bytes);
+  if (e != hipSuccess) return e;
+  char* base = reinterpret_cast<char*>(ix->centroids);
+  if (planes) {
+    ix->c_planes = carve_planes(base + at, ix->g.nlist, ix->g.d);
+    ix->has_planes = true;
+  }
+  if (more != 0) ix->ms_mem = base + own;
+  return hipSuccess;
 }
 
 // After an index's preparation has completed: what the host wants to know of its centroids (learn_planes), and whether
@@ -1042,7 +1050,7 @@ int vs_ivfpq_create(vs_ivfpq** out, int32_t d, int32_t metric, int32_t nlist, in
   TRY_C(hipGetDevice(&ix->device));
   const size_t cb = (size_t)nlist * d * sizeof(float);
   const size_t tb = (size_t)M * ix->g.K * ix->g.dsub * sizeof(float);
-  TRY_C(mfma_knn_supported(d, 1) ? alloc_centroids(ix, kMsPq, cb) : hipMalloc(reinterpret_cast<void**>(&ix->centroids), cb));
+  TRY_C(alloc_centroids(ix, kMsPq, cb));
   // (the codebooks twice: [M, K, dsub] as given, and behind it [K, M, dsub], the order in which the
   // per-query tables of the wavefront-private scan are computed)
   TRY_C(hipMalloc(reinterpret_cast<void**>(&ix->codebooks), 2 * tb));
@@ -1053,13 +1061,10 @@ int vs_ivfpq_create(vs_ivfpq** out, int32_t d, int32_t metric, int32_t nlist, in
   TRY_C(hipMalloc(reinterpret_cast<void**>(&ix->cnorm), (size_t)nlist * sizeof(float)));
   launch_row_norms(ix->centroids, nlist, d, ix->cnorm, st);
   TRY_C(hipMemsetAsync(ix->list_off, 0, ((size_t)nlist + 1) * sizeof(int64_t), st));
-  if (mfma_knn_supported(d, 1)) {
-    TRY_C(hipMalloc(&ix->plane_mem, planes_bytes(nlist, d)));
-    ix->c_planes = carve_planes(static_cast<char*>(ix->plane_mem), nlist, d);
+  if (ix->has_planes) {
     launch_prep(ix->centroids, nlist, d, ix->c_planes.hi, ix->c_planes.lo, ix->c_planes.norm,
                 ix->c_planes.info, st, true);
     ix->c_planes.try_heads_only = true;
-    ix->has_planes = true;
     if (ix->ms_mem) launch_mscan_index(kMsPq, ix->g, ix->centroids, ix->codebooks, ix->c_planes.info, ix->ms_mem, st);
   }
   TRY_C(hipStreamSynchronize(st));
@@ -1078,12 +1083,10 @@ static void ivf_free_device_memory(vs_ivfpq* ix) {
   if (ix->codebooks) (void)hipFree(ix->codebooks);
   if (ix->list_off) (void)hipFree(ix->list_off);
   if (ix->codes) (void)hipFree(ix->codes);
-  if (ix->ids) (void)hipFree(ix->ids);
   if (ix->norms) (void)hipFree(ix->norms);
   if (ix->cnorm) (void)hipFree(ix->cnorm);
   if (ix->list_tables) (void)hipFree(ix->list_tables);
   if (ix->ms_units_apart) (void)hipFree(ix->ms_units);
-  if (ix->plane_mem) (void)hipFree(ix->plane_mem);
   ix->scratch.release();
 }
 
@@ -1192,19 +1195,18 @@ int ivf_assign_and_place(vs_ivfpq* ix, const float* x, int64_t n, size_t extra, 
   return VS_OK;
 }
 
-// Installs the grown storage (already filled on the stream) in place of the old one.
+// Installs the grown storage (already filled on the stream; the ids are part of the codes' memory) in place of the old.
 int ivf_commit_storage(vs_ivfpq* ix, uint8_t* codes, int64_t* new_ids, float* new_norms,
                        int64_t total, Placement* pl, hipStream_t st, const char* who) {
   hipError_t e = hipMemcpyAsync(ix->list_off, pl->new_off, pl->h_new.size() * sizeof(int64_t), hipMemcpyDeviceToDevice, st);
   if (e == hipSuccess) e = hipStreamSynchronize(st);
   if (e == hipSuccess) e = hipGetLastError();
   if (e != hipSuccess) {
-    (void)hipFree(codes); (void)hipFree(new_ids);
+    (void)hipFree(codes);
     if (new_norms) (void)hipFree(new_norms);
     return fail(VS_ERR_DEVICE, "%s: %s", who, hipGetErrorString(e));
   }
   if (ix->codes) (void)hipFree(ix->codes);
-  if (ix->ids) (void)hipFree(ix->ids);
   if (ix->norms) (void)hipFree(ix->norms);
   ix->codes = codes; ix->ids = new_ids; ix->norms = new_norms; ix->ntotal = total;
   ix->h_off.swap(pl->h_new);
@@ -1216,8 +1218,10 @@ int ivf_commit_storage(vs_ivfpq* ix, uint8_t* codes, int64_t* new_ids, float* ne
 
 }  // namespace
 
-// entries that a store is longer than its vectors: the matrix-core scan reads blocks of 16
+// Entries that a store is longer than its vectors (the matrix-core scan reads blocks of 16), and where the ids of
+// `total` vectors of `size` bytes lie behind them.
 constexpr int64_t kStorePad = 16;
+static size_t store_ids_at(int64_t total, int size) { return align_up((size_t)(total + kStorePad) * size); }
 
 int vs_ivfpq_add(vs_ivfpq* ix, const float* x, int64_t n, const int64_t* ids, void* hip_stream) {
   if (!ix) return fail(VS_ERR_INVALID_ARG, "vs_ivfpq_add: index is null");
@@ -1244,25 +1248,21 @@ int vs_ivfpq_add(vs_ivfpq* ix, const float* x, int64_t n, const int64_t* ids, vo
 
   const int64_t total = ix->ntotal + n;
   uint8_t* codes = nullptr;
-  int64_t* new_ids = nullptr;
   float* new_norms = nullptr;
-  // The codes, and behind them the codes in the matrix-core scan's order (one allocation: a second one takes the host
-  // about as long as the kernel that fills it).  Above 128 MiB they lie apart, so that they can go when an index outgrows
-  // the memory, and an index that they would leave little memory goes without.  Wherever memory is short the copy is
-  // what is given up: an add succeeds if it would without one.
-  const size_t own = align_up((size_t)(total + kStorePad) * g.code_size);
+  // The codes, their ids, and behind them the codes in the matrix-core scan's order: one allocation (see alloc_centroids).
+  // That copy lies apart where it is above 128 MiB, so that it can go when an index outgrows the memory, and an index
+  // that it would leave little memory goes without.  Wherever memory is short the copy is what is given up: an add
+  // succeeds if it would without one.
+  const size_t ids_at = store_ids_at(total, g.code_size), own = ids_at + align_up((size_t)total * sizeof(int64_t));
   const size_t more = ix->ms_mem ? mscan_units_bytes(g, total) : 0;
   const bool apart = more > (128ull << 20);
   auto allocate = [&](size_t behind) {
     if (hipMalloc(reinterpret_cast<void**>(&codes), own + behind) == hipSuccess &&
-        hipMalloc(reinterpret_cast<void**>(&new_ids), (size_t)total * sizeof(int64_t)) == hipSuccess &&
         (!with_norms || hipMalloc(reinterpret_cast<void**>(&new_norms), (size_t)total * sizeof(float)) == hipSuccess))
       return true;
     (void)hipGetLastError();
     if (codes) (void)hipFree(codes);
-    if (new_ids) (void)hipFree(new_ids);
     codes = nullptr;
-    new_ids = nullptr;
     new_norms = nullptr;
     return false;
   };
@@ -1278,6 +1278,7 @@ int vs_ivfpq_add(vs_ivfpq* ix, const float* x, int64_t n, const int64_t* ids, vo
     room = allocate(0);
   }
   if (!room) return fail(VS_ERR_OOM, "vs_ivfpq_add: code / id / norm storage allocation failed");
+  int64_t* new_ids = reinterpret_cast<int64_t*>(codes + ids_at);
   launch_relayout(g, ix->codes, ix->ids, ix->norms, ix->ntotal, ix->list_off, pl.new_off, tmp_codes,
                   ids, ix->ntotal, tmp_norms, pl.dest, pl.list_of, n, codes, new_ids, new_norms, st);
   if (apart) {
@@ -1700,17 +1701,14 @@ int vs_ivfflat_create(vs_ivfflat** out, int32_t d, int32_t metric, int32_t nlist
   } while (0)
   TRY_C(hipGetDevice(&ix->device));
   const size_t cb = (size_t)nlist * d * sizeof(float);
-  TRY_C(mfma_knn_supported(d, 1) ? alloc_centroids(ix, kMsFlat, cb) : hipMalloc(reinterpret_cast<void**>(&ix->centroids), cb));
+  TRY_C(alloc_centroids(ix, kMsFlat, cb));
   TRY_C(hipMalloc(reinterpret_cast<void**>(&ix->list_off), ((size_t)nlist + 1) * sizeof(int64_t)));
   TRY_C(hipMemcpyAsync(ix->centroids, centroids, cb, hipMemcpyDeviceToDevice, st));
   TRY_C(hipMemsetAsync(ix->list_off, 0, ((size_t)nlist + 1) * sizeof(int64_t), st));
-  if (mfma_knn_supported(d, 1)) {
-    TRY_C(hipMalloc(&ix->plane_mem, planes_bytes(nlist, d)));
-    ix->c_planes = carve_planes(static_cast<char*>(ix->plane_mem), nlist, d);
+  if (ix->has_planes) {
     launch_prep(ix->centroids, nlist, d, ix->c_planes.hi, ix->c_planes.lo, ix->c_planes.norm,
                 ix->c_planes.info, st, true);
     ix->c_planes.try_heads_only = true;
-    ix->has_planes = true;
     if (ix->ms_mem) launch_mscan_index(kMsFlat, ix->g, ix->centroids, nullptr, ix->c_planes.info, ix->ms_mem, st);
   }
   TRY_C(hipStreamSynchronize(st));
@@ -1741,12 +1739,9 @@ int vs_ivfflat_add(vs_ivfflat* fx, const float* x, int64_t n, const int64_t* ids
   if (int rc = ivf_assign_and_place(ix, x, n, 0, &pl, st, "vs_ivfflat_add")) return rc;
   const int64_t total = ix->ntotal + n;
   uint8_t* rows = nullptr;
-  int64_t* new_ids = nullptr;
-  HIP_TRY(hipMalloc(reinterpret_cast<void**>(&rows), (size_t)(total + kStorePad) * g.code_size));
-  if (hipMalloc(reinterpret_cast<void**>(&new_ids), (size_t)total * sizeof(int64_t)) != hipSuccess) {
-    (void)hipFree(rows);
-    return fail(VS_ERR_OOM, "vs_ivfflat_add: id storage allocation failed");
-  }
+  const size_t ids_at = store_ids_at(total, g.code_size);
+  HIP_TRY(hipMalloc(reinterpret_cast<void**>(&rows), ids_at + (size_t)total * sizeof(int64_t)));
+  int64_t* new_ids = reinterpret_cast<int64_t*>(rows + ids_at);
   launch_ivfflat_relayout(g.d, g.nlist, reinterpret_cast<const float*>(ix->codes), ix->ids, ix->ntotal,
                           ix->list_off, pl.new_off, x, ids, ix->ntotal, pl.dest, n,
                           reinterpret_cast<float*>(rows), new_ids, st);
@@ -1876,7 +1871,7 @@ int vs_ivfsq8_create(vs_ivfsq8** out, int32_t d, int32_t metric, int32_t nlist,
   } while (0)
   TRY_C(hipGetDevice(&ix->device));
   const size_t cb = (size_t)nlist * d * sizeof(float), pb = (size_t)d * sizeof(float);
-  TRY_C(mfma_knn_supported(d, 1) ? alloc_centroids(ix, kMsSq8, cb) : hipMalloc(reinterpret_cast<void**>(&ix->centroids), cb));
+  TRY_C(alloc_centroids(ix, kMsSq8, cb));
   TRY_C(hipMalloc(reinterpret_cast<void**>(&ix->list_off), ((size_t)nlist + 1) * sizeof(int64_t)));
   TRY_C(hipMalloc(reinterpret_cast<void**>(&sx->vmin), pb));
   TRY_C(hipMalloc(reinterpret_cast<void**>(&sx->step), pb));
@@ -1884,13 +1879,10 @@ int vs_ivfsq8_create(vs_ivfsq8** out, int32_t d, int32_t metric, int32_t nlist,
   TRY_C(hipMemcpyAsync(sx->vmin, vmin, pb, hipMemcpyDeviceToDevice, st));
   TRY_C(hipMemcpyAsync(sx->step, step, pb, hipMemcpyDeviceToDevice, st));
   TRY_C(hipMemsetAsync(ix->list_off, 0, ((size_t)nlist + 1) * sizeof(int64_t), st));
-  if (mfma_knn_supported(d, 1)) {
-    TRY_C(hipMalloc(&ix->plane_mem, planes_bytes(nlist, d)));
-    ix->c_planes = carve_planes(static_cast<char*>(ix->plane_mem), nlist, d);
+  if (ix->has_planes) {
     launch_prep(ix->centroids, nlist, d, ix->c_planes.hi, ix->c_planes.lo, ix->c_planes.norm,
                 ix->c_planes.info, st, true);
     ix->c_planes.try_heads_only = true;
-    ix->has_planes = true;
     if (ix->ms_mem) launch_mscan_index(kMsSq8, ix->g, ix->centroids, nullptr, ix->c_planes.info, ix->ms_mem, st);
   }
   TRY_C(hipStreamSynchronize(st));
@@ -1925,12 +1917,9 @@ int vs_ivfsq8_add(vs_ivfsq8* sx, const float* x, int64_t n, const int64_t* ids, 
   launch_sq8_encode(x, n, g.d, sx->vmin, sx->step, tmp_codes, st);
   const int64_t total = ix->ntotal + n;
   uint8_t* codes = nullptr;
-  int64_t* new_ids = nullptr;
-  HIP_TRY(hipMalloc(reinterpret_cast<void**>(&codes), (size_t)(total + kStorePad) * g.code_size));
-  if (hipMalloc(reinterpret_cast<void**>(&new_ids), (size_t)total * sizeof(int64_t)) != hipSuccess) {
-    (void)hipFree(codes);
-    return fail(VS_ERR_OOM, "vs_ivfsq8_add: id storage allocation failed");
-  }
+  const size_t ids_at = store_ids_at(total, g.code_size);
+  HIP_TRY(hipMalloc(reinterpret_cast<void**>(&codes), ids_at + (size_t)total * sizeof(int64_t)));
+  int64_t* new_ids = reinterpret_cast<int64_t*>(codes + ids_at);
   launch_relayout(g, ix->codes, ix->ids, nullptr, ix->ntotal, ix->list_off, pl.new_off, tmp_codes,
                   ids, ix->ntotal, nullptr, pl.dest, pl.list_of, n, codes, new_ids, nullptr, st);
   return ivf_commit_storage(ix, codes, new_ids, nullptr, total, &pl, st, "vs_ivfsq8_add");

@@ -1237,8 +1237,13 @@ __global__ __launch_bounds__(512) void ms_codebook_kernel(const float* __restric
   __shared__ u32 part_max[8];
   const int total = M * K * dsub;
   u32 mx = 0;
+  // (four at a time, M is a multiple of four: read one by one this was half of the kernel's 9 us at 4096 x 128)
 #pragma unroll 8
-  for (int i = threadIdx.x; i < total; i += 512) mx = max(mx, __float_as_uint(codebooks[i]) & 0x7FFFFFFFu);
+  for (int i = threadIdx.x; i < total / 4; i += 512) {
+    const u32x4 v = reinterpret_cast<const u32x4*>(codebooks)[i];
+#pragma unroll
+    for (int t = 0; t < 4; ++t) mx = max(mx, v[t] & 0x7FFFFFFFu);
+  }
   for (int o = 32; o > 0; o >>= 1) mx = max(mx, (u32)__shfl_xor((int)mx, o, 64));
   if ((threadIdx.x & 63) == 0) part_max[threadIdx.x >> 6] = mx;
   __syncthreads();
@@ -1266,12 +1271,16 @@ __global__ __launch_bounds__(512) void ms_codebook_kernel(const float* __restric
 }
 
 // Codes of the list-contiguous store into units (see PqSide): a wavefront per eight units, a lane per (code, lane row).
-// The first unit's list is found by steps of 64 candidates at a time, the next ones are it or its successor (a list
-// has at least one unit number of its own).  Entries past a list's end repeat the store's first code.
+// The first unit's list is found by steps of 64 candidates at a time; a list has at least one unit number of its own, so
+// that the other units' lists are among the 64 from there on, whose offsets one load brings.  The eight units then wait
+// for memory together.  Entries past a list's end repeat the store's first code.
 constexpr int kUnitsPerWave = 8;
+template <int CBP>
 __global__ __launch_bounds__(256) void ms_units_kernel(const uint8_t* __restrict__ codes, const int64_t* __restrict__ list_off,
-                                                       int nlist, int cs, int cby, int cbp, int rot_m, int64_t units,
+                                                       int nlist, int cs, int cby, int rot_m, int64_t units,
                                                        uint8_t* __restrict__ out) {
+  constexpr int NW = CBP >= 4 ? CBP / 4 : 1;                    // words of a code in a lane
+  constexpr int UNROLL = CBP <= 4 ? kUnitsPerWave : 2;
   const int lane = lane_id(), col = lane & 15, g = lane >> 4;
   const int64_t unit0 = ((int64_t)blockIdx.x * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6)) * kUnitsPerWave;
   if (unit0 >= units) return;
@@ -1282,26 +1291,38 @@ __global__ __launch_bounds__(256) void ms_units_kernel(const uint8_t* __restrict
     lo += ((int)__popcll(__builtin_amdgcn_ballot_w64(before)) - 1) * step;
     hi = min(hi, lo + step);
   }
-  const int nw = max(1, cbp / 4), words = cs / 4;
+  const u32 off = (u32)list_off[min(lo + lane, nlist)];         // lane i: where list lo + i begins
+  const int64_t first = lo + lane < nlist ? (int64_t)(off >> 5) + lo + lane : units;   // ... and its first unit
+  const int words = cs / 4;
+#pragma unroll UNROLL
   for (int u = 0; u < kUnitsPerWave; ++u) {
     const int64_t unit = unit0 + u;
     if (unit >= units) return;
-    if (lo + 1 < nlist && (list_off[lo + 1] >> 5) + lo + 1 <= unit) ++lo;
-    const int64_t lb = list_off[lo], le = list_off[lo + 1];
+    const int l = (int)__popcll(__builtin_amdgcn_ballot_w64(first <= unit)) - 1;       // (below 8, and lo + l below nlist)
+    const u32 lb = (u32)__builtin_amdgcn_readlane((int)off, l), le = (u32)__builtin_amdgcn_readlane((int)off, l + 1);
+    u32 v[2][NW];
+#pragma unroll
     for (int block = 0; block < 2; ++block) {
-      const int64_t rel = (unit - (lb >> 5) - lo) * 32 + 16 * block + col;
+      const int64_t rel = (unit - (lb >> 5) - lo - l) * 32 + 16 * block + col;
       const u32* src = reinterpret_cast<const u32*>(codes + (lb + rel < le ? lb + rel : 0) * cs);
       // stored byte b of the code at list position p is c_{(b + p) mod M} where the codes are rotated
       const int o = rot_m ? (int)(((int64_t)g * cby - rel) & (rot_m - 1)) : g * cby;
-      uint8_t* dst = out + ((unit * 64 + lane) * 2 + block) * cbp;
-      for (int w = 0; w < nw; ++w) {
+#pragma unroll
+      for (int w = 0; w < NW; ++w) {
         int i0 = (o >> 2) + w, i1 = i0 + 1;
         if (rot_m) { i0 &= words - 1; i1 &= words - 1; }
         else { i0 = min(i0, words - 1); i1 = min(i1, words - 1); }   // (bytes past the code's end are not used)
-        const u32 v = __builtin_amdgcn_alignbyte(src[i1], src[i0], (u32)(o & 3));
-        if (cbp == 2) *reinterpret_cast<unsigned short*>(dst) = (unsigned short)v;
-        else *reinterpret_cast<u32*>(dst + 4 * w) = v;
+        v[block][w] = __builtin_amdgcn_alignbyte(src[i1], src[i0], (u32)(o & 3));
       }
+    }
+    uint8_t* dst = out + (unit * 64 + lane) * (2 * CBP);
+    if constexpr (CBP == 2) *reinterpret_cast<u32*>(dst) = (v[0][0] & 0xFFFFu) | (v[1][0] << 16);
+    else if constexpr (CBP == 4) *reinterpret_cast<u32x2*>(dst) = u32x2{v[0][0], v[1][0]};
+    else {
+#pragma unroll
+      for (int w = 0; w < 2 * NW; w += 4)
+        *reinterpret_cast<u32x4*>(dst + 4 * w) = u32x4{v[w / NW][w % NW], v[(w + 1) / NW][(w + 1) % NW],
+                                                       v[(w + 2) / NW][(w + 2) % NW], v[(w + 3) / NW][(w + 3) % NW]};
     }
   }
 }
@@ -1409,9 +1430,12 @@ size_t mscan_units_bytes(const IvfpqDims& g, int64_t ntotal) {
 void launch_mscan_units(const IvfpqDims& g, const uint8_t* codes, const int64_t* list_off, int64_t ntotal, void* out,
                         hipStream_t st) {
   const int64_t units = (ntotal >> 5) + g.nlist + 1;
-  hipLaunchKernelGGL(ms_units_kernel, dim3((unsigned)((units + 4 * kUnitsPerWave - 1) / (4 * kUnitsPerWave))), dim3(256), 0, st, codes, list_off, g.nlist,
-                     g.code_size, g.code_size / 4, pq_lane_bytes(g.code_size / 4), ivfpq_codes_rotated(g) ? g.M : 0, units,
-                     static_cast<uint8_t*>(out));
+  const int cby = g.code_size / 4, rot = ivfpq_codes_rotated(g) ? g.M : 0;
+  const dim3 grid((unsigned)((units + 4 * kUnitsPerWave - 1) / (4 * kUnitsPerWave)));
+#define UNITS(CBP) hipLaunchKernelGGL((ms_units_kernel<CBP>), grid, dim3(256), 0, st, codes, list_off, g.nlist, g.code_size, cby, \
+                                      rot, units, static_cast<uint8_t*>(out))
+  switch (pq_lane_bytes(cby)) { case 2: UNITS(2); break; case 4: UNITS(4); break; case 8: UNITS(8); break; default: UNITS(16); }
+#undef UNITS
 }
 
 void launch_mscan_index(int kind, const IvfpqDims& g, const float* centroids, const float* codebooks, PrepInfo* info,
