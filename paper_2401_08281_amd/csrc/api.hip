@@ -1441,10 +1441,7 @@ bool mscan_chosen(const vs_ivfpq* ix, const MscanIndex& m, int form, int64_t nq,
   const bool pays = m.kind == kMsPq ? visited >= (form == 0 ? 3e6 : 2e7) || (form == 0 && nq * (int64_t)npr >= 8192)
                                     : visited * ((m.g.d + 31) / 32) >= 4e6;
   if (opt == 0 && !pays) return false;
-  // candidates per query: four times what the list-major scan keeps (it only sees those behind the first lists), less
-  // for batches beyond 16,384 queries so that they stay near 1 GiB
-  const int64_t cap = std::max<int64_t>(256, std::min<int64_t>(4 * (int64_t)g_lm_cap.load(), (1ll << 26) / nq));
-  return mscan_plan(m, nq, npr, k, (int)cap, plan) && ix->ms_has_room(plan->bytes);
+  return mscan_plan(m, nq, npr, k, g_lm_cap.load(), plan) && ix->ms_has_room(plan->bytes);
 }
 
 // Work space of one search, carved from one buffer.

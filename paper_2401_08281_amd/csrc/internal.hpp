@@ -171,8 +171,8 @@ bool mscan_scale_fits(int kind, u32 bits);
 size_t mscan_units_bytes(const IvfpqDims& g, int64_t ntotal);
 void launch_mscan_units(const IvfpqDims& g, const uint8_t* codes, const int64_t* list_off, int64_t ntotal, void* out,
                         hipStream_t st);
-// plan of a search of npr probes per query, k results, cap candidates per query; false: not by this scan
-bool mscan_plan(const MscanIndex& ix, int64_t nq, int npr, int k, int cap, MscanPlan* out);
+// plan of a search of npr probes per query and k results (asked: option "list_major_candidates"); false: not by this scan
+bool mscan_plan(const MscanIndex& ix, int64_t nq, int npr, int k, int asked, MscanPlan* out);
 // form: 0 residual tables (or no PQ), 1 inner product, 2 stored norms, 3 precomputed tables.  Parts 0, 1, 2 in
 // turn; then the queries of mscan_rescan are the caller's to scan query by query.
 void launch_mscan(int part, const MscanIndex& ix, const MscanPlan& p, const float* q, const int32_t* probes,

@@ -1237,7 +1237,7 @@ __global__ __launch_bounds__(512) void ms_codebook_kernel(const float* __restric
   __shared__ u32 part_max[8];
   const int total = M * K * dsub;
   u32 mx = 0;
-  // (four at a time, M is a multiple of four: read one by one this was half of the kernel's 9 us at 4096 x 128)
+  // (four at a time, M is a multiple of four; 4096 lists of 128 dimensions, 16 x 8: 9.1 -> 8.0 us)
 #pragma unroll 8
   for (int i = threadIdx.x; i < total / 4; i += 512) {
     const u32x4 v = reinterpret_cast<const u32x4*>(codebooks)[i];
@@ -1273,7 +1273,8 @@ __global__ __launch_bounds__(512) void ms_codebook_kernel(const float* __restric
 // Codes of the list-contiguous store into units (see PqSide): a wavefront per eight units, a lane per (code, lane row).
 // The first unit's list is found by steps of 64 candidates at a time; a list has at least one unit number of its own, so
 // that the other units' lists are among the 64 from there on, whose offsets one load brings.  The eight units then wait
-// for memory together.  Entries past a list's end repeat the store's first code.
+// for memory together (one by one, a million codes of 16 bytes: 13.9 us, now 11.7).  Entries past a list's end repeat the
+// store's first code.
 constexpr int kUnitsPerWave = 8;
 template <int CBP>
 __global__ __launch_bounds__(256) void ms_units_kernel(const uint8_t* __restrict__ codes, const int64_t* __restrict__ list_off,
@@ -1499,18 +1500,31 @@ bool mscan_supported(const MscanIndex& ix, int k) {
 }
 
 // Sizes of a search.  slots: groups of four codes that give a query's threshold; seg: codes of a list per work item.
-bool mscan_plan(const MscanIndex& ix, int64_t nq, int npr, int k, int cap, MscanPlan* out) {
+bool mscan_plan(const MscanIndex& ix, int64_t nq, int npr, int k, int asked, MscanPlan* out) {
   MscanPlan& p = *out;
   if (!mscan_supported(ix, k) || ix.ntotal < 1 || nq < 1 || nq * (int64_t)std::max(npr, 1024) >= (1ll << 32) || ix.max_list < 1)
     return false;
   const MsShape s = ms_shape(ix.kind, ix.g);
-  p.nq = nq; p.npr = npr; p.cap = cap;
+  p.nq = nq; p.npr = npr;
   const int64_t np = nq * npr;
   p.slots = k <= 16 ? 128 : (k <= 32 ? 256 : (k <= 64 ? 512 : 1024));
   p.capcodes = (u32)p.slots * 4u;
+  // Candidates per query: four times what the list-major scan keeps (it only sees those behind the first lists), less
+  // for batches beyond 16,384 queries so that they stay near 1 GiB.  A query whose buffer overflows is scanned again, and
+  // where nothing tells the probed lists apart -- unstructured data -- the threshold lets k of `capcodes` vectors
+  // pass and the error bounds about as many again: that much is kept too as far as 1 GiB goes, and whatever 256 MB
+  // hold (12 million Gaussian vectors, 64 lists of 1465, 32 x 4 bits, k = 100: 40 queries 2123 us with 4096 candidates
+  // each, 574 with all of them, 431 query-major; 256 queries 2455, 714, 818).  Not where fewer than the default are
+  // asked for.  No query has more candidates than its lists have vectors.
+  const int64_t mean = (ix.ntotal + ix.g.nlist - 1) / ix.g.nlist, visited = npr * mean;
+  int64_t cap = std::max<int64_t>(256, std::min<int64_t>(4ll * asked, (1ll << 26) / nq));
+  if (asked >= 1024) {
+    cap = std::max(cap, std::min<int64_t>(2 * k * visited / p.capcodes, (1ll << 26) / nq));
+    cap = std::max<int64_t>(cap, (1ll << 24) / nq);
+  }
+  p.cap = (int)std::max<int64_t>(256, std::min<int64_t>(cap, (npr * ix.max_list + 63) / 64 * 64));
   // (short segments where there would be few work items for 2048 and more wavefronts, long ones to spread an item's
   // set-up)
-  const int64_t mean = (ix.ntotal + ix.g.nlist - 1) / ix.g.nlist;
   int64_t seg = std::min<int64_t>(np, ix.g.nlist) * ((mean + 511) / 512) < 32768 ? 256 : 1024;
   const int64_t group = 16 * s.nt, lists = std::min<int64_t>(np, ix.g.nlist);
   const int64_t first = std::min<int64_t>(npr, p.slots / 16);    // pairs of a query in the bound sweep, at most
@@ -1525,7 +1539,8 @@ bool mscan_plan(const MscanIndex& ix, int64_t nq, int npr, int k, int cap, Mscan
   p.seg = (u32)seg;
   p.max_a = (u32)max_a;
   p.max_b = (u32)max_b;
-  p.surv = (u32)std::min<int64_t>(nq * std::min(cap, 4 * k + 128), 1ll << 30);
+  // survivors of all queries: 4 k + 128 of each, and 84 MB at least
+  p.surv = (u32)std::min<int64_t>(std::min<int64_t>(nq * p.cap, std::max<int64_t>(nq * (4 * k + 128), 1 << 22)), 1ll << 30);
   p.bytes = ms_layout(ix, p).bytes;
   return true;
 }
@@ -1704,7 +1719,8 @@ void launch_mscan(int part, const MscanIndex& ix, const MscanPlan& p, const floa
       lds = pq_eval_bytes(ix.g.M, ix.g.K, ix.g.dsub, pq_lanes(ix.g.M), B.batch);
       if (lds <= 160 * 1024) break;
     }
-    const int64_t most = std::min<int64_t>((p.nq * k + 8 * B.batch - 1) / (8 * B.batch) + 1, 256ll * (160 * 1024 / lds));
+    // (as many workgroups as the list could keep busy: those without a survivor leave before they stage the codebook)
+    const int64_t most = std::min<int64_t>(((int64_t)p.surv + 8 * B.batch - 1) / (8 * B.batch), 256ll * (160 * 1024 / lds));
 #define RK(LPC, DS, NB, ROT)                                                                                       \
     do {                                                                                                           \
       auto kern = &ms_eval_pq_kernel<LPC, DS, NB, ROT>;                                                            \

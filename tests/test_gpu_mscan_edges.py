@@ -43,17 +43,17 @@ def both_scans(vs, ix, q, k, nprobe, tell=""):
 @pytest.mark.parametrize("d,M,nbits", [(128, 16, 8), (100, 20, 8), (64, 32, 4)])
 @pytest.mark.parametrize("what", ["equal vectors", "queries that are not finite"])
 def test_survivors_beyond_their_list(vs, d, M, nbits, what):
-    """More survivors per query than their common list has room for on average, 4 k + 128, and fewer than a query's own
-    buffer holds; behind a larger search, whose values lie where the list is."""
+    """More survivors than their common list has room for, 4 k + 128 per query and 4 million at least, and fewer of a query
+    than its own buffer holds; behind another search, whose values lie where the list is."""
     rng = np.random.default_rng(d)
-    k, nprobe, nq = 10, 8, 200
+    k, nprobe, nq = 10, 8, 20_000
     cent, x = lists_of(rng, d, [60] * 24)
     if what == "equal vectors":
         x = np.repeat(x[rng.permutation(len(x))[:24]], 300, axis=0)       # every vector 300 times
     ix = make(vs, "pq", d, M, nbits, L2, cent, x, rng)
     try:
         ix.add(dev(x))
-        other = (x[rng.integers(0, len(x), 777)] + 20 * rng.standard_normal((777, d))).astype(np.float32)
+        other = (x[rng.integers(0, len(x), 7777)] + 20 * rng.standard_normal((7777, d))).astype(np.float32)
         q = (x[rng.integers(0, len(x), nq)] + 0.1 * rng.standard_normal((nq, d))).astype(np.float32)
         if what != "equal vectors":
             q[:, 3] = np.where(np.arange(nq) % 2, np.nan, np.inf)
@@ -61,7 +61,7 @@ def test_survivors_beyond_their_list(vs, d, M, nbits, what):
         both_scans(vs, ix, dev(other), 100, 24)
         both_scans(vs, ix, dev(q), k, nprobe)
         n = ix.search_stats(dev(q), k, nprobe)[2]["list_major_rescanned"]
-        assert 0 < n <= nq, n        # (some had no room and were scanned again)
+        assert 0 < n < nq, n         # (some had no room and were scanned again)
     finally:
         ix.close()
 
@@ -242,5 +242,22 @@ def test_an_add_that_has_no_room_for_the_copy_of_the_codes(vs):
         n_first = vs.vs_profile_read()["scan_first"][1]
         vs.vs_profile_enable(0)
         assert n_first
+    finally:
+        ix.close()
+
+
+@pytest.mark.parametrize("nq,k,nprobe", [(40, 100, 64), (256, 10, 64), (1000, 100, 32)])
+def test_unstructured_data_is_not_scanned_twice(vs, nq, k, nprobe):
+    """Gaussian vectors and queries, coarse codes: the first lists of a query are no nearer than the others, and several
+    thousand vectors of each query pass the threshold.  Their buffers hold them."""
+    g = torch.Generator(device="cuda").manual_seed(1)
+    x = torch.randn((300_000, 64), generator=g, device="cuda")
+    cb = torch.randn((32, 16, 2), generator=g, device="cuda") * 0.8
+    q = torch.randn((nq, 64), generator=g, device="cuda")
+    ix = vs.IVFPQ(64, L2, x[:64].contiguous(), cb, nbits=4)
+    try:
+        ix.add(x)
+        both_scans(vs, ix, q, k, nprobe)
+        assert ix.search_stats(q, k, nprobe)[2]["list_major_rescanned"] == 0
     finally:
         ix.close()
