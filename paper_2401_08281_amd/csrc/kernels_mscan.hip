@@ -1512,15 +1512,16 @@ bool mscan_plan(const MscanIndex& ix, int64_t nq, int npr, int k, int asked, Msc
   // Candidates per query: four times what the list-major scan keeps (it only sees those behind the first lists), less
   // for batches beyond 16,384 queries so that they stay near 1 GiB.  A query whose buffer overflows is scanned again, and
   // where nothing tells the probed lists apart -- unstructured data -- the threshold lets k of `capcodes` vectors
-  // pass and the error bounds about as many again: that much is kept too as far as 1 GiB goes, and whatever 256 MB
-  // hold (12 million Gaussian vectors, 64 lists of 1465, 32 x 4 bits, k = 100: 40 queries 2123 us with 4096 candidates
-  // each, 574 with all of them, 431 query-major; 256 queries 2455, 714, 818).  Not where fewer than the default are
-  // asked for.  No query has more candidates than its lists have vectors.
-  const int64_t mean = (ix.ntotal + ix.g.nlist - 1) / ix.g.nlist, visited = npr * mean;
+  // pass, `likely` of all that a query visits, and the error bounds two or three times that: four times it is kept as
+  // far as 1 GiB goes, and eight times what it is for lists of the longest one's length as far as 128 MB go.
+  // (12 million Gaussian vectors, 64 lists of 1465, 32 x 4 bits, k = 100: 40 queries 2123 us with 4096 candidates each,
+  // 574 with room for them, 431 query-major; 256 queries 2455, 714, 818.)  Not where fewer than the default are asked
+  // for.  No query has more candidates than its lists have vectors.
+  const int64_t mean = (ix.ntotal + ix.g.nlist - 1) / ix.g.nlist, likely = k * npr * mean / p.capcodes;
   int64_t cap = std::max<int64_t>(256, std::min<int64_t>(4ll * asked, (1ll << 26) / nq));
   if (asked >= 1024) {
-    cap = std::max(cap, std::min<int64_t>(2 * k * visited / p.capcodes, (1ll << 26) / nq));
-    cap = std::max<int64_t>(cap, (1ll << 24) / nq);
+    cap = std::max(cap, std::min<int64_t>(4 * likely, (1ll << 26) / nq));
+    cap = std::max(cap, std::min<int64_t>(8 * k * npr * ix.max_list / p.capcodes, (1ll << 23) / nq));
   }
   p.cap = (int)std::max<int64_t>(256, std::min<int64_t>(cap, (npr * ix.max_list + 63) / 64 * 64));
   // (short segments where there would be few work items for 2048 and more wavefronts, long ones to spread an item's
@@ -1539,8 +1540,8 @@ bool mscan_plan(const MscanIndex& ix, int64_t nq, int npr, int k, int asked, Msc
   p.seg = (u32)seg;
   p.max_a = (u32)max_a;
   p.max_b = (u32)max_b;
-  // survivors of all queries: 4 k + 128 of each, and 84 MB at least
-  p.surv = (u32)std::min<int64_t>(std::min<int64_t>(nq * p.cap, std::max<int64_t>(nq * (4 * k + 128), 1 << 22)), 1ll << 30);
+  // survivors of all queries: 4 k + 128 of each, and half a million (10 MB) at least
+  p.surv = (u32)std::min<int64_t>(std::min<int64_t>(nq * p.cap, std::max<int64_t>(nq * (4 * k + 128), 1 << 19)), 1ll << 30);
   p.bytes = ms_layout(ix, p).bytes;
   return true;
 }

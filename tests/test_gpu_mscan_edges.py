@@ -43,7 +43,7 @@ def both_scans(vs, ix, q, k, nprobe, tell=""):
 @pytest.mark.parametrize("d,M,nbits", [(128, 16, 8), (100, 20, 8), (64, 32, 4)])
 @pytest.mark.parametrize("what", ["equal vectors", "queries that are not finite"])
 def test_survivors_beyond_their_list(vs, d, M, nbits, what):
-    """More survivors than their common list has room for, 4 k + 128 per query and 4 million at least, and fewer of a query
+    """More survivors than their common list has room for, 4 k + 128 per query and half a million at least, and fewer of a query
     than its own buffer holds; behind another search, whose values lie where the list is."""
     rng = np.random.default_rng(d)
     k, nprobe, nq = 10, 8, 20_000
