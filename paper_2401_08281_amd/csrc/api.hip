@@ -1425,22 +1425,54 @@ int table_form(const vs_ivfpq* ix) {
   if (ix->search_type == VS_ST_STORED_NORMS && ix->norms) return 2;
   return ix->search_type == VS_ST_PRECOMPUTED_TABLES && ix->list_tables ? 3 : 0;
 }
-// Whether a search goes through the matrix-core scan.  Its ten or so launches and the sorting of the pairs take some
-// 70 us more than the query-major scan of a small problem, its cost per visited vector is a small part of that scan's.
-// Measured, query-major -> matrix cores:
-//   residual tables (built for every pair by the query-major scan): 2752 pairs 105 -> 123 us, 4239 pairs 109 -> 144,
-//   7992 pairs and 4.0e6 vectors visited 264 -> 194, 14,058 pairs 277 -> 164, 22,960 pairs 277 -> 175;
-//   tables per query (inner product, stored norms, precomputed): 6.4e6 vectors visited 218 -> 204, 6.7e6 200 -> 217,
-//   1.3e7 185 -> 177, 2.2e7 301 -> 299, 2.3e7 750 -> 418, 4.3e7 822 -> 341;
-//   raw vectors and scalar codes by 32-dimension steps: 7.6e5 109 -> 146, 1.0e6 93 -> 93, 1.6e6 72 -> 103, 1.0e7 438 ->
-//   344, 1.3e7 351 -> 163.
+// Whether the matrix-core scan is the faster one for a batch.  Its ten or so launches and the sorting of the pairs take
+// some 70 us more than the query-major scan of a small problem, and it decodes every probed list once per 16 to 64 queries:
+// what it gains grows with the queries that share a list (pairs per list), and its first sweep, over the lists that
+// bound a query's distances, is a second pass over everything where few lists are probed.  The query-major scan pays per
+// pair (a table each with residual tables), per vector visited and per value that passes its threshold (k).
+// Measured over 2000 batches (indexes of 2e4 to 1.2e7 vectors, k = 1, 10, 100, 1 to 64 probes, 1 to 10,000 queries),
+// query-major -> matrix cores in us:
+//   residual tables, 8-bit codes.  32 x 8, lists of 1465: 0.5 pairs per list 203 -> 255, 2 480 -> 601, 4 with 16 probes
+//     437 -> 300; lists of 122: 1 pair 241 -> 280, 2 with 16 probes 238 -> 202; 100 results, 16 probes or more, 0.5 pairs
+//     276 -> 236.  16 x 8, lists of 1465: 2 pairs 256 -> 324, 16 probes or more 1.3 times as fast at 1.  8 x 8,
+//     lists of 1465: 0.3 pairs 161 -> 251, 0.5 232 -> 200.
+//   tables per query, 8-bit codes: 2 pairs per list of 1465 325 -> 411, 8 889 -> 463; 4 probes and 4 pairs per list
+//     449 -> 677 (but 16 x 8, inner product: 723 -> 388).  The short-list kernels of 8 x 8 and 16 x 8 hold out longer: 8 x 8,
+//     inner product, lists of 195 198 -> 252 at 5e7 vectors visited, of 488 1076 -> 537 at 1.3e8; stored norms
+//     of 16 x 8, lists of 244, k = 10 353 -> 339 at 6.4e7, 636 -> 512 at 1.6e8, k = 100 441 -> 580 at 3.9e7, 745 -> 731 at 1.6e8, of
+//     98 458 -> 521 at 6.2e7; precomputed tables from 2.4e7 on, 623 -> 393 at 3.9e7.
+//   4-bit codes: 0.3 pairs per list of 1465 326 -> 389, 2 1109 -> 605; 1 million of them, 2e7 visited 750 -> 418.
+//   raw vectors (by 32-dimension steps): 7.6e5 visited 109 -> 146, 4e6 where 1 pair probes a list of 244, 4 probes, 357 ->
+//     464, with 64 probes 286 -> 277, at k = 100 684 -> 494; dimensions that are no multiple of 32 2978 -> 240.
+//     Inner products of vectors of uneven norm crowd into few lists: 745 -> 321 at 2 pairs per list on average.
+//   scalar codes (the query-major scan reads a quarter of the bytes): 96 dimensions, 1.6 pairs per list of 1000 69 ->
+//     108, 5 146 -> 130; 128 dimensions, 16 probes, 1 pair per list of 244 1.1 times as fast; 100 dimensions as raw
+//     vectors.
+bool mscan_pays(const MscanIndex& m, int form, int64_t nq, int npr, int k) {
+  const IvfpqDims& g = m.g;
+  const double pairs = (double)nq * npr, shared = pairs / g.nlist, mean = (double)m.ntotal / g.nlist, visited = pairs * mean;
+  if (m.kind != kMsPq) {
+    if (visited * ((g.d + 31) / 32) < 4e6) return false;
+    if (g.d % 32 != 0) return true;
+    if (m.kind == kMsFlat) return g.metric == VS_METRIC_IP || k > 16 || npr > 16 || shared >= 1.7;
+    return shared >= 5 || (npr >= 16 && ((k > 16 && shared >= 1.5) || (g.d >= 128 && mean <= 300 && shared >= 1)));
+  }
+  if (form == 0 ? visited < 3e6 && pairs < 8192 : visited < 2e7) return false;
+  if (g.nbits == 4) return true;
+  const double enough = 3.0 / 32.0 * g.M;                        // pairs per long list
+  if (form == 0)
+    return shared >= enough || (mean <= 800 && shared >= 0.5 * enough) ||
+           (npr >= 16 && ((k > 16 && shared >= 0.3) || (g.M <= 16 && shared >= 0.5)));
+  const bool wave = ivfpq_wave_scan_applies(g, m.ntotal);        // the short-list kernels
+  if (form == 3) return wave || shared >= enough || npr >= 16;
+  if (wave && form == 1) return g.M == 16 || mean >= 400;
+  if (wave) return g.M == 8 || mean >= 400 || (mean >= 200 && visited >= (k <= 16 ? 5e7 : 1.5e8));
+  return shared >= enough && (npr >= 8 || shared >= 8 || g.M <= 8 || (g.M == 16 && form == 1));
+}
+// Whether a search goes through it.
 bool mscan_chosen(const vs_ivfpq* ix, const MscanIndex& m, int form, int64_t nq, int npr, int k, MscanPlan* plan) {
   const int opt = g_matrix_scan.load();
-  if (opt < 0 || g_list_major.load() == 1) return false;
-  const double visited = (double)nq * npr * ((double)m.ntotal / m.g.nlist);
-  const bool pays = m.kind == kMsPq ? visited >= (form == 0 ? 3e6 : 2e7) || (form == 0 && nq * (int64_t)npr >= 8192)
-                                    : visited * ((m.g.d + 31) / 32) >= 4e6;
-  if (opt == 0 && !pays) return false;
+  if (opt < 0 || g_list_major.load() == 1 || (opt == 0 && !mscan_pays(m, form, nq, npr, k))) return false;
   return mscan_plan(m, nq, npr, k, g_lm_cap.load(), plan) && ix->ms_has_room(plan->bytes);
 }
 

@@ -261,3 +261,38 @@ def test_unstructured_data_is_not_scanned_twice(vs, nq, k, nprobe):
         assert ix.search_stats(q, k, nprobe)[2]["list_major_rescanned"] == 0
     finally:
         ix.close()
+
+
+# (kind, nlist, queries, k, probes, whether the lists are scanned on the matrix cores): either side of the lines that
+# pairs per list, list length, probes and k draw
+@pytest.mark.parametrize("kind,d,M,nlist,metric,nq,k,nprobe,matrix", [
+    ("pq", 96, 32, 1024, L2, 512, 10, 4, False), ("pq", 96, 32, 1024, L2, 128, 100, 16, True),
+    ("pq", 96, 32, 1024, L2, 800, 10, 4, True), ("pq", 96, 32, 1024, IP, 2600, 10, 4, True),
+    ("pq", 96, 32, 1024, IP, 800, 10, 16, True), ("pq", 128, 16, 8192, IP, 5300, 10, 16, True),
+    ("pq", 32, 8, 8192, IP, 5300, 10, 16, False), ("flat", 96, 0, 1024, L2, 50, 10, 16, False),
+    ("flat", 96, 0, 1024, L2, 50, 100, 16, True), ("flat", 96, 0, 1024, IP, 50, 10, 16, True),
+    ("sq8", 96, 0, 1024, L2, 100, 10, 16, False), ("sq8", 96, 0, 1024, L2, 330, 10, 16, True),
+    ("sq8", 100, 0, 1024, L2, 50, 10, 16, True)])
+def test_lists_of_few_queries_are_scanned_query_by_query(vs, kind, d, M, nlist, metric, nq, k, nprobe, matrix):
+    """Batches large enough for the matrix-core scan whose queries share their lists with too few others (that scan was
+    up to 1.9 times as slow on them)."""
+    n = 2_000_000
+    g = torch.Generator(device="cuda").manual_seed(2)
+    x = torch.randn((n, d), generator=g, device="cuda")
+    cent = x[:nlist].contiguous()
+    if kind == "pq":
+        ix = vs.IVFPQ(d, metric, cent, torch.randn((M, 256, d // M), generator=g, device="cuda"), nbits=8)
+    elif kind == "flat":
+        ix = vs.IVFFlat(d, metric, cent)
+    else:
+        ix = vs.IVFSQ8(d, metric, cent, torch.full((d,), -5.0, device="cuda"), torch.full((d,), 10.0 / 255, device="cuda"))
+    try:
+        ix.add(x)
+        vs.vs_profile_enable(1)
+        vs.vs_profile_read()
+        ix.search(x[:nq].contiguous(), k, nprobe)
+        torch.cuda.synchronize()
+        assert (vs.vs_profile_read()["scan_first"][1] > 0) == matrix
+    finally:
+        vs.vs_profile_enable(0)
+        ix.close()
