@@ -1410,7 +1410,7 @@ int vs_ivfpq_coarse(const vs_ivfpq* ix, const float* q, int64_t nq, int32_t npro
 namespace {
 
 // An index as the matrix-core scan sees it.
-MscanIndex mscan_index(int kind, const vs_ivfpq* ix, const float* vmin = nullptr, const float* step = nullptr) {
+extern "C++" MscanIndex mscan_index(int kind, const vs_ivfpq* ix, const float* vmin = nullptr, const float* step = nullptr) {
   MscanIndex m;
   m.kind = kind; m.g = ix->g; m.ntotal = ix->ntotal; m.max_list = ix->max_list;
   m.centroids = ix->centroids; m.list_off = ix->list_off; m.codes = ix->codes; m.codebooks = ix->codebooks;

@@ -1386,8 +1386,8 @@ int pq_lanes(int M) { return M <= 8 ? 8 : (M <= 16 ? 16 : (M <= 32 ? 32 : 64)); 
 // tables: 48 look-ups per code and lane for 16, 2590 us for 2000 at 262k queries x lists of 1526 codes.)
 #define VS_MS_PQ_FORMS(X)                                                                                   \
   X(2, 1, 8, 8, true) X(4, 1, 16, 8, true) X(8, 1, 8, 8, true)                                              \
-  X(2, 1, 16, 8, false) X(4, 1, 16, 8, false) X(5, 1, 16, 8, false) X(8, 1, 16, 8, false)                   \
-  X(4, 1, 8, 8, false) X(8, 1, 8, 8, false) X(16, 1, 8, 8, false)                                           \
+  X(2, 1, 16, 8, false) X(4, 1, 16, 8, false) X(5, 1, 16, 8, false)                                         \
+  X(4, 1, 8, 8, false) X(8, 1, 8, 8, false)                                                                 \
   X(8, 1, 4, 4, false) X(16, 1, 4, 4, false) X(4, 1, 8, 4, false) X(8, 1, 8, 4, false) X(16, 1, 8, 4, false)
 
 // Whether the data that an index's scale is taken from -- bits of the codebooks' largest magnitude (PQ) or of the
@@ -1607,9 +1607,8 @@ void launch_sweep_any(const MscanIndex& ix, const MsShape& s, const SweepArgs& A
 #undef Y
 }
 
-SweepArgs sweep_args(const MscanIndex& ix, const MscanPlan& p, const MsShape& s, const MsLayout& L, const float* q,
-                     const float* cdist, int form, float eps_scale, char* ws) {
-  (void)q;
+SweepArgs sweep_args(const MscanIndex& ix, const MscanPlan& p, const MsShape& s, const MsLayout& L, const float* cdist,
+                     int form, float eps_scale, char* ws) {
   SweepArgs A;
   A.qperm = reinterpret_cast<float*>(ws + L.o_qperm);
   A.kp = 32 * s.ks; A.npr = p.npr; A.slots = p.slots;
@@ -1651,14 +1650,14 @@ SweepArgs sweep_args(const MscanIndex& ix, const MscanPlan& p, const MsShape& s,
 }  // namespace
 
 // Grouping, bound sweep and thresholds (part 0), collect sweep (part 1), exact evaluation (part 2; the queries that
-// it leaves to the query-major scan are listed: mscan_rescan_list / _count).
+// it leaves to the query-major scan are listed: mscan_rescan).
 void launch_mscan(int part, const MscanIndex& ix, const MscanPlan& p, const float* q, const int32_t* probes,
                   const float* cdist, int form, int k, float eps_scale, char* ws, const int64_t* ids, float* out_dist,
                   int64_t* out_ids, hipStream_t st) {
   const MsShape s = ms_shape(ix.kind, ix.g);
   const MsLayout L = ms_layout(ix, p);
-  SweepArgs A = sweep_args(ix, p, s, L, q, cdist, form, eps_scale, ws);
-  u32* ctr = reinterpret_cast<u32*>(ws + L.o_ctr);   // items of both sweeps, their cursors, queries to scan again
+  SweepArgs A = sweep_args(ix, p, s, L, cdist, form, eps_scale, ws);
+  u32* ctr = reinterpret_cast<u32*>(ws + L.o_ctr);   // items of both sweeps; from 4 on: queries to scan again, survivors, ...
   const int64_t np = p.nq * p.npr;
   if (part == 0) {
     launch_fill_u64(reinterpret_cast<u64*>(ws + L.o_lfirst), (int64_t)(L.zero_bytes / 8), 0ull, st);
@@ -1684,7 +1683,7 @@ void launch_mscan(int part, const MscanIndex& ix, const MscanPlan& p, const floa
     const dim3 grid((unsigned)((p.nq + 3) / 4)), block(256);
 #define BOUND(RR) hipLaunchKernelGGL((ms_bound_kernel<RR>), grid, block, 0, st, A.gmin, qslots, p.nq, p.slots, k, \
                                      reinterpret_cast<float*>(ws + L.o_bound))
-    if (p.slots <= 64) BOUND(1); else if (p.slots <= 128) BOUND(2); else if (p.slots <= 256) BOUND(4); else if (p.slots <= 512) BOUND(8); else BOUND(16);
+    if (p.slots <= 128) BOUND(2); else if (p.slots <= 256) BOUND(4); else if (p.slots <= 512) BOUND(8); else BOUND(16);
 #undef BOUND
     return;
   }
