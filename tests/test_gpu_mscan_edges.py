@@ -296,3 +296,87 @@ def test_lists_of_few_queries_are_scanned_query_by_query(vs, kind, d, M, nlist, 
     finally:
         vs.vs_profile_enable(0)
         ix.close()
+
+
+# every form of VS_MS_PQ_FORMS that test_gpu_mscan does not reach, at the ends of its range of d / M, and the steps of raw
+# vectors and scalar codes between those there
+@pytest.mark.parametrize("kind,d,M,nbits,metric,form,nq,k,nprobe", [
+    ("pq", 40, 8, 8, L2, 1, 333, 10, 9), ("pq", 64, 8, 8, IP, 0, 65, 100, 33), ("pq", 80, 16, 8, L2, 0, 130, 17, 9),
+    ("pq", 112, 16, 8, IP, 0, 333, 1, 9), ("pq", 140, 20, 8, IP, 0, 65, 64, 33), ("pq", 120, 20, 8, L2, 1, 130, 10, 9),
+    ("pq", 48, 16, 8, L2, 0, 65, 128, 64), ("pq", 64, 16, 8, L2, 1, 333, 33, 9), ("pq", 128, 32, 8, L2, 0, 130, 10, 9),
+    ("pq", 128, 32, 8, IP, 0, 65, 65, 33), ("pq", 32, 32, 4, L2, 0, 130, 10, 9), ("pq", 64, 64, 4, IP, 0, 65, 16, 9),
+    ("pq", 128, 64, 4, L2, 1, 333, 100, 33), ("pq", 48, 16, 4, L2, 0, 65, 10, 9), ("pq", 64, 16, 4, IP, 0, 130, 1, 64),
+    ("pq", 96, 32, 4, L2, 1, 65, 64, 9), ("pq", 128, 32, 4, IP, 0, 333, 10, 9), ("pq", 192, 64, 4, L2, 0, 130, 17, 9),
+    ("pq", 256, 64, 4, IP, 0, 65, 128, 33),
+    ("flat", 50, 0, 0, IP, 0, 130, 10, 9), ("flat", 96, 0, 0, L2, 0, 65, 100, 33), ("flat", 160, 0, 0, L2, 0, 333, 1, 9),
+    ("flat", 217, 0, 0, IP, 0, 65, 65, 9), ("sq8", 20, 0, 0, L2, 0, 130, 10, 9), ("sq8", 128, 0, 0, IP, 0, 65, 128, 33),
+    ("sq8", 150, 0, 0, L2, 0, 333, 33, 9), ("sq8", 190, 0, 0, IP, 0, 65, 1, 64), ("sq8", 220, 0, 0, L2, 0, 130, 10, 9)])
+def test_every_form(vs, kind, d, M, nbits, metric, form, nq, k, nprobe):
+    import test_gpu_mscan
+    test_gpu_mscan.test_matrix_scan_equals_query_major(vs, kind, d, M, nbits, metric, form, nq, k, nprobe)
+    rng = np.random.default_rng(d)
+    cent, x = lists_of(rng, d, [50] * 8)
+    ix = make(vs, kind, d, M, nbits, metric, cent, x, rng)
+    try:                                                        # that scan is the one that runs
+        if form:
+            ix.set_search_type(form)
+        ix.add(dev(x))
+        vs.vs_profile_enable(1)
+        vs.vs_profile_read()
+        both_scans(vs, ix, dev(x[:nq]), k, 4)
+        assert vs.vs_profile_read()["scan_first"][1] == 1
+    finally:
+        vs.vs_profile_enable(0)
+        ix.close()
+
+
+@pytest.mark.parametrize("kind,d,M", [("pq", 32, 8), ("pq", 100, 20), ("flat", 40, 0), ("sq8", 64, 0)])
+def test_more_lists_than_a_workgroup_takes(vs, kind, d, M):
+    """The offsets' workgroups take 1024 lists each; most of these are empty or hold a few vectors."""
+    rng = np.random.default_rng(d)
+    cent, x = lists_of(rng, d, list(rng.integers(0, 4, 2047)) + [70] + list(rng.integers(0, 9, 1500)))
+    ix = make(vs, kind, d, M, 8, L2, cent, x, rng)
+    try:
+        for part in dev(x).split(len(x) // 2 + 1):
+            ix.add(part.contiguous())
+        q = (x[rng.integers(0, len(x), 500)] + 5 * rng.standard_normal((500, d))).astype(np.float32)
+        for k, nprobe in ((10, 64), (100, 200)):
+            both_scans(vs, ix, dev(q), k, nprobe)
+    finally:
+        ix.close()
+
+
+def test_one_list_holds_nearly_everything(vs):
+    """Segments are doubled where there would be more than four million work items."""
+    g = torch.Generator(device="cuda").manual_seed(4)
+    rng = np.random.default_rng(4)
+    d, M = 32, 8
+    cent = np.concatenate([np.zeros((1, d)), 6 * rng.standard_normal((30, d))]).astype(np.float32)
+    x = torch.cat([torch.randn((300_000, d), generator=g, device="cuda"),
+                   dev(np.repeat(cent[1:], 100, axis=0)) + torch.randn((3000, d), generator=g, device="cuda")])
+    ix = vs.IVFPQ(d, L2, dev(cent), torch.randn((M, 256, d // M), generator=g, device="cuda"), nbits=8)
+    try:
+        ix.add(x)
+        q = torch.randn((12_000, d), generator=g, device="cuda")
+        both_scans(vs, ix, q, 10, 11)
+    finally:
+        ix.close()
+
+
+def test_copy_of_the_codes_in_memory_of_its_own(vs):
+    """Above 128 MiB the copy lies apart; the index grows into that and on."""
+    g = torch.Generator(device="cuda").manual_seed(5)
+    d, M = 96, 32
+    x = torch.randn((2_200_000, d), generator=g, device="cuda")
+    ix = vs.IVFPQ(d, L2, x[:512].contiguous(), torch.randn((M, 256, d // M), generator=g, device="cuda"), nbits=8)
+    try:
+        q = x[:700] + 0.1
+        vs.vs_profile_enable(1)
+        for _ in range(3):                                      # 70, 141 and 211 MB
+            ix.add(x)
+            vs.vs_profile_read()
+            both_scans(vs, ix, q, 20, 16)
+            assert vs.vs_profile_read()["scan_first"][1] == 1
+    finally:
+        vs.vs_profile_enable(0)
+        ix.close()
