@@ -22,6 +22,7 @@ int fail(int code, const char* fmt, ...) {
   va_start(ap, fmt);
   vsnprintf(g_err, sizeof(g_err), fmt, ap);
   va_end(ap);
+  if (code == VS_ERR_OOM || code == VS_ERR_DEVICE) (void)hipGetLastError();   // said here, not again by the next call
   return code;
 }
 
