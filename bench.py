@@ -48,15 +48,6 @@ MATRIX_SCAN_KERNEL = "ms_sweep_kernel"
 MATRIX_SCAN_BOUND = re.compile(r"ms_sweep_kernel<.*, \d+, 0, \d+>")   # its MODE 0 (Side, METRIC, MODE, NT)
 
 
-def matrix_scan(cfg, search_type, nq, npr, k):
-    """Whether the library scans the lists on the matrix cores (same rule as mscan_chosen in csrc/api.hip, for the
-    shapes of the workloads here: up to eight steps of 32 dimensions)."""
-    if cfg["d"] > 256 or cfg["M"] % 4 or k > 128:
-        return False
-    residual_tables = cfg["metric"] == 0 and search_type == "tables"
-    return nq * npr * (cfg["nb"] / cfg["nlist"]) >= (3e6 if residual_tables else 2e7) or (residual_tables and nq * npr >= 8192)
-
-
 def scan_kernel_name(cfg, search_type, list_major=False, on_matrix_cores=False):
     """The scan kernel the library picks for this shape (same rule as its launcher).  list_major:
     the search ran list by list (the call's statistics say so): the dominant kernel is that scan."""
@@ -373,7 +364,8 @@ def main():
     # a list-major search: stage "scan" is the list-major kernel alone, which visits the codes of
     # all probes but the first few of every query (those are stage "scan_first", query-major)
     list_major = stats["list_major_first_probes"] > 0
-    on_matrix_cores = not list_major and matrix_scan(cfg, args.search_type, nq, min(nprobe, cfg["nlist"]), k)
+    # (without such probes that stage is the grouping and bounding of the scan on the matrix cores: the search took it)
+    on_matrix_cores = not list_major and prof["scan_first"][1] > 0
     scanned_dominant = scanned - stats["list_major_first_codes"]
     algo_bytes = scanned_dominant * code_size
     if list_major:

@@ -463,10 +463,12 @@ VS_API int vs_profile_read(double* stage_ms, int64_t* launches);
  * "matrix_scan": whether vs_ivfpq_search, vs_ivfflat_search and vs_ivfsq8_search scan a batch list by
  *   list on the matrix cores: products in fp16 decide which stored vectors can be among a query's k
  *   best, these are evaluated with the arithmetic of the other scans.  k <= 128; raw
- *   vectors and scalar codes of 16 < d <= 256; PQ of up to 64 sub-quantizers, a multiple of four, each
- *   of up to 8 dimensions.  0 (default): where
- *   it pays, by the number of vectors visited; 1: wherever there is a kernel; -1: never.
- *   "list_major" = 1 goes before it.  Results are identical either way.
+ *   vectors and scalar codes of 16 < d <= 256; PQ of (sub-quantizers x dimensions of each) 8 x 4..8,
+ *   16 x 3..8, 20 x 5..7 and 32 x 3..4 with 8-bit codes, 16 x 3..4, 32 x 1..4 and 64 x 1..4 with 4-bit
+ *   codes; not for indexes whose codebooks (raw vectors and scalar codes: centroids) are not finite or
+ *   whose largest component (norm) is below about 1e-11 or above 1e10.  0 (default): where it pays, by
+ *   the vectors visited, the queries that share a list, k and the probes; 1: wherever there is a kernel;
+ *   -1: never.  "list_major" = 1 goes before it.  Results are identical either way.
  * Options are process-wide. */
 VS_API int vs_set_option(const char* name, double value);
 /* counters[0] = rows evaluated through the matrix-core route, counters[1] = rows
