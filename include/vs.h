@@ -229,11 +229,12 @@ VS_API int vs_ivfpq_add(vs_ivfpq* ix, const float* x, int64_t n, const int64_t* 
  *   q [nq, d] fp32; out_dist [nq, k] fp32; out_ids [nq, k] int64.
  * Errors: null pointers (with nq > 0), k or nprobe < 1 or > VS_MAX_K.
  * Large batches are scanned list by list on the matrix cores (option "matrix_scan" below): same
- * results, one read of every probed list per batch.  The work space then also holds, per query, 16
- * bytes for each candidate -- 4 x "list_major_candidates" (default 1024) of them, fewer in batches
- * beyond 16,384 queries (1 GiB together, 4 KiB per query at least), more where k and the vectors
- * visited may need them (up to 1 GiB together) -- 20 bytes for each of 4 k + 128 survivors (10 MB
- * together at least), 0.5 to 4 KiB for its bounds by k, and 4 bytes per dimension.
+ * results, one read of every probed list per batch (beyond 65,536 queries: per equal pieces of at most
+ * that many).  The work space then also holds, per query of a piece, 16 bytes for each candidate --
+ * 4 x "list_major_candidates" (default 1024) of them, fewer beyond 16,384 queries (1 GiB together),
+ * more where k and the vectors visited may need them (up to 1 GiB together) -- 20 bytes for each of
+ * 4 k + 128 survivors (10 MB together at least), 0.5 to 4 KiB for its bounds by k, and 4 bytes per
+ * dimension.
  * Where it does not fit, and in batches that are too small, the lists are scanned query by query; a
  * search that found no memory for it is not tried again before the index grows or vs_trim is called.
  * Work space: one grow-only buffer per index (the first call of a size allocates it; later

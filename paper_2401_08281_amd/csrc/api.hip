@@ -1470,11 +1470,50 @@ bool mscan_pays(const MscanIndex& m, int form, int64_t nq, int npr, int k) {
   if (wave) return g.M == 8 || mean >= 400 || (mean >= 200 && visited >= (k <= 16 ? 5e7 : 1.5e8));
   return shared >= enough && (npr >= 8 || shared >= 8 || g.M <= 8 || (g.M == 16 && form == 1));
 }
-// Whether a search goes through it.
+// Queries that go through the scan at a time: batches beyond 65,536 in equal pieces, so that the candidate buffers stay
+// near 1 GiB with room for 1024 of each query (262,145 queries, k = 100: with 256 more than a quarter were scanned twice).
+int64_t mscan_piece(int64_t nq) {
+  const int64_t pieces = (nq + 65535) / 65536;
+  return (nq + pieces - 1) / pieces;
+}
+// Whether a search goes through it (plan: of one piece).
 bool mscan_chosen(const vs_ivfpq* ix, const MscanIndex& m, int form, int64_t nq, int npr, int k, MscanPlan* plan) {
   const int opt = g_matrix_scan.load();
+  nq = mscan_piece(nq);
   if (opt < 0 || g_list_major.load() == 1 || (opt == 0 && !mscan_pays(m, form, nq, npr, k))) return false;
   return mscan_plan(m, nq, npr, k, g_lm_cap.load(), plan) && ix->ms_has_room(plan->bytes);
+}
+
+// The scan of a search, piece by piece.  again(first query, queries, Rescan): scans the queries that a piece leaves, query
+// by query.  stats: receives their number.
+extern "C++" template <class F>
+int mscan_run(const MscanIndex& m, const MscanPlan& plan, int64_t nq, const float* q, const int32_t* probes,
+              const float* cdist, int form, int k, char* ws, u64* partial, const int64_t* ids, float* out_dist,
+              int64_t* out_ids, hipStream_t st, bool timed, vs_search_stats* stats, F&& again) {
+  for (int64_t q0 = 0; q0 < nq; q0 += plan.nq) {
+    MscanPlan p = plan;
+    p.nq = std::min(plan.nq, nq - q0);
+    const int64_t o = q0 * p.npr;
+    auto part = [&](int which) {
+      launch_mscan(which, m, p, q + q0 * m.g.d, probes + o, cdist ? cdist + o : nullptr, form, k, g_knn_eps_scale.load(),
+                   ws, ids, out_dist + q0 * k, out_ids + q0 * k, st);
+    };
+    {
+      StageTimer t(timed ? VS_STAGE_SCAN_FIRST : -1, st);
+      part(0);
+    }
+    {
+      StageTimer t(timed ? VS_STAGE_SCAN : -1, st);
+      part(1);
+    }
+    StageTimer t(timed ? VS_STAGE_MERGE : -1, st);
+    part(2);
+    const Rescan rs = mscan_rescan(m, p, ws, partial);
+    if (int rc = again(q0, p.nq, rs)) return rc;
+    launch_rescan_merge(rs, k, m.g.metric, ids, out_dist + q0 * k, out_ids + q0 * k, st);
+    if (stats) launch_search_stats_rescan(mscan_rescan_count(m, p, ws), reinterpret_cast<long long*>(stats), st);
+  }
+  return VS_OK;
 }
 
 // Work space of one search, carved from one buffer.
@@ -1572,30 +1611,17 @@ int search_run(const char* who, const vs_ivfpq* ix, const SearchLayout& L, char*
   const bool split = ix->search_type == VS_ST_PRECOMPUTED_TABLES && ix->list_tables;
   bool scanned = false;
   if (L.mscan) {
-    const MscanIndex m = mscan_index(kMsPq, ix);
-    char* ms = base + L.o_ms;
-    const int form = table_form(ix);
-    auto part = [&](int which) {
-      launch_mscan(which, m, L.ms, q, probes, cdist, form, k, g_knn_eps_scale.load(), ms, ix->ids, out_dist, out_ids, st);
-    };
-    {
-      StageTimer t(timed ? VS_STAGE_SCAN_FIRST : -1, st);
-      part(0);
-    }
-    {
-      StageTimer t(timed ? VS_STAGE_SCAN : -1, st);
-      part(1);
-    }
-    StageTimer t(timed ? VS_STAGE_MERGE : -1, st);
-    part(2);
-    const Rescan rs = mscan_rescan(m, L.ms, ms, partial);
-    if (launch_ivfpq_scan(g, q, nq, ix->centroids, ix->codebooks, probes, cdist, L.npr, 1, ix->list_off, ix->codes,
-                          with_norms ? ix->norms : nullptr, ix->cnorm, split ? ix->list_tables : nullptr, nullptr,
-                          ix->ntotal, k, partial, counter, ix->ids, out_dist, out_ids, st, rs) != 0)
-      return fail(VS_ERR_UNSUPPORTED, "%s: look-up tables of M * 2^nbits = %d floats plus selection state for k = %d exceed the LDS", who, g.M * g.K, k);
-    launch_rescan_merge(rs, k, g.metric, ix->ids, out_dist, out_ids, st);
-    if (stats)
-      launch_search_stats_rescan(mscan_rescan_count(m, L.ms, ms), reinterpret_cast<long long*>(stats), st);
+    const int rc = mscan_run(
+        mscan_index(kMsPq, ix), L.ms, nq, q, probes, cdist, table_form(ix), k, base + L.o_ms, partial, ix->ids, out_dist,
+        out_ids, st, timed, stats, [&](int64_t q0, int64_t n, const Rescan& rs) {
+          if (launch_ivfpq_scan(g, q + q0 * g.d, n, ix->centroids, ix->codebooks, probes + q0 * L.npr,
+                                cdist + q0 * L.npr, L.npr, 1, ix->list_off, ix->codes, with_norms ? ix->norms : nullptr,
+                                ix->cnorm, split ? ix->list_tables : nullptr, nullptr, ix->ntotal, k, partial, counter,
+                                ix->ids, out_dist + q0 * k, out_ids + q0 * k, st, rs) != 0)
+            return fail(VS_ERR_UNSUPPORTED, "%s: look-up tables of M * 2^nbits = %d floats plus selection state for k = %d exceed the LDS", who, g.M * g.K, k);
+          return (int)VS_OK;
+        });
+    if (rc) return rc;
     scanned = true;
   }
   if (L.list_major) {   // (where its selection state does not fit the LDS: the query-major scan below)
@@ -1819,24 +1845,15 @@ int vs_ivfflat_search(const vs_ivfflat* fx, const float* q, int64_t nq, int32_t 
   u64* partial = reinterpret_cast<u64*>(base + o_part);
   if (int rc = coarse_select(ix, plan, base + o_knn, q, nq, npr, probes, nullptr, st)) return rc;
   if (mscan) {
-    char* wm = base + o_ms;
-    auto part = [&](int which) {
-      launch_mscan(which, m, ms, q, probes, nullptr, 0, k, g_knn_eps_scale.load(), wm, ix->ids, out_dist, out_ids, st);
-    };
-    {
-      StageTimer t(VS_STAGE_SCAN_FIRST, st);
-      part(0);
-    }
-    {
-      StageTimer t(VS_STAGE_SCAN, st);
-      part(1);
-    }
-    StageTimer t(VS_STAGE_MERGE, st);
-    part(2);
-    const Rescan rs = mscan_rescan(m, ms, wm, partial);
-    launch_ivfflat_scan(g.d, g.metric, q, nq, probes, npr, 1, ix->list_off,
-                          reinterpret_cast<const float*>(ix->codes), k, partial, ix->ids, out_dist, out_ids, st, rs);
-    launch_rescan_merge(rs, k, g.metric, ix->ids, out_dist, out_ids, st);
+    const int rc = mscan_run(
+        m, ms, nq, q, probes, nullptr, 0, k, base + o_ms, partial, ix->ids, out_dist, out_ids, st, true, nullptr,
+        [&](int64_t q0, int64_t n, const Rescan& rs) {
+          launch_ivfflat_scan(g.d, g.metric, q + q0 * g.d, n, probes + q0 * npr, npr, 1, ix->list_off,
+                              reinterpret_cast<const float*>(ix->codes), k, partial, ix->ids, out_dist + q0 * k,
+                              out_ids + q0 * k, st, rs);
+          return (int)VS_OK;
+        });
+    if (rc) return rc;
     HIP_TRY(hipGetLastError());
     return VS_OK;
   }
@@ -1995,24 +2012,14 @@ int vs_ivfsq8_search(const vs_ivfsq8* sx, const float* q, int64_t nq, int32_t k,
   u64* partial = reinterpret_cast<u64*>(base + o_part);
   if (int rc = coarse_select(ix, plan, base + o_knn, q, nq, npr, probes, nullptr, st)) return rc;
   if (mscan) {
-    char* wm = base + o_ms;
-    auto part = [&](int which) {
-      launch_mscan(which, m, ms, q, probes, nullptr, 0, k, g_knn_eps_scale.load(), wm, ix->ids, out_dist, out_ids, st);
-    };
-    {
-      StageTimer t(VS_STAGE_SCAN_FIRST, st);
-      part(0);
-    }
-    {
-      StageTimer t(VS_STAGE_SCAN, st);
-      part(1);
-    }
-    StageTimer t(VS_STAGE_MERGE, st);
-    part(2);
-    const Rescan rs = mscan_rescan(m, ms, wm, partial);
-    launch_ivfsq8_scan(g.d, g.metric, q, nq, sx->vmin, sx->step, probes, npr, 1, ix->list_off, ix->codes, k, partial,
-                         ix->ids, out_dist, out_ids, st, rs);
-    launch_rescan_merge(rs, k, g.metric, ix->ids, out_dist, out_ids, st);
+    const int rc = mscan_run(
+        m, ms, nq, q, probes, nullptr, 0, k, base + o_ms, partial, ix->ids, out_dist, out_ids, st, true, nullptr,
+        [&](int64_t q0, int64_t n, const Rescan& rs) {
+          launch_ivfsq8_scan(g.d, g.metric, q + q0 * g.d, n, sx->vmin, sx->step, probes + q0 * npr, npr, 1, ix->list_off,
+                             ix->codes, k, partial, ix->ids, out_dist + q0 * k, out_ids + q0 * k, st, rs);
+          return (int)VS_OK;
+        });
+    if (rc) return rc;
     HIP_TRY(hipGetLastError());
     return VS_OK;
   }

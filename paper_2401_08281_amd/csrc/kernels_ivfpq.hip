@@ -1724,7 +1724,7 @@ __global__ __launch_bounds__(256) void search_stats_kernel(const int32_t* __rest
 }
 __global__ void search_stats_rescan_kernel(const unsigned* __restrict__ rescan_count,
                                            unsigned long long* __restrict__ stats) {
-  stats[6] = (unsigned long long)*rescan_count;
+  stats[6] += (unsigned long long)*rescan_count;   // (of a piece of the batch; the block was zeroed)
 }
 
 // ------------------------------------------------------------------ launchers

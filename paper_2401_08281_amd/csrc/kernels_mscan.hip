@@ -1510,7 +1510,7 @@ bool mscan_plan(const MscanIndex& ix, int64_t nq, int npr, int k, int asked, Msc
   p.slots = k <= 16 ? 128 : (k <= 32 ? 256 : (k <= 64 ? 512 : 1024));
   p.capcodes = (u32)p.slots * 4u;
   // Candidates per query: four times what the list-major scan keeps (it only sees those behind the first lists), less
-  // for batches beyond 16,384 queries so that they stay near 1 GiB.  A query whose buffer overflows is scanned again, and
+  // beyond 16,384 queries so that they stay near 1 GiB.  A query whose buffer overflows is scanned again, and
   // where nothing tells the probed lists apart -- unstructured data -- the threshold lets k of `capcodes` vectors
   // pass, `likely` of all that a query visits, and the error bounds two or three times that: four times it is kept as
   // far as 1 GiB goes, and eight times what it is for lists of the longest one's length as far as 128 MB go.

@@ -380,3 +380,24 @@ def test_copy_of_the_codes_in_memory_of_its_own(vs):
     finally:
         vs.vs_profile_enable(0)
         ix.close()
+
+
+@pytest.mark.parametrize("kind,d,M", [("pq", 32, 8), ("flat", 40, 0), ("sq8", 40, 0)])
+def test_batches_beyond_a_piece(vs, kind, d, M):
+    """More than 65,536 queries are scanned in pieces, the last one shorter; each has room for the candidates of k = 100
+    (as one batch each query had 256, and more than a quarter were scanned again)."""
+    rng = np.random.default_rng(d)
+    nq, k, nprobe = 262_145, 100, 24
+    x = rng.standard_normal((24_000, d)).astype(np.float32)
+    ix = make(vs, kind, d, M, 8, L2, x[:40], x, rng)
+    try:
+        ix.add(dev(x))
+        g = torch.Generator(device="cuda").manual_seed(6)
+        q = torch.randn((nq, d), generator=g, device="cuda")
+        both_scans(vs, ix, q, k, nprobe)
+        if kind == "pq":
+            assert ix.search_stats(q, k, nprobe)[2]["list_major_rescanned"] < nq // 50
+            vs.vs_set_option("knn_eps_scale", -1.0)             # (all of every piece are counted)
+            assert ix.search_stats(q, k, nprobe)[2]["list_major_rescanned"] == nq
+    finally:
+        ix.close()
