@@ -159,7 +159,7 @@ def test_no_memory_for_the_candidates(vs, kind, d, M):
     from test_gpu_nearest import hold_memory
     rng = np.random.default_rng(d)
     nq, k, nprobe = 30_000, 10, 8
-    cent, x = lists_of(rng, d, [100] * 40)
+    cent, x = lists_of(rng, d, [400] * 40)
     q = dev((x[rng.integers(0, len(x), nq)] + 0.1 * rng.standard_normal((nq, d))).astype(np.float32))
     ix = make(vs, kind, d, M, 8, L2, cent, x, rng)
     vs.vs_set_option("matrix_scan", 1)
@@ -178,19 +178,21 @@ def test_no_memory_for_the_candidates(vs, kind, d, M):
         vs.vs_trim()
         torch.cuda.empty_cache()
         print("little memory", kind, flush=True)
-        hold = hold_memory(400 << 20)
+        out = [torch.empty((nq, k), dtype=t, device="cuda") for t in (torch.float32, torch.int64) * 2]
+        D0, I0, D1, I1 = out
+        hold = hold_memory(600 << 20)
         try:
-            D0, I0 = [t.clone() for t in ix.search(q, k, nprobe)]
+            ix.search(q, k, nprobe, D0, I0)
             torch.cuda.synchronize()
             g = torch.cuda.CUDAGraph()
             with torch.cuda.graph(g):
-                D1, I1 = ix.search(q, k, nprobe)
+                ix.search(q, k, nprobe, D1, I1)
             for _ in range(3):
                 D1.zero_()
                 g.replay()
                 torch.cuda.synchronize()
-                assert same(D0, D1) and same(I0, I1)
-            del g, D1, I1
+                assert bool((D0 == D1).all()) and bool((I0 == I1).all())
+            del g
         finally:
             del hold
             torch.cuda.empty_cache()
