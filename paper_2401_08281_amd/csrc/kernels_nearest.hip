@@ -28,11 +28,8 @@ typedef float floatx16 __attribute__((ext_vector_type(16)));
 
 constexpr float kPadScore = -3.0e38f;   // finite: tagging an infinity would make it a NaN
 
-__device__ __forceinline__ unsigned short bf16_bits(float f) {
-  u32 u = __float_as_uint(f);
-  u += 0x7FFFu + ((u >> 16) & 1u);   // round to nearest even (inputs are finite)
-  return (unsigned short)(u >> 16);
-}
+// (round to nearest even; one instruction for two of them)
+__device__ __forceinline__ unsigned short bf16_bits(float f) { return __builtin_bit_cast(unsigned short, (__bf16)f); }
 __device__ __forceinline__ float bf16_value(unsigned short b) { return __uint_as_float(((u32)b) << 16); }
 
 template <bool F16>
@@ -43,7 +40,7 @@ __device__ __forceinline__ floatx16 mfma16(u16x8 a, u16x8 b, floatx16 c) {
     return __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, a), __builtin_bit_cast(bf16x8, b), c, 0, 0, 0);
 }
 
-// Best and runner-up of a stream of scores, the best tagged in its four low bits (2^-19 of its
+// Best and runner-up of a stream of scores, the best tagged with a number below TAGS in its low bits (16: 2^-19 of its
 // magnitude, part of the error bound): v_and_or, v_med3, v_max.  (The maximum is written as
 // assembly because fmaxf would first quiet its inputs, two more instructions; it never reads a
 // matrix result directly, only the tagged copy.)
@@ -52,15 +49,25 @@ __device__ __forceinline__ float raw_max(float a, float b) {
   asm("v_max_f32 %0, %1, %2" : "=v"(r) : "v"(a), "v"(b));
   return r;
 }
+template <int TAGS>
 struct Top2 {
   float b1, b2;
   __device__ __forceinline__ void init() { b1 = b2 = -__builtin_inff(); }
   __device__ __forceinline__ void put(float s, int tag) {
-    const float p = __uint_as_float((__float_as_uint(s) & 0xFFFFFFF0u) | (u32)tag);
+    const float p = __uint_as_float((__float_as_uint(s) & ~(u32)(TAGS - 1)) | (u32)tag);
     b2 = __builtin_amdgcn_fmed3f(b1, b2, p);
     b1 = raw_max(b1, p);
   }
+  __device__ __forceinline__ int tag() const { return (int)(__float_as_uint(b1) & (u32)(TAGS - 1)); }
 };
+// (a register at a time, not a half)
+__device__ __forceinline__ u16x8 pick(int second, u16x8 a, u16x8 b) {
+  const u32x4 x = __builtin_bit_cast(u32x4, a), y = __builtin_bit_cast(u32x4, b);
+  u32x4 r;
+#pragma unroll
+  for (int u = 0; u < 4; ++u) r[u] = second ? y[u] : x[u];
+  return __builtin_bit_cast(u16x8, r);
+}
 // row inside a 32-row block of accumulator register v in lane half h
 __device__ __forceinline__ int block_row(int v, int h) { return 8 * (v >> 2) + 4 * h + (v & 3); }
 
@@ -125,11 +132,22 @@ __global__ __launch_bounds__(256, 2) void nearest_kernel(
   unsigned short* bt = reinterpret_cast<unsigned short*>(smem);   // [2][NPL][BN][LDB]
   float* nrm_s = reinterpret_cast<float*>(bt + 2 * NPL * BN * LDB);   // [2][BN] starting values
   const int tid = threadIdx.x, wave = tid >> 6, lane = lane_id(), half = lane >> 5;
-  const int64_t split = blockIdx.x / tiles, tile = blockIdx.x - split * tiles;
   const int64_t total = COLLECT ? min((int64_t)state->listed[BF], n) : pass_vectors(state, n, BF, rows);
+  // The second sweep cuts B by the vectors that are listed, which only the device knows: as many splits as two
+  // workgroups per compute unit and the grid allow, of two steps or more (its results depend on no split).  Cut like
+  // the first sweep, a few listed vectors of a million walked over all rows of B in one workgroup: 210 us at 4096 rows,
+  // 24 like this; 262144 vectors against 1024 trained rows: 104 -> 40.
+  if constexpr (COLLECT) {
+    tiles = max((total + 128 * RB - 1) / (128 * RB), (int64_t)1);
+    const int64_t steps = (nb + BN - 1) / BN, want = min((int64_t)gridDim.x, (int64_t)512) / tiles;
+    const int64_t splits = max(min(want, steps / 2), (int64_t)1);
+    cols_per_split = (steps + splits - 1) / splits * BN;
+  }
+  const int64_t split = blockIdx.x / tiles, tile = blockIdx.x - split * tiles;
   const int64_t e0 = tile * 128 * RB;
   if (e0 >= total) return;
   const int64_t c_begin = split * cols_per_split, c_end = min(nb, c_begin + cols_per_split);
+  if (COLLECT && c_begin >= c_end) return;
   const bool use_bl = BF && Binfo->all_bf16 == 0u;
   const bool vec = (d & 3) == 0;
 
@@ -198,7 +216,7 @@ __global__ __launch_bounds__(256, 2) void nearest_kernel(
     if (tid < BN) nrm_s[buf * BN + tid] = ct + tid < c_end ? (METRIC == 0 ? -0.5f * stn : 0.f) : kPadScore;
   };
 
-  Top2 top[RB];
+  Top2<16> top[RB];
   int blk[RB] = {};
   float th_e[RB];
 #pragma unroll
@@ -280,7 +298,7 @@ __global__ __launch_bounds__(256, 2) void nearest_kernel(
 #pragma unroll
   for (int rb = 0; rb < RB; ++rb) {   // the two lanes of a vector
     const int64_t e = e0 + wave * (32 * RB) + rb * 32 + (lane & 31);
-    int idx = blk[rb] * 32 + block_row((int)(__float_as_uint(top[rb].b1) & 15u), half);
+    int idx = blk[rb] * 32 + block_row(top[rb].tag(), half);
     const float o1 = __shfl_xor(top[rb].b1, 32), o2 = __shfl_xor(top[rb].b2, 32);
     const int oi = __shfl_xor(idx, 32);
     const float b1 = fmaxf(top[rb].b1, o1);
@@ -461,15 +479,21 @@ __global__ void nearest_state_kernel(const PrepInfo* __restrict__ Binfo, Nearest
 //     vector   [ head | head | tail | 1 1 1 0 ... ]
 //     codeword [ head | tail | head | -|t|^2 / 2 in three bf16 pieces ]
 // (NP groups of each kind for 8 NP dimensions), so the score <r, t> - |t|^2 / 2 comes out finished
-// and costs only the selection: 3 vector instructions per (sub-vector, codeword) where the canon
-// chain costs 2 per dimension.  Sub-vectors whose best two are within the error bound are decided
+// and costs only the selection.  A lane's four consecutive codewords of a product share one tag: their
+// largest score is selected, 5 vector instructions for four scores (3 for every one of them before, which was most of
+// the kernel), and the canon chain decides among the best four, two on either half of the wavefront.
+// Sub-vectors whose best two fours are within the error bound are decided
 // by the canon chain over all codewords, 64 codewords at a time (about one in a hundred;
 // all of them where eps_scale, which scales the bound, is negative).
 // RES: sub-vector m of x_i minus its list's centroid; else x is [M][n][dsub].
-// Encoding 1M vectors of 16 x 8 dimensions: 1.29 -> 0.72 ms.
+// Encoding 1M vectors of 16 x 8 dimensions: 688 -> 515 us; 16 x 262144 sub-vectors of 8 in training: 175 -> 117.  (Half
+// the vector instructions; the second half of the gain is the padded codebook and the pieces of a row asked for together.)
 // ---------------------------------------------------------------------------
 // (four resp. two wavefronts per SIMD; a bound on the registers also keeps the products' results in
 // vector registers, where the selection can read them without a copy)
+// floats from one four of codewords to the next in LDS: 16-byte pieces stay aligned, and consecutive fours start in
+// different banks
+__host__ __device__ constexpr int pq_four_stride(int dsub, bool vec) { return 4 * dsub + (vec ? 4 : 1); }
 template <int NP, int KB, bool RES, bool VEC>
 __global__ __launch_bounds__(256, NP == 1 ? 4 : 2) void pq_nearest_kernel(
     const float* __restrict__ x, int64_t n, int d, int dsub, const float* __restrict__ centroids,
@@ -477,7 +501,11 @@ __global__ __launch_bounds__(256, NP == 1 ? 4 : 2) void pq_nearest_kernel(
     int groups, float eps_scale, uint8_t* __restrict__ codes, int64_t stride_i, int64_t stride_m,
     float* __restrict__ val) {
   constexpr int NG = 3 * NP + 1, S = (NG + 1) / 2, DP = 8 * NP;
-  extern __shared__ __attribute__((aligned(16))) float T[];       // [K][dsub]
+  // [K / 4][4][dsub] and padding: the gathers of a best four by every lane would otherwise fall into a few banks
+  // (dsub = 8 without it: 676 cycles a product group waited for, and the whole kernel 35 % slower)
+  extern __shared__ __attribute__((aligned(16))) float T[];
+  const int fours = pq_four_stride(dsub, VEC);
+  auto word = [&](int j) { return T + (j >> 2) * fours + (j & 3) * dsub; };
   const int tid = threadIdx.x, wave = tid >> 6, lane = lane_id(), half = lane >> 5;
   // workgroup ids go round the eight XCDs: an XCD takes all sub-quantizers of a chunk of vectors in
   // a row, so that a chunk's rows come into its L2 once
@@ -486,7 +514,7 @@ __global__ __launch_bounds__(256, NP == 1 ? 4 : 2) void pq_nearest_kernel(
   const int m = (int)(seq % M);
   if (chunk >= chunks) return;
   const float* __restrict__ Tm = codebooks + (int64_t)m * K * dsub;
-  for (int e = tid; e < K * dsub; e += 256) T[e] = Tm[e];
+  for (int e = tid; e < K * dsub; e += 256) T[e / (4 * dsub) * fours + e % (4 * dsub)] = Tm[e];
   __syncthreads();
 
   bool odd = false;   // a codeword with a NaN or a norm that overflows: its scores say nothing
@@ -502,7 +530,7 @@ __global__ __launch_bounds__(256, NP == 1 ? 4 : 2) void pq_nearest_kernel(
 #pragma unroll
       for (int u = 0; u < 8; ++u) {
         const int t = 8 * p + u;
-        const float v = t < dsub && j < K ? T[j * dsub + t] : 0.f;
+        const float v = t < dsub && j < K ? word(j)[t] : 0.f;
         tt = __builtin_fmaf(v, v, tt);
         const unsigned short h = bf16_bits(v);
         th[p][u] = h;
@@ -521,30 +549,40 @@ __global__ __launch_bounds__(256, NP == 1 ? 4 : 2) void pq_nearest_kernel(
 #pragma unroll
     for (int s = 0; s < S; ++s) {
       auto group = [&](int g) { return g < NP ? th[g % NP] : (g < 2 * NP ? tl[g % NP] : (g < 3 * NP ? th[g % NP] : (g == 3 * NP ? tn : zero))); };
-      const u16x8 lo = group(2 * s), hi = group(2 * s + 1);
-#pragma unroll
-      for (int u = 0; u < 8; ++u) af[b][s][u] = half ? hi[u] : lo[u];
+      af[b][s] = pick(half, group(2 * s), group(2 * s + 1));
     }
   }
   // (no difference of scores is larger than a NaN: every sub-vector goes through the canon branch)
   const float bound = __builtin_amdgcn_ballot_w64(odd) != 0 || eps_scale < 0.f ? __builtin_nanf("") : eps_scale * 4e-5f;
   const floatx16 fzero = {0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0};
+  float infinity = __builtin_inff();
+  asm volatile("" : "+s"(infinity));                              // (a scalar register: known, it would be fmaxf again)
   const int64_t base = (chunk * 4 + wave) * 32ll * groups;
+  // (a group's list numbers are there a group early, and all pieces of its rows are requested together)
+  int next_list = RES ? list_of[min(base + (lane & 31), n - 1)] : 0;
   for (int g = 0; g < groups; ++g) {
     const int64_t i0 = base + g * 32;
     if (i0 >= n) break;
     const int64_t i = min(i0 + (lane & 31), n - 1);
+    const int list = next_list;
+    if (RES) next_list = list_of[min(i0 + 32 + (lane & 31), n - 1)];
     float r[DP];
     {
       const float* __restrict__ xi = RES ? x + i * d + m * dsub : x + ((int64_t)m * n + i) * dsub;
-      const float* __restrict__ c = RES ? centroids + (int64_t)list_of[i] * d + m * dsub : nullptr;
-      if constexpr (VEC) {   // dsub % 4 == 0, rows of 16-byte pieces
+      const float* __restrict__ c = RES ? centroids + (int64_t)list * d + m * dsub : nullptr;
+      if constexpr (VEC) {   // dsub % 4 == 0, rows of 16-byte pieces (those past the end: the first again, dropped)
+        u32x4 a[DP / 4], cc[DP / 4];
 #pragma unroll
         for (int t = 0; t < DP; t += 4) {
-          float4 a = make_float4(0.f, 0.f, 0.f, 0.f), cc = a;
-          if (t < dsub) { a = *reinterpret_cast<const float4*>(xi + t); if (RES) cc = *reinterpret_cast<const float4*>(c + t); }
-          r[t] = a.x; r[t + 1] = a.y; r[t + 2] = a.z; r[t + 3] = a.w;
-          if (RES) { r[t] -= cc.x; r[t + 1] -= cc.y; r[t + 2] -= cc.z; r[t + 3] -= cc.w; }
+          const int at = t < dsub ? t : 0;
+          a[t / 4] = *reinterpret_cast<const u32x4*>(xi + at);
+          if (RES) cc[t / 4] = *reinterpret_cast<const u32x4*>(c + at);
+        }
+#pragma unroll
+        for (int t = 0; t < DP; ++t) {
+          const float v = __uint_as_float(a[t / 4][t & 3]);
+          r[t] = RES ? v - __uint_as_float(cc[t / 4][t & 3]) : v;
+          if (t >= dsub) r[t] = 0.f;
         }
       } else {
 #pragma unroll
@@ -573,37 +611,65 @@ __global__ __launch_bounds__(256, NP == 1 ? 4 : 2) void pq_nearest_kernel(
 #pragma unroll
       for (int s = 0; s < S; ++s) {
         auto group = [&](int q) { return q < 2 * NP ? rh[q % NP] : (q < 3 * NP ? rl[q % NP] : (q == 3 * NP ? ones : zero)); };
-        const u16x8 lo = group(2 * s), hi = group(2 * s + 1);
-#pragma unroll
-        for (int u = 0; u < 8; ++u) xf[s][u] = half ? hi[u] : lo[u];
+        xf[s] = pick(half, group(2 * s), group(2 * s + 1));
       }
     }
-    Top2 top;
+    Top2<4 * KB> top;
     top.init();
-    int blk = 0;
+    // (the first maximum of four as a median: fmaxf would quiet both operands first)
+    auto max_of = [&](float p, float q) { return __builtin_amdgcn_fmed3f(p, q, infinity); };
 #pragma unroll
     for (int b = 0; b < KB; ++b) {
       floatx16 s = mfma16<false>(af[b][0], xf[0], fzero);
 #pragma unroll
       for (int st = 1; st < S; ++st) s = mfma16<false>(af[b][st], xf[st], s);
-      const float before = top.b1;
 #pragma unroll
-      for (int v = 0; v < 16; ++v) top.put(s[v], v);
-      if (b > 0) blk = top.b1 > before ? b : blk;
+      for (int q = 0; q < 4; ++q)
+        top.put(fmaxf(fmaxf(max_of(s[4 * q], s[4 * q + 1]), s[4 * q + 2]), s[4 * q + 3]), 4 * b + q);
     }
-    int best = blk * 32 + block_row((int)(__float_as_uint(top.b1) & 15u), half);
+    int best = 8 * top.tag() + 4 * half;                          // first codeword of the best four
     const float o1 = __shfl_xor(top.b1, 32), o2 = __shfl_xor(top.b2, 32);
     const int ob = __shfl_xor(best, 32);
     const float b1 = fmaxf(top.b1, o1), b2 = fmaxf(fminf(top.b1, o1), fmaxf(top.b2, o2));
     if (o1 > top.b1) best = ob;
-    best = min(best, K - 1);
+    best = min(best, K - 4);
+    // the canon best of these four: two by either half of the wavefront
+    float val_best;
+    {
+      const int j0 = best + 2 * half;
+      const float* w0 = word(j0);
+      float a0 = 0.f, a1 = 0.f;
+      auto add = [&](int t, float t0, float t1) {
+        const float d0 = r[t] - t0, d1 = r[t] - t1;
+        a0 = __builtin_fmaf(d0, d0, a0);
+        a1 = __builtin_fmaf(d1, d1, a1);
+      };
+#pragma unroll
+      for (int t = 0; t < DP; t += VEC ? 4 : 1) {
+        if (t >= dsub) continue;
+        if constexpr (VEC) {
+          const float4 t0 = *reinterpret_cast<const float4*>(w0 + t), t1 = *reinterpret_cast<const float4*>(w0 + dsub + t);
+          add(t, t0.x, t1.x); add(t + 1, t0.y, t1.y); add(t + 2, t0.z, t1.z); add(t + 3, t0.w, t1.w);
+        } else {
+          add(t, w0[t], w0[dsub + t]);
+        }
+      }
+      int j = a1 < a0 ? j0 + 1 : j0;
+      float a = a1 < a0 ? a1 : a0;
+      const float oa = __shfl_xor(a, 32);
+      const int oj = __shfl_xor(j, 32);
+      if (oa < a || (oa == a && oj < j)) { a = oa; j = oj; }
+      best = j;
+      val_best = a;
+    }
     // Error of a score: 1.2e-5 |r||t| (dropped tails), 2e-6 (fp32, at most 48 terms, and the canon
-    // chain), 2e-6 (tags) of N = |r|^2 + |t|^2, and any codeword that could be the nearest has
+    // chain), 3.9e-6 (tags) of N = |r|^2 + |t|^2, and any codeword that could be the nearest has
     // |t| <= |r| + its distance, whose square is at most |r|^2 - 2 b2 up to that error.
     const float dist = sqrtf(fmaxf(rr - 2.f * b2, 0.f)), tmax = sqrtf(rr) + 1.01f * dist;
     // (+ 1e-30: the tags alone tell scores of zero apart, and products of tiny numbers vanish)
     const bool unsure = !(b1 - b2 > bound * (rr + tmax * tmax) + 1e-30f);
     u32 todo = (u32)__builtin_amdgcn_ballot_w64(unsure);          // (both halves agree)
+    const bool redone = todo != 0;
     while (todo != 0) {
       const int src = __builtin_ctz(todo);
       todo &= todo - 1;
@@ -612,10 +678,11 @@ __global__ __launch_bounds__(256, NP == 1 ? 4 : 2) void pq_nearest_kernel(
       for (int t = 0; t < DP; ++t) rs[t] = __uint_as_float((u32)__builtin_amdgcn_readlane((int)__float_as_uint(r[t]), src));
       u64 key = KEY_EMPTY;
       for (int j = lane; j < K; j += VS_WAVE) {
+        const float* w = word(j);
         float acc = 0.f;
 #pragma unroll
         for (int t = 0; t < DP; ++t)
-          if (t < dsub) { const float diff = rs[t] - T[j * dsub + t]; acc = __builtin_fmaf(diff, diff, acc); }
+          if (t < dsub) { const float diff = rs[t] - w[t]; acc = __builtin_fmaf(diff, diff, acc); }
         // (encoding never chose a codeword at a distance that is not finite; training orders a NaN's bits
         // like the keys of the nearest-row routes)
         const u64 kk = RES && !(acc < __builtin_inff()) ? KEY_EMPTY : make_key(acc, (u32)j, 0);
@@ -628,11 +695,13 @@ __global__ __launch_bounds__(256, NP == 1 ? 4 : 2) void pq_nearest_kernel(
     if (half == 0 && i0 + lane < n) {
       codes[(i0 + lane) * stride_i + m * stride_m] = (uint8_t)best;
       if (val) {
-        float acc = 0.f;
+        if (redone) {
+          val_best = 0.f;
 #pragma unroll
-        for (int t = 0; t < DP; ++t)
-          if (t < dsub) { const float diff = r[t] - T[best * dsub + t]; acc = __builtin_fmaf(diff, diff, acc); }
-        val[(int64_t)m * n + i0 + lane] = acc;
+          for (int t = 0; t < DP; ++t)
+            if (t < dsub) { const float diff = r[t] - word(best)[t]; val_best = __builtin_fmaf(diff, diff, val_best); }
+        }
+        val[(int64_t)m * n + i0 + lane] = val_best;
       }
     }
   }
@@ -756,9 +825,9 @@ void launch_pq_nearest(const float* x, int64_t n, int d, int dsub, const float* 
   int groups = (int)std::max<int64_t>(1, std::min<int64_t>(16, n * M / (128 * 2048)));
   const int64_t chunks = (n + 128ll * groups - 1) / (128ll * groups);
   const dim3 grid((unsigned)((chunks + 7) / 8 * 8 * M)), block(256);
-  const size_t lds = (size_t)K * dsub * sizeof(float);
   const bool vec = dsub % 4 == 0 && (centroids == nullptr || d % 4 == 0) &&
                    (reinterpret_cast<uintptr_t>(x) & 15) == 0;
+  const size_t lds = (size_t)K / 4 * pq_four_stride(dsub, vec) * sizeof(float);
 #define GO(NP, KB, RES, VEC) \
   hipLaunchKernelGGL((pq_nearest_kernel<NP, KB, RES, VEC>), grid, block, lds, st, x, n, d, dsub, centroids, list_of, \
                      codebooks, K, M, chunks, groups, eps_scale, codes, stride_i, stride_m, val)

@@ -374,6 +374,28 @@ def test_nearest_codewords_match_oracle(vs, oracle, n, M, dsub, nbits):
 
 
 @pytest.mark.parametrize("nbits", [4, 8])
+@pytest.mark.parametrize("dsub", [1, 3, 4, 8, 9, 16])
+@pytest.mark.parametrize("gap", [1, 2, 3, 4, 8, 13])
+def test_twin_codewords_of_one_four_and_of_two(vs, oracle, dsub, nbits, gap):
+    """The kernel selects fours of consecutive codewords: twins `gap` apart lie in one or in two of them, equal (the
+    smaller number wins) or one rounding apart, where the canon chain decides."""
+    say("twins dsub=%d nbits=%d gap=%d" % (dsub, nbits, gap))
+    n, M, K = 2_113, 4, 1 << nbits
+    d = M * dsub
+    x, cent = rows("gauss", n, d, 60), rows("gauss", 3, d, 61)
+    cb = np.ascontiguousarray(rows("gauss", K, d, 62).reshape(K, M, dsub).transpose(1, 0, 2))
+    for j in range(0, K - gap, 2 * gap):
+        cb[0, j + gap] = cb[0, j]
+        cb[1, j + gap] = np.nextafter(cb[1, j], np.float32(9), dtype=np.float32)
+        cb[2, j] = np.nextafter(cb[2, j + gap], np.float32(-9), dtype=np.float32)
+    ix = vs.IVFPQ(d, L2, dev(cent), dev(cb), nbits)
+    ix.add(dev(x))
+    orc = oracle.OracleIVFPQ(d, L2, cent, cb, nbits)
+    orc.add(x)
+    np.testing.assert_array_equal(host(ix.codes()), orc.codes)
+
+
+@pytest.mark.parametrize("nbits", [4, 8])
 @pytest.mark.parametrize("dsub", [2, 5, 8, 12, 16])
 @pytest.mark.parametrize("kind", ["gauss", "tiny", "huge", "nonfinite_vectors", "nonfinite_codewords"])
 def test_nearest_codewords_on_all_routes(vs, kind, dsub, nbits):
