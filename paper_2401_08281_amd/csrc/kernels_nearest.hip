@@ -40,23 +40,27 @@ __device__ __forceinline__ floatx16 mfma16(u16x8 a, u16x8 b, floatx16 c) {
     return __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, a), __builtin_bit_cast(bf16x8, b), c, 0, 0, 0);
 }
 
+// The larger of two as their median with infinity: one instruction where fmaxf would first quiet its inputs, and one
+// that the scheduler knows.  (The infinity sits in a scalar register the compiler knows nothing of, or it would be fmaxf
+// again.)
+struct Largest {
+  float infinity;
+  __device__ __forceinline__ void init() {
+    infinity = __builtin_inff();
+    asm volatile("" : "+s"(infinity));
+  }
+  __device__ __forceinline__ float operator()(float a, float b) const { return __builtin_amdgcn_fmed3f(a, b, infinity); }
+};
 // Best and runner-up of a stream of scores, the best tagged with a number below TAGS in its low bits (16: 2^-19 of its
-// magnitude, part of the error bound): v_and_or, v_med3, v_max.  (The maximum is written as
-// assembly because fmaxf would first quiet its inputs, two more instructions; it never reads a
-// matrix result directly, only the tagged copy.)
-__device__ __forceinline__ float raw_max(float a, float b) {
-  float r;
-  asm("v_max_f32 %0, %1, %2" : "=v"(r) : "v"(a), "v"(b));
-  return r;
-}
+// magnitude, part of the error bound): v_and_or and two v_med3.
 template <int TAGS>
 struct Top2 {
   float b1, b2;
   __device__ __forceinline__ void init() { b1 = b2 = -__builtin_inff(); }
-  __device__ __forceinline__ void put(float s, int tag) {
+  __device__ __forceinline__ void put(const Largest& largest, float s, int tag) {
     const float p = __uint_as_float((__float_as_uint(s) & ~(u32)(TAGS - 1)) | (u32)tag);
     b2 = __builtin_amdgcn_fmed3f(b1, b2, p);
-    b1 = raw_max(b1, p);
+    b1 = largest(b1, p);
   }
   __device__ __forceinline__ int tag() const { return (int)(__float_as_uint(b1) & (u32)(TAGS - 1)); }
 };
@@ -218,6 +222,8 @@ __global__ __launch_bounds__(256, 2) void nearest_kernel(
 
   Top2<16> top[RB];
   int blk[RB] = {};
+  Largest largest;
+  largest.init();
   float th_e[RB];
 #pragma unroll
   for (int rb = 0; rb < RB; ++rb) {
@@ -229,6 +235,45 @@ __global__ __launch_bounds__(256, 2) void nearest_kernel(
   wait_all_global_loads();
   block_sync_lds();
   int buf = 0;
+  // The first sweep selects from the block of rows before while the products of the next one run: the matrix cores and
+  // the vector units work side by side for one wavefront too, and not only where two of them happen to be out of step
+  // (1M x 4096 x 128: 1092 -> 1015 us; the fragments' LDS reads are the next limit).
+  floatx16 done[COLLECT ? 1 : RB];
+  int done_block = -1;
+  float before[RB];
+  auto select = [&](int rb, int v0, int v1) {
+    if constexpr (!COLLECT) {
+      if (v0 == 0) before[rb] = top[rb].b1;
+#pragma unroll
+      for (int v = v0; v < v1; ++v) top[rb].put(largest, done[rb][v], v);
+      if (v1 == 16) blk[rb] = top[rb].b1 > before[rb] ? done_block : blk[rb];
+    }
+  };
+  auto collect = [&](const floatx16 (&m)[RB], int64_t c0) {
+#pragma unroll
+    for (int rb = 0; rb < RB; ++rb) {
+      float mx = m[rb][0];
+#pragma unroll
+      for (int v = 1; v < 16; ++v) mx = fmaxf(mx, m[rb][v]);
+      if (__builtin_amdgcn_ballot_w64(mx >= th_e[rb]) == 0) continue;
+      const int64_t e = e0 + wave * (32 * RB) + rb * 32 + (lane & 31);
+#pragma unroll
+      for (int v = 0; v < 16; ++v)
+        if (m[rb][v] >= th_e[rb]) {
+          const int64_t c = c0 + block_row(v, half);
+          if (c < c_end) {
+            const int pos = atomicAdd(&cnt[e], 1);
+            if ((u32)pos < (u32)kCandidates) cand[e * kCandidates + pos] = (int)c;
+          }
+        }
+    }
+  };
+  if constexpr (!COLLECT) {
+#pragma unroll
+    for (int rb = 0; rb < RB; ++rb)
+#pragma unroll
+      for (int v = 0; v < 16; ++v) done[rb][v] = kPadScore;       // (no block before the first: loses to every row)
+  }
   for (int64_t ct = c_begin; ct < c_end; ct += BN, buf ^= 1) {
     const bool more = ct + BN < c_end;
     if (more) fetch(ct + BN);                                     // in flight during the products
@@ -243,15 +288,24 @@ __global__ __launch_bounds__(256, 2) void nearest_kernel(
       }
       const unsigned short* __restrict__ fr = th + (cb * 32 + (lane & 31)) * LDB + 8 * half;
       floatx16 m[RB];
+      constexpr int PF = KSTEPS < 3 ? KSTEPS : 3;                 // fragments requested ahead
+      u16x8 frag[PF];
+#pragma unroll
+      for (int f = 0; f < PF; ++f) frag[f] = *reinterpret_cast<const u16x8*>(fr + f * 16);
 #pragma unroll
       for (int kk = 0; kk < KSTEPS; ++kk) {
-        const u16x8 b = *reinterpret_cast<const u16x8*>(fr + kk * 16);
+        const u16x8 b = frag[kk % PF];
+        if (kk + PF < KSTEPS) frag[kk % PF] = *reinterpret_cast<const u16x8*>(fr + (kk + PF) * 16);
 #pragma unroll
-        for (int rb = 0; rb < RB; ++rb) m[rb] = mfma16<!BF>(b, xh[rb][kk], kk == 0 ? c0 : m[rb]);
-        if constexpr (BF) {
-          if (use_al) {
-#pragma unroll
-            for (int rb = 0; rb < RB; ++rb) m[rb] = mfma16<false>(b, xl[rb][kk], m[rb]);
+        for (int rb = 0; rb < RB; ++rb) {
+          m[rb] = mfma16<!BF>(b, xh[rb][kk], kk == 0 ? c0 : m[rb]);
+          if constexpr (BF) {
+            if (use_al) m[rb] = mfma16<false>(b, xl[rb][kk], m[rb]);
+          }
+          select(rb, 16 * kk / KSTEPS, 16 * (kk + 1) / KSTEPS);
+          if constexpr (!COLLECT && !BF) {   // (keeps that order: a product, and 16 / KSTEPS selections beside it)
+            asm volatile("" : "+v"(top[rb].b1), "+v"(top[rb].b2));
+            __builtin_amdgcn_sched_barrier(0);
           }
         }
       }
@@ -265,34 +319,20 @@ __global__ __launch_bounds__(256, 2) void nearest_kernel(
           }
         }
       }
-      const int here = (int)((ct - c_begin) >> 5) + cb;
+      if constexpr (COLLECT) {
+        collect(m, ct + cb * 32);
+      } else {
 #pragma unroll
-      for (int rb = 0; rb < RB; ++rb) {
-        if constexpr (COLLECT) {
-          float mx = m[rb][0];
-#pragma unroll
-          for (int v = 1; v < 16; ++v) mx = fmaxf(mx, m[rb][v]);
-          if (__builtin_amdgcn_ballot_w64(mx >= th_e[rb]) == 0) continue;
-          const int64_t e = e0 + wave * (32 * RB) + rb * 32 + (lane & 31);
-#pragma unroll
-          for (int v = 0; v < 16; ++v)
-            if (m[rb][v] >= th_e[rb]) {
-              const int64_t c = ct + cb * 32 + block_row(v, half);
-              if (c < c_end) {
-                const int pos = atomicAdd(&cnt[e], 1);
-                if ((u32)pos < (u32)kCandidates) cand[e * kCandidates + pos] = (int)c;
-              }
-            }
-        } else {
-          const float before = top[rb].b1;
-#pragma unroll
-          for (int v = 0; v < 16; ++v) top[rb].put(m[rb][v], v);
-          blk[rb] = top[rb].b1 > before ? here : blk[rb];
-        }
+        for (int rb = 0; rb < RB; ++rb) done[rb] = m[rb];
+        done_block = (int)((ct - c_begin) >> 5) + cb;
       }
     }
     if (more) stash(buf ^ 1, ct + BN);
     block_sync_lds();
+  }
+  if constexpr (!COLLECT) {
+#pragma unroll
+    for (int rb = 0; rb < RB; ++rb) select(rb, 0, 16);
   }
   if constexpr (COLLECT) return;
 #pragma unroll
@@ -555,8 +595,8 @@ __global__ __launch_bounds__(256, NP == 1 ? 4 : 2) void pq_nearest_kernel(
   // (no difference of scores is larger than a NaN: every sub-vector goes through the canon branch)
   const float bound = __builtin_amdgcn_ballot_w64(odd) != 0 || eps_scale < 0.f ? __builtin_nanf("") : eps_scale * 4e-5f;
   const floatx16 fzero = {0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0};
-  float infinity = __builtin_inff();
-  asm volatile("" : "+s"(infinity));                              // (a scalar register: known, it would be fmaxf again)
+  Largest largest;
+  largest.init();
   const int64_t base = (chunk * 4 + wave) * 32ll * groups;
   // (a group's list numbers are there a group early, and all pieces of its rows are requested together)
   int next_list = RES ? list_of[min(base + (lane & 31), n - 1)] : 0;
@@ -616,8 +656,6 @@ __global__ __launch_bounds__(256, NP == 1 ? 4 : 2) void pq_nearest_kernel(
     }
     Top2<4 * KB> top;
     top.init();
-    // (the first maximum of four as a median: fmaxf would quiet both operands first)
-    auto max_of = [&](float p, float q) { return __builtin_amdgcn_fmed3f(p, q, infinity); };
 #pragma unroll
     for (int b = 0; b < KB; ++b) {
       floatx16 s = mfma16<false>(af[b][0], xf[0], fzero);
@@ -625,7 +663,7 @@ __global__ __launch_bounds__(256, NP == 1 ? 4 : 2) void pq_nearest_kernel(
       for (int st = 1; st < S; ++st) s = mfma16<false>(af[b][st], xf[st], s);
 #pragma unroll
       for (int q = 0; q < 4; ++q)
-        top.put(fmaxf(fmaxf(max_of(s[4 * q], s[4 * q + 1]), s[4 * q + 2]), s[4 * q + 3]), 4 * b + q);
+        top.put(largest, fmaxf(fmaxf(largest(s[4 * q], s[4 * q + 1]), s[4 * q + 2]), s[4 * q + 3]), 4 * b + q);
     }
     int best = 8 * top.tag() + 4 * half;                          // first codeword of the best four
     const float o1 = __shfl_xor(top.b1, 32), o2 = __shfl_xor(top.b2, 32);
