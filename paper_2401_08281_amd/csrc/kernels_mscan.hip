@@ -257,6 +257,19 @@ struct SweepArgs {
   float norm_lo, norm_hi;       // PqSide::NORM: what the stored half norm is multiplied by, below and above 1
 };
 
+// The next item of this workgroup for this wavefront.  Items differ by the lengths of lists and the queries that probe
+// them: dealt out to the wavefronts in turn as well, a few items each left half of them idle at the end of a sweep (eight
+// wavefronts of a workgroup even out what one cannot: collect sweeps of 16 x 8 at 16 probes 91 -> 85 us, at 64 probes 159 ->
+// 147, of 100 million 32 x 8 1190 -> 1142, of scalar codes 243 -> 229).  A counter in memory for all is no way: one address
+// serves some 50 requests a microsecond, and the first requests of all wavefronts alone took 30 us with eight counters.
+__device__ __forceinline__ u32 take_item(u32* taken) {
+  constexpr u32 kWaves = kSweepThreads / VS_WAVE;
+  u32 n = 0;
+  if (lane_id() == 0) n = __hip_atomic_fetch_add((__attribute__((address_space(3))) u32*)taken, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+  n = (u32)__builtin_amdgcn_readfirstlane((int)n);
+  return (n / kWaves * gridDim.x + (u32)blockIdx.x) * kWaves + n % kWaves;
+}
+
 // power of two that scales the data: a vector of the norm (or a component of the size) `v` becomes 2^exp
 // (nothing but zeros: as it is)
 __device__ __forceinline__ float scale_of(u32 bits, int exp, int is_square) {
@@ -508,6 +521,8 @@ void ms_sweep_kernel(const SweepArgs A) {
   constexpr int KS = S::KS;
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
   S::stage(A, smem);
+  u32* taken = reinterpret_cast<u32*>(smem + S::lds_bytes(A)) + (kSweepThreads / VS_WAVE) * queue_words(NT);
+  if (threadIdx.x == 0) *taken = kSweepThreads / VS_WAVE;
   __syncthreads();
   const int lane = lane_id(), col = lane & 15, g = lane >> 4, wave = threadIdx.x >> 6;
   typedef __attribute__((address_space(3))) volatile u32* lds_u32_ptr;
@@ -522,12 +537,10 @@ void ms_sweep_kernel(const SweepArgs A) {
   const u32 nitems = *A.nitems;
   const float inf = __builtin_inff();
 
-  // Items are dealt out in turn: neighbours (groups of one list, segments of one list) to the wavefronts of one
-  // workgroup.  (Handed out by a counter in memory they cost more than the uneven end: one address serves some 50
-  // requests a microsecond, and the first requests of all wavefronts alone took 30 us with eight counters.)  The
-  // next item's list and pairs are fetched during this one's codes.
-  const u32 stride = gridDim.x * (kSweepThreads / VS_WAVE);
-  u32 item = blockIdx.x * (kSweepThreads / VS_WAVE) + (u32)__builtin_amdgcn_readfirstlane(wave);
+  // Items are dealt out to workgroups in turn, neighbours (groups of one list, segments of one list) to the same one,
+  // and its wavefronts take the next one when they are through with theirs (take_item).  The next item's list and
+  // pairs are fetched during this one's codes.
+  u32 item = (u32)blockIdx.x * (kSweepThreads / VS_WAVE) + (u32)__builtin_amdgcn_readfirstlane(wave);
   if (item >= nitems) return;
   uint4 it = A.items[item];
   u32 lb = (u32)A.list_off[it.x], len = (u32)A.list_off[it.x + 1] - lb;
@@ -537,7 +550,7 @@ void ms_sweep_kernel(const SweepArgs A) {
   for (;;) {
     const u32 l = it.x, sg = it.w;
     const int np = (int)it.z;
-    const u32 next = item + stride;
+    const u32 next = take_item(taken);
     if (MODE == 0) len = min(len, A.capcodes);
     const u32 cb = lb + sg * A.seg, cn = min(len - sg * A.seg, A.seg);   // the segment: cn codes from cb on
     const int nb = (int)((cn + 15) >> 4), nt = (np + 15) >> 4;
@@ -1575,7 +1588,7 @@ void launch_sweep(const SweepArgs& A, size_t lds, u32 max_items, hipStream_t st)
 
 template <int MODE>
 void launch_sweep_any(const MscanIndex& ix, const MsShape& s, const SweepArgs& A, u32 max_items, hipStream_t st) {
-  const size_t q = (size_t)(kSweepThreads / 64) * queue_words(s.nt) * 4;
+  const size_t q = (size_t)(kSweepThreads / 64) * queue_words(s.nt) * 4 + 16;
   const bool rot = ix.kind == kMsPq && ivfpq_codes_rotated(ix.g);
   const int gb = 2 * s.map.gh;
   if (ix.kind == kMsPq) {
