@@ -1443,6 +1443,10 @@ int table_form(const vs_ivfpq* ix) {
 //     of 16 x 8, lists of 244, k = 10 353 -> 339 at 6.4e7, 636 -> 512 at 1.6e8, k = 100 441 -> 580 at 3.9e7, 745 -> 731 at 1.6e8, of
 //     98 458 -> 521 at 6.2e7; precomputed tables from 2.4e7 on, 623 -> 393 at 3.9e7.
 //   4-bit codes: 0.3 pairs per list of 1465 326 -> 389, 2 1109 -> 605; 1 million of them, 2e7 visited 750 -> 418.
+//   4-bit inner products as one-hot rows: 64 x 12, lists of 1000, 16 probes, 1e7 visited 226 -> 193, k = 100 297 -> 220, 5e7 544
+//     -> 379; 4 probes 3e6 165 -> 176, 1e7 307 -> 280; lists of 125, 16 probes, 1e7 k = 100 559 -> 589, 2e7 830 -> 737; lists of
+//     1480, 16 probes and 2.5 pairs per list 288 -> 325; 32 x 8, 4 probes, 1e7 208 -> 211, 2e7 280 -> 279; 16 x 8, 4 probes,
+//     1e7 317 -> 325, 64 probes 197 -> 170.
 //   raw vectors (by 32-dimension steps): 7.6e5 visited 109 -> 146, 4e6 where 1 pair probes a list of 244, 4 probes, 357 ->
 //     464, with 64 probes 286 -> 277, at k = 100 684 -> 494; dimensions that are no multiple of 32 2978 -> 240.
 //     Inner products of vectors of uneven norm crowd into few lists: 745 -> 321 at 2 pairs per list on average.
@@ -1458,6 +1462,7 @@ bool mscan_pays(const MscanIndex& m, int form, int64_t nq, int npr, int k) {
     if (m.kind == kMsFlat) return g.metric == VS_METRIC_IP || k > 16 || npr > 16 || shared >= 1.7;
     return shared >= 5 || (npr >= 16 && ((k > 16 && shared >= 1.5) || (g.d >= 128 && mean <= 300 && shared >= 1)));
   }
+  if (mscan_onehot(m.kind, g)) return visited >= 2e7 || (visited >= 1e7 && npr >= 16 && shared >= 5 && mean >= 200);
   if (form == 0 ? visited < 3e6 && pairs < 8192 : visited < 2e7) return false;
   if (g.nbits == 4) return true;
   const double enough = 3.0 / 32.0 * g.M;                        // pairs per long list

@@ -169,6 +169,8 @@ void launch_mscan_index(int kind, const IvfpqDims& g, const float* centroids, co
 // Whether the scan's bounds hold for an index: bits of the number that its scale is taken from (sigma_src)
 bool mscan_scale_fits(int kind, u32 bits);
 size_t mscan_units_bytes(const IvfpqDims& g, int64_t ntotal);
+// indexes whose codes are swept as one-hot rows: the scan keeps nothing of them
+bool mscan_onehot(int kind, const IvfpqDims& g);
 void launch_mscan_units(const IvfpqDims& g, const uint8_t* codes, const int64_t* list_off, int64_t ntotal, void* out,
                         hipStream_t st);
 // plan of a search of npr probes per query and k results (asked: option "list_major_candidates"); false: not by this scan

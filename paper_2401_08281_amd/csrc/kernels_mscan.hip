@@ -29,6 +29,8 @@
 //   subnormals, hence |D^ - D| <= 3u D + u (|a|^2 + |b|^2) + small terms; fp32 sums of either evaluation
 //   differ from the real sums by at most phi (|a|^2 + |b|^2) with phi = 2^-22 per addition in a chain.
 //   Inner products: |<a, b> - <a^, b^>| <= (2u + u^2) |a| |b| + s sqrt(d) (|a| + |b|) + d s^2.
+//   4-bit inner products of long sub-vectors (see ms_onehot_sweep_kernel) have a bound of their own: every table entry
+//   is rounded to a whole number of steps, and the largest error of each sub-quantizer is added up.
 // The kernels use kappa = 1.02 u + phi, 4 u for 3 u, and absolute terms of 2^-26 d in scaled units (which also
 // cover subnormal squares that the dot product instruction may drop).  Where a value has no finite fp16
 // image (overflow, NaN), the vector or the query passes every test and is decided exactly.
@@ -41,6 +43,7 @@
 #include <cmath>
 #include <cstdlib>
 #include <cstring>
+#include <type_traits>
 
 #include "common.hpp"
 #include "internal.hpp"
@@ -74,6 +77,18 @@ __device__ __forceinline__ float dot8(f16x8 a, f16x8 b, float c) {
     c = __builtin_amdgcn_fdot2(x, y, c, false);
   }
   return c;
+}
+
+// lanes with a candidate of this lane's query (of an item's 64)
+__device__ __forceinline__ u64 same_lanes(bool on, u32 lp) {
+  u64 same = __builtin_amdgcn_ballot_w64(on);
+#pragma unroll
+  for (int b = 0; b < 6; ++b) {
+    const bool bit = (lp >> b) & 1u;
+    const u64 m = __builtin_amdgcn_ballot_w64(bit);
+    same &= bit ? m : ~m;
+  }
+  return same;
 }
 
 // ---- the order of a vector's components in matrix fragments -----------------------------------
@@ -255,6 +270,9 @@ struct SweepArgs {
   SlotMap map;
   float kappa, c4u, phi, phi2, abs_err, u2, sd;   // see sweep_args
   float norm_lo, norm_hi;       // PqSide::NORM: what the stored half norm is multiplied by, below and above 1
+  const u32x4* tables;          // one-hot: [nq][M] entries of a sub-quantizer in steps, 16 signed bytes
+  const float4* tinfo;          // one-hot: [nq] step, sum of the tables' middles, error bound
+  float phi_c;                  // one-hot: rounding of the exact sum by the size of <q, c>
 };
 
 // The next item of this workgroup for this wavefront.  Items differ by the lengths of lists and the queries that probe
@@ -695,13 +713,7 @@ void ms_sweep_kernel(const SweepArgs A) {
         const float ra = __uint_as_float(qrow[2 * lp]), rb = __uint_as_float(qrow[2 * lp + 1]);
         const u32 prn = A.pairs[it.y + lp];
         const u32 qi = prn / (u32)A.npr, p = prn - qi * (u32)A.npr;
-        u64 same = __builtin_amdgcn_ballot_w64(on);              // lanes with a candidate of this lane's query
-#pragma unroll
-        for (int b = 0; b < 6; ++b) {
-          const bool bit = (lp >> b) & 1u;
-          const u64 m = __builtin_amdgcn_ballot_w64(bit);
-          same &= bit ? m : ~m;
-        }
+        const u64 same = same_lanes(on, lp);
         const int first = on ? (int)__builtin_ctzll(same) : 0;
         u32 at = 0;
         if (on && lane == first) at = atomicAdd(&A.cand_count[qi], (u32)__popcll(same));
@@ -866,6 +878,332 @@ void ms_sweep_kernel(const SweepArgs A) {
   }
 }
 
+// ---- 4-bit codes, inner product, long sub-vectors -------------------------------------------------------
+// A stored vector's score is a sum of one table entry per sub-quantizer, that is the product of the query's M x 16 table
+// and a vector with a one in each of its M blocks of 16.  Decoding sub-vectors of 12 dimensions costs three look-ups per
+// sub-quantizer and 24 matrix steps for 64 of them; one-hot rows cost one conflict-free look-up of 16 bytes (an entry is
+// its own set of banks) and 16 steps of the 8-bit matrix product, which run at twice the rate, and need neither the
+// centroid nor a copy of the codes.  The table is rounded to steps of 1 / 127 of its largest deviation from the
+// sub-quantizers' middles; what that loses, at most half a step per sub-quantizer, is some tenth of the scores' spread.
+// One lane per (query, sub-quantizer) and two such pairs at a time: the sixteen entries by the canon chain (the exact
+// evaluation's bits, kept for it), rounded, and written as one piece.  The codebook lies in LDS, a sub-quantizer's
+// codewords consecutive; V: dsub is a multiple of four and they are read 16 bytes at a time.
+// (A lane per entry took 75 us for 10,000 queries of 64 x 12: every extremum went over 16 lanes.)
+__host__ __device__ constexpr int onehot_row(int dsub) { return 16 * dsub + (dsub % 4 == 0 ? 4 : 1); }   // floats; spreads the lanes over the banks
+template <int MG, bool V>
+__global__ __launch_bounds__(256) void ms_onehot_tables_kernel(const float* __restrict__ q, int64_t nq, int d, int dsub,
+                                                               const float* __restrict__ codebooks, float eps_scale,
+                                                               int passes, u32x4* __restrict__ tables,
+                                                               float* __restrict__ exact, float4* __restrict__ tinfo) {
+  constexpr int M = 4 * MG, QW = 64 / M, Q = 2;                  // queries of a wavefront side by side; in turn
+  extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
+  float* T = reinterpret_cast<float*>(smem);
+  const int row = onehot_row(dsub), wave = threadIdx.x >> 6, lane = lane_id(), m = lane % M;
+  for (int r = wave; r < M; r += 4) {
+    if constexpr (V) {
+#pragma unroll 4
+      for (int e = lane; e < 4 * dsub; e += VS_WAVE)
+        reinterpret_cast<f32x4*>(T + r * row)[e] = reinterpret_cast<const f32x4*>(codebooks + r * 16 * dsub)[e];
+    } else {
+      for (int e = lane; e < 16 * dsub; e += VS_WAVE) T[r * row + e] = codebooks[r * 16 * dsub + e];
+    }
+  }
+  __syncthreads();
+  const float* Tm = T + m * row;
+  auto over_m = [](float v, auto op) {                           // over the M lanes of a query
+    for (int o = 1; o < M; o <<= 1) v = op(v, __shfl_xor(v, o));
+    return v;
+  };
+  auto sum = [](float x, float y) { return x + y; };
+  auto larger = [](float x, float y) { return fmaxf(x, y); };
+  for (int pass = 0; pass < passes; ++pass) {
+    const int64_t q0 = (((int64_t)blockIdx.x * 4 + wave) * passes + pass) * (Q * QW) + lane / M * Q;
+    const float* qp[Q];
+#pragma unroll
+    for (int r = 0; r < Q; ++r) qp[r] = q + min(q0 + r, nq - 1) * d + m * dsub;
+    float e[Q][16];
+#pragma unroll
+    for (int r = 0; r < Q; ++r)
+#pragma unroll
+      for (int j = 0; j < 16; ++j) e[r][j] = 0.f;
+    for (int u = 0; u < dsub; u += V ? 4 : 1) {
+      float x[Q][V ? 4 : 1];
+#pragma unroll
+      for (int r = 0; r < Q; ++r)
+#pragma unroll
+        for (int w = 0; w < (V ? 4 : 1); ++w) x[r][w] = qp[r][u + w];
+#pragma unroll
+      for (int j = 0; j < 16; ++j) {
+        if constexpr (V) {
+          const float4 t = *reinterpret_cast<const float4*>(Tm + j * dsub + u);
+#pragma unroll
+          for (int r = 0; r < Q; ++r)
+            e[r][j] = __builtin_fmaf(x[r][3], t.w, __builtin_fmaf(x[r][2], t.z, __builtin_fmaf(x[r][1], t.y, __builtin_fmaf(x[r][0], t.x, e[r][j]))));
+        } else {
+          const float t = Tm[j * dsub + u];
+#pragma unroll
+          for (int r = 0; r < Q; ++r) e[r][j] = __builtin_fmaf(x[r][0], t, e[r][j]);
+        }
+      }
+    }
+#pragma unroll
+    for (int r = 0; r < Q; ++r) {
+      const int64_t qi = q0 + r;
+      float hi = e[r][0], lo = hi;
+      bool fine = true;
+#pragma unroll
+      for (int j = 0; j < 16; ++j) {
+        hi = fmaxf(hi, e[r][j]);
+        lo = fminf(lo, e[r][j]);
+        fine = fine && __builtin_fabsf(e[r][j]) < 1.0e30f;
+      }
+      const float mid = 0.5f * (lo + hi);
+      const float step = fmaxf(over_m(fmaxf(hi - mid, mid - lo), larger) * (1.f / 127.f), 1.0e-36f), inv = 1.f / step;
+      u32x4 out = {0u, 0u, 0u, 0u};
+      float err = 0.f;
+#pragma unroll
+      for (int j = 0; j < 16; ++j) {
+        const float off = e[r][j] - mid, v = fine ? fminf(fmaxf(rintf(off * inv), -127.f), 127.f) : 0.f;
+        err = fmaxf(err, __builtin_fabsf(off - v * step));
+        out[j >> 2] |= ((u32)(int)v & 0xFFu) << (8 * (j & 3));
+      }
+      const float size = over_m(fmaxf(__builtin_fabsf(lo), __builtin_fabsf(hi)), sum), base = over_m(mid, sum);
+      const float bad = over_m(fine ? 0.f : 1.f, larger);
+      // (the middles, their sum, an entry's deviation and the M additions of the exact sum each round by 2^-24 of `size`)
+      err = eps_scale * (over_m(err, sum) * 1.0001f + (2 * M + 16) * 0x1p-23f * size);
+      if (qi >= nq) continue;
+      tables[qi * M + m] = out;
+      f32x4* to = reinterpret_cast<f32x4*>(exact + (qi * M + m) * 16);
+#pragma unroll
+      for (int j = 0; j < 16; j += 4) to[j >> 2] = f32x4{e[r][j], e[r][j + 1], e[r][j + 2], e[r][j + 3]};
+      if (m == 0) tinfo[qi] = bad != 0.f || !(size < 1.0e30f) ? make_float4(step, 0.f, __builtin_inff(), 0.f) : make_float4(step, base, err, 0.f);
+    }
+  }
+}
+
+// The sweeps, like ms_sweep_kernel: queries as rows, codes as columns.  A lane's MG sub-quantizers g * MG .. are read
+// from the codes themselves, 16 of which are consecutive memory.
+// 16384 lists of 610 codes of 64 x 4 bits, 10,000 queries x 32 probes: the query-major scan, a table per query in LDS and 64
+// look-ups per pair, takes 1240 us; this one 90 for its bounds and 320 for the candidates (one look-up in flight: 420),
+// and 60 for their exact evaluation.  Matrix cores and LDS are busy 40 % of the time each; 44 % of the wavefronts' time
+// is the wait for an item's 32 KB of tables, which nothing but the SIMD's other wavefront hides.
+template <int MG, int MODE, int NT>
+__global__ __launch_bounds__(kSweepThreads) __attribute__((amdgpu_waves_per_eu(2)))
+void ms_onehot_sweep_kernel(const SweepArgs A) {
+  typedef int i32x4 __attribute__((ext_vector_type(4)));
+  constexpr int M = 4 * MG, CB = MG / 2, NW = (CB + 3) / 4, AHEAD = 3;
+  constexpr int kNone = -(1 << 30);
+  // (an array of its own: its address is a constant that the look-ups carry as their offset)
+  __shared__ __attribute__((aligned(256))) u32 hot[64];
+  extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
+  if (threadIdx.x < 64)
+    hot[threadIdx.x] = (threadIdx.x >> 4) == (threadIdx.x & 3) ? 1u << (8 * ((threadIdx.x >> 2) & 3)) : 0u;
+  u32* taken = reinterpret_cast<u32*>(smem) + (kSweepThreads / VS_WAVE) * (2 * kQueue + 64 * NT);
+  if (threadIdx.x == 0) *taken = kSweepThreads / VS_WAVE;
+  __syncthreads();
+  const int lane = lane_id(), col = lane & 15, g = lane >> 4, wave = threadIdx.x >> 6;
+  typedef __attribute__((address_space(3))) volatile u32* lds_u32_ptr;
+  u32* qmem = reinterpret_cast<u32*>(smem) + wave * (2 * kQueue + 64 * NT);
+  // candidates: (query of the item << 26 | code of the segment), sum; and per query of the item what a bound is formed
+  // from (MODE 0: place, groups, ...): centre, step, error, threshold
+  const lds_u32_ptr queue = (lds_u32_ptr)qmem, qrow = (lds_u32_ptr)(qmem + 2 * kQueue);
+  const u32 nitems = *A.nitems;
+  const float inf = __builtin_inff();
+  const uint8_t* codes = static_cast<const uint8_t*>(A.codes);
+  const u32 lane_at = (u32)col * (2 * MG) + (u32)g * CB;
+  struct Raw { u32 w[NW]; };
+  auto load = [&](u64 first) {
+    Raw r;
+    const uint8_t* p = codes + first * (2 * MG) + lane_at;
+    if constexpr (CB == 8) { const u32x2 v = *reinterpret_cast<const u32x2*>(p); r.w[0] = v[0]; r.w[1] = v[1]; }
+    else if constexpr (CB == 4) r.w[0] = *reinterpret_cast<const u32*>(p);
+    else r.w[0] = *reinterpret_cast<const unsigned short*>(p);
+    return r;
+  };
+
+  u32 item = (u32)blockIdx.x * (kSweepThreads / VS_WAVE) + (u32)__builtin_amdgcn_readfirstlane(wave);
+  if (item >= nitems) return;
+  uint4 it = A.items[item];
+  u32 lb = (u32)A.list_off[it.x], len = (u32)A.list_off[it.x + 1] - lb;
+  u32 pr[NT];
+#pragma unroll
+  for (int t = 0; t < NT; ++t) pr[t] = A.pairs[it.y + min((u32)(t * 16 + col), it.z - 1)];
+  for (;;) {
+    const u32 sg = it.w;
+    const int np = (int)it.z;
+    const u32 next = take_item(taken);
+    if (MODE == 0) len = min(len, A.capcodes);
+    const u32 cb = lb + sg * A.seg, cn = min(len - sg * A.seg, A.seg);   // the segment: cn codes from cb on
+    const int nb = (int)((cn + 15) >> 4), nt = (np + 15) >> 4;
+    const uint4 nit = A.items[min(next, nitems - 1)];
+    // (lanes past the end read what follows -- the store is 16 codes longer -- and are masked)
+    Raw raw[AHEAD];
+#pragma unroll
+    for (int i = 0; i < AHEAD; ++i) raw[i] = load((u64)cb + 16u * (u32)min(i, nb - 1));
+
+    // -- the queries' tables, and their terms (lane: query col of the tile)
+    i32x4 qa[NT][MG];
+    i32x4 start[NT];
+    wave_lds_sync();
+#pragma unroll
+    for (int t = 0; t < NT; ++t) {
+      if (t >= nt) continue;
+      const u32 qi = pr[t] / (u32)A.npr;
+#pragma unroll
+      for (int s = 0; s < MG; ++s) qa[t][s] = __builtin_bit_cast(i32x4, A.tables[(u64)qi * M + g * MG + s]);
+      const float4 ti = A.tinfo[qi];
+      const float c = A.cdist[pr[t]], centre = c + ti.y;
+      float ex = ti.z + A.phi_c * __builtin_fabsf(c) + 0x1p-20f * (__builtin_fabsf(c) + __builtin_fabsf(ti.y)) + 1.0e-36f;
+      if (!(__builtin_fabsf(centre) < 1.0e30f) || !(ex < 1.0e30f)) ex = inf;
+      const int at = t * 16 + col;
+      int from = kNone;                                           // sums from here on are candidates
+      if (MODE == 1) {
+        const float U = A.qbound[qi];
+        const float x = -(centre + U + ex + 0x1p-20f * __builtin_fabsf(U)) / ti.x;
+        // (an infinite bound, a NaN: everything)
+        if (x > -20000.f && ex < inf) from = (int)fminf(floorf(x) - 1.f, 20000.f);
+        if (at >= np) from = 1 << 20;
+      }
+      if (g == 0) {
+        if (MODE == 0) {
+          const u32 sl = at < np ? A.pair_slot[pr[t]] : 0u;
+          qrow[4 * at] = qi * (u32)A.slots + (sl & 0xFFFFu);
+          qrow[4 * at + 1] = sl >> 16;
+          qrow[4 * at + 2] = __float_as_uint(ex - centre);
+          qrow[4 * at + 3] = __float_as_uint(ti.x);
+        } else {
+          qrow[4 * at] = __float_as_uint(centre);
+          qrow[4 * at + 1] = __float_as_uint(ti.x);
+          qrow[4 * at + 2] = __float_as_uint(ex);
+          qrow[4 * at + 3] = (u32)from;
+        }
+      }
+#pragma unroll
+      for (int i = 0; i < 4; ++i) start[t][i] = MODE == 1 ? -__shfl(from, 4 * g + i, 64) : 0;
+    }
+    wave_lds_sync();
+    const u32 nlb = (u32)A.list_off[nit.x], nlen = (u32)A.list_off[nit.x + 1] - nlb;
+#pragma unroll
+    for (int t = 0; t < NT; ++t) pr[t] = A.pairs[nit.y + min((u32)(t * 16 + col), nit.z - 1)];
+
+    int queued = 0;
+    i32x4 best[NT];
+#pragma unroll
+    for (int t = 0; t < NT; ++t) best[t] = i32x4{kNone, kNone, kNone, kNone};
+    auto flush = [&]() {
+      wave_lds_sync();
+      for (int e0 = 0; e0 < queued; e0 += VS_WAVE) {
+        const bool on = e0 + lane < queued;
+        const u32 e = on ? queue[2 * (e0 + lane)] : 0u;
+        const int sum = on ? (int)queue[2 * (e0 + lane) + 1] : 0;
+        const u32 lp = e >> 26;
+        const float centre = __uint_as_float(qrow[4 * lp]), step = __uint_as_float(qrow[4 * lp + 1]), ex = __uint_as_float(qrow[4 * lp + 2]);
+        const u32 prn = A.pairs[it.y + lp];
+        const u32 qi = prn / (u32)A.npr, p = prn - qi * (u32)A.npr;
+        const u64 same = same_lanes(on, lp);
+        const int first = on ? (int)__builtin_ctzll(same) : 0;
+        u32 at = 0;
+        if (on && lane == first) at = atomicAdd(&A.cand_count[qi], (u32)__popcll(same));
+        const float dev = step * (float)(sum + (int)qrow[4 * lp + 3]), v = -(centre + dev), sl = ex + 0x1p-20f * __builtin_fabsf(dev);
+        float lo = v - sl, hi = v + sl;
+        if (!(fabsf(lo) < 1.0e30f) || !(fabsf(hi) < 1.0e30f)) { lo = -inf; hi = inf; }
+        at = __shfl(at, first, 64) + (u32)__popcll(same & ((1ull << lane) - 1ull));
+        if (on && at < (u32)A.cap)
+          A.cand[(u64)qi * (u32)A.cap + at] = make_uint4(cb + (e & 0x3FFFFFFu), p, __float_as_uint(lo), __float_as_uint(hi));
+      }
+      queued = 0;
+      wave_lds_sync();
+    };
+    // all blocks of the segment against `count` tiles of queries
+    auto sweep = [&](auto count) {
+      constexpr int N = decltype(count)::value;
+      // Rows of a block are looked up PF steps ahead of their products, into the next block's: with the one or two in
+      // flight that the compiler leaves, every step waited for the LDS.
+      constexpr int PF = MG >= 8 ? 6 : 4;
+      static_assert(AHEAD * MG % PF == 0, "the ring begins anew with raw[0]");
+      i32x4 ring[PF];
+      auto look_up = [&](const Raw& r, int s) {
+        const u32 w = r.w[s >> 3], at = ((s & 7) == 0 ? w << 4 : w >> (4 * ((s & 7) - 1))) & 0xF0u;
+        return *reinterpret_cast<const i32x4*>(reinterpret_cast<const unsigned char*>(hot) + at);
+      };
+      // (block i of AHEAD: rows of block b lie in the ring from i * MG on)
+      auto block = [&](int b, int i, const Raw& r, const Raw& after) {
+        i32x4 acc[N];
+#pragma unroll
+        for (int t = 0; t < N; ++t) acc[t] = start[t];
+#pragma unroll
+        for (int s = 0; s < MG; ++s) {
+          const int at = (i * MG + s) % PF;
+#pragma unroll
+          for (int t = 0; t < N; ++t) acc[t] = __builtin_amdgcn_mfma_i32_16x16x64_i8(qa[t][s], ring[at], acc[t], 0, 0, 0);
+          ring[at] = s + PF < MG ? look_up(r, s + PF) : look_up(after, s + PF - MG);
+          __builtin_amdgcn_sched_barrier(0);
+        }
+        const u32 rel = 16u * (u32)b + (u32)col;
+        const bool valid = rel < cn;
+        if (MODE == 0) {
+#pragma unroll
+          for (int t = 0; t < N; ++t)
+#pragma unroll
+            for (int i = 0; i < 4; ++i) best[t][i] = max(best[t][i], valid ? acc[t][i] : kNone);
+          if ((b & 3) == 3 || b + 1 == nb) {
+            const u32 at = (sg * A.seg >> 6) * 16u + (u32)(b >> 2) * 16u + (u32)col;
+#pragma unroll
+            for (int t = 0; t < N; ++t)
+#pragma unroll
+              for (int i = 0; i < 4; ++i) {
+                const int rw = 4 * (t * 16 + 4 * g + i);
+                const float dev = __uint_as_float(qrow[rw + 3]) * (float)best[t][i];
+                const float v = __uint_as_float(qrow[rw + 2]) - dev + 0x1p-20f * __builtin_fabsf(dev);
+                if (at < qrow[rw + 1]) A.gmin[qrow[rw] + at] = best[t][i] != kNone && v < inf ? v : inf;
+                best[t][i] = kNone;
+              }
+          }
+        } else {
+#pragma unroll
+          for (int t = 0; t < N; ++t) {
+            const int most = max(max(max(acc[t][0], acc[t][1]), acc[t][2]), acc[t][3]);
+            if (__builtin_amdgcn_ballot_w64(most >= 0 && valid) == 0) continue;
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+              const bool pass = acc[t][i] >= 0 && valid;
+              const u64 mask = __builtin_amdgcn_ballot_w64(pass);
+              if (mask == 0) continue;
+              if (queued + VS_WAVE > kQueue) flush();
+              if (pass) {
+                const int at = 2 * (queued + (int)__popcll(mask & ((1ull << lane) - 1ull)));
+                queue[at] = ((u32)(t * 16 + 4 * g + i) << 26) | rel;
+                queue[at + 1] = (u32)acc[t][i];
+              }
+              queued += (int)__popcll(mask);
+            }
+          }
+        }
+      };
+#pragma unroll
+      for (int s = 0; s < PF; ++s) ring[s] = look_up(raw[0], s);
+      for (int b = 0; b < nb; b += AHEAD) {
+#pragma unroll
+        for (int i = 0; i < AHEAD; ++i) {
+          if (b + i >= nb) break;
+          const Raw now = raw[i];
+          raw[i] = load((u64)cb + 16u * (u32)min(b + i + AHEAD, nb - 1));
+          block(b + i, i, now, raw[(i + 1) % AHEAD]);
+        }
+      }
+    };
+    if constexpr (NT == 1) sweep(std::integral_constant<int, 1>{});
+    else if (nt == 1) sweep(std::integral_constant<int, 1>{});
+    else sweep(std::integral_constant<int, NT>{});
+    if (MODE == 1 && queued > 0) flush();
+    if (next >= nitems) break;
+    item = next;
+    it = nit;
+    lb = nlb;
+    len = nlen;
+  }
+}
+
 // ---- thresholds -----------------------------------------------------------------------------------
 // The k-th smallest of the keys a wavefront holds in its first `used` registers, by bisection on the bits, the lowest
 // eight rounded up (2^-15 of a value's magnitude).
@@ -936,6 +1274,7 @@ inline size_t pq_eval_bytes(int M, int K, int dsub, int lanes, int batch) {
 __host__ __device__ constexpr size_t rows_rerank_wave_bytes(int tot, int d, bool tiled) {
   return (size_t)tot * 8 + 1024 + VS_WAVE * 8 + (size_t)((d + 3) & ~3) * 4 + (tiled ? VS_WAVE * 36 * 4 : 0);
 }
+__host__ __device__ constexpr size_t onehot_rerank_wave_bytes(int M, int tot) { return (size_t)M * 64 + 1024 + (size_t)tot * 8; }
 __host__ __device__ constexpr size_t sq8_rerank_wave_bytes(int tot, int d) {
   return ((size_t)tot * 8 + 1024 + (size_t)2 * d * 4 + 15) / 16 * 16;
 }
@@ -1160,6 +1499,43 @@ __global__ __launch_bounds__(256) void ms_select_kernel(const RerankArgs A) {
   for (int j = lane; j < A.k; j += VS_WAVE) A.sink.put(qi * A.k + j, ws.s[j]);
 }
 
+// 4-bit inner products: one wavefront per query, its table in LDS, one candidate per lane; the entries are added in the
+// query-major scan's order.
+template <int MG, int R>
+__global__ __launch_bounds__(256) void ms_rerank_onehot_kernel(const RerankArgs A, const float* __restrict__ exact) {
+  constexpr int M = 4 * MG, W = MG / 2;                          // words of a code
+  extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
+  const int wave = threadIdx.x >> 6, lane = lane_id();
+  unsigned char* mine = smem + (size_t)wave * onehot_rerank_wave_bytes(M, A.tot);
+  float* T = reinterpret_cast<float*>(mine);
+  u32* keep = reinterpret_cast<u32*>(T + M * 16);
+  u64* slots = reinterpret_cast<u64*>(keep + 256);
+  const int64_t qi = (int64_t)blockIdx.x * 4 + wave;
+  if (qi >= A.nq) return;
+  const u32 n = A.cand_count[qi];
+  if (ms_overflowed(A, qi, n)) return;
+#pragma unroll
+  for (int i = lane; i < M * 4; i += VS_WAVE)
+    reinterpret_cast<f32x4*>(T)[i] = reinterpret_cast<const f32x4*>(exact + qi * M * 16)[i];
+  WaveSelect<R> ws;
+  ws.init(slots, A.tot, A.k);
+  ws.set_metric(1);
+  const u32* codes = static_cast<const u32*>(A.codes);
+  const u32 limit = ms_limit(A, qi, n);
+  wave_lds_sync();
+  ms_survivors(A, qi, n, limit, keep, [&](int num, u32 pos, u32 p) {
+    u32 w[W];
+#pragma unroll
+    for (int i = 0; i < W; ++i) w[i] = codes[(u64)pos * W + i];
+    float dist = A.cdist[qi * A.npr + p];
+#pragma unroll
+    for (int m = 0; m < M; ++m) dist += T[m * 16 + (int)((w[m >> 3] >> (4 * (m & 7))) & 15u)];
+    ws.push_value(lane < num, dist, pos);
+  });
+  ws.finish();
+  for (int j = lane; j < A.k; j += VS_WAVE) A.sink.put(qi * A.k + j, ws.s[j]);
+}
+
 // raw vectors: the canon distance of every candidate row
 template <int METRIC, bool TILED, int R>
 __global__ __launch_bounds__(256) void ms_rerank_flat_kernel(const RerankArgs A) {
@@ -1364,9 +1740,12 @@ int flat_ksteps(int d) { return (d + 31) / 32; }
 constexpr int pq_tiles(int ks) { return ks <= 5 ? 2 : 1; }
 constexpr int rows_tiles(int ks) { return ks <= 4 ? 4 : (ks <= 6 ? 2 : 1); }
 
-struct MsShape { int ks, nt; SlotMap map; int cb16 = 0; };
+// LDS of the one-hot tables' kernel
+size_t onehot_tables_bytes(const IvfpqDims& g) { return (size_t)g.M * onehot_row(g.dsub) * sizeof(float); }
+
+struct MsShape { int ks, nt; SlotMap map; int cb16 = 0; bool onehot = false; };
 // queries per work item: 16 per tile, as many tiles as the registers hold
-MsShape ms_shape(int kind, const IvfpqDims& g) {
+MsShape fragment_shape(int kind, const IvfpqDims& g) {
   MsShape s;
   s.map = SlotMap{kind, g.d, g.dsub, 0, 1, 8};
   if (kind == kMsPq) {
@@ -1386,6 +1765,16 @@ MsShape ms_shape(int kind, const IvfpqDims& g) {
   return s;
 }
 
+MsShape ms_shape(int kind, const IvfpqDims& g) {
+  if (!mscan_onehot(kind, g)) return fragment_shape(kind, g);
+  MsShape s;
+  s.map = SlotMap{kind, g.d, g.dsub, 0, 1, 8};
+  s.ks = 0;
+  s.nt = 2;
+  s.onehot = true;
+  return s;
+}
+
 // L2 with d / M = 3: see PqSide::NORM
 int norm_slot(const IvfpqDims& g) { return g.metric == 0 && ivfpq_codes_rotated(g) && g.M == 32 ? 1 : 0; }
 
@@ -1394,9 +1783,16 @@ int pq_lanes(int M) { return M <= 8 ? 8 : (M <= 16 ? 16 : (M <= 32 ? 32 : 64)); 
 
 }  // namespace
 
+// 4-bit inner-product codes without a form below: the one-hot sweeps, where the tables' kernel has the LDS.  (Where there is such a form its matrix steps are fewer: 64 dimensions of 32 x 4 bits take 2, one-hot 8.)
+bool mscan_onehot(int kind, const IvfpqDims& g) {
+  return kind == kMsPq && g.metric == 1 && g.nbits == 4 && (g.M == 16 || g.M == 32 || g.M == 64) &&
+         mscan_index_bytes(kind, g) == 0 && onehot_tables_bytes(g) <= 160 * 1024;
+}
+
 // The (sub-quantizers per lane row, granules per sub-vector, granule bytes, bits, rotated) forms with kernels: up to
 // eight matrix steps per vector.  (64 sub-quantizers of 12 dimensions, 24 steps, are slower this way than by
-// tables: 48 look-ups per code and lane for 16, 2590 us for 2000 at 262k queries x lists of 1526 codes.)
+// tables: 48 look-ups per code and lane for 16, 2590 us for 2000 at 262k queries x lists of 1526 codes; their inner
+// products go one-hot.)
 #define VS_MS_PQ_FORMS(X)                                                                                   \
   X(2, 1, 8, 8, true) X(4, 1, 16, 8, true) X(8, 1, 8, 8, true)                                              \
   X(2, 1, 16, 8, false) X(4, 1, 16, 8, false) X(5, 1, 16, 8, false)                                         \
@@ -1426,7 +1822,7 @@ size_t mscan_index_bytes(int kind, const IvfpqDims& g) {
     return up256((size_t)g.nlist * flat_ksteps(g.d) * 32 * 2);
   }
   if (g.M % 4 != 0 || g.M > 64 || (g.code_size & 3) != 0) return 0;
-  const MsShape s = ms_shape(kind, g);
+  const MsShape s = fragment_shape(kind, g);
   const bool rot = ivfpq_codes_rotated(g);
   bool found = false;
 #define X(MG, PARTS, GB, NB, ROT) \
@@ -1471,7 +1867,7 @@ namespace {
 
 struct MsLayout {
   size_t o_lfirst, o_lrest, o_count, o_ctr, zero_bytes;
-  size_t o_poff, o_pairs, o_rank, o_pslot, o_qslots, o_items_a, o_items_b, o_qperm, o_bound, o_gmin, o_cand, o_rlist;
+  size_t o_poff, o_pairs, o_rank, o_pslot, o_qslots, o_items_a, o_items_b, o_qperm, o_tinfo, o_exact, o_bound, o_gmin, o_cand, o_rlist;
   size_t o_surv, o_sfirst, o_snum, o_sval, bytes;
 };
 MsLayout ms_layout(const MscanIndex& ix, const MscanPlan& p) {
@@ -1492,12 +1888,14 @@ MsLayout ms_layout(const MscanIndex& ix, const MscanPlan& p) {
   L.o_qslots = take((size_t)p.nq * 4);
   L.o_items_a = take((size_t)p.max_a * 16);
   L.o_items_b = take((size_t)p.max_b * 16);
-  L.o_qperm = take((size_t)p.nq * s.ks * 32 * 4);
+  L.o_qperm = take(s.onehot ? (size_t)p.nq * ix.g.M * 16 : (size_t)p.nq * s.ks * 32 * 4);   // (one-hot: tables)
+  L.o_tinfo = take(s.onehot ? (size_t)p.nq * sizeof(float4) : 0);
+  L.o_exact = take(s.onehot ? (size_t)p.nq * ix.g.M * 16 * sizeof(float) : 0);
   L.o_bound = take((size_t)p.nq * 4);
   L.o_gmin = take((size_t)p.nq * p.slots * 4);
   L.o_cand = take((size_t)p.nq * p.cap * 16);
   L.o_rlist = take((size_t)p.nq * 4);
-  const size_t most = ix.kind == kMsPq ? p.surv : 0;
+  const size_t most = ix.kind == kMsPq && !s.onehot ? p.surv : 0;
   L.o_surv = take(most * 16);
   L.o_sval = take(most * 4);
   L.o_sfirst = take((size_t)p.nq * 4);
@@ -1509,7 +1907,9 @@ MsLayout ms_layout(const MscanIndex& ix, const MscanPlan& p) {
 }  // namespace
 
 bool mscan_supported(const MscanIndex& ix, int k) {
-  return k >= 1 && k <= 128 && ix.mem != nullptr && (ix.kind != kMsPq || ix.units != nullptr);
+  if (k < 1 || k > 128) return false;
+  if (mscan_onehot(ix.kind, ix.g)) return ix.codes != nullptr;
+  return ix.mem != nullptr && (ix.kind != kMsPq || ix.units != nullptr);
 }
 
 // Sizes of a search.  slots: groups of four codes that give a query's threshold; seg: codes of a list per work item.
@@ -1539,7 +1939,7 @@ bool mscan_plan(const MscanIndex& ix, int64_t nq, int npr, int k, int asked, Msc
   p.cap = (int)std::max<int64_t>(256, std::min<int64_t>(cap, (npr * ix.max_list + 63) / 64 * 64));
   // (short segments where there would be few work items for 2048 and more wavefronts, long ones to spread an item's
   // set-up)
-  int64_t seg = std::min<int64_t>(np, ix.g.nlist) * ((mean + 511) / 512) < 32768 ? 256 : 1024;
+  int64_t seg = std::min<int64_t>(np, ix.g.nlist) * ((mean + 511) / 512) < 32768 ? 256 : (s.onehot ? 512 : 1024);
   const int64_t group = 16 * s.nt, lists = std::min<int64_t>(np, ix.g.nlist);
   const int64_t first = std::min<int64_t>(npr, p.slots / 16);    // pairs of a query in the bound sweep, at most
   int64_t max_a, max_b;
@@ -1586,8 +1986,23 @@ void launch_sweep(const SweepArgs& A, size_t lds, u32 max_items, hipStream_t st)
   hipLaunchKernelGGL(kern, dim3((unsigned)std::max<int64_t>(1, grid)), dim3(kSweepThreads), lds, st, A);
 }
 
+template <int MG, int MODE>
+void launch_onehot_sweep(const SweepArgs& A, u32 max_items, hipStream_t st) {
+  constexpr int NT = 2;
+  const size_t lds = (size_t)(kSweepThreads / VS_WAVE) * (2 * kQueue + 64 * NT) * 4 + 16;
+  const int64_t grid = std::min<int64_t>(256, ((int64_t)max_items + 7) / 8);      // (two wavefronts per SIMD)
+  hipLaunchKernelGGL((ms_onehot_sweep_kernel<MG, MODE, NT>), dim3((unsigned)std::max<int64_t>(1, grid)), dim3(kSweepThreads),
+                     lds, st, A);
+}
+
 template <int MODE>
 void launch_sweep_any(const MscanIndex& ix, const MsShape& s, const SweepArgs& A, u32 max_items, hipStream_t st) {
+  if (s.onehot) {
+    if (ix.g.M == 16) launch_onehot_sweep<4, MODE>(A, max_items, st);
+    else if (ix.g.M == 32) launch_onehot_sweep<8, MODE>(A, max_items, st);
+    else launch_onehot_sweep<16, MODE>(A, max_items, st);
+    return;
+  }
   const size_t q = (size_t)(kSweepThreads / 64) * queue_words(s.nt) * 4 + 16;
   const bool rot = ix.kind == kMsPq && ivfpq_codes_rotated(ix.g);
   const int gb = 2 * s.map.gh;
@@ -1655,6 +2070,9 @@ SweepArgs sweep_args(const MscanIndex& ix, const MscanPlan& p, const MsShape& s,
   A.sd = (float)(std::sqrt(32.0 * s.ks) * 0x1p-25 * es);
   // (the norm inside the product is rounded to fp16: one u more; both factors are exact in fp16)
   const double off = A.kappa + 1.01 * u * es;
+  A.tables = reinterpret_cast<const u32x4*>(ws + L.o_qperm);
+  A.tinfo = reinterpret_cast<const float4*>(ws + L.o_tinfo);
+  A.phi_c = (float)((ix.g.M + 4) * 0x1p-23 * es);
   A.norm_lo = (float)(1.0 - std::ceil(off * 0x1p11) * 0x1p-11);
   A.norm_hi = (float)(1.0 + std::ceil(off * 0x1p10) * 0x1p-10);
   return A;
@@ -1690,6 +2108,25 @@ void launch_mscan(int part, const MscanIndex& ix, const MscanPlan& p, const floa
     hipLaunchKernelGGL(ms_scatter_kernel, dim3((unsigned)((np + 255) / 256)), dim3(256), 0, st, probes, np, pslot, rank,
                        lfirst, lrest, off, ix.list_off, (u32)(16 * s.nt), p.seg, p.capcodes, items_a, p.max_a, items_b, p.max_b,
                        reinterpret_cast<u32*>(ws + L.o_pairs));
+    if (s.onehot) {
+      // (passes of a wavefront: enough that staging the codebook is not what it does)
+      const int per = 8 * (64 / ix.g.M), passes = (int)std::max<int64_t>(1, std::min<int64_t>(8, p.nq / (256 * per)));
+      const size_t lds = onehot_tables_bytes(ix.g);
+      const dim3 tg((unsigned)((p.nq + per * passes - 1) / (per * passes)));
+#define OT(MG, V)                                                                                                     \
+      do {                                                                                                            \
+        auto kern = &ms_onehot_tables_kernel<MG, V>;                                                                  \
+        if (lds > 48 * 1024)                                                                                          \
+          (void)hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds); \
+        hipLaunchKernelGGL(kern, tg, dim3(256), lds, st, q, p.nq, ix.g.d, ix.g.dsub, ix.codebooks,                    \
+                           std::max(0.f, eps_scale), passes, reinterpret_cast<u32x4*>(ws + L.o_qperm),                \
+                           reinterpret_cast<float*>(ws + L.o_exact), reinterpret_cast<float4*>(ws + L.o_tinfo));      \
+      } while (0)
+#define OT2(MG) do { if (ix.g.dsub % 4 == 0) OT(MG, true); else OT(MG, false); } while (0)
+      if (ix.g.M == 16) OT2(4); else if (ix.g.M == 32) OT2(8); else OT2(16);
+#undef OT2
+#undef OT
+    }
     A.items = items_a;
     A.nitems = ctr;
     launch_sweep_any<0>(ix, s, A, p.max_a, st);
@@ -1725,6 +2162,16 @@ void launch_mscan(int part, const MscanIndex& ix, const MscanPlan& p, const floa
   B.centroids = ix.centroids; B.codebooks = ix.codebooks; B.cdist = cdist; B.cnorm = ix.cnorm; B.norms = ix.norms;
   B.list_tables = ix.list_tables; B.vmin = ix.vmin; B.step = ix.step;
   const int r = B.tot <= 128 ? 2 : 4;
+  if (s.onehot) {
+    const size_t lds = 4 * onehot_rerank_wave_bytes(ix.g.M, B.tot);
+    const float* exact = reinterpret_cast<const float*>(ws + L.o_exact);
+    const dim3 grid((unsigned)((p.nq + 3) / 4));
+#define RO(MG) do { if (r == 2) hipLaunchKernelGGL((ms_rerank_onehot_kernel<MG, 2>), grid, dim3(256), lds, st, B, exact); \
+                    else hipLaunchKernelGGL((ms_rerank_onehot_kernel<MG, 4>), grid, dim3(256), lds, st, B, exact); } while (0)
+    if (ix.g.M == 16) RO(4); else if (ix.g.M == 32) RO(8); else RO(16);
+#undef RO
+    return;
+  }
   if (ix.kind == kMsPq) {
     hipLaunchKernelGGL(ms_list_kernel, dim3((unsigned)((p.nq + 15) / 16)), dim3(1024), 0, st, B);
     size_t lds = 0;

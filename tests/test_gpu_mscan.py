@@ -49,6 +49,9 @@ CASES = [
     ("pq", 128, 16, 8, L2, 0, 333, 1, 9), ("pq", 128, 16, 8, L2, 2, 129, 100, 33), ("pq", 128, 16, 8, IP, 0, 64, 128, 9),
     ("pq", 96, 32, 8, L2, 0, 333, 100, 33), ("pq", 96, 32, 8, L2, 1, 65, 16, 9), ("pq", 96, 32, 8, IP, 0, 63, 17, 1),
     ("pq", 100, 20, 8, L2, 0, 130, 10, 9), ("pq", 64, 32, 4, L2, 0, 333, 33, 9), ("pq", 64, 32, 4, IP, 0, 17, 128, 64),
+    # 4-bit inner products as one-hot rows: 2, 4 and 8 code bytes of a lane, sub-vectors of 1 to 12 dimensions
+    ("pq", 768, 64, 4, IP, 0, 333, 10, 33), ("pq", 320, 64, 4, IP, 0, 65, 128, 9), ("pq", 160, 32, 4, IP, 0, 130, 65, 64),
+    ("pq", 16, 16, 4, IP, 0, 333, 1, 9), ("pq", 144, 16, 4, IP, 0, 17, 100, 33),
     ("flat", 32, 0, 0, L2, 0, 333, 10, 9), ("flat", 128, 0, 0, L2, 0, 65, 128, 33), ("flat", 161, 0, 0, IP, 0, 130, 5, 9),
     ("flat", 250, 0, 0, L2, 0, 16, 1, 64),
     ("sq8", 33, 0, 0, L2, 0, 333, 10, 9), ("sq8", 96, 0, 0, IP, 0, 129, 65, 33), ("sq8", 256, 0, 0, L2, 0, 17, 64, 9),

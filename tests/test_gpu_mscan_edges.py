@@ -116,6 +116,33 @@ def test_data_of_any_size(vs, kind, d, M, form, metric, size):
         ix.close()
 
 
+@pytest.mark.parametrize("size", [1e-43, 1e-30, 1e-19, 1e-6, 1.0, 1e12, 1e18, 1e30])
+@pytest.mark.parametrize("d,M", [(320, 64), (192, 32), (16, 16)])
+@pytest.mark.parametrize("what", ["plain", "one large sub-quantizer", "equal codewords", "not finite"])
+def test_one_hot_sums_of_any_size(vs, d, M, size, what):
+    """4-bit inner products: tables whose entries vanish, overflow, are all equal, or of which one sub-quantizer's set the
+    step of all others."""
+    rng = np.random.default_rng(d + M)
+    cent, x = lists_of(rng, d, [100] * 12)
+    cb = rng.standard_normal((M, 16, d // M)).astype(np.float32)
+    if what == "one large sub-quantizer":
+        cb[3] *= 1000
+    if what == "equal codewords":
+        cb[:] = cb[:, :1]
+    if what == "not finite":
+        cb[0, 1, 0], cb[M - 1, 15, 0] = np.nan, np.inf
+    with np.errstate(over="ignore", under="ignore"):
+        cent, x, cb = [(a * np.float32(size)).astype(np.float32) for a in (cent, x, cb)]
+        q = (x[rng.integers(0, len(x), 150)] * rng.uniform(0.9, 1.1, (150, d))).astype(np.float32)
+    q[0], q[1, 0], q[2, 0] = 0, np.nan, np.inf
+    ix = vs.IVFPQ(d, IP, dev(cent), dev(cb), nbits=4)
+    try:
+        ix.add(dev(x))
+        both_scans(vs, ix, dev(q), 10, 6)
+    finally:
+        ix.close()
+
+
 @pytest.mark.parametrize("kind,d,M", [("pq", 128, 16), ("pq", 100, 20), ("flat", 64, 0), ("sq8", 96, 0)])
 def test_centroids_far_larger_than_residuals(vs, kind, d, M):
     """Stored norms and inner products whose terms are near the end of fp32 while residuals are of ordinary size."""
