@@ -375,11 +375,19 @@ void mfma_sweep_kernel(const unsigned short* __restrict__ Ahi, const unsigned sh
 #pragma unroll
     for (int v = 0; v < 16; ++v) {
       const int64_t r = row0 + rb * 32 + 8 * (v >> 2) + 4 * (lane >> 5) + (v & 3);
-      // (rows past the end of A start from -inf: nothing of them passes the collect test)
-      tr[rb][v] = MODE == 1 ? (r < na ? tau[r] * INV_S : -__builtin_inff()) : 0.f;
+      // (asked for in any case: one by one behind a condition they took a round trip to memory each)
+      tr[rb][v] = MODE == 1 ? tau[min(r, na - 1)] * INV_S : 0.f;
 #pragma unroll
       for (int cb = 0; cb < 2; ++cb) mn[rb][cb][v] = __builtin_inff();
     }
+  // (rows past the end of A start from -inf: nothing of them passes the collect test)
+  if (MODE == 1 && row0 + 32 * RB > na) {
+#pragma unroll
+    for (int rb = 0; rb < RB; ++rb)
+#pragma unroll
+      for (int v = 0; v < 16; ++v)
+        if (row0 + rb * 32 + 8 * (v >> 2) + 4 * (lane >> 5) + (v & 3) >= na) tr[rb][v] = -__builtin_inff();
+  }
 
   // global -> registers -> LDS staging of one 64-row B tile (spelled as macros so that the
   // staging registers stay registers).  B planes are padded to a multiple of 64 rows; tile
