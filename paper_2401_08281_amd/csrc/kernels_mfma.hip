@@ -291,32 +291,26 @@ __global__ void prep_info_init_kernel(PrepInfo* info, u32 heads_only, u32 keep_h
 // sufficiency test needs.
 // ---------------------------------------------------------------------------
 template <int KSTEPS, int RB, int METRIC, int MODE, int PREC>
-__global__ __launch_bounds__(256, 2)
-void mfma_sweep_kernel(const unsigned short* __restrict__ Ahi, const unsigned short* __restrict__ Alo,
-                       const float* __restrict__ Anorm, const PrepInfo* __restrict__ Ainfo, int64_t na,
-                       const unsigned short* __restrict__ Bhi, const unsigned short* __restrict__ Blo,
-                       const float* __restrict__ Bnorm, const PrepInfo* __restrict__ Binfo, int64_t nb,
-                       int nsplit, int64_t cols_per_split, int stride, int nphase,
-                       int64_t cols_per_phase,
-                       float* __restrict__ minima, int g_raw,       // MODE 0 out: [na][g_raw]
-                       const float* __restrict__ tau,               // MODE 1 in:  [na]
-                       int* __restrict__ cnt, u64* __restrict__ shortlist, int cap,    // MODE 1 out
-                       int allow_two) {
+__device__ __forceinline__
+void mfma_sweep(const unsigned short* __restrict__ Ahi, const unsigned short* __restrict__ Alo,
+                const float* __restrict__ Anorm, int64_t na,
+                const unsigned short* __restrict__ Bhi, const unsigned short* __restrict__ Blo,
+                const float* __restrict__ Bnorm, int64_t nb,
+                int nsplit, int64_t cols_per_split, int stride, int nphase,
+                int64_t cols_per_phase,
+                float* __restrict__ minima, int g_raw,       // MODE 0 out: [na][g_raw]
+                const float* __restrict__ tau,               // MODE 1 in:  [na]
+                int* __restrict__ cnt, u64* __restrict__ shortlist, int cap) {    // MODE 1 out
   // PREC: which products the operands need.  0: both are exactly bf16 -- heads only.  1: A is
   // exact, B is not -- A's tails are zero, so head x head + head x tail (two passes; A's tail
   // plane is never read).  2: head x head + head x tail + tail x head (three passes).  3: one
-  // product on the fp16 heads, which the host passes in place of the bf16 heads (Ahi, Bhi).
+  // product on the fp16 heads, passed in place of the bf16 heads (Ahi, Bhi).
   constexpr bool THREE = PREC == 2, LOB = PREC == 1 || PREC == 2, F16 = PREC == 3;
   constexpr int D = KSTEPS * 16, BN = 64, LDB = D + 8;            // LDS row stride in bf16 elements
   constexpr int NPL = LOB ? 2 : 1;                                // planes of B in LDS
   constexpr int CHUNKS = BN * (D / 8);                            // 16-byte chunks per plane per step
   constexpr int CPT = (CHUNKS + 255) / 256;                       // chunks per lane
   constexpr float SCALE = METRIC == 0 ? -2.f : -1.f;
-  // the variants that may be needed are all launched; those that do not match the operands'
-  // flags leave at once (the two-pass variant is only enqueued for long A: allow_two)
-  // allow_two: bit 0 = the two-pass variant was enqueued; bits 1.. = this call's bit of heads_only
-  if (precision_variant(Ainfo, Binfo, allow_two >> 1, (allow_two & 1) != 0) != PREC) return;
-
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
   unsigned short* bt = reinterpret_cast<unsigned short*>(smem);   // [2 buffers][NPL][BN][LDB]
   float* bns = reinterpret_cast<float*>(bt + 2 * NPL * BN * LDB); // [2][BN] norms (+inf past the end)
@@ -600,6 +594,27 @@ void mfma_sweep_kernel(const unsigned short* __restrict__ Ahi, const unsigned sh
   }
 }
 
+// The sweep in the variant that the operands' flags ask for.  One kernel holds them all: a launch that finds nothing to do
+// costs 4 us, and with a kernel for each variant a search made three or four of them (10,000 queries, 16 of 4096 rows of
+// 128 dimensions: 18 of 380 us; 1000 queries against 200,003 rows that are handed over with the call: 18 of 275).
+// RB: row blocks of a wavefront where the operands need one product.  HEADS: the fp16 heads may be tried, and then not
+// two products.  flags: bit 0 = two products are allowed; bits 1.. = this call's bit of heads_only
+template <int KSTEPS, int RB, int METRIC, int MODE, bool HEADS>
+__global__ __launch_bounds__(256, 2)
+void mfma_sweep_kernel(const MfmaOperand A, const MfmaOperand B, int nsplit, int64_t cols_per_split, int stride, int nphase,
+                       int64_t cols_per_phase, float* __restrict__ minima, int g_raw, const float* __restrict__ tau,
+                       int* __restrict__ cnt, u64* __restrict__ shortlist, int cap, int flags) {
+#define SWEEP(RB_, PREC, AH, BH)                                                                                   \
+  mfma_sweep<KSTEPS, RB_, METRIC, MODE, PREC>(AH, A.lo, A.norm, A.n, BH, B.lo, B.norm, B.n, nsplit, cols_per_split, stride, \
+                                              nphase, cols_per_phase, minima, g_raw, tau, cnt, shortlist, cap)
+  const int variant = precision_variant(A.info, B.info, flags >> 1, (flags & 1) != 0);
+  if (variant == 0) SWEEP(RB, 0, A.hi, B.hi);
+  else if (variant == 2) SWEEP(1, 2, A.hi, B.hi);
+  else if (HEADS) { if (variant == 3) SWEEP(RB, 3, A.h16, B.h16); }
+  else if (variant == 1) SWEEP(1, 1, A.hi, B.hi);
+#undef SWEEP
+}
+
 // ---------------------------------------------------------------------------
 // The same two sweeps for any d that is a multiple of 32 (up to 2048), where the fragments
 // of a row block no longer fit in registers: a tiled contraction.  Workgroup = 8 wavefronts
@@ -620,24 +635,22 @@ void mfma_sweep_kernel(const unsigned short* __restrict__ Ahi, const unsigned sh
 // The selection epilogue runs once per tile, after the last stage -- MODE 0 / MODE 1 exactly
 // as in mfma_sweep_kernel.
 // ---------------------------------------------------------------------------
-template <int METRIC, int MODE, int PREC>   // PREC: 0, 2 or 3 as in mfma_sweep_kernel
-__global__ __launch_bounds__(512)
-void mfma_sweep_kc_kernel(const unsigned short* __restrict__ Ahi, const unsigned short* __restrict__ Alo,
-                          const float* __restrict__ Anorm, const PrepInfo* __restrict__ Ainfo, int64_t na,
-                          const unsigned short* __restrict__ Bhi, const unsigned short* __restrict__ Blo,
-                          const float* __restrict__ Bnorm, const PrepInfo* __restrict__ Binfo, int64_t nb,
-                          int d, int nsplit, int64_t cols_per_split, int stride, int nphase,
-                          int64_t cols_per_phase, float* __restrict__ minima, int g_raw,
-                          const float* __restrict__ tau, int* __restrict__ cnt,
-                          u64* __restrict__ shortlist, int cap, int hbit) {
+template <int METRIC, int MODE, int PREC>   // PREC: 0, 2 or 3 as in mfma_sweep
+__device__ __forceinline__
+void mfma_sweep_kc(const unsigned short* __restrict__ Ahi, const unsigned short* __restrict__ Alo,
+                   const float* __restrict__ Anorm, int64_t na,
+                   const unsigned short* __restrict__ Bhi, const unsigned short* __restrict__ Blo,
+                   const float* __restrict__ Bnorm, int64_t nb,
+                   int d, int nsplit, int64_t cols_per_split, int stride, int nphase,
+                   int64_t cols_per_phase, float* __restrict__ minima, int g_raw,
+                   const float* __restrict__ tau, int* __restrict__ cnt,
+                   u64* __restrict__ shortlist, int cap) {
   constexpr int BM = 256, BN = 256, BLK = 1024;                  // BLK: bytes of a 32-row x 16-element block
   constexpr bool THREE = PREC == 2, F16 = PREC == 3;
   constexpr int NPL = THREE ? 2 : 1;
   constexpr int STAGE = NPL * 2 * 16 * BLK;                      // [plane][panel][8 A + 8 B blocks][BLK]
   constexpr float SCALE = METRIC == 0 ? -2.f : -1.f;
   constexpr float INV_S = METRIC == 0 ? 0.5f : 1.f;
-  if (precision_variant(Ainfo, Binfo, hbit, false) != PREC) return;
-
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
   unsigned char* tiles = smem;                                           // [2][STAGE]
   float* bns = reinterpret_cast<float*>(tiles + 2 * STAGE);              // [2][BN]
@@ -885,6 +898,22 @@ void mfma_sweep_kc_kernel(const unsigned short* __restrict__ Ahi, const unsigned
           if (r < na) minima[r * g_raw + (split * nphase + ph) * 64 + wc * 32 + (lane & 31)] = __builtin_inff();
         }
   }
+}
+
+template <int METRIC, int MODE, bool HEADS>   // as mfma_sweep_kernel
+__global__ __launch_bounds__(512)
+void mfma_sweep_kc_kernel(const MfmaOperand A, const MfmaOperand B, int d, int nsplit, int64_t cols_per_split, int stride,
+                          int nphase, int64_t cols_per_phase, float* __restrict__ minima, int g_raw,
+                          const float* __restrict__ tau, int* __restrict__ cnt, u64* __restrict__ shortlist, int cap,
+                          int hbit) {
+#define SWEEP(PREC, AH, BH)                                                                                        \
+  mfma_sweep_kc<METRIC, MODE, PREC>(AH, A.lo, A.norm, A.n, BH, B.lo, B.norm, B.n, d, nsplit, cols_per_split, stride, nphase, \
+                                    cols_per_phase, minima, g_raw, tau, cnt, shortlist, cap)
+  const int variant = precision_variant(A.info, B.info, hbit, false);
+  if (variant == 0) SWEEP(0, A.hi, B.hi);
+  else if (variant == 2) SWEEP(2, A.hi, B.hi);
+  else if (HEADS && variant == 3) SWEEP(3, A.h16, B.h16);
+#undef SWEEP
 }
 
 // tau(row) = kp-th smallest of the row's g_raw group minima (min-combined down to 64 * RG
@@ -1487,81 +1516,52 @@ size_t mfma_knn_shortlist_bytes(int64_t na, int64_t nb, int d, int k, int* nspli
   return p.bytes;
 }
 
-// which operand-precision variant is ruled out by what the host knows of the operands
-static bool certainly_three(const MfmaOperand& A, const MfmaOperand& B) {
-  return A.known_bf16 == 0 || B.known_bf16 == 0;
+// whether the fp16 heads may have to be swept (not on operands that the host knows to be exactly bf16)
+static bool heads_possible(const MfmaOperand& A, const MfmaOperand& B) {
+  return B.try_heads_only && !(A.known_bf16 == 1 && B.known_bf16 == 1);
 }
-static bool certainly_one(const MfmaOperand& A, const MfmaOperand& B) {
-  return A.known_bf16 == 1 && B.known_bf16 == 1;
-}
-// The two-pass variant is one more (possibly empty) launch: only for an A long enough that
-// the sweeps, not the launches, are what a call costs.  The kernels get the same answer as
-// a flag, so that exactly one variant takes the work.
-static bool two_pass_allowed(const MfmaOperand& A) { return A.n >= 256; }
-// ... and not next to the fp16 attempt (one more empty launch per sweep in nearly every call; when
-// the attempt has been given up on such an operand, exactly-bf16 queries take the three-pass variant)
-static bool two_pass_allowed(const MfmaOperand& A, const MfmaOperand& B) {
-  return two_pass_allowed(A) && !B.try_heads_only;
-}
+// Two products in place of three, where A is exactly bf16 and B is not: not next to the fp16 heads (when the attempt has
+// been given up on such an operand, exactly-bf16 queries take three).
+static bool two_pass_allowed(const MfmaOperand& A, const MfmaOperand& B) { return A.n >= 256 && !B.try_heads_only; }
 
-template <int KSTEPS, int RB, int METRIC, int MODE, int PREC>
+template <int KSTEPS, int RB, int METRIC, int MODE, bool HEADS>
 static void launch_sweep_t(const MfmaPlan& p, const MfmaOperand& A, const MfmaOperand& B, char* work,
                            hipStream_t st) {
-  constexpr int D = KSTEPS * 16, NPL = PREC == 1 || PREC == 2 ? 2 : 1;
-  const size_t shmem = (size_t)2 * NPL * 64 * (D + 8) * sizeof(unsigned short) + 2 * 64 * sizeof(float) +
-                       (size_t)128 * RB * (sizeof(int) + sizeof(float)) +
-                       4 * 128 * (sizeof(u64) + sizeof(int));
-  auto kern = &mfma_sweep_kernel<KSTEPS, RB, METRIC, MODE, PREC>;
+  constexpr int D = KSTEPS * 16;
+  // (three products: two planes of B and one row block; one product: one and RB)
+  constexpr size_t plane = (size_t)2 * 64 * (D + 8) * sizeof(unsigned short), rows = 128 * (sizeof(int) + sizeof(float));
+  constexpr size_t shmem = std::max(2 * plane + rows, plane + RB * rows) + 2 * 64 * sizeof(float) + 4 * 128 * (sizeof(u64) + sizeof(int));
+  auto kern = &mfma_sweep_kernel<KSTEPS, RB, METRIC, MODE, HEADS>;
   if (shmem > 48 * 1024)
     (void)hipFuncSetAttribute(reinterpret_cast<const void*>(kern),
                               hipFuncAttributeMaxDynamicSharedMemorySize, (int)shmem);
-  const int64_t row_tiles = (A.n + 128 * RB - 1) / (128 * RB);   // (the lists are per row: any RB fits)
-  const int64_t per_xcd = (row_tiles * p.nsplit + 7) / 8;         // the kernel deals the items out by XCD
-  hipLaunchKernelGGL(kern, dim3((unsigned)(8 * per_xcd)), dim3(256), shmem, st,
-                     PREC == 3 ? A.h16 : A.hi, A.lo, A.norm, A.info, A.n,
-                     PREC == 3 ? B.h16 : B.hi, B.lo, B.norm, B.info, B.n, p.nsplit, p.cols_per_split,
+  // a workgroup for every item of the variant with the most of them (one row block a wavefront; the lists are per row:
+  // any number fits); the kernel deals the items out by XCD
+  const int64_t row_tiles = (A.n + 127) / 128, per_xcd = (row_tiles * p.nsplit + 7) / 8;
+  hipLaunchKernelGGL(kern, dim3((unsigned)(8 * per_xcd)), dim3(256), shmem, st, A, B, p.nsplit, p.cols_per_split,
                      MODE == 0 ? p.stride : 1, p.nphase, p.cols_per_phase,
                      reinterpret_cast<float*>(work + p.o_minima), p.g_raw,
                      reinterpret_cast<const float*>(work + p.o_tau), reinterpret_cast<int*>(work + p.o_cnt),
                      reinterpret_cast<u64*>(work), p.cap, (two_pass_allowed(A, B) ? 1 : 0) | (p.hbit << 1));
 }
 
-template <int KSTEPS, int METRIC, int MODE>
+template <int KSTEPS, int METRIC, int MODE, bool HEADS>
 static void launch_sweep_k(const MfmaPlan& p, const MfmaOperand& A, const MfmaOperand& B, char* work,
                            hipStream_t st) {
-  // both operand-precision variants are enqueued; the kernel that does not match the flags
-  // written by operand preparation returns immediately (the flags live in device memory) --
-  // unless the host already knows an operand's flag and with it which variant cannot run
-  // (an operand that may be swept by its fp16 heads alone needs that variant enqueued too)
-  if (B.try_heads_only && !certainly_one(A, B)) {
-    if (MODE == 1 && p.RB == 2) launch_sweep_t<KSTEPS, MODE == 1 ? 2 : 1, METRIC, MODE, 3>(p, A, B, work, st);
-    else launch_sweep_t<KSTEPS, 1, METRIC, MODE, 3>(p, A, B, work, st);
-  }
-  if (!certainly_three(A, B)) {
-    if (MODE == 1 && p.RB == 2) launch_sweep_t<KSTEPS, MODE == 1 ? 2 : 1, METRIC, MODE, 0>(p, A, B, work, st);
-    else launch_sweep_t<KSTEPS, 1, METRIC, MODE, 0>(p, A, B, work, st);
-  }
-  if (!certainly_one(A, B)) {
-    // A exact and B not (integer vectors against trained centroids): two passes instead of three
-    if (two_pass_allowed(A, B) && A.known_bf16 != 0 && B.known_bf16 != 1)
-      launch_sweep_t<KSTEPS, 1, METRIC, MODE, 1>(p, A, B, work, st);
-    launch_sweep_t<KSTEPS, 1, METRIC, MODE, 2>(p, A, B, work, st);
-  }
+  if (MODE == 1 && p.RB == 2) launch_sweep_t<KSTEPS, MODE == 1 ? 2 : 1, METRIC, MODE, HEADS>(p, A, B, work, st);
+  else launch_sweep_t<KSTEPS, 1, METRIC, MODE, HEADS>(p, A, B, work, st);
 }
 
-template <int METRIC, int MODE, int PREC>
-static void launch_sweep_kc_t(const MfmaPlan& p, const MfmaOperand& A, const MfmaOperand& B, int d,
-                              char* work, hipStream_t st) {
-  constexpr int NPL = PREC == 2 ? 2 : 1;
-  const size_t shmem = (size_t)2 * NPL * 2 * 16 * 1024 + 2 * 256 * sizeof(float) +
+template <int METRIC, int MODE, bool HEADS>
+static void launch_sweep_kc(const MfmaPlan& p, const MfmaOperand& A, const MfmaOperand& B, int d,
+                            char* work, hipStream_t st) {
+  const size_t shmem = (size_t)2 * 2 * 2 * 16 * 1024 + 2 * 256 * sizeof(float) +      // (of three products; one workgroup per CU)
                        (size_t)256 * (sizeof(int) + 2 * sizeof(float)) + 8 * 128 * (sizeof(u64) + sizeof(int));
-  auto kern = &mfma_sweep_kc_kernel<METRIC, MODE, PREC>;
+  auto kern = &mfma_sweep_kc_kernel<METRIC, MODE, HEADS>;
   (void)hipFuncSetAttribute(reinterpret_cast<const void*>(kern),
                             hipFuncAttributeMaxDynamicSharedMemorySize, (int)shmem);
   const int64_t per_xcd = (p.row_tiles * p.nsplit + 7) / 8;       // the kernel deals the items out by XCD
-  hipLaunchKernelGGL(kern, dim3((unsigned)(8 * per_xcd)), dim3(512), shmem, st,
-                     PREC == 3 ? A.h16 : A.hi, A.lo, A.norm, A.info, A.n,
-                     PREC == 3 ? B.h16 : B.hi, B.lo, B.norm, B.info, B.n, d, p.nsplit, p.cols_per_split,
+  hipLaunchKernelGGL(kern, dim3((unsigned)(8 * per_xcd)), dim3(512), shmem, st, A, B, d, p.nsplit, p.cols_per_split,
                      MODE == 0 ? p.stride : 1, p.nphase, p.cols_per_phase,
                      reinterpret_cast<float*>(work + p.o_minima), p.g_raw,
                      reinterpret_cast<const float*>(work + p.o_tau), reinterpret_cast<int*>(work + p.o_cnt),
@@ -1571,24 +1571,17 @@ static void launch_sweep_kc_t(const MfmaPlan& p, const MfmaOperand& A, const Mfm
 template <int MODE>
 static void launch_sweep(const MfmaPlan& p, const MfmaOperand& A, const MfmaOperand& B, int d,
                          int metric, char* work, hipStream_t st) {
-  if (p.kc) {   // both operand-precision variants, as below
-    const bool one = !certainly_three(A, B), three = !certainly_one(A, B), f16 = B.try_heads_only && three;
+  const bool heads = heads_possible(A, B);
+  if (p.kc) {
     d = mfma_padded_dim(d);
-    if (metric == 0) {
-      if (f16) launch_sweep_kc_t<0, MODE, 3>(p, A, B, d, work, st);
-      if (one) launch_sweep_kc_t<0, MODE, 0>(p, A, B, d, work, st);
-      if (three) launch_sweep_kc_t<0, MODE, 2>(p, A, B, d, work, st);
-    } else {
-      if (f16) launch_sweep_kc_t<1, MODE, 3>(p, A, B, d, work, st);
-      if (one) launch_sweep_kc_t<1, MODE, 0>(p, A, B, d, work, st);
-      if (three) launch_sweep_kc_t<1, MODE, 2>(p, A, B, d, work, st);
-    }
+    if (metric == 0) { if (heads) launch_sweep_kc<0, MODE, true>(p, A, B, d, work, st); else launch_sweep_kc<0, MODE, false>(p, A, B, d, work, st); }
+    else             { if (heads) launch_sweep_kc<1, MODE, true>(p, A, B, d, work, st); else launch_sweep_kc<1, MODE, false>(p, A, B, d, work, st); }
     return;
   }
-#define GO(KS)                                                                      \
-  do {                                                                              \
-    if (metric == 0) launch_sweep_k<KS, 0, MODE>(p, A, B, work, st);                \
-    else             launch_sweep_k<KS, 1, MODE>(p, A, B, work, st);                \
+#define GO(KS)                                                                                                     \
+  do {                                                                                                             \
+    if (metric == 0) { if (heads) launch_sweep_k<KS, 0, MODE, true>(p, A, B, work, st); else launch_sweep_k<KS, 0, MODE, false>(p, A, B, work, st); } \
+    else             { if (heads) launch_sweep_k<KS, 1, MODE, true>(p, A, B, work, st); else launch_sweep_k<KS, 1, MODE, false>(p, A, B, work, st); } \
   } while (0)
   switch (mfma_padded_dim(d) / 16) {
     case 2: GO(2); break;
