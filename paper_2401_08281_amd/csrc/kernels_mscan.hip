@@ -1348,7 +1348,31 @@ __global__ __launch_bounds__(1024) void ms_list_kernel(const RerankArgs A) {
   const u32 n = qi < A.nq ? A.cand_count[qi] : 0u;
   const bool left = qi < A.nq && ms_overflowed(A, qi, n);
   u32 limit = 0u, mine = 0;
-  if (!left && n > 0) {
+  // Up to 256 candidates (nearly all queries of a few results) stay in registers: read once instead of three times, and
+  // the survivors' lists are asked for before the wait for a place.  Every step of this kernel is a round trip to memory;
+  // 10,000 queries, k = 10, 32.2 -> 31.2 us; 333 queries, k = 100, 16.7 -> 14.1.
+  constexpr int RC = 4;
+  const bool few = !left && n > 0 && n <= 64u * RC;
+  uint4 e[RC];
+  u32 list[RC], rel[RC];
+  if (few) {
+    const uint4* __restrict__ src = A.cand + (u64)qi * (u32)A.cap;
+    u32 key[RC];
+#pragma unroll
+    for (int r = 0; r < RC; ++r) e[r] = src[min((u32)(r * 64 + lane), n - 1)];
+#pragma unroll
+    for (int r = 0; r < RC; ++r) key[r] = (u32)(r * 64 + lane) < n ? order_f32(__uint_as_float(e[r].w)) : 0xFFFFFFFFu;
+    limit = n <= (u32)A.k ? 0xFFFFFFFFu : kth_smallest<RC>(key, (int)((n + 63) >> 6), A.k);
+#pragma unroll
+    for (int r = 0; r < RC; ++r) {
+      const bool on = (u32)(r * 64 + lane) < n && order_f32(__uint_as_float(e[r].z)) <= limit;
+      e[r].w = on;
+      mine += (u32)__popcll(__builtin_amdgcn_ballot_w64(on));
+      list[r] = on ? (u32)A.probes[(u32)qi * (u32)A.npr + e[r].y] : 0u;
+    }
+#pragma unroll
+    for (int r = 0; r < RC; ++r) rel[r] = e[r].x - (u32)A.list_off[list[r]];
+  } else if (!left && n > 0) {
     limit = ms_limit(A, qi, n);
     const uint4* __restrict__ src = A.cand + (u64)qi * (u32)A.cap;
     for (u32 c0 = 0; c0 < n; c0 += VS_WAVE)
@@ -1372,6 +1396,15 @@ __global__ __launch_bounds__(1024) void ms_list_kernel(const RerankArgs A) {
     if (place.unwritten) *A.surv_unwritten = place.unwritten;   // (one query at most)
   }
   if (mine == 0 || place.full) return;
+  if (few) {
+#pragma unroll
+    for (int r = 0; r < RC; ++r) {
+      const u64 mask = __builtin_amdgcn_ballot_w64(e[r].w != 0u);
+      if (e[r].w) A.surv[at + (u32)__popcll(mask & ((1ull << lane) - 1ull))] = make_uint4(e[r].x, (u32)qi * (u32)A.npr + e[r].y, list[r], rel[r]);
+      at += (u32)__popcll(mask);
+    }
+    return;
+  }
   ms_survivors(A, qi, n, limit, keep_s[wave], [&](int num, u32 pos, u32 p) {
     const u32 pr = (u32)qi * (u32)A.npr + p;
     const int l = A.probes[pr];
