@@ -211,9 +211,10 @@ VS_API int vs_ivfpq_create(vs_ivfpq** out, int32_t d, int32_t metric, int32_t nl
  * c_{2i} | c_{2i+1} << 4.
  * The list storage is re-laid-out contiguously; the call synchronises.
  * Shapes that the matrix-core scan serves (option "matrix_scan"; not 4-bit inner products that go by
- * their tables) also keep the codes in that scan's order, about their own size once more: up to 128 MiB wherever there is room, more than that while it
- * is at most a quarter of the free memory.  An add that does not find the memory gives that copy up
- * (searches then scan the lists query by query) before it fails.
+ * their tables) also keep the codes in that scan's order, about their own size once more: up to
+ * 128 MiB wherever there is room, more than that while it is at most a quarter of the free memory.
+ * An add that does not find the memory gives that copy up (searches then scan the lists query by
+ * query) before it fails.
  * n == 0 is a no-op.  The total number of stored vectors must stay < 2^32.
  */
 VS_API int vs_ivfpq_add(vs_ivfpq* ix, const float* x, int64_t n, const int64_t* ids, void* hip_stream);
@@ -466,11 +467,14 @@ VS_API int vs_profile_read(double* stage_ms, int64_t* launches);
  *   best, these are evaluated with the arithmetic of the other scans.  k <= 128; raw
  *   vectors and scalar codes of 16 < d <= 256; PQ of (sub-quantizers x dimensions of each) 8 x 4..8,
  *   16 x 3..8, 20 x 5..7 and 32 x 3..4 with 8-bit codes, 16 x 3..4, 32 x 1..4 and 64 x 1..4 with 4-bit
- *   codes (other inner products of 16, 32 or 64 x 4 bits by their tables rounded to whole steps, for which
- *   an index keeps nothing); not for indexes whose codebooks (raw vectors and scalar codes: centroids) are not finite or
- *   whose largest component (norm) is below about 1e-11 or above 1e10.  0 (default): where it pays, by
- *   the vectors visited, the queries that share a list, k and the probes; 1: wherever there is a kernel;
- *   -1: never.  "list_major" = 1 goes before it.  Results are identical either way.
+ *   codes; not for indexes whose codebooks (raw vectors and scalar codes: centroids) are not finite or
+ *   whose largest component (norm) is below about 1e-11 or above 1e10.  Other inner products of 16, 32 or
+ *   64 x 4 bits, of up to 159, 79 or 39 dimensions each, go by their tables rounded to whole
+ *   steps, whatever their codebooks, and an index keeps nothing for it.
+ *   0 (default): where it pays, by the vectors visited, the queries that share a list, k and the probes,
+ *   for rounded tables also by the codebooks (finite, no sub-quantizer far larger than the others) and by
+ *   the lists (no few of them that hold most vectors); 1: wherever there is a kernel; -1: never.
+ *   "list_major" = 1 goes before it.  Results are identical either way.
  * Options are process-wide. */
 VS_API int vs_set_option(const char* name, double value);
 /* counters[0] = rows evaluated through the matrix-core route, counters[1] = rows

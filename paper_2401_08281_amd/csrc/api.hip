@@ -365,6 +365,8 @@ struct vs_ivfpq {
   int64_t* list_off = nullptr;  // device [nlist + 1]
   std::vector<int64_t> h_off;   // host copy
   int64_t max_list = 0;         // the longest list's length
+  double crowding = 0.0;        // length of a stored vector's list, on average, over the mean length of a list
+  float ms_slack = 0.f;         // one-hot rows: error bound of a sum over its spread, nine of ten sampled tables at most
   void* ms_mem = nullptr;       // what the matrix-core scan of the lists keeps (shapes that have one), behind centroids
   void* ms_units = nullptr;     // the codes in that scan's order (IVF-PQ), behind codes and ids
   bool ms_units_apart = false;  // ... in memory of its own
@@ -1054,7 +1056,10 @@ int vs_ivfpq_create(vs_ivfpq** out, int32_t d, int32_t metric, int32_t nlist, in
   TRY_C(alloc_centroids(ix, kMsPq, cb));
   // (the codebooks twice: [M, K, dsub] as given, and behind it [K, M, dsub], the order in which the
   // per-query tables of the wavefront-private scan are computed)
-  TRY_C(hipMalloc(reinterpret_cast<void**>(&ix->codebooks), 2 * tb));
+  // (behind them what the tables of one-hot rows lose, kOnehotSamples floats)
+  const bool onehot = mscan_onehot(kMsPq, ix->g);
+  TRY_C(hipMalloc(reinterpret_cast<void**>(&ix->codebooks), 2 * tb + (onehot ? kOnehotSamples * sizeof(float) : 0)));
+  float* slack = ix->codebooks + 2 * (tb / sizeof(float));
   TRY_C(hipMalloc(reinterpret_cast<void**>(&ix->list_off), ((size_t)nlist + 1) * sizeof(int64_t)));
   TRY_C(hipMemcpyAsync(ix->centroids, centroids, cb, hipMemcpyDeviceToDevice, st));
   TRY_C(hipMemcpyAsync(ix->codebooks, codebooks, tb, hipMemcpyDeviceToDevice, st));
@@ -1068,8 +1073,15 @@ int vs_ivfpq_create(vs_ivfpq** out, int32_t d, int32_t metric, int32_t nlist, in
     ix->c_planes.try_heads_only = true;
     if (ix->ms_mem) launch_mscan_index(kMsPq, ix->g, ix->centroids, ix->codebooks, ix->c_planes.info, ix->ms_mem, st);
   }
+  if (onehot) launch_mscan_onehot_slack(ix->g, ix->centroids, ix->codebooks, slack, st);
   TRY_C(hipStreamSynchronize(st));
   TRY_C(learn_index(ix, kMsPq));
+  if (onehot) {
+    float h[kOnehotSamples];
+    TRY_C(hipMemcpy(h, slack, sizeof(h), hipMemcpyDeviceToHost));
+    std::nth_element(h, h + kOnehotSamples * 9 / 10, h + kOnehotSamples);
+    ix->ms_slack = h[kOnehotSamples * 9 / 10];
+  }
 #undef TRY_C
   {   // set-up for vs_ivfpq_search_static: this device's address of the static work space
     char* unused = nullptr;
@@ -1213,7 +1225,13 @@ int ivf_commit_storage(vs_ivfpq* ix, uint8_t* codes, int64_t* new_ids, float* ne
   ix->h_off.swap(pl->h_new);
   ix->ms_refused = SIZE_MAX;
   ix->max_list = 0;
-  for (int l = 0; l < ix->g.nlist; ++l) ix->max_list = std::max(ix->max_list, ix->h_off[l + 1] - ix->h_off[l]);
+  double squares = 0.0;
+  for (int l = 0; l < ix->g.nlist; ++l) {
+    const int64_t len = ix->h_off[l + 1] - ix->h_off[l];
+    ix->max_list = std::max(ix->max_list, len);
+    squares += (double)len * (double)len;
+  }
+  ix->crowding = squares * ix->g.nlist / ((double)total * (double)total);
   return VS_OK;
 }
 
@@ -1417,6 +1435,7 @@ extern "C++" MscanIndex mscan_index(int kind, const vs_ivfpq* ix, const float* v
   m.centroids = ix->centroids; m.list_off = ix->list_off; m.codes = ix->codes; m.codebooks = ix->codebooks;
   m.mem = ix->ms_mem; m.units = ix->ms_units; m.cnorm = ix->cnorm; m.norms = ix->norms; m.list_tables = ix->list_tables;
   m.vmin = vmin; m.step = step;
+  m.slack = ix->ms_slack; m.crowding = ix->crowding;
   if (ix->has_planes) m.sigma_src = kind == kMsPq ? &ix->c_planes.info->codebook_max_bits : &ix->c_planes.info->max_norm_bits;
   return m;
 }
@@ -1447,6 +1466,13 @@ int table_form(const vs_ivfpq* ix) {
 //     -> 379; 4 probes 3e6 165 -> 176, 1e7 307 -> 280; lists of 125, 16 probes, 1e7 k = 100 559 -> 589, 2e7 830 -> 737; lists of
 //     1480, 16 probes and 2.5 pairs per list 288 -> 325; 32 x 8, 4 probes, 1e7 208 -> 211, 2e7 280 -> 279; 16 x 8, 4 probes,
 //     1e7 317 -> 325, 64 probes 197 -> 170.
+//     One step serves all sub-quantizers of a query, so the bounds tell little apart where one sub-quantizer is far larger than
+//     the others, and candidates overflow their buffers.  2000 queries, 8 probes of 1000 lists of 1000, k = 100, by the bounds'
+//     share of the spread (slack): 64 x 12 0.13 455 -> 354, 0.28 (one sub-quantizer twice the others) 468 -> 432, 0.6 (three
+//     times) 619 -> 850; 32 x 5 0.1 311 -> 219, 0.2 394 -> 315, 0.4 652 -> 923; 16 x 9 0.06 324 -> 203, 0.15 411 -> 258, 0.33
+//     581 -> 489, 0.6 684 -> 898; a codeword that is not finite 452 -> 799, 312 -> 661 and 323 -> 941.
+//     And where most vectors lie in few lists a query visits many more than the buffers are sized for: 32 probes, 32 x 5,
+//     crowding 1.3 529 -> 261, 2.5 671 -> 591, 3.5 786 -> 765, 4.2 810 -> 861; 16 x 9, 11 749 -> 808; 64 x 12, 10 1359 -> 1374.
 //   raw vectors (by 32-dimension steps): 7.6e5 visited 109 -> 146, 4e6 where 1 pair probes a list of 244, 4 probes, 357 ->
 //     464, with 64 probes 286 -> 277, at k = 100 684 -> 494; dimensions that are no multiple of 32 2978 -> 240.
 //     Inner products of vectors of uneven norm crowd into few lists: 745 -> 321 at 2 pairs per list on average.
@@ -1462,7 +1488,9 @@ bool mscan_pays(const MscanIndex& m, int form, int64_t nq, int npr, int k) {
     if (m.kind == kMsFlat) return g.metric == VS_METRIC_IP || k > 16 || npr > 16 || shared >= 1.7;
     return shared >= 5 || (npr >= 16 && ((k > 16 && shared >= 1.5) || (g.d >= 128 && mean <= 300 && shared >= 1)));
   }
-  if (mscan_onehot(m.kind, g)) return visited >= 2e7 || (visited >= 1e7 && npr >= 16 && shared >= 5 && mean >= 200);
+  if (mscan_onehot(m.kind, g))
+    return m.slack <= 0.35f && m.crowding <= 3.0 &&
+           (visited >= 2e7 || (visited >= 1e7 && npr >= 16 && shared >= 5 && mean >= 200));
   if (form == 0 ? visited < 3e6 && pairs < 8192 : visited < 2e7) return false;
   if (g.nbits == 4) return true;
   const double enough = 3.0 / 32.0 * g.M;                        // pairs per long list

@@ -153,6 +153,8 @@ struct MscanIndex {
   const float *cnorm = nullptr, *norms = nullptr, *list_tables = nullptr;
   const float *vmin = nullptr, *step = nullptr;   // kMsSq8
   const u32* sigma_src = nullptr;      // bits of the codebooks' largest magnitude (kMsPq), of the centroids' largest squared norm
+  float slack = 0.f;                   // one-hot rows: see launch_mscan_onehot_slack
+  double crowding = 0.0;               // length of a stored vector's list, on average, over the mean length of a list
 };
 struct MscanPlan {
   int64_t nq = 0;
@@ -171,6 +173,10 @@ bool mscan_scale_fits(int kind, u32 bits);
 size_t mscan_units_bytes(const IvfpqDims& g, int64_t ntotal);
 // indexes whose codes are swept as one-hot rows: the scan keeps nothing of them
 bool mscan_onehot(int kind, const IvfpqDims& g);
+// out [kOnehotSamples]: error bounds of one-hot sums, with centroids in the place of queries, over the spread of such sums
+// (infinite where a table entry is not finite)
+constexpr int kOnehotSamples = 256;
+void launch_mscan_onehot_slack(const IvfpqDims& g, const float* centroids, const float* codebooks, float* out, hipStream_t st);
 void launch_mscan_units(const IvfpqDims& g, const uint8_t* codes, const int64_t* list_off, int64_t ntotal, void* out,
                         hipStream_t st);
 // plan of a search of npr probes per query and k results (asked: option "list_major_candidates"); false: not by this scan

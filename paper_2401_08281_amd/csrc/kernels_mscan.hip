@@ -981,6 +981,55 @@ __global__ __launch_bounds__(256) void ms_onehot_tables_kernel(const float* __re
   }
 }
 
+// What those tables lose, before any query is there: sampled centroids in their place, a wavefront each, a lane per
+// sub-quantizer.  The error is set against the spread that the sums would have if every sub-quantizer were like the middle
+// one: those that set the step stand out, and codes that agree in them are what the bounds have to tell apart.
+__global__ __launch_bounds__(256) void ms_onehot_slack_kernel(const float* __restrict__ centroids, int64_t nlist, int d, int M,
+                                                              int dsub, const float* __restrict__ codebooks,
+                                                              float* __restrict__ out) {
+  const int lane = lane_id(), m = lane & (M - 1), s = (int)blockIdx.x * 4 + (threadIdx.x >> 6);
+  const float* __restrict__ q = centroids + s * nlist / kOnehotSamples * d + m * dsub;
+  const float* __restrict__ t = codebooks + m * 16 * dsub;
+  float e[16] = {};
+  for (int u = 0; u < dsub; ++u) {
+    const float x = q[u];
+#pragma unroll
+    for (int j = 0; j < 16; ++j) e[j] = __builtin_fmaf(x, t[j * dsub + u], e[j]);
+  }
+  float hi = e[0], lo = e[0];
+  bool fine = true;
+#pragma unroll
+  for (int j = 0; j < 16; ++j) {
+    hi = fmaxf(hi, e[j]);
+    lo = fminf(lo, e[j]);
+    fine = fine && __builtin_fabsf(e[j]) < 1.0e30f;
+  }
+  const float dev = 0.5f * (hi - lo);
+  float most = dev;                                              // (lanes from M on repeat the others)
+  for (int o = 1; o < VS_WAVE; o <<= 1) most = fmaxf(most, __shfl_xor(most, o));
+  const float inv = 1.f / most;                                  // (everything in units of it: squares stay in range)
+  float mean = 0.f, var = 0.f, err = fminf(dev * inv, 0.5f / 127.f);
+#pragma unroll
+  for (int j = 0; j < 16; ++j) mean += (e[j] - lo) * inv;
+  mean *= 1.f / 16.f;
+#pragma unroll
+  for (int j = 0; j < 16; ++j) {
+    const float off = (e[j] - lo) * inv - mean;
+    var += off * off;
+  }
+  var *= 1.f / 16.f;
+  for (int o = 1; o < M; o <<= 1) err += __shfl_xor(err, o);
+  int smaller = 0;
+  for (int o = 0; o < M; ++o) {
+    const float other = __shfl(var, o);
+    smaller += other < var || (other == var && o < m);
+  }
+  const u64 middle = __builtin_amdgcn_ballot_w64(smaller == M / 2);
+  const float typical = __shfl(var, middle ? (int)__builtin_ctzll(middle) : 0);
+  const float share = err / sqrtf((float)M * typical);
+  if (lane == 0) out[s] = __builtin_amdgcn_ballot_w64(!fine) == 0 && share < 1.0e30f ? share : __builtin_inff();
+}
+
 // The sweeps, like ms_sweep_kernel: queries as rows, codes as columns.  A lane's MG sub-quantizers g * MG .. are read
 // from the codes themselves, 16 of which are consecutive memory.
 // 16384 lists of 610 codes of 64 x 4 bits, 10,000 queries x 32 probes: the query-major scan, a table per query in LDS and 64
@@ -1820,6 +1869,11 @@ int pq_lanes(int M) { return M <= 8 ? 8 : (M <= 16 ? 16 : (M <= 32 ? 32 : 64)); 
 bool mscan_onehot(int kind, const IvfpqDims& g) {
   return kind == kMsPq && g.metric == 1 && g.nbits == 4 && (g.M == 16 || g.M == 32 || g.M == 64) &&
          mscan_index_bytes(kind, g) == 0 && onehot_tables_bytes(g) <= 160 * 1024;
+}
+
+void launch_mscan_onehot_slack(const IvfpqDims& g, const float* centroids, const float* codebooks, float* out, hipStream_t st) {
+  hipLaunchKernelGGL(ms_onehot_slack_kernel, dim3(kOnehotSamples / 4), dim3(256), 0, st, centroids, (int64_t)g.nlist, g.d, g.M, g.dsub,
+                     codebooks, out);
 }
 
 // The (sub-quantizers per lane row, granules per sub-vector, granule bytes, bits, rotated) forms with kernels: up to
