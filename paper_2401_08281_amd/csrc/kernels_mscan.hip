@@ -2062,24 +2062,30 @@ Rescan mscan_rescan(const MscanIndex& ix, const MscanPlan& p, const char* ws, u6
 
 namespace {
 
-template <class S, int METRIC, int MODE, int NT>
-void launch_sweep(const SweepArgs& A, size_t lds, u32 max_items, hipStream_t st) {
-  auto kern = &ms_sweep_kernel<S, METRIC, MODE, NT>;
-  if (lds > 48 * 1024)
-    (void)hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+// As many workgroups as the chip holds at a time; each takes several items.  (One-hot rows of 16 sub-quantizers leave room for
+// two per compute unit, of 32 and 64 for one: 10,000 queries of 16 x 1, 16 probes 525 -> 449 us, 64 probes, k = 100 1108 -> 915;
+// of 16 x 9 350 -> 331 and 789 -> 702.)
+void launch_persistent(void (*kern)(const SweepArgs), const SweepArgs& A, size_t lds, u32 max_items, hipStream_t st) {
   int per_cu = 0;
   if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kern, kSweepThreads, lds) != hipSuccess || per_cu < 1) per_cu = 1;
   const int64_t grid = std::min<int64_t>(256ll * per_cu, ((int64_t)max_items + 7) / 8);
   hipLaunchKernelGGL(kern, dim3((unsigned)std::max<int64_t>(1, grid)), dim3(kSweepThreads), lds, st, A);
 }
 
+template <class S, int METRIC, int MODE, int NT>
+void launch_sweep(const SweepArgs& A, size_t lds, u32 max_items, hipStream_t st) {
+  auto kern = &ms_sweep_kernel<S, METRIC, MODE, NT>;
+  if (lds > 48 * 1024)
+    (void)hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+  launch_persistent(kern, A, lds, max_items, st);
+}
+
 template <int MG, int MODE>
 void launch_onehot_sweep(const SweepArgs& A, u32 max_items, hipStream_t st) {
   constexpr int NT = 2;
+  auto kern = &ms_onehot_sweep_kernel<MG, MODE, NT>;
   const size_t lds = (size_t)(kSweepThreads / VS_WAVE) * (2 * kQueue + 64 * NT) * 4 + 16;
-  const int64_t grid = std::min<int64_t>(256, ((int64_t)max_items + 7) / 8);      // (two wavefronts per SIMD)
-  hipLaunchKernelGGL((ms_onehot_sweep_kernel<MG, MODE, NT>), dim3((unsigned)std::max<int64_t>(1, grid)), dim3(kSweepThreads),
-                     lds, st, A);
+  launch_persistent(kern, A, lds, max_items, st);
 }
 
 template <int MODE>
