@@ -1416,7 +1416,10 @@ MfmaPlan make_plan(int64_t na, int64_t nb, int k, int d) {
   } else {
     // Splits of B so that the workgroups come in full rounds for both variants of the
     // collect sweep (which one runs is decided on the device): 128-row tiles on 512
-    // resident workgroups, and 256-row tiles on 512 or 128-row tiles on 768.
+    // resident workgroups, and 256-row tiles on 512 or 128-row tiles on 768.  (One kernel holds
+    // all variants, and 768 of it are resident at 32 dimensions only; a plan for 512 is no better on
+    // the whole: 33 and 128 rows against a million 1.05 times as fast, 900 rows 0.95, against 4096
+    // rows 0.96.)
     const int64_t tiles_b = p.RB == 2 ? (na + 255) / 256 : p.row_tiles;
     const double slots_b = p.RB == 2 ? 512.0 : 768.0;
     ns = 1;
@@ -1532,8 +1535,11 @@ static void launch_sweep_t(const MfmaPlan& p, const MfmaOperand& A, const MfmaOp
   if (shmem > 48 * 1024)
     (void)hipFuncSetAttribute(reinterpret_cast<const void*>(kern),
                               hipFuncAttributeMaxDynamicSharedMemorySize, (int)shmem);
-  // a workgroup for every item of the variant with the most of them (one row block a wavefront; the lists are per row:
-  // any number fits); the kernel deals the items out by XCD
+  // A workgroup for every item of the variant with the most of them (one row block a wavefront; the lists are per row:
+  // any number fits); the kernel deals the items out by XCD.  Two are resident per compute unit, three at 32 dimensions:
+  // the registers and the LDS are those of three products, where one product alone would leave room for three up to
+  // 128.  What that costs a short A is less than the launches saved: 33 to 900 rows against 4096, 65,536 and a million rows
+  // of 32 to 128 dimensions take 0.84 to 1.0 of the time with a kernel for each variant.
   const int64_t row_tiles = (A.n + 127) / 128, per_xcd = (row_tiles * p.nsplit + 7) / 8;
   hipLaunchKernelGGL(kern, dim3((unsigned)(8 * per_xcd)), dim3(256), shmem, st, A, B, p.nsplit, p.cols_per_split,
                      MODE == 0 ? p.stride : 1, p.nphase, p.cols_per_phase,

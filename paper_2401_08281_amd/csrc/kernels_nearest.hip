@@ -93,7 +93,7 @@ enum { VEC_INT = 1, VEC_EXACT = 2, VEC_NONNEG = 4, VEC_LARGE = 8 };
 // Per 32 x 32 block: KSTEPS products of 32 cycles against 16 x 3 selection instructions of 4.
 // rows: the numbers of the vectors to do, where they are not all.
 // Assignment of 1M integer vectors to 4096 rows at d = 128 (two sweeps, threshold, re-rank and
-// operand preparation before): 6.1 -> 1.4 ms (first sweep 1.13, second 0.22).
+// operand preparation before): 6.1 -> 1.06 ms (first sweep 1.02, second 0.02).
 // ---------------------------------------------------------------------------
 // 32-vector blocks per wavefront: two, and one where heads and tails of two do not fit the registers
 template <int KSTEPS, bool BF> constexpr int kNearestBlocks = BF && KSTEPS > 4 ? 1 : 2;
@@ -239,7 +239,7 @@ __global__ __launch_bounds__(256, 2) void nearest_kernel(
   // the vector units work side by side for one wavefront too, and not only where two of them happen to be out of step
   // (1M x 4096 x 128: 1092 -> 1015 us; the fragments' LDS reads are the next limit).
   floatx16 done[COLLECT ? 1 : RB];
-  int done_block = -1;
+  int done_block = 0;   // (what stands before the first block wins where no score compares, and has to name a row of B)
   float before[RB];
   auto select = [&](int rb, int v0, int v1) {
     if constexpr (!COLLECT) {
