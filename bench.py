@@ -31,6 +31,7 @@ if ROOT not in sys.path:
 HBM_PEAK_GBS = 8000.0          # MI355X HBM3E, published
 FP32_VECTOR_PEAK_TFLOPS = 157.3
 BF16_MFMA_PEAK_TFLOPS = 2500.0   # MI355X dense bf16 matrix cores, published
+INT8_MFMA_PEAK_TOPS = 5000.0     # ... and in 8 bits
 # ADC look-ups per second the vector ALUs can issue: 256 CUs x 4 SIMDs x 16 lanes x 2.4 GHz lane-operations
 # (no packed fp32), 1.5 of them per look-up (its addition + half an address instruction), in units of 1e12
 LOOKUP_PEAK_T = 256 * 4 * 16 * 2.4e9 / 1.5 / 1e12
@@ -44,8 +45,17 @@ def log(msg):
     print("[bench] " + msg, file=sys.stderr, flush=True)
 
 
-MATRIX_SCAN_KERNEL = "ms_sweep_kernel"
-MATRIX_SCAN_BOUND = re.compile(r"ms_sweep_kernel<.*, \d+, 0, \d+>")   # its MODE 0 (Side, METRIC, MODE, NT)
+# MODE 0 of the matrix-core scans' sweeps: (Side, METRIC, MODE, NT) and (MG, MODE, NT)
+MATRIX_SCAN_BOUND = re.compile(r"ms_sweep_kernel<.*, \d+, 0, \d+>|ms_onehot_sweep_kernel<\d+, 0, \d+>")
+
+
+def one_hot(cfg):
+    """4-bit inner products of long sub-vectors go by one-hot rows (the rule of csrc/kernels_mscan.hip)."""
+    return cfg["metric"] == 1 and cfg["nbits"] == 4 and cfg["M"] in (16, 32, 64) and cfg["d"] // cfg["M"] > 4
+
+
+def matrix_scan_kernel(cfg):
+    return "ms_onehot_sweep_kernel" if one_hot(cfg) else "ms_sweep_kernel"
 
 
 def scan_kernel_name(cfg, search_type, list_major=False, on_matrix_cores=False):
@@ -53,7 +63,7 @@ def scan_kernel_name(cfg, search_type, list_major=False, on_matrix_cores=False):
     the search ran list by list (the call's statistics say so): the dominant kernel is that scan."""
     code_size = cfg["M"] * cfg["nbits"] // 8
     if on_matrix_cores:
-        return MATRIX_SCAN_KERNEL
+        return matrix_scan_kernel(cfg)
     if list_major:
         return "ivfpq_scan_listmajor_kernel"
     if cfg["nbits"] == 8 and (cfg["M"], cfg["d"] // cfg["M"]) in ((16, 8), (32, 3), (8, 4)):
@@ -152,8 +162,8 @@ def record_traffic(args):
     kernel = scan_kernel_name(cfg, args.search_type, list_major)
     for path in glob.glob(os.path.join(args.record_traffic[0], "**", "*counter_collection.csv"), recursive=True):
         with open(path, newline="") as f:   # a run whose lists were scanned on the matrix cores
-            if any(MATRIX_SCAN_KERNEL in r["Kernel_Name"] for r in csv.DictReader(f)):
-                kernel = MATRIX_SCAN_KERNEL
+            if any(matrix_scan_kernel(cfg) in r["Kernel_Name"] for r in csv.DictReader(f)):
+                kernel = matrix_scan_kernel(cfg)
     GIB_KIB = float(1 << 20)
     got = {}
     for counter, folder in zip(("FETCH_SIZE", "WRITE_SIZE"), args.record_traffic):
@@ -165,7 +175,7 @@ def record_traffic(args):
                 for r in csv.DictReader(f):
                     if r["Counter_Name"] != counter:
                         continue
-                    if kernel == MATRIX_SCAN_KERNEL and MATRIX_SCAN_BOUND.search(r["Kernel_Name"]):
+                    if MATRIX_SCAN_BOUND.search(r["Kernel_Name"]):
                         continue                     # the sweep over a query's first lists, another stage
                     if kernel in r["Kernel_Name"]:
                         vals["scan"].append(float(r["Counter_Value"]))
@@ -473,11 +483,14 @@ def main():
     if on_matrix_cores:
         # The lists' codes are decoded once per batch and multiplied with all queries that probe the list: 2 d flop per
         # (query, code) pair in fp16.  (Stage "scan" is the sweep over all probed lists; the sweep that bounds the
-        # distances is part of "scan_first", the exact evaluation of the candidates of "merge".)
-        flop = 2.0 * float(scanned) * cfg["d"]
+        # distances is part of "scan_first", the exact evaluation of the candidates of "merge".)  As one-hot rows: the
+        # product with the query's table of 16 M entries, in 8 bits.
+        hot = one_hot(cfg)
+        flop = 2.0 * float(scanned) * (16 * cfg["M"] if hot else cfg["d"])
         tf = flop / (scan_ms * 1e-3) / 1e12 if scan_ms > 0 else 0.0
-        roofline = {"bound": "mfma", "kernel": MATRIX_SCAN_KERNEL, "achieved": tf, "peak": BF16_MFMA_PEAK_TFLOPS,
-                    "unit": "TFLOP/s", "frac": tf / BF16_MFMA_PEAK_TFLOPS,
+        peak = INT8_MFMA_PEAK_TOPS if hot else BF16_MFMA_PEAK_TFLOPS
+        roofline = {"bound": "mfma", "kernel": matrix_scan_kernel(cfg), "achieved": tf, "peak": peak,
+                    "unit": "TOP/s" if hot else "TFLOP/s", "frac": tf / peak,
                     "peak_measured_mfma_loop": peaks.get("mfma_loop_TFLOPs"),
                     "algorithmic_flop_per_launch": flop, "traffic": traffic, "kernel_ms": scan_ms,
                     "pairs_per_launch": pairs, "probed_nonempty_lists_per_launch": stats["probed_lists"],

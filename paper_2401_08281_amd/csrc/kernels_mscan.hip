@@ -1865,7 +1865,9 @@ int pq_lanes(int M) { return M <= 8 ? 8 : (M <= 16 ? 16 : (M <= 32 ? 32 : 64)); 
 
 }  // namespace
 
-// 4-bit inner-product codes without a form below: the one-hot sweeps, where the tables' kernel has the LDS.  (Where there is such a form its matrix steps are fewer: 64 dimensions of 32 x 4 bits take 2, one-hot 8.)
+// 4-bit inner-product codes without a form below: the one-hot sweeps, where the tables' kernel has the LDS (sub-vectors of up
+// to 159, 79 or 39 dimensions for 16, 32 or 64 sub-quantizers).  (Where there is such a form its matrix steps are fewer: 64
+// dimensions of 32 x 4 bits take 2, one-hot 8.)
 bool mscan_onehot(int kind, const IvfpqDims& g) {
   return kind == kMsPq && g.metric == 1 && g.nbits == 4 && (g.M == 16 || g.M == 32 || g.M == 64) &&
          mscan_index_bytes(kind, g) == 0 && onehot_tables_bytes(g) <= 160 * 1024;
