@@ -1539,7 +1539,7 @@ static void launch_sweep_t(const MfmaPlan& p, const MfmaOperand& A, const MfmaOp
   // any number fits); the kernel deals the items out by XCD.  Two are resident per compute unit, three at 32 dimensions:
   // the registers and the LDS are those of three products, where one product alone would leave room for three up to
   // 128.  What that costs a short A is less than the launches saved: 33 to 900 rows against 4096, 65,536 and a million rows
-  // of 32 to 128 dimensions take 0.84 to 1.0 of the time with a kernel for each variant.
+  // of 32 to 128 dimensions take 0.90 to 0.99 of the time with a kernel for each variant.
   const int64_t row_tiles = (A.n + 127) / 128, per_xcd = (row_tiles * p.nsplit + 7) / 8;
   hipLaunchKernelGGL(kern, dim3((unsigned)(8 * per_xcd)), dim3(256), shmem, st, A, B, p.nsplit, p.cols_per_split,
                      MODE == 0 ? p.stride : 1, p.nphase, p.cols_per_phase,
