@@ -1471,6 +1471,8 @@ int table_form(const vs_ivfpq* ix) {
 //     share of the spread (slack): 64 x 12 0.13 455 -> 354, 0.28 (one sub-quantizer twice the others) 468 -> 432, 0.6 (three
 //     times) 619 -> 850; 32 x 5 0.1 311 -> 219, 0.2 394 -> 315, 0.4 652 -> 923; 16 x 9 0.06 324 -> 203, 0.15 411 -> 258, 0.33
 //     581 -> 489, 0.6 684 -> 898; a codeword that is not finite 452 -> 799, 312 -> 661 and 323 -> 941.
+//     (Queries that stand out in one sub-quantizer, ten times the others, on an index that does not: 32 probes, k = 10,
+//     610 -> 535, 370 -> 304 and 366 -> 250.)
 //     And where most vectors lie in few lists a query visits many more than the buffers are sized for: 32 probes, 32 x 5,
 //     crowding 1.3 529 -> 261, 2.5 671 -> 591, 3.5 786 -> 765, 4.2 810 -> 861; 16 x 9, 11 749 -> 808; 64 x 12, 10 1359 -> 1374.
 //   raw vectors (by 32-dimension steps): 7.6e5 visited 109 -> 146, 4e6 where 1 pair probes a list of 244, 4 probes, 357 ->
