@@ -1465,7 +1465,7 @@ int table_form(const vs_ivfpq* ix) {
 //   4-bit inner products as one-hot rows: 64 x 12, lists of 1000, 16 probes, 1e7 visited 226 -> 193, k = 100 297 -> 220, 5e7 544
 //     -> 379; 4 probes 3e6 165 -> 176, 1e7 307 -> 280; lists of 125, 16 probes, 1e7 k = 100 559 -> 589, 2e7 830 -> 737; lists of
 //     1480, 16 probes and 2.5 pairs per list 288 -> 325; 32 x 8, 4 probes, 1e7 208 -> 211, 2e7 280 -> 279; 16 x 8, 4 probes,
-//     1e7 317 -> 325, 64 probes 197 -> 170.
+//     1e7 311 -> 305, 64 probes 194 -> 157.
 //     One step serves all sub-quantizers of a query, so the bounds tell little apart where one sub-quantizer is far larger than
 //     the others, and candidates overflow their buffers.  2000 queries, 8 probes of 1000 lists of 1000, k = 100, by the bounds'
 //     share of the spread (slack): 64 x 12 0.13 455 -> 354, 0.28 (one sub-quantizer twice the others) 468 -> 432, 0.6 (three
